@@ -555,14 +555,18 @@ __device__ __forceinline__ void mf_products(const MfOps<MODE, NT> &o, int nt, f3
                 acc[t] = mfma(o.a[t], o.bx[0], acc[t]);
                 acc[t] = mfma(o.a[t], o.bx[1], acc[t]);
             } else {
-                f32x4 z = {0.0f, 0.0f, 0.0f, 0.0f};
+                // the leading products apart from the 2^-8 smaller ones: the latter then
+                // round at their own size, and a step leaves one rounding of the leading
+                // sum (added together in FP32, five: the defect step's noise, where a
+                // mixed solve to 1e-9 ends, was 2 to 3 times higher)
+                f32x4 z = {0.0f, 0.0f, 0.0f, 0.0f}, y = {0.0f, 0.0f, 0.0f, 0.0f};
                 z = mfma(o.a[t], o.bx[0], z);
-                z = mfma(o.a[t], o.bx[1], z);
-                z = mfma(o.a[t], o.bx[2], z);
-                z = mfma(o.al[t], o.bx[0], z);
-                z = mfma(o.al[t], o.bx[1], z);
+                y = mfma(o.a[t], o.bx[2], y);
+                y = mfma(o.al[t], o.bx[1], y);
+                y = mfma(o.a[t], o.bx[1], y);
+                y = mfma(o.al[t], o.bx[0], y);
 #pragma unroll
-                for (int v = 0; v < 4; ++v) a64[t][v] += (double)z[v];
+                for (int v = 0; v < 4; ++v) a64[t][v] += (double)z[v] + (double)y[v];
             }
         }
     }
