@@ -1026,18 +1026,16 @@ void assemble_band(HMat &H, int band, const double *kappa_band, hipStream_t s) {
     // them is queued (band_settle, which an ACA batch may call, releases what
     // B.retire holds)
     BandStore &B = H.bands[band];
+    DevBuf kt = kink_table(*H.mesh, kappa_band, s);
     if (H.precision == RTE_FP64) {
-        DevBuf kt = tet_table<double>(*H.mesh, kappa_band, s);
-        assemble_typed<double>(H, band, BandKappa<double>{kappa_band, kt.as<double>()}, s);
-        B.retire.push_back(std::move(kt));
+        assemble_typed<double>(H, band, BandKappa<double>{kappa_band, kappa_band, kt.as<double>()}, s);
     } else {
         DevBuf kf = DevBuf::scratch(sizeof(float) * (size_t)H.mesh->N);
         to_float(kappa_band, kf.as<float>(), H.mesh->N, s);
-        DevBuf kt = tet_table<float>(*H.mesh, kf.as<float>(), s);
-        assemble_typed<float>(H, band, BandKappa<float>{kf.as<float>(), kt.as<float>()}, s);
+        assemble_typed<float>(H, band, BandKappa<float>{kf.as<float>(), kappa_band, kt.as<double>()}, s);
         B.retire.push_back(std::move(kf));
-        B.retire.push_back(std::move(kt));
     }
+    B.retire.push_back(std::move(kt));
 }
 
 void band_settle(BandStore &B, hipStream_t s) {

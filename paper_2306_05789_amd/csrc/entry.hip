@@ -93,65 +93,43 @@ void to_float(const double *in, float *out, int64_t n, hipStream_t s) {
     HIP_LAUNCH_CHECK();
 }
 
-// The four vertex values of every (cell base b, Kuhn tetrahedron t) pair, in
-// the order tet_sample reads them: b, b + s_L, b + s0 + s1 + 1 - s_S and
-// b + s0 + s1 + 1, L and S the tetrahedron's largest and smallest axes
-// (t = 2 L + (S > L ? S - 1 : S)).  A vertex past the grid (bases on the
-// upper faces) gives 0.
-template <typename T>
-__global__ void k_tet_table(GridDev g, const T *__restrict__ kap, T *__restrict__ out) {
-    const int64_t N = (int64_t)g.n[0] * g.n[1] * g.n[2];
-    const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= N * 6) return;
-    const int64_t b = k / 6;
-    const int t = (int)(k - b * 6), L = t >> 1, r = t & 1, S = r < L ? r : r + 1;
-    const int64_t s0 = g.stride[0], s1 = g.stride[1];
-    const int64_t sL = L == 0 ? s0 : (L == 1 ? s1 : 1), sS = S == 0 ? s0 : (S == 1 ? s1 : 1);
-    const int64_t v3 = b + s0 + s1 + 1;
-    const int64_t v1 = b + sL, v2 = v3 - sS;
-    out[4 * k + 0] = kap[b];
-    out[4 * k + 1] = v1 < N ? kap[v1] : (T)0;
-    out[4 * k + 2] = v2 < N ? kap[v2] : (T)0;
-    out[4 * k + 3] = v3 < N ? kap[v3] : (T)0;
+// The kinks of kappa (march.h): per family and vertex v of the grid extended by
+// one plane on its upper sides, where kappa continues by its nearest value.
+__global__ void k_kink_table(GridDev g, const double *__restrict__ kap, double *__restrict__ out) {
+    const int64_t S0 = (int64_t)(g.n[1] + 1) * (g.n[2] + 1), S1 = g.n[2] + 1, M = (g.n[0] + 1) * S0;
+    const int64_t o = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (o >= M) return;
+    const int x = (int)(o / S0), y = (int)(o % S0 / S1), z = (int)(o % S1);
+    auto k = [&](int dx, int dy, int dz) {
+        const int i = min(max(x + dx, 0), g.n[0] - 1), j = min(max(y + dy, 0), g.n[1] - 1),
+                  l = min(max(z + dz, 0), g.n[2] - 1);
+        return kap[(int64_t)i * g.stride[0] + (int64_t)j * g.stride[1] + l];
+    };
+    const double v = k(0, 0, 0), all = k(1, 1, 1);
+    const double x1 = k(1, 0, 0), y1 = k(0, 1, 0), z1 = k(0, 0, 1);
+    const double xy = k(1, 1, 0), yz = k(0, 1, 1), xz = k(1, 0, 1);
+    out[0 * M + o] = all - yz - v + k(-1, 0, 0);
+    out[1 * M + o] = all - xz - v + k(0, -1, 0);
+    out[2 * M + o] = all - xy - v + k(0, 0, -1);
+    out[3 * M + o] = x1 + y1 - v - xy;
+    out[4 * M + o] = y1 + z1 - v - yz;
+    out[5 * M + o] = x1 + z1 - v - xz;
 }
 
-// FP64: the eight corner values of every cell base b, in the order
-// b, b + s0 + s1 + 1, b + s0, b + s1, b + 1, b + s0 + s1, b + s1 + 1, b + s0 + 1
-// (a vertex past the grid gives 0)
-__global__ void k_cell_table(GridDev g, const double *__restrict__ kap, double *__restrict__ out) {
-    const int64_t N = (int64_t)g.n[0] * g.n[1] * g.n[2];
-    const int64_t b = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (b >= N) return;
-    const int64_t s0 = g.stride[0], s1 = g.stride[1];
-    const int64_t v[8] = {b, b + s0 + s1 + 1, b + s0, b + s1, b + 1, b + s0 + s1, b + s1 + 1, b + s0 + 1};
-#pragma unroll
-    for (int q = 0; q < 8; ++q) out[8 * b + q] = v[q] < N ? kap[v[q]] : 0.0;
+DevBuf kink_table(const Mesh &m, const double *kappa, hipStream_t s) {
+    const int64_t M = (int64_t)(m.dev.n[0] + 1) * (m.dev.n[1] + 1) * (m.dev.n[2] + 1);
+    DevBuf d = DevBuf::scratch(sizeof(double) * 6 * (size_t)M);
+    k_kink_table<<<(unsigned)((M + 255) / 256), 256, 0, s>>>(m.dev, kappa, d.as<double>());
+    HIP_LAUNCH_CHECK();
+    return d;
 }
-
-template <typename T>
-DevBuf tet_table(const Mesh &m, const T *kappa, hipStream_t s) {
-    if constexpr (sizeof(T) == 4) {
-        DevBuf d = DevBuf::scratch(sizeof(T) * (size_t)m.N * 24);
-        const int64_t n = m.N * 6;
-        k_tet_table<T><<<(unsigned)((n + 255) / 256), 256, 0, s>>>(m.dev, kappa, d.as<T>());
-        HIP_LAUNCH_CHECK();
-        return d;
-    } else {
-        DevBuf d = DevBuf::scratch(sizeof(T) * (size_t)m.N * 8);
-        k_cell_table<<<(unsigned)((m.N + 255) / 256), 256, 0, s>>>(m.dev, kappa, d.as<T>());
-        HIP_LAUNCH_CHECK();
-        return d;
-    }
-}
-template DevBuf tet_table<float>(const Mesh &, const float *, hipStream_t);
-template DevBuf tet_table<double>(const Mesh &, const double *, hipStream_t);
 
 template <typename T>
 EntryCtx<T> make_ctx(const Mesh &m, BandKappa<T> kappa) {
     EntryCtx<T> c;
     c.g = m.dev;
     c.kappa = kappa.v;
-    c.ktet = kappa.tet;
+    c.kink = KinkTab{kappa.kinks, kappa.v64};
     c.near = static_cast<const T *>(m.near_table(std::is_same<T, double>::value));
     if constexpr (std::is_same<T, double>::value) c.st = stencil_device().d;
     else c.st = stencil_device().f;
@@ -164,9 +142,9 @@ void entries_launch(const Mesh &m, int kind, const double *kappa, int64_t n, con
                     const int64_t *cols, double *out, int precision, hipStream_t s) {
     if (n == 0) return;
     const unsigned grid = (unsigned)((n + 255) / 256);
+    DevBuf kt = kink_table(m, kappa, s);
     if (precision == RTE_FP64) {
-        DevBuf kt = tet_table<double>(m, kappa, s);
-        auto c = make_ctx<double>(m, BandKappa<double>{kappa, kt.as<double>()});
+        auto c = make_ctx<double>(m, BandKappa<double>{kappa, kappa, kt.as<double>()});
         if (kind == RTE_VOLUME) k_entries<double, RTE_VOLUME><<<grid, 256, 0, s>>>(c, n, rows, cols, out);
         else k_entries<double, RTE_SURFACE><<<grid, 256, 0, s>>>(c, n, rows, cols, out);
         HIP_LAUNCH_CHECK();
@@ -174,8 +152,7 @@ void entries_launch(const Mesh &m, int kind, const double *kappa, int64_t n, con
     } else {
         DevBuf kf(sizeof(float) * (size_t)m.N);
         to_float(kappa, kf.as<float>(), m.N, s);
-        DevBuf kt = tet_table<float>(m, kf.as<float>(), s);
-        auto c = make_ctx<float>(m, BandKappa<float>{kf.as<float>(), kt.as<float>()});
+        auto c = make_ctx<float>(m, BandKappa<float>{kf.as<float>(), kappa, kt.as<double>()});
         if (kind == RTE_VOLUME) k_entries<float, RTE_VOLUME><<<grid, 256, 0, s>>>(c, n, rows, cols, out);
         else k_entries<float, RTE_SURFACE><<<grid, 256, 0, s>>>(c, n, rows, cols, out);
         HIP_LAUNCH_CHECK();

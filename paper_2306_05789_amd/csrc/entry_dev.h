@@ -11,11 +11,7 @@
 // at the wall.  One optical depth per vertex pair; near rule (degree 5)
 // when the grid Chebyshev distance is <= 2, degree 2 otherwise.
 //
-// tau is computed by a march over the six plane families that bound the
-// Kuhn tetrahedra (x_a = const and x_a - x_b = const in grid units): the
-// next crossing of every family is kept, the smallest one ends the current
-// piece, and kappa is linear on each piece, so the piece contributes its
-// length times kappa at its midpoint.
+// tau comes from the kinks of kappa along the ray (march.h).
 #pragma once
 
 #include <type_traits>
@@ -25,13 +21,29 @@
 
 namespace rte {
 
+// 1/x for positive, normal x (distances, crossing counts): the hardware
+// reciprocal refined by two Newton steps (FP64: the seed's relative error e
+// becomes e^4, below one ulp), or the hardware reciprocal alone (FP32, one
+// ulp): cheaper than the IEEE division sequence.
+__device__ __forceinline__ double recip(double x) {
+    double r = __builtin_amdgcn_rcp(x);
+    r = fma(fma(-x, r, 1.0), r, r);
+    r = fma(fma(-x, r, 1.0), r, r);
+    return r;
+}
+__device__ __forceinline__ float recip(float x) { return __builtin_amdgcn_rcpf(x); }
+
+}  // namespace rte
+
+#include "march.h"
+
+namespace rte {
+
 template <typename T>
 struct EntryCtx {
     GridDev g;
     const T *__restrict__ kappa;   // [N] P1 vertex values of one band
-    const T *__restrict__ ktet;    // the march's table of kappa (k_tet_table): FP32 [N][6][4], per cell
-                                   // base and Kuhn tetrahedron its four vertex values; FP64 [N][8], per
-                                   // cell base its eight corner values
+    KinkTab kink;                  // the march's table of kappa's kinks (FP64 for every T)
     StencilDev<T> st;
     const T *__restrict__ near;    // quadrature tables of the mesh: near [125][8][8], then far [24][4][8]
 };
@@ -86,203 +98,7 @@ constexpr KuhnStar make_star() {
 
 constexpr KuhnStar kStar = make_star();
 
-// ---------------------------------------------------------------- P1 kappa and the march
-// Minimum of two finite values without the quieting of signalling NaNs that
-// fmin() adds on this target (two extra instructions per call in the march).
-__device__ __forceinline__ double fmin_finite(double a, double b) {
-    double r;
-    asm("v_min_f64 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
-    return r;
-}
-__device__ __forceinline__ float fmin_finite(float a, float b) {
-    float r;
-    asm("v_min_f32 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
-    return r;
-}
-
-
-// The four vertex values of the Kuhn tetrahedron of a point in the cell with
-// flat base index b, at local coordinates (u0, u1, u2) in [0, 1]^3 (grid
-// units), and the coordinates sorted decreasingly: kappa there is the P1
-// (Freudenthal) interpolant kb + u0 (k1 - kb) + u1 (k2 - k1) + u2 (k3 - k2).
-template <typename T>
-struct TetSample {
-    T kb, k1, k2, k3, u0, u1, u2;
-    __device__ __forceinline__ T value() const { return kb + u0 * (k1 - kb) + u1 * (k2 - k1) + u2 * (k3 - k2); }
-};
-
-// The Kuhn tetrahedron of the point is given by the decreasing order of its
-// local coordinates: from the base corner it adds the axis of the largest
-// coordinate, then that of the middle one.  Ties pick the lowest axis as the
-// largest and the highest axis as the smallest, so the two never coincide
-// (the value is continuous across the faces the ties lie on).
-//
-// The vertices are b, b + s_L, b + s0 + s1 + 1 - s_S and b + s0 + s1 + 1 (s_a
-// the axis strides, L and S the largest and smallest axes).  src is what the
-// march reads kappa from (KappaSrc<T>):
-//   FP32: the table of every (cell base, tetrahedron) pair, the tetrahedron
-//   numbered t = 2 L + (S > L ? S - 1 : S): one 16-byte load per piece
-//   instead of four gathers over the grid (the ACA entry launches of the 41^3
-//   operator 98.6 -> 78.0 ms).  A base outside the grid (only the unused
-//   sample after a segment's last piece, or a piece of rounding length) reads
-//   the nearest row.
-//   FP64: the table of the eight corner values of every cell base, in the
-//   order k(b), k(b + s0 + s1 + 1), then b + s0, b + s1, b + 1, b + s0 + s1,
-//   b + s1 + 1, b + s0 + 1: three loads from one 64-byte row per piece (the
-//   first two values together).  In FP64 this runs as fast as four gathers
-//   over the grid and as 32-byte rows per tetrahedron (41^3: 123 ms of entry
-//   launches either way): a lane needs more than one load there whatever the
-//   layout.
-template <typename T>
-struct KappaSrc {
-    const T *__restrict__ tab;   // FP32 [N][6][4], FP64 [N][8]
-};
-template <typename T>
-__device__ __forceinline__ KappaSrc<T> kappa_src(const T *tab) {
-    return {tab};
-}
-
-template <typename T>
-__device__ __forceinline__ TetSample<T> tet_sample(const GridDev &g, const KappaSrc<T> &src, int b, T u0, T u1,
-                                                   T u2) {
-    const bool c01 = u0 >= u1, c02 = u0 >= u2, c12 = u1 >= u2;
-    const T hi = fmax(fmax(u0, u1), u2), lo = fmin(fmin(u0, u1), u2);
-    const T mid = fmax(fmin(u0, u1), fmin(fmax(u0, u1), u2));
-    if constexpr (sizeof(T) == 4) {
-        const int L = (c01 && c02) ? 0 : (c12 ? 1 : 2);
-        const int S = (c02 && c12) ? 2 : (c01 ? 1 : 0);
-        const int t = 2 * L + (S > L ? S - 1 : S);
-        const int nv = g.n[0] * g.n[1] * g.n[2];
-        const int bc = min(max(b, 0), nv - 1);
-        const float4 q = *reinterpret_cast<const float4 *>(src.tab + ((int64_t)bc * 6 + t) * 4);
-        return {q.x, q.y, q.z, q.w, hi, mid, lo};
-    } else {
-        // row slots: v1 = b + s_L at 2 + L; v2 = b + s0 + s1 + 1 - s_S at 6, 7, 5 for S = 0, 1, 2
-        const int i1 = (c01 && c02) ? 2 : (c12 ? 3 : 4);
-        const int i2 = (c02 && c12) ? 5 : (c01 ? 7 : 6);
-        const int nv = g.n[0] * g.n[1] * g.n[2];
-        const int bc = min(max(b, 0), nv - 1);
-        const double *r = src.tab + (int64_t)bc * 8;
-        const double2 q = *reinterpret_cast<const double2 *>(r);
-        return {q.x, r[i1], r[i2], q.y, hi, mid, lo};
-    }
-}
-
-// The state of the march along one segment: start() sets it up for P -> Q
-// and samples the tetrahedron of its first piece; piece() moves the families
-// crossed at the end of the current piece on, samples the next piece's
-// tetrahedron into nxt (its loads run while this piece is added) and adds the
-// current one, true once that piece ends the segment; tau() is the optical
-// depth.
-template <typename T>
-struct March {
-    T D[3], tn[6], dt[6], w[3], ws[3];
-    T len, tp, t, acc;
-    int b, db[3];
-
-    __device__ __forceinline__ T next_end() const {
-        return fmin_finite(fmin_finite(fmin_finite(tn[0], tn[1]), fmin_finite(tn[2], tn[3])),
-                           fmin_finite(fmin_finite(tn[4], tn[5]), (T)1));
-    }
-
-    // false when the segment has zero length (tau = 0, nothing sampled)
-    __device__ __forceinline__ bool start(const GridDev &g, const KappaSrc<T> &kt, const T P[3], const T Q[3],
-                                          TetSample<T> &first) {
-#pragma unroll
-        for (int a = 0; a < 3; ++a) D[a] = Q[a] - P[a];
-        const T wx = D[0] * (T)g.h[0], wy = D[1] * (T)g.h[1], wz = D[2] * (T)g.h[2];
-        len = sqrt(wx * wx + wy * wy + wz * wz);
-        if (len == (T)0) return false;
-        const T F0[6] = {P[0], P[1], P[2], P[0] - P[1], P[1] - P[2], P[0] - P[2]};
-        const T dF[6] = {D[0], D[1], D[2], D[0] - D[1], D[1] - D[2], D[0] - D[2]};
-#pragma unroll
-        for (int f = 0; f < 6; ++f) {
-            if (dF[f] != (T)0) {
-                const T next = dF[f] > (T)0 ? floor(F0[f]) + (T)1 : ceil(F0[f]) - (T)1;
-                dt[f] = (T)1 / fabs(dF[f]);
-                tn[f] = (next - F0[f]) / dF[f];
-            } else {
-                dt[f] = (T)0;
-                tn[f] = (T)2;   // never before the end of the segment
-            }
-        }
-        // cell of the first piece: along a, the one the segment enters from P
-        // (the top cell when the segment lies in the top plane of a)
-        b = 0;
-#pragma unroll
-        for (int a = 0; a < 3; ++a) {
-            const int sa = D[a] > (T)0 ? 1 : (D[a] < (T)0 ? -1 : 0);
-            int ca = D[a] < (T)0 ? (int)ceil(P[a]) - 1 : (int)floor(P[a]);
-            ca = min(max(ca, 0), g.n[a] - 2);
-            b += ca * g.stride[a];
-            db[a] = sa * g.stride[a];
-            w[a] = P[a] - (T)ca;
-            ws[a] = (T)sa;
-        }
-        tp = (T)0;
-        t = next_end();
-        acc = (T)0;
-        const T tm0 = (T)0.5 * t;
-        first = tet_sample(g, kt, b, w[0] + tm0 * D[0], w[1] + tm0 * D[1], w[2] + tm0 * D[2]);
-        return true;
-    }
-
-    __device__ __forceinline__ bool piece(const GridDev &g, const KappaSrc<T> &kt, const TetSample<T> &cur,
-                                          TetSample<T> &nxt) {
-        const bool last = t >= (T)1;
-#pragma unroll
-        for (int f = 0; f < 3; ++f)
-            if (tn[f] <= t) {
-                tn[f] += dt[f];
-                b += db[f];
-                w[f] -= ws[f];
-            }
-#pragma unroll
-        for (int f = 3; f < 6; ++f)
-            if (tn[f] <= t) tn[f] += dt[f];
-        const T tq = next_end();
-        const T tm = (T)0.5 * (t + tq);
-        nxt = tet_sample(g, kt, b, w[0] + tm * D[0], w[1] + tm * D[1], w[2] + tm * D[2]);
-        acc += (t - tp) * cur.value();
-        tp = t;
-        t = tq;
-        return last;
-    }
-
-    __device__ __forceinline__ T tau() const { return len * acc; }
-};
-
-// every piece advances at least one family: a segment has at most
-// sum_f |dF_f| + 7 <= 3 (|D0|+|D1|+|D2|) + 7 pieces
-__device__ __forceinline__ int march_cap(const GridDev &g) { return 3 * (g.n[0] + g.n[1] + g.n[2]) + 16; }
-
-// tau along the segment P -> Q given in grid coordinates, both in the closed
-// box.  The P1 kappa is linear between consecutive crossings of the six plane
-// families, so each piece contributes its length times kappa at its midpoint
-// (exact).  The next crossing time of family f advances by the constant
-// 1/|dF_f| per crossing; a crossing of family a (a < 3) moves the cell by one
-// along axis a, which updates its flat index and P's coordinates relative to
-// the cell corner.  Only the last crossing of a family can be taken a few
-// rounding units early (the segment ends on a vertex, that is on a plane of
-// every family); the piece that follows is of rounding length, and its
-// loads stay in bounds through the buffer resource.  The loop is software
-// pipelined: the kappa values of the next piece are loaded while the current
-// one is added (a piece of zero length, where two families cross together,
-// adds zero; after the last piece one more sample is loaded and unused).
-template <typename T>
-__device__ T tau_segment(const GridDev &g, const KappaSrc<T> &kt, const T P[3], const T Q[3]) {
-    March<T> m;
-    // two named samples in turn, so that no copy closes the loop
-    TetSample<T> sa, sb;
-    if (!m.start(g, kt, P, Q, sa)) return (T)0;
-    const int cap = march_cap(g);
-    for (int it = 0; it < cap; it += 2) {
-        if (m.piece(g, kt, sa, sb)) break;
-        if (m.piece(g, kt, sb, sa)) break;
-    }
-    return m.tau();
-}
-
+// ---------------------------------------------------------------- walls
 // Wall w's axis, side and coefficient, picked by selects over the constant
 // indices: an index into the grid's arrays that is not a compile-time constant
 // would copy the whole kernel argument to scratch memory.
@@ -298,26 +114,15 @@ __device__ __forceinline__ WallInfo wall_info(const GridDev &g, int w) {
     return r;
 }
 
-// Optical depth of the path from x (grid coords P) to wall w and on to y (Q),
-// the wall point being where the segment from the mirror image of x to y meets it.
-template <typename T>
-__device__ T tau_mirror(const GridDev &g, int w, const KappaSrc<T> &kt, const T P[3], const T Q[3]) {
+// optical depth of the path from x (grid index P) to wall w and on to y (Q)
+__device__ __forceinline__ double tau_mirror(const GridDev &g, int w, const KinkTab &kt, const int P[3],
+                                             const int Q[3]) {
     const WallInfo wi = wall_info(g, w);
-    const int a = wi.axis;
-    const T C = wi.side ? (T)(g.n[a] - 1) : (T)0;
-    T Pb[3] = {P[0], P[1], P[2]};
-    Pb[a] = (T)2 * C - P[a];
-    T X[3];
-    const T den = Q[a] - Pb[a];
-    if (den == (T)0) {
-        X[0] = Q[0]; X[1] = Q[1]; X[2] = Q[2];
-    } else {
-        const T t = (C - Pb[a]) / den;
+    int C = 0;
 #pragma unroll
-        for (int b = 0; b < 3; ++b) X[b] = Pb[b] + t * (Q[b] - Pb[b]);
-        X[a] = C;
-    }
-    return tau_segment(g, kt, P, X) + tau_segment(g, kt, X, Q);
+    for (int b = 0; b < 3; ++b)
+        if (b == wi.axis && wi.side) C = g.n[b] - 1;
+    return tau_reflected(g, kt, wi.axis, C, P, Q);
 }
 
 // grid index of the mirror image of vertex xi in wall w
@@ -461,19 +266,6 @@ __device__ __forceinline__ void vtx_index(const GridDev &g, int64_t v, int idx[3
     idx[2] = (int)(r - i1 * s1);
 }
 
-// ---------------------------------------------------------------- quadrature helpers
-// 1/x for the positive, normal distances of the quadrature: the hardware
-// reciprocal refined by two Newton steps (FP64: the seed's relative error e
-// becomes e^4, below one ulp), or the hardware reciprocal alone (FP32, one
-// ulp): cheaper than the IEEE division sequence.
-__device__ __forceinline__ double recip(double x) {
-    double r = __builtin_amdgcn_rcp(x);
-    r = fma(fma(-x, r, 1.0), r, r);
-    r = fma(fma(-x, r, 1.0), r, r);
-    return r;
-}
-__device__ __forceinline__ float recip(float x) { return __builtin_amdgcn_rcpf(x); }
-
 // ---------------------------------------------------------------- volume quadrature
 // Near field (grid offset d = x - x_j with |d_a| <= 2): the degree-5 rule's
 // sums, tabulated per mesh by cell and corner, so g is 64 products with the
@@ -593,23 +385,23 @@ __device__ __forceinline__ T vol_sum(const EntryCtx<T> &c, T att, const T att_w[
     return G * (T)g.vol_scale;
 }
 
-// The optical depths of a pair: direct, and R_w exp(-tau_w) per wall; a path
-// that the hole blocks has tau = +infinity (no march).  Pi, Qi: the vertices'
-// grid indices, P, Q the same as reals.
+// The attenuations of a pair: exp(-tau) along the direct path, and R_w
+// exp(-tau_w) per wall; a path that the hole blocks has tau = +infinity (no
+// march).  Pi, Qi: the vertices' grid indices.
 template <typename T, int NW>
-__device__ __forceinline__ T attenuations(const GridDev &g, const KappaSrc<T> &kt, const int Pi[3],
-                                          const int Qi[3], const T P[3], const T Q[3], T att_w[6]) {
+__device__ __forceinline__ T attenuations(const GridDev &g, const KinkTab &kt, const int Pi[3], const int Qi[3],
+                                          T att_w[6]) {
     if constexpr (NW == kAnyWalls) {
         const bool hole = g.has_hole;
-        const T att = (hole && hole_blocks(g, Pi, Qi)) ? (T)0 : exp(-tau_segment(g, kt, P, Q));
+        const T att = (hole && hole_blocks(g, Pi, Qi)) ? (T)0 : exp(-(T)tau_direct(g, kt, Pi, Qi));
         for (int w = 0; w < g.n_walls; ++w)
             att_w[w] = (hole && hole_blocks_mirror(g, w, Pi, Qi))
                            ? (T)0
-                           : (T)wall_info(g, w).R * exp(-tau_mirror(g, w, kt, P, Q));
+                           : (T)wall_info(g, w).R * exp(-(T)tau_mirror(g, w, kt, Pi, Qi));
         return att;
     } else {
-        const T att = exp(-tau_segment(g, kt, P, Q));
-        if constexpr (NW == kOneWall) att_w[0] = (T)g.R[0] * exp(-tau_mirror(g, 0, kt, P, Q));
+        const T att = exp(-(T)tau_direct(g, kt, Pi, Qi));
+        if constexpr (NW == kOneWall) att_w[0] = (T)g.R[0] * exp(-(T)tau_mirror(g, 0, kt, Pi, Qi));
         return att;
     }
 }
@@ -625,10 +417,8 @@ __device__ T volume_entry(const EntryCtx<T> &c, int64_t i, int64_t j) {
     vtx_index(g, j, jj);
     if constexpr (NW == kAnyWalls)
         if (!vertex_active(g, ii)) return (T)0;   // a removed vertex (its column: an empty star)
-    const T P[3] = {(T)ii[0], (T)ii[1], (T)ii[2]};
-    const T Q[3] = {(T)jj[0], (T)jj[1], (T)jj[2]};
     T att_w[6];
-    const T att = attenuations<T, NW>(g, kappa_src(c.ktet), ii, jj, P, Q, att_w);
+    const T att = attenuations<T, NW>(g, c.kink, ii, jj, att_w);
     return vol_sum<T, NW>(c, att, att_w, ii, jj);
 }
 
@@ -641,10 +431,8 @@ __device__ __forceinline__ void volume_entry_pair(const EntryCtx<T> &c, int64_t 
     int ii[3], jj[3];
     vtx_index(g, i, ii);
     vtx_index(g, j, jj);
-    const T P[3] = {(T)ii[0], (T)ii[1], (T)ii[2]};
-    const T Q[3] = {(T)jj[0], (T)jj[1], (T)jj[2]};
     T att_w[6];
-    const T att = attenuations<T, NW>(g, kappa_src(c.ktet), ii, jj, P, Q, att_w);
+    const T att = attenuations<T, NW>(g, c.kink, ii, jj, att_w);
     gij = vol_sum<T, NW>(c, att, att_w, ii, jj);
     gji = vol_sum<T, NW>(c, att, att_w, jj, ii);
     if constexpr (NW == kAnyWalls) {   // removed vertices have zero rows
@@ -849,12 +637,10 @@ __device__ T surface_entry(const EntryCtx<T> &c, int64_t i, int64_t l) {
     int ii[3], ll[3];
     vtx_index(g, i, ii);
     vtx_index(g, l, ll);
-    const T P[3] = {(T)ii[0], (T)ii[1], (T)ii[2]};
-    const T Q[3] = {(T)ll[0], (T)ll[1], (T)ll[2]};
     if constexpr (NW == kAnyWalls) {
         if (!vertex_active(g, ii)) return (T)0;   // a removed vertex
         T att_w[6];
-        const T att = attenuations<T, NW>(g, kappa_src(c.ktet), ii, ll, P, Q, att_w);
+        const T att = attenuations<T, NW>(g, c.kink, ii, ll, att_w);
         T S = att == (T)0 ? (T)0 : att * surf_quad_rects(c, ii, ll, cheb3(ii, ll) <= kNearCheb);
         for (int w = 0; w < g.n_walls; ++w) {
             if (att_w[w] == (T)0) continue;
@@ -864,12 +650,12 @@ __device__ T surface_entry(const EntryCtx<T> &c, int64_t i, int64_t l) {
         }
         return S;
     } else {
-        const KappaSrc<T> ks = kappa_src(c.ktet);
-        T S = exp(-tau_segment(g, ks, P, Q)) * surf_quad(c, ii, ll, cheb3(ii, ll) <= kNearCheb);
+        T att_w[6];
+        T S = attenuations<T, NW>(g, c.kink, ii, ll, att_w) * surf_quad(c, ii, ll, cheb3(ii, ll) <= kNearCheb);
         if constexpr (NW == kOneWall) {
             int mi[3];
             mirror_index(g, 0, ii, mi);
-            S += (T)g.R[0] * exp(-tau_mirror(g, 0, ks, P, Q)) * surf_quad(c, mi, ll, cheb3(mi, ll) <= kNearCheb);
+            S += att_w[0] * surf_quad(c, mi, ll, cheb3(mi, ll) <= kNearCheb);
         }
         return S;
     }

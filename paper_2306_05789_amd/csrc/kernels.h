@@ -113,19 +113,19 @@ struct EventTimer {
 };
 
 template <typename T> struct EntryCtx;
-// One band's absorption as the entry kernels read it: the vertex values and
-// the table the ray march samples (tet_table): FP32 the four vertex values
-// of every (cell base, Kuhn tetrahedron) pair, FP64 the eight corner values
-// of every cell base.
+// One band's absorption as the entry kernels read it: the vertex values in the
+// entries' type (quadrature) and in FP64 (ends of a ray), and the table of
+// their kinks (march.h).
 template <typename T>
 struct BandKappa {
-    const T *v;     // [N]
-    const T *tet;   // FP32 [N][6][4], FP64 [N][8]
+    const T *v;            // [N]
+    const double *v64;     // [N]
+    const double *kinks;   // [6][n0 + 1][n1 + 1][n2 + 1]
 };
 template <typename T> EntryCtx<T> make_ctx(const Mesh &m, BandKappa<T> kappa);
 // the march's table of `kappa` on the mesh, queued on s (scratch; the caller
 // keeps it until the launches that read it have run)
-template <typename T> DevBuf tet_table(const Mesh &m, const T *kappa, hipStream_t s);
+DevBuf kink_table(const Mesh &m, const double *kappa, hipStream_t s);
 void to_float(const double *in, float *out, int64_t n, hipStream_t s);
 // queues the fill on s without waiting: the task list and the launch's event
 // pair go to B.retire / B.fill_events (read by band_settle); split: write BF16 hi/lo
