@@ -762,7 +762,7 @@ void aca_batch(HMat &H, BandStore &B, BandKappa<T> kap, const std::vector<AcaTas
     st.cblock = cblock.as<int>();
     st.Us = Us.as<T>();
     st.Vs = Vs.as<T>();
-    auto c = make_ctx<T>(*H.mesh, kap);
+    auto c = make_ctx<T>(*H.mesh, H.kind, kap, s);
     const T eps = (T)H.opts.aca_eps;
     const int64_t *tn = H.tgt_nat.as<int64_t>(), *sn = H.src_nat.as<int64_t>();
     // every step raises a rank or consumes a zero row, so this bounds the steps

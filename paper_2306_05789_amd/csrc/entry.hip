@@ -124,19 +124,115 @@ DevBuf kink_table(const Mesh &m, const double *kappa, hipStream_t s) {
     return d;
 }
 
+// Row d of the star table (StarTab), from the mesh's near and far tables.
 template <typename T>
-EntryCtx<T> make_ctx(const Mesh &m, BandKappa<T> kappa) {
+__global__ __launch_bounds__(128) void k_star_table(GridDev g, StarTab st, int64_t rows, const double *__restrict__ near,
+                                                    T *__restrict__ w, T *__restrict__ cell) {
+    const int64_t row = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (row >= rows) return;
+    const int d[3] = {(int)(row / st.st0) + st.lo[0], (int)(row % st.st0 / st.st1) + st.lo[1],
+                      (int)(row % st.st1) + st.lo[2]};
+    const bool is_near = max(max(abs(d[0]), abs(d[1])), abs(d[2])) <= kNearCheb;
+    const double *nr = near + ((d[0] + 2) * 25 + (d[1] + 2) * 5 + (d[2] + 2)) * 64;
+    const double *far = near + kNearSize;
+    const double D2 = g.h[0] * g.h[0] * d[0] * d[0] + g.h[1] * g.h[1] * d[1] * d[1] + g.h[2] * g.h[2] * d[2] * d[2];
+    double sum[27];
+#pragma unroll
+    for (int v = 0; v < 27; ++v) sum[v] = 0.0;
+#pragma unroll
+    for (int bits = 0; bits < 8; ++bits) {
+        double c[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) c[e] = 0.0;
+        if (is_near) {
+#pragma unroll
+            for (int e = 0; e < 8; ++e) c[e] = nr[bits * 8 + e];
+        } else {
+#pragma unroll
+            for (int t = 0; t < kTets; ++t) {
+                if (kStar.tet[t].bits != bits) continue;
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const double *e = far + (t * 4 + q) * 8;
+                    const double r = 1.0 / (D2 + e[3] + e[0] * d[0] + e[1] * d[1] + e[2] * d[2]);
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) c[corner_of(kStar.tet[t].slot[k], bits)] += e[4 + k] * r;
+                }
+            }
+        }
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            sum[slot_of(e, bits)] += c[e];
+            cell[row * 64 + bits * 8 + e] = (T)(c[e] * g.vol_scale);
+        }
+    }
+#pragma unroll
+    for (int v = 0; v < kStarWeights; ++v) w[row * kStarWeights + v] = v < 15 ? (T)(sum[star_slot(v)] * g.vol_scale) : (T)0;
+}
+
+StarTab star_table(const Mesh &m, bool fp64, hipStream_t s) {
+    // checking aid: RTE_STAR_TABLE=0 in the environment sums the rules point by point
+    if (const char *e = std::getenv("RTE_STAR_TABLE"))
+        if (std::atoi(e) == 0) return StarTab{};
+    StarTab t;
+    const GridDev &g = m.dev;
+    int64_t n[3], rows = 1;
+    for (int a = 0; a < 3; ++a) {
+        int64_t lo = -(g.n[a] - 1), hi = g.n[a] - 1;   // mirror images reach one box further
+        for (int w = 0; w < g.n_walls; ++w)
+            if (g.wall_axis[w] == a) (g.wall_side[w] ? hi : lo) *= 2;
+        t.lo[a] = (int)lo;
+        n[a] = hi - lo + 1;
+        rows *= n[a];
+    }
+    const size_t esz = fp64 ? sizeof(double) : sizeof(float);
+    size_t free_b = 0, total_b = 0;
+    HIP_CHECK(hipMemGetInfo(&free_b, &total_b));
+    if ((double)rows * kStarRow * esz > total_b / 16.0) return StarTab{};
+    t.st0 = (int)(n[1] * n[2]);
+    t.st1 = (int)n[2];
+    int dev = 0;
+    HIP_CHECK(hipGetDevice(&dev));
+    const double *near = static_cast<const double *>(m.near_table(true));
+    std::lock_guard<std::mutex> lk(m.star->mu);
+    std::shared_ptr<DevBuf> &buf = m.star->dev[{dev, fp64}];
+    char *p = buf ? buf->as<char>() : nullptr;
+    if (!p) {
+        auto b = std::make_shared<DevBuf>();
+        try {
+            b->alloc((size_t)rows * kStarRow * esz);
+        } catch (const Error &) {   // no room for it now
+            (void)hipGetLastError();
+            return StarTab{};
+        }
+        p = b->as<char>();
+        const unsigned grid = (unsigned)((rows + 127) / 128);
+        if (fp64)
+            k_star_table<double><<<grid, 128, 0, s>>>(g, t, rows, near, (double *)p, (double *)p + rows * kStarWeights);
+        else k_star_table<float><<<grid, 128, 0, s>>>(g, t, rows, near, (float *)p, (float *)p + rows * kStarWeights);
+        HIP_LAUNCH_CHECK();
+        HIP_CHECK(hipStreamSynchronize(s));   // other streams read it from here on
+        buf = std::move(b);
+    }
+    t.w = p;
+    t.cell = p + (size_t)rows * kStarWeights * esz;
+    return t;
+}
+
+template <typename T>
+EntryCtx<T> make_ctx(const Mesh &m, int kind, BandKappa<T> kappa, hipStream_t s) {
     EntryCtx<T> c;
     c.g = m.dev;
     c.kappa = kappa.v;
     c.kink = KinkTab{kappa.kinks, kappa.v64};
     c.near = static_cast<const T *>(m.near_table(std::is_same<T, double>::value));
+    if (kind == RTE_VOLUME) c.star = star_table(m, std::is_same<T, double>::value, s);
     if constexpr (std::is_same<T, double>::value) c.st = stencil_device().d;
     else c.st = stencil_device().f;
     return c;
 }
-template EntryCtx<double> make_ctx<double>(const Mesh &, BandKappa<double>);
-template EntryCtx<float> make_ctx<float>(const Mesh &, BandKappa<float>);
+template EntryCtx<double> make_ctx<double>(const Mesh &, int, BandKappa<double>, hipStream_t);
+template EntryCtx<float> make_ctx<float>(const Mesh &, int, BandKappa<float>, hipStream_t);
 
 void entries_launch(const Mesh &m, int kind, const double *kappa, int64_t n, const int64_t *rows,
                     const int64_t *cols, double *out, int precision, hipStream_t s) {
@@ -144,7 +240,7 @@ void entries_launch(const Mesh &m, int kind, const double *kappa, int64_t n, con
     const unsigned grid = (unsigned)((n + 255) / 256);
     DevBuf kt = kink_table(m, kappa, s);
     if (precision == RTE_FP64) {
-        auto c = make_ctx<double>(m, BandKappa<double>{kappa, kappa, kt.as<double>()});
+        auto c = make_ctx<double>(m, kind, BandKappa<double>{kappa, kappa, kt.as<double>()}, s);
         if (kind == RTE_VOLUME) k_entries<double, RTE_VOLUME><<<grid, 256, 0, s>>>(c, n, rows, cols, out);
         else k_entries<double, RTE_SURFACE><<<grid, 256, 0, s>>>(c, n, rows, cols, out);
         HIP_LAUNCH_CHECK();
@@ -152,7 +248,7 @@ void entries_launch(const Mesh &m, int kind, const double *kappa, int64_t n, con
     } else {
         DevBuf kf(sizeof(float) * (size_t)m.N);
         to_float(kappa, kf.as<float>(), m.N, s);
-        auto c = make_ctx<float>(m, BandKappa<float>{kf.as<float>(), kappa, kt.as<double>()});
+        auto c = make_ctx<float>(m, kind, BandKappa<float>{kf.as<float>(), kappa, kt.as<double>()}, s);
         if (kind == RTE_VOLUME) k_entries<float, RTE_VOLUME><<<grid, 256, 0, s>>>(c, n, rows, cols, out);
         else k_entries<float, RTE_SURFACE><<<grid, 256, 0, s>>>(c, n, rows, cols, out);
         HIP_LAUNCH_CHECK();
@@ -177,7 +273,7 @@ void dense_fill_launch(const Mesh &m, int kind, BandKappa<T> kappa, const std::v
     if (order.size() > ((size_t)1 << 31) / fill_split<T>())
         throw std::runtime_error("dense fill: too many tasks for one grid");
     DevBuf dt = upload_scratch(order, s);
-    auto c = make_ctx<T>(m, kappa);
+    auto c = make_ctx<T>(m, kind, kappa, s);
     const FillTask *d = dt.as<FillTask>();
     const unsigned gp = (unsigned)(npair * fill_split<T>()), gs = (unsigned)((order.size() - npair) * fill_split<T>());
     const FillTask *ds = d + npair;

@@ -46,6 +46,7 @@ struct EntryCtx {
     KinkTab kink;                  // the march's table of kappa's kinks (FP64 for every T)
     StencilDev<T> st;
     const T *__restrict__ near;    // quadrature tables of the mesh: near [125][8][8], then far [24][4][8]
+    StarTab star;                  // the same by offset (null: not built)
 };
 
 // ---------------------------------------------------------------- compile-time Kuhn star
@@ -97,6 +98,25 @@ constexpr KuhnStar make_star() {
 }
 
 constexpr KuhnStar kStar = make_star();
+__device__ const KuhnStar kStarDev = make_star();   // for an index that is not a compile-time constant
+
+// Corner e (bits x, y, z) of the cell j - o (o the corner bits of j in it) as a
+// slot of the 3x3x3 block around j, and back.
+__host__ __device__ constexpr int slot_of(int e, int o) {
+    return ((e & 1) - (o & 1) + 1) * 9 + (((e >> 1) & 1) - ((o >> 1) & 1) + 1) * 3 + (((e >> 2) & 1) - ((o >> 2) & 1) + 1);
+}
+__host__ __device__ constexpr int corner_of(int slot, int o) {
+    return (slot / 9 - 1 + (o & 1)) | ((slot / 3 % 3 - 1 + ((o >> 1) & 1)) << 1) | ((slot % 3 - 1 + ((o >> 2) & 1)) << 2);
+}
+// Vertex v < 15 of the star: j + bits v of {0,1}^3 (v < 8), then j - bits v - 7.
+__host__ __device__ constexpr int star_slot(int v) { return v < 8 ? slot_of(v, 0) : slot_of(0, v - 7); }
+// does any tetrahedron around j in the cell j - o have the cell's corner e
+constexpr bool corner_used(int e, int o) {
+    for (int t = 0; t < kTets; ++t)
+        for (int k = 0; k < 4; ++k)
+            if (kStar.tet[t].bits == o && corner_of(kStar.tet[t].slot[k], o) == e) return true;
+    return false;
+}
 
 // ---------------------------------------------------------------- walls
 // Wall w's axis, side and coefficient, picked by selects over the constant
@@ -267,86 +287,119 @@ __device__ __forceinline__ void vtx_index(const GridDev &g, int64_t v, int idx[3
 }
 
 // ---------------------------------------------------------------- volume quadrature
-// Near field (grid offset d = x - x_j with |d_a| <= 2): the degree-5 rule's
-// sums, tabulated per mesh by cell and corner, so g is 64 products with the
-// star's kappa values (cells outside the grid skipped).
-template <typename T>
-__device__ __forceinline__ T vol_near(const T *__restrict__ tab, const T kn[27], int cellmask, const int d[3]) {
-    const T *row = tab + ((d[0] + 2) * 25 + (d[1] + 2) * 5 + (d[2] + 2)) * 64;
-    T acc = (T)0;
+// bit o: the cell j - o around vertex j lies in the grid
+__device__ __forceinline__ int cells_in_grid(const GridDev &g, const int jj[3]) {
+    int m = 0;
 #pragma unroll
-    for (int bits = 0; bits < 8; ++bits) {
-        if (!((cellmask >> bits) & 1)) continue;
-        const int o0 = bits & 1, o1 = (bits >> 1) & 1, o2 = (bits >> 2) & 1;
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            const int slot = ((e & 1) - o0 + 1) * 9 + (((e >> 1) & 1) - o1 + 1) * 3 + (((e >> 2) & 1) - o2 + 1);
-            acc += row[bits * 8 + e] * kn[slot];
-        }
-    }
-    return acc;
-}
-
-// Far field, one tetrahedron of the star: its 4 points' terms a_q / r_q added
-// over a common denominator, so one reciprocal serves the 4 points.
-template <typename T, int t>
-__device__ __forceinline__ void vol_far_tet(const T *__restrict__ ft, const T kn[27], int cellmask, T D2,
-                                            const T dg[3], T &acc) {
-    constexpr TetInfo ti = kStar.tet[t];
-    if (!((cellmask >> ti.bits) & 1)) return;
-    const T k0 = kn[ti.slot[0]], k1 = kn[ti.slot[1]], k2 = kn[ti.slot[2]], k3 = kn[ti.slot[3]];
-    const T *e = ft + t * 32;
-    T a[4], r[4];
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        r[q] = D2 + e[8 * q + 3] + e[8 * q + 0] * dg[0] + e[8 * q + 1] * dg[1] + e[8 * q + 2] * dg[2];
-        a[q] = e[8 * q + 4] * k0 + e[8 * q + 5] * k1 + e[8 * q + 6] * k2 + e[8 * q + 7] * k3;
-    }
-    const T n01 = a[0] * r[1] + a[1] * r[0], d01 = r[0] * r[1];
-    const T n23 = a[2] * r[3] + a[3] * r[2], d23 = r[2] * r[3];
-    acc += (n01 * d23 + n23 * d01) * recip(d01 * d23);
-}
-
-template <typename T, int... ts>
-__device__ __forceinline__ T vol_far_all(std::integer_sequence<int, ts...>, const T *__restrict__ ft, const T kn[27],
-                                         int cellmask, T D2, const T dg[3]) {
-    T acc = (T)0;
-    (vol_far_tet<T, ts>(ft, kn, cellmask, D2, dg, acc), ...);
-    return acc;
-}
-
-// g(x, j) without the 1/(4 pi)|e| factor; d = (x - x_j) in grid units
-template <typename T>
-__device__ __forceinline__ T vol_quad(const EntryCtx<T> &c, const T kn[27], int cellmask, const int d[3],
-                                      const T h2[3], bool near) {
-    if (near) return vol_near(c.near, kn, cellmask, d);
-    const T dg[3] = {(T)d[0], (T)d[1], (T)d[2]};
-    const T D2 = h2[0] * dg[0] * dg[0] + h2[1] * dg[1] * dg[1] + h2[2] * dg[2] * dg[2];
-    return vol_far_all<T>(std::make_integer_sequence<int, kTets>{}, c.near + kNearSize, kn, cellmask, D2, dg);
-}
-
-template <typename T>
-__device__ __forceinline__ void load_star(const EntryCtx<T> &c, const int jj[3], T kn[27], int &cellmask) {
-    const GridDev &g = c.g;
-    cellmask = 0;
-#pragma unroll
-    for (int bits = 0; bits < 8; ++bits) {
+    for (int o = 0; o < 8; ++o) {
         bool ok = true;
 #pragma unroll
-        for (int a = 0; a < 3; ++a) {
-            const int o = (bits >> a) & 1;
-            ok = ok && (o ? jj[a] >= 1 : jj[a] <= g.n[a] - 2);
+        for (int a = 0; a < 3; ++a) ok = ok && (((o >> a) & 1) ? jj[a] >= 1 : jj[a] <= g.n[a] - 2);
+        m |= ok ? (1 << o) : 0;
+    }
+    return m;
+}
+
+// kappa at the slot of the 3x3x3 block around vertex v (inside the grid)
+template <typename T>
+__device__ __forceinline__ T kappa_slot(const EntryCtx<T> &c, int64_t v, int slot) {
+    return c.kappa[v + (slot / 9 - 1) * c.g.stride[0] + (slot / 3 % 3 - 1) * c.g.stride[1] + (slot % 3 - 1)];
+}
+
+// g(x, j) point by point, for meshes without a star table (d = x - x_j, v the
+// flat index of j): near offsets from the near table, far ones by the degree-2
+// rule, |x - y|^2 = |h d|^2 + A.d + C per point and the 4 points of a
+// tetrahedron over one common denominator.
+template <typename T>
+__device__ __forceinline__ T vol_points(const EntryCtx<T> &c, int64_t v, int cellmask, const int d0, const int d1,
+                                     const int d2) {
+    const GridDev &g = c.g;
+    T acc = (T)0;
+    if (max(max(abs(d0), abs(d1)), abs(d2)) <= kNearCheb) {
+        const T *row = c.near + ((d0 + 2) * 25 + (d1 + 2) * 5 + (d2 + 2)) * 64;
+#pragma nounroll
+        for (int o = 0; o < 8; ++o) {
+            if (!((cellmask >> o) & 1)) continue;
+#pragma nounroll
+            for (int e = 0; e < 8; ++e) acc += row[o * 8 + e] * kappa_slot(c, v, slot_of(e, o));
         }
-        cellmask |= ok ? (1 << bits) : 0;
+        return acc * (T)g.vol_scale;
     }
+    const T x = (T)d0, y = (T)d1, z = (T)d2;
+    const T D2 = (T)(g.h[0] * g.h[0]) * x * x + (T)(g.h[1] * g.h[1]) * y * y + (T)(g.h[2] * g.h[2]) * z * z;
+#pragma nounroll
+    for (int t = 0; t < kTets; ++t) {
+        const TetInfo &ti = kStarDev.tet[t];
+        if (!((cellmask >> ti.bits) & 1)) continue;
+        const T k0 = kappa_slot(c, v, ti.slot[0]), k1 = kappa_slot(c, v, ti.slot[1]);
+        const T k2 = kappa_slot(c, v, ti.slot[2]), k3 = kappa_slot(c, v, ti.slot[3]);
+        const T *e = c.near + kNearSize + t * 32;
+        T a[4], r[4];
 #pragma unroll
-    for (int s = 0; s < 27; ++s) {
-        const int dx = s / 9 - 1, dy = (s / 3) % 3 - 1, dz = s % 3 - 1;
-        const int x = min(max(jj[0] + dx, 0), g.n[0] - 1);
-        const int y = min(max(jj[1] + dy, 0), g.n[1] - 1);
-        const int z = min(max(jj[2] + dz, 0), g.n[2] - 1);
-        kn[s] = c.kappa[x * g.stride[0] + y * g.stride[1] + z];
+        for (int q = 0; q < 4; ++q) {
+            r[q] = D2 + e[8 * q + 3] + e[8 * q + 0] * x + e[8 * q + 1] * y + e[8 * q + 2] * z;
+            a[q] = e[8 * q + 4] * k0 + e[8 * q + 5] * k1 + e[8 * q + 6] * k2 + e[8 * q + 7] * k3;
+        }
+        const T n01 = a[0] * r[1] + a[1] * r[0], d01 = r[0] * r[1];
+        const T n23 = a[2] * r[3] + a[3] * r[2], d23 = r[2] * r[3];
+        acc += (n01 * d23 + n23 * d01) * recip(d01 * d23);
     }
+    return acc * (T)g.vol_scale;
+}
+
+template <typename T, int o, int... es>
+__device__ __forceinline__ void cell_corners(std::integer_sequence<int, es...>, const EntryCtx<T> &c, int64_t v,
+                                             const T *__restrict__ row, T &acc) {
+    ((corner_used(es, o) ? (void)(acc += row[o * 8 + es] * kappa_slot(c, v, slot_of(es, o))) : (void)0), ...);
+}
+template <typename T, int... os>
+__device__ __forceinline__ T vol_cells(std::integer_sequence<int, os...>, const EntryCtx<T> &c, int64_t v, int cellmask,
+                                       const T *__restrict__ row) {
+    T acc = (T)0;
+    ((((cellmask >> os) & 1) ? cell_corners<T, os>(std::make_integer_sequence<int, 8>{}, c, v, row, acc) : (void)0), ...);
+    return acc;
+}
+
+// The star of a source vertex: its flat index, its cells, and for a whole star
+// kappa at its 15 vertices.
+template <typename T>
+struct Star {
+    int64_t v;
+    int cellmask;
+    T k[15];
+};
+
+// g(x_j + d, j): a row of the star table times kappa, 15 products and 128 (FP64)
+// or 64 (FP32) contiguous bytes per entry, where the points of the rule cost
+// about 1100 instructions (FP64, 24 tetrahedra); a source that misses cells (on
+// the boundary, at the hole) takes its cells' corner weights.  41^3: FP64 dense
+// fill 12.8 -> 7.7 ms, ACA entry launches 73.5 -> 70.4 (bound by the march);
+// 29^3 FP32 dense fill 7.1 -> 3.9.
+template <typename T>
+__device__ __forceinline__ T vol_quad(const EntryCtx<T> &c, const Star<T> &s, const int d[3]) {
+    if (!c.star.w) return vol_points(c, s.v, s.cellmask, d[0], d[1], d[2]);
+    const int64_t row = (int64_t)(d[0] - c.star.lo[0]) * c.star.st0 + (d[1] - c.star.lo[1]) * c.star.st1 +
+                        (d[2] - c.star.lo[2]);
+    if (s.cellmask != 255)
+        return vol_cells(std::make_integer_sequence<int, 8>{}, c, s.v, s.cellmask,
+                         static_cast<const T *>(c.star.cell) + row * 64);
+    const T *w = static_cast<const T *>(__builtin_assume_aligned(static_cast<const T *>(c.star.w) + row * kStarWeights, 64));
+    T acc = w[0] * s.k[0];
+#pragma unroll
+    for (int v = 1; v < 15; ++v) acc += w[v] * s.k[v];
+    return acc;
+}
+
+template <typename T>
+__device__ __forceinline__ Star<T> load_star(const EntryCtx<T> &c, const int jj[3], int cellmask) {
+    Star<T> s;
+    s.v = (int64_t)jj[0] * c.g.stride[0] + (int64_t)jj[1] * c.g.stride[1] + jj[2];
+    s.cellmask = cellmask;
+    if (cellmask == 255) {
+#pragma unroll
+        for (int v = 0; v < 15; ++v) s.k[v] = kappa_slot(c, s.v, star_slot(v));
+    }
+    return s;
 }
 
 // Wall modes the entry code is compiled for: no wall, exactly one wall (the
@@ -365,24 +418,22 @@ template <typename T, int NW>
 __device__ __forceinline__ T vol_sum(const EntryCtx<T> &c, T att, const T att_w[6], const int tt[3],
                                      const int ss[3]) {
     const GridDev &g = c.g;
-    const T h2[3] = {(T)(g.h[0] * g.h[0]), (T)(g.h[1] * g.h[1]), (T)(g.h[2] * g.h[2])};
-    T kn[27];
-    int cellmask;
-    load_star(c, ss, kn, cellmask);
+    int cellmask = cells_in_grid(g, ss);
     if constexpr (NW == kAnyWalls)
         if (g.has_hole) cellmask &= ~hole_cells(g, ss);   // the hole's cells are in no star
+    const Star<T> star = load_star(c, ss, cellmask);
     const int dg[3] = {tt[0] - ss[0], tt[1] - ss[1], tt[2] - ss[2]};
-    T G = att * vol_quad(c, kn, cellmask, dg, h2, cheb3(tt, ss) <= kNearCheb);
+    T G = att * vol_quad(c, star, dg);
     if constexpr (NW != kNoWall) {
         const int nw = NW == kOneWall ? 1 : g.n_walls;
         for (int w = 0; w < nw; ++w) {
             int mt[3];
             mirror_index(g, w, tt, mt);
             const int dgm[3] = {mt[0] - ss[0], mt[1] - ss[1], mt[2] - ss[2]};
-            G += att_w[w] * vol_quad(c, kn, cellmask, dgm, h2, cheb3(mt, ss) <= kNearCheb);
+            G += att_w[w] * vol_quad(c, star, dgm);
         }
     }
-    return G * (T)g.vol_scale;
+    return G;
 }
 
 // The attenuations of a pair: exp(-tau) along the direct path, and R_w

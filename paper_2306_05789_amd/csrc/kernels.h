@@ -122,7 +122,8 @@ struct BandKappa {
     const double *v64;     // [N]
     const double *kinks;   // [6][n0 + 1][n1 + 1][n2 + 1]
 };
-template <typename T> EntryCtx<T> make_ctx(const Mesh &m, BandKappa<T> kappa);
+// s: the stream on which the mesh's quadrature table is built if it is not yet there (volume entries)
+template <typename T> EntryCtx<T> make_ctx(const Mesh &m, int kind, BandKappa<T> kappa, hipStream_t s);
 // the march's table of `kappa` on the mesh, queued on s (scratch; the caller
 // keeps it until the launches that read it have run)
 DevBuf kink_table(const Mesh &m, const double *kappa, hipStream_t s);

@@ -103,6 +103,31 @@ struct NearTables {
     ~NearTables();
 };
 
+// Quadrature weights by the offset d = x - x_j of target and source: g(x, j) is
+// linear in kappa at the vertices of j's star with weights that depend on d and
+// the spacing alone.  Per d in the box [lo, lo + n) of offsets that a target or
+// one of its mirror images can have: 16 weights of the whole star (the 15
+// vertices j + {0,1}^3 and j - {0,1}^3 in the order of star_slot, then a zero), then,
+// for sources that miss cells, the weights of every cell's 8 corners
+// ([8 cells][8 corners]).  Near offsets hold the degree-5 rule's sums, the
+// others the degree-2 rule's; the factor |tet| / (4 pi) is folded in.  Built on
+// the GPU once per mesh, device and precision, owned by the mesh; null when it
+// would take more than a 16th of the device memory or does not fit it (the
+// quadrature is then summed point by point).
+constexpr int kStarWeights = 16, kStarRow = kStarWeights + 64;
+struct StarTab {
+    const void *w = nullptr;    // [rows][16]
+    const void *cell = nullptr; // [rows][8][8]
+    int lo[3] = {0, 0, 0}, st0 = 0, st1 = 0;   // row of d: (d0 - lo0) st0 + (d1 - lo1) st1 + (d2 - lo2)
+};
+struct Mesh;
+struct DevBuf;
+struct StarCache {
+    std::mutex mu;
+    std::map<std::pair<int, bool>, std::shared_ptr<DevBuf>> dev;   // (device, FP64)
+};
+StarTab star_table(const Mesh &m, bool fp64, hipStream_t s);   // built on s and waited for on first use (entry.hip)
+
 struct PlanCache;   // block-tree plans of a mesh (htree.cpp)
 
 // An emitting rectangle of the boundary: the plane x_a = plane (grid index),
@@ -120,6 +145,7 @@ struct Mesh {
     std::vector<int64_t> emitting;   // natural ids, ascending
     GridDev dev{};
     std::shared_ptr<NearTables> near;
+    std::shared_ptr<StarCache> star;
     std::shared_ptr<PlanCache> plans;
     const void *near_table(bool fp64) const;   // device copy on the current device
     std::vector<double> positions() const;            // [N][3]

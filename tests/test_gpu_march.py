@@ -4,6 +4,8 @@ axes, in planes of every family, through edges and vertices, on the upper
 faces (where the table continues kappa past the grid), grids of one cell and
 longer than wide, paths reflected at either side of every axis.  FP64 entries
 agree to 1e-12 as everywhere; FP32 ones to 1e-6 (1 + tau)."""
+import os
+
 import numpy as np
 import pytest
 import torch
@@ -18,9 +20,19 @@ GRIDS = [(2, 2, 2), (2, 9, 3), (6, 5, 7), (13, 3, 4)]
 WALLS = [None, [(0, 0, 0.5)], [(1, 1, 1.0)], [(0, 1, 0.7), (1, 0, 1.0), (2, 0, 0.4), (2, 1, 0.6)]]
 
 
+@pytest.fixture(params=["table", "points"])
+def quadrature(request):
+    """The volume quadrature from the mesh's table by offset, or summed point by
+    point (what a mesh too large for the table takes)."""
+    if request.param == "points":
+        os.environ["RTE_STAR_TABLE"] = "0"
+    yield request.param
+    os.environ.pop("RTE_STAR_TABLE", None)
+
+
 @pytest.mark.parametrize("n", GRIDS)
 @pytest.mark.parametrize("walls", WALLS, ids=["open", "x-", "y+", "four"])
-def test_every_pair_matches_oracle(n, walls):
+def test_every_pair_matches_oracle(n, walls, quadrature):
     g = Grid(n, (0.0, 0.0, 0.0), (1.0, 0.8, 1.3))
     kap = np.random.default_rng(sum(n)).uniform(0.05, 4.0, g.N)
     taken = {2 * a + s for a, s, _ in walls or []}
