@@ -23,6 +23,7 @@
 #include <algorithm>
 #include <map>
 #include <climits>
+#include <functional>
 #include <numeric>
 
 #include "entry_dev.h"
@@ -41,7 +42,7 @@ struct AcaState {
     int *k, *istar, *jstar, *status, *havepiv;
     int *hits;                  // per block: consecutive rank steps that met the stopping test
     int64_t *ents;              // per block: entries evaluated (rows and columns)
-    T *pivot, *normS2;
+    T *normS2;
     unsigned *used;             // row bitmaps
     const int64_t *ubase;       // first bitmap word of each block
     int64_t *rowoff, *coloff;   // [nb + 1] prefix sums of the active widths
@@ -52,15 +53,27 @@ struct AcaState {
     T *Us, *Vs;                 // U^T [kcap][m] and V^T [kcap][n] per block
     T *part;                    // per chunk: [2][half] partial dot products (half > every kcap)
     int half;                   // partials per kind in a chunk
-    T *pmax;                    // per chunk: |u| max and its signed value
+    T *pmax;                    // per chunk: |u| max
     int *pidx;                  // per chunk: row of the max
-    int *hint_r, *hint_c;       // per 256 row / column entries: position in act / act2 of the
+    int *hint_r, *hint_c;       // per workgroup of a row / column launch: position in act / act2 of the
                                 // block holding the first one (set after every scan)
     int *cblock;                // per update chunk: its block (set after every scan)
 };
 
 // elements of the concatenated (u_k, v_k) range of a block handled by one update chunk
 constexpr int kChunk = 1024;
+
+// Lanes per entry of k_aca_wide, and the lanes it may put on the chip: what four
+// wavefronts per SIMD hold, one round of waves (ACA entry launches of 13x21x13
+// with three walls 20.7 ms without it, 16.8 at 2^18 lanes, 18.6 at 2^17, 21.4 at
+// 2^20; of the 41^3 surface operator 20.4, 15.1, 15.3, 14.3); more than 8 lanes
+// per entry while a quarter of that holds them (33x17x17, one wall: 166 against
+// 168 ms).
+constexpr int kWideMin = 8, kWideMax = 32;
+constexpr int64_t kWideLanes = (int64_t)1 << 18;
+// Workgroups of k_aca_dots below which the rank indices of a chunk are split
+// over several (two per CU).
+constexpr int64_t kDotsFill = 512;
 
 template <typename T>
 __device__ __forceinline__ T wave_sum(T v) {
@@ -110,7 +123,6 @@ __global__ __launch_bounds__(256) void k_aca_init(AcaState<T> st) {
         st.havepiv[b] = 0;
         st.hits[b] = 0;
         st.normS2[b] = (T)0;
-        st.pivot[b] = (T)0;
         st.ents[b] = 0;
     }
     const int words = (st.task[b].m + 31) / 32;
@@ -178,15 +190,15 @@ __global__ __launch_bounds__(1024) void k_aca_scan(AcaState<T> st) {
     }
 }
 
-// For each run of 256 entries (one workgroup of the row or column launch):
+// For each run of `run` entries (one workgroup of the row or column launch):
 // the position in the active list of the block holding its first entry, so
 // that a lane finds its block by stepping forward over a few blocks instead
 // of a binary search over all of them.
 template <typename T, bool COLS>
-__global__ __launch_bounds__(256) void k_aca_hint(AcaState<T> st, int64_t nwg, int nact) {
+__global__ __launch_bounds__(256) void k_aca_hint(AcaState<T> st, int64_t nwg, int nact, int run) {
     const int64_t c = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (c >= nwg) return;
-    const int64_t e = c * 256;
+    const int64_t e = c * run;
     const int64_t *off = COLS ? st.coloff : st.rowoff;
     const int *list = COLS ? st.act2 : st.act;
     int lo = 0, hi = nact;   // first i with off[list[i] + 1] > e
@@ -278,7 +290,8 @@ __global__ __launch_bounds__(256, (entry_waves<T, KIND, NW>())) void k_aca_rows(
     V[(int64_t)k * tk.n + j] = a;
 }
 
-// Step 2: pivot column of each active block, or the next row after a zero row.
+// Step 2: pivot column of each active block and the scaled row v_k = r / r_{j*},
+// or the next row after a zero row.
 template <typename T>
 __global__ __launch_bounds__(256) void k_aca_pivot(AcaState<T> st) {
     __shared__ T sa[4], ss[4];
@@ -287,7 +300,7 @@ __global__ __launch_bounds__(256) void k_aca_pivot(AcaState<T> st) {
     if (st.status[b] != kActive) return;
     const AcaTask tk = st.task[b];
     const int k = st.k[b];
-    const T *V = st.Vs + tk.voff + (int64_t)k * tk.n;
+    T *V = st.Vs + tk.voff + (int64_t)k * tk.n;
     if (threadIdx.x == 0) st.ents[b] += tk.n;
     unsigned *bits = st.used + st.ubase[b];
     T best = (T)-1, sv = (T)0;
@@ -302,9 +315,10 @@ __global__ __launch_bounds__(256) void k_aca_pivot(AcaState<T> st) {
         bits[is >> 5] |= 1u << (is & 31);
     }
     if (best > (T)0) {
+        const T inv = (T)1 / sv;
+        for (int j = threadIdx.x; j < tk.n; j += 256) V[j] *= inv;
         if (threadIdx.x == 0) {
             st.jstar[b] = bj;
-            st.pivot[b] = sv;
             st.havepiv[b] = 1;
         }
         return;
@@ -343,29 +357,81 @@ __global__ __launch_bounds__(256, (entry_waves<T, KIND, NW>())) void k_aca_cols(
     const int k = st.k[b], js = st.jstar[b];
     T *U = st.Us + tk.uoff;
     const T *V = st.Vs + tk.voff;
-    // V_l(j*) for l < k is already scaled; V_k is scaled in step 4
     a = residual(a, V + js, tk.n, U + i, tk.m, k);
     U[(int64_t)k * tk.m + i] = a;
 }
 
-// Steps 4-5, first part: scale v_k and form the partial dot products
-// (u_l.u_k), (v_l.v_k), l <= k, and the partial argmax of |u_k| over unused
-// rows, on one chunk of the concatenated (u_k, v_k) range of a block.  The
-// chunk of (u_k, v_k) is staged in LDS (v_k scaled there and in memory).  For
-// l < k a group of P consecutive lanes owns rank index l: its lanes read
-// every P-th element of row l (contiguous across the group), and one
-// butterfly over the group ends the sum, for all groups of a wavefront at
-// once.  P is the largest power of two with 256 / P groups covering the k
-// indices (at most 64), but at least 8 (64 contiguous bytes of a row per
-// load; the 32 groups then take the k indices in passes).  The squares of
-// u_k and v_k (l = k) come from the staging pass.
+// Steps 1 and 3 for launches that leave most of the chip idle (the tail of a
+// batch, small operators, many walls): P lanes per entry share its ray
+// (group_entry) and the loads of the residual, whose terms are then subtracted
+// in order by every lane, so that an entry is that of the one-lane kernels bit
+// for bit and the choice between them (aca_batch) does not show in the factors.
+// Such a launch lasts as long as one entry, a chain of loads: 6 families of
+// about N / 4 batches each (13 legs of them with six walls), then k / 8 batches
+// of the residual.
+template <typename T, int KIND, int NW, bool COLS>
+__global__ __launch_bounds__(256, 3) void k_aca_wide(EntryCtx<T> c, AcaState<T> st, int64_t total, int P,
+                                                     const int64_t *__restrict__ tgt_nat,
+                                                     const int64_t *__restrict__ src_nat) {
+    constexpr int R = 4;   // residual terms in flight per lane
+    __shared__ double tasks[256 / kWideMin * kGroupTasks<NW>];
+    __shared__ T terms[256 * R][2];
+    const int tid = threadIdx.x, grp = tid / P, sub = tid - grp * P;
+    const int64_t e = (int64_t)blockIdx.x * (256 / P) + grp;
+    if (e >= total) return;   // groups leave together; no barrier spans groups
+    const int64_t *off = COLS ? st.coloff : st.rowoff;
+    const int b = hinted_block(off, COLS ? st.act2 : st.act, COLS ? st.hint_c : st.hint_r, e);
+    if (st.status[b] != kActive || (COLS && !st.havepiv[b])) return;
+    const AcaTask tk = st.task[b];
+    const int x = (int)(e - off[b]), k = st.k[b], y = COLS ? st.jstar[b] : st.istar[b];
+    T a = group_entry<T, KIND, NW>(c, tgt_nat[tk.t0 + (COLS ? x : y)], src_nat[tk.s0 + (COLS ? y : x)], P, sub,
+                                   tasks + grp * kGroupTasks<NW>);
+    T *U = st.Us + tk.uoff, *V = st.Vs + tk.voff;
+    // row: sum_l U_l(i*) V_l(x); column: sum_l V_l(j*) U_l(x)
+    const T *p = COLS ? V + y : U + y, *q = COLS ? U + x : V + x;
+    const int64_t sp = COLS ? tk.n : tk.m, sq = COLS ? tk.m : tk.n;
+    T(*mine)[2] = terms + grp * P * R;
+    for (int l0 = 0; l0 < k; l0 += P * R) {
+        T u[R], v[R];
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const int l = min(l0 + r * P + sub, k - 1);
+            u[r] = p[(int64_t)l * sp];
+            v[r] = q[(int64_t)l * sq];
+        }
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            mine[r * P + sub][0] = u[r];
+            mine[r * P + sub][1] = v[r];
+        }
+        group_sync();
+        const int n = min(P * R, k - l0);
+        for (int l = 0; l < n; ++l) a -= mine[l][0] * mine[l][1];
+        group_sync();
+    }
+    if (sub == 0) (COLS ? U : V)[(int64_t)k * sq + x] = a;
+}
+
+// Steps 4-5, first part: the partial dot products (u_l.u_k), (v_l.v_k), l <= k,
+// and the partial argmax of |u_k| over unused rows, on one chunk of the
+// concatenated (u_k, v_k) range of a block, staged in LDS.  For l < k a group of
+// P consecutive lanes owns rank index l: its lanes read every P-th element of
+// row l (contiguous across the group), and one butterfly over the group ends
+// the sum, for all groups of a wavefront at once.  P is the largest power of
+// two with 256 / P groups covering the k indices (at most 64), but at least 8
+// (64 contiguous bytes of a row per load; the 32 groups then take the k indices
+// in passes).  The squares of u_k and v_k (l = k) come from the staging pass.
+// With few chunks (the tail of a batch) `split` workgroups share a chunk, each
+// taking every split-th pass: a step of 4 blocks at rank 370 spent 125 us here
+// in 12 passes on 20 workgroups.
 template <typename T>
-__global__ __launch_bounds__(256) void k_aca_dots(AcaState<T> st) {
+__global__ __launch_bounds__(256) void k_aca_dots(AcaState<T> st, int split) {
     __shared__ T ck[kChunk];
     __shared__ T sq[2][4];
     __shared__ T sa[4], ss[4];
     __shared__ int si[4];
-    const int64_t c = blockIdx.x;
+    const int64_t c = blockIdx.x / split;
+    const int part_no = (int)(blockIdx.x - c * split);
     const int b = st.cblock[c];
     if (st.status[b] != kActive || !st.havepiv[b]) return;   // uniform over the workgroup
     const AcaTask tk = st.task[b];
@@ -373,10 +439,12 @@ __global__ __launch_bounds__(256) void k_aca_dots(AcaState<T> st) {
     const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
     const int e0 = (int)(c - st.chunkoff[b]) * kChunk;
     const int e1 = min(e0 + kChunk, m + n);
-    const T *U = st.Us + tk.uoff;
-    T *V = st.Vs + tk.voff;
+    const T *U = st.Us + tk.uoff, *V = st.Vs + tk.voff;
+    int P = 64;
+    while (P > 8 && 256 / P < k) P >>= 1;
+    const int G = 256 / P, g = tid / P, q = tid - g * P;
+    if (part_no > 0 && part_no * G >= k) return;
     const unsigned *bits = st.used + st.ubase[b];
-    const T inv = (T)1 / st.pivot[b];
     T bu = (T)-1, busv = (T)0, su = (T)0, sv = (T)0;
     int bi = INT_MAX;
     for (int e = e0 + tid; e < e1; e += 256) {
@@ -384,87 +452,89 @@ __global__ __launch_bounds__(256) void k_aca_dots(AcaState<T> st) {
             const T u = U[(int64_t)k * m + e];
             ck[e - e0] = u;
             su += u * u;
-            if (!is_used(bits, e) && fabs(u) > bu) { bu = fabs(u); bi = e; busv = u; }
+            if (part_no == 0 && !is_used(bits, e) && fabs(u) > bu) { bu = fabs(u); bi = e; busv = u; }
         } else {
-            T *vp = V + (int64_t)k * n + (e - m);
-            const T v = *vp * inv;
-            *vp = v;
+            const T v = V[(int64_t)k * n + (e - m)];
             ck[e - e0] = v;
             sv += v * v;
         }
     }
-    su = wave_sum(su);
-    sv = wave_sum(sv);
-    if (lane == 0) { sq[0][wid] = su; sq[1][wid] = sv; }
-    block_argmax(bu, bi, busv, sa, si, ss);   // its barriers publish ck and sq
     T *part = st.part + c * 2 * (int64_t)st.half;
-    if (k > 0) {
-        int P = 64;
-        while (P > 8 && 256 / P < k) P >>= 1;
-        const int G = 256 / P, g = tid / P, q = tid - g * P;
-        const int eu1 = min(e1, m), ev0 = max(e0, m);
-        for (int l0 = 0; l0 < k; l0 += G) {
-            const int l = l0 + g;
-            T pu = (T)0, pv = (T)0;
-            if (l < k) {
-                const T *ur = U + (int64_t)l * m;
-                const T *vr = V + (int64_t)l * n - m;
-#pragma unroll 8
-                for (int e = e0 + q; e < eu1; e += P) pu += ur[e] * ck[e - e0];
-#pragma unroll 8
-                for (int e = ev0 + q; e < e1; e += P) pv += vr[e] * ck[e - e0];
-            }
-            for (int o = P >> 1; o > 0; o >>= 1) {
-                pu += __shfl_xor(pu, o, 64);
-                pv += __shfl_xor(pv, o, 64);
-            }
-            if (l < k && q == 0) {
-                part[l] = pu;
-                part[st.half + l] = pv;
-            }
+    if (part_no == 0) {
+        su = wave_sum(su);
+        sv = wave_sum(sv);
+        if (lane == 0) { sq[0][wid] = su; sq[1][wid] = sv; }
+        block_argmax(bu, bi, busv, sa, si, ss);   // its barriers publish ck and sq
+        if (tid == 0) {
+            part[k] = ((sq[0][0] + sq[0][1]) + sq[0][2]) + sq[0][3];
+            part[st.half + k] = ((sq[1][0] + sq[1][1]) + sq[1][2]) + sq[1][3];
+            st.pmax[c] = bu;
+            st.pidx[c] = bi;
         }
+    } else {
+        __syncthreads();
     }
-    if (tid == 0) {
-        part[k] = ((sq[0][0] + sq[0][1]) + sq[0][2]) + sq[0][3];
-        part[st.half + k] = ((sq[1][0] + sq[1][1]) + sq[1][2]) + sq[1][3];
-        st.pmax[2 * c] = bu;
-        st.pmax[2 * c + 1] = busv;
-        st.pidx[c] = bi;
+    const int eu1 = min(e1, m), ev0 = max(e0, m);
+    for (int l0 = part_no * G; l0 < k; l0 += G * split) {
+        const int l = l0 + g;
+        T pu = (T)0, pv = (T)0;
+        if (l < k) {
+            const T *ur = U + (int64_t)l * m;
+            const T *vr = V + (int64_t)l * n - m;
+#pragma unroll 8
+            for (int e = e0 + q; e < eu1; e += P) pu += ur[e] * ck[e - e0];
+#pragma unroll 8
+            for (int e = ev0 + q; e < e1; e += P) pv += vr[e] * ck[e - e0];
+        }
+        for (int o = P >> 1; o > 0; o >>= 1) {
+            pu += __shfl_xor(pu, o, 64);
+            pv += __shfl_xor(pv, o, 64);
+        }
+        if (l < k && q == 0) {
+            part[l] = pu;
+            part[st.half + l] = pv;
+        }
     }
 }
 
 // Steps 4-5, second part: add the chunk partials in order, update ||S_k||,
-// test convergence and pick the next row.  One wavefront per pivoted block.
+// test convergence and pick the next row.  One workgroup per pivoted block.
 template <typename T>
-__global__ __launch_bounds__(64) void k_aca_finish(AcaState<T> st, T eps, int need) {
+__global__ __launch_bounds__(256) void k_aca_finish(AcaState<T> st, T eps, int need) {
+    __shared__ T sa[4], ss[4], sx[4];
+    __shared__ T last[2];
+    __shared__ int si[4];
     const int b = st.act2[blockIdx.x];
-    if (st.status[b] != kActive || !st.havepiv[b]) return;
+    if (st.status[b] != kActive || !st.havepiv[b]) return;   // uniform over the workgroup
     const AcaTask tk = st.task[b];
-    const int k = st.k[b], lane = threadIdx.x;
-    if (lane == 0) st.ents[b] += tk.m;
+    const int k = st.k[b], tid = threadIdx.x;
     const int64_t c0 = st.chunkoff[b], c1 = st.chunkoff[b + 1];
-    T cross = (T)0, u2 = (T)0, v2 = (T)0;
-    for (int l = lane; l <= k; l += 64) {
+    const int64_t row = 2 * (int64_t)st.half;
+    T cross = (T)0;
+    for (int l = tid; l <= k; l += 256) {
         T su = (T)0, sv = (T)0;
+#pragma unroll 4
         for (int64_t c = c0; c < c1; ++c) {
-            su += st.part[c * 2 * st.half + l];
-            sv += st.part[c * 2 * st.half + st.half + l];
+            su += st.part[c * row + l];
+            sv += st.part[c * row + st.half + l];
         }
         if (l < k) cross += su * sv;
-        else { u2 = su; v2 = sv; }
+        else { last[0] = su; last[1] = sv; }
     }
     cross = wave_sum(cross);
-    u2 = wave_sum(u2);
-    v2 = wave_sum(v2);
-    if (lane != 0) return;
-    T bu = (T)-1, busv = (T)0;
+    if ((tid & 63) == 0) sx[tid >> 6] = cross;
+    T bu = (T)-1, none = (T)0;
     int bi = INT_MAX;
-    for (int64_t c = c0; c < c1; ++c) {
-        const T a = st.pmax[2 * c];
+    for (int64_t c = c0 + tid; c < c1; c += 256) {
+        const T a = st.pmax[c];
         const int i = st.pidx[c];
-        if (a > bu || (a == bu && i < bi)) { bu = a; bi = i; busv = st.pmax[2 * c + 1]; }
+        if (a > bu || (a == bu && i < bi)) { bu = a; bi = i; }
     }
-    (void)busv;
+    block_argmax(bu, bi, none, sa, si, ss);   // its barriers publish sx and last
+    if (tid != 0) return;
+    st.ents[b] += tk.m;
+    const T u2 = last[0], v2 = last[1];
+    cross = ((sx[0] + sx[1]) + sx[2]) + sx[3];
     const T s2 = st.normS2[b] + u2 * v2 + (T)2 * cross;
     st.normS2[b] = s2;
     // the stopping test, met by `need` consecutive rank steps
@@ -717,17 +787,19 @@ void aca_batch(HMat &H, BandStore &B, BandKappa<T> kap, const std::vector<AcaTas
     int64_t max_chunks = 0;
     for (auto &t : tasks) max_chunks += (t.m + t.n + kChunk - 1) / kChunk;
     DevBuf ents = scratch(sizeof(int64_t) * (size_t)nb);
-    DevBuf ints = scratch(sizeof(int) * (size_t)nb * 8), reals = scratch(sizeof(T) * (size_t)nb * 2),
+    DevBuf ints = scratch(sizeof(int) * (size_t)nb * 8), reals = scratch(sizeof(T) * (size_t)nb),
            used = scratch(sizeof(unsigned) * (size_t)words), offs = scratch(sizeof(int64_t) * (size_t)(nb + 1) * 3),
            tot = scratch(sizeof(int64_t) * 5),
            part = scratch(sizeof(T) * (size_t)max_chunks * 2 * (size_t)(kmax + 1)),
-           pmax = scratch(sizeof(T) * (size_t)max_chunks * 2), pidx = scratch(sizeof(int) * (size_t)max_chunks);
+           pmax = scratch(sizeof(T) * (size_t)max_chunks), pidx = scratch(sizeof(int) * (size_t)max_chunks);
     int64_t sum_m = 0, sum_n = 0;
     for (auto &t : tasks) {
         sum_m += t.m;
         sum_n += t.n;
     }
-    DevBuf hints = scratch(sizeof(int) * (size_t)((sum_n + 255) / 256 + (sum_m + 255) / 256 + 2));
+    // a launch has a workgroup per 256 entries, or at most kWideLanes / 256
+    const int64_t wg_r = std::max((sum_n + 255) / 256, kWideLanes / 256) + 1, wg_c = std::max((sum_m + 255) / 256, kWideLanes / 256) + 1;
+    DevBuf hints = scratch(sizeof(int) * (size_t)(wg_r + wg_c));
     AcaState<T> st;
     st.task = dt.as<AcaTask>();
     st.nb = nb;
@@ -741,8 +813,7 @@ void aca_batch(HMat &H, BandStore &B, BandKappa<T> kap, const std::vector<AcaTas
     st.act2 = ip + 6 * nb;
     st.hits = ip + 7 * nb;
     st.ents = ents.as<int64_t>();
-    st.pivot = reals.as<T>();
-    st.normS2 = reals.as<T>() + nb;
+    st.normS2 = reals.as<T>();
     st.used = used.as<unsigned>();
     st.ubase = dub.as<int64_t>();
     st.rowoff = offs.as<int64_t>();
@@ -754,7 +825,7 @@ void aca_batch(HMat &H, BandStore &B, BandKappa<T> kap, const std::vector<AcaTas
     st.pmax = pmax.as<T>();
     st.pidx = pidx.as<int>();
     st.hint_r = hints.as<int>();
-    st.hint_c = hints.as<int>() + (sum_n + 255) / 256 + 1;
+    st.hint_c = hints.as<int>() + wg_r;
     DevBuf cblock = scratch(sizeof(int) * (size_t)std::max<int64_t>(max_chunks, 1));
     // pooled scratch holds what an earlier batch left: the checking aid fills it with NaN bytes
     for (DevBuf *d : {&Us, &Vs, &ents, &ints, &reals, &used, &offs, &tot, &part, &pmax, &pidx, &hints, &cblock})
@@ -787,6 +858,9 @@ void aca_batch(HMat &H, BandStore &B, BandKappa<T> kap, const std::vector<AcaTas
     // blocks that have stopped, so a step costs five launches and no host
     // synchronisation.
     constexpr int kCompact = 8;
+    // checking aid: RTE_ACA_WIDE=0 in the environment keeps every launch at one lane per entry
+    const char *wide_env = std::getenv("RTE_ACA_WIDE");
+    const bool wide_on = !wide_env || std::atoi(wide_env) != 0;
     int64_t ht[5];
     for (int step = 0; step <= max_steps;) {
         k_aca_scan<T, false><<<1, 1024, 0, s>>>(st);
@@ -796,37 +870,43 @@ void aca_batch(HMat &H, BandStore &B, BandKappa<T> kap, const std::vector<AcaTas
         HIP_CHECK(hipStreamSynchronize(s));
         if (ht[1] == 0) break;
         const int64_t nrow = ht[0], nact = ht[1], ncol = ht[2], nchunk = ht[4];
-        const int64_t wr = (nrow + 255) / 256, wc = (ncol + 255) / 256;
-        k_aca_hint<T, false><<<(unsigned)((wr + 255) / 256), 256, 0, s>>>(st, wr, (int)nact);
-        k_aca_hint<T, true><<<(unsigned)((wc + 255) / 256), 256, 0, s>>>(st, wc, (int)ht[3]);
+        // lanes per entry: 1, or as many of 8 .. 32 as fit the chip at once (an
+        // open mesh has 6 families to share, so 8)
+        const int wm = wall_mode(c.g);
+        auto lanes = [&](int64_t n) {
+            int P = wm == kNoWall ? kWideMin : kWideMax;
+            while (P > kWideMin && n * P > kWideLanes / 4) P >>= 1;
+            return wide_on && n * P <= kWideLanes ? P : 1;
+        };
+        const int Pr = lanes(nrow), Pc = lanes(ncol);
+        const int64_t wr = (nrow * Pr + 255) / 256, wc = (ncol * Pc + 255) / 256;
+        const int split = (int)std::max<int64_t>(1, std::min<int64_t>(16, kDotsFill / std::max<int64_t>(nchunk, 1)));
+        k_aca_hint<T, false><<<(unsigned)((wr + 255) / 256), 256, 0, s>>>(st, wr, (int)nact, 256 / Pr);
+        k_aca_hint<T, true><<<(unsigned)((wc + 255) / 256), 256, 0, s>>>(st, wc, (int)ht[3], 256 / Pc);
         k_aca_chunk_block<T><<<(unsigned)((nchunk + 255) / 256), 256, 0, s>>>(st, nchunk, (int)ht[3]);
         HIP_LAUNCH_CHECK();
-        // the entry launches, compiled for the mesh's wall mode (no wall, one, several)
-        const int wm = wall_mode(c.g);
-        auto rows = [&](auto kernel) { kernel<<<(unsigned)((nrow + 255) / 256), 256, 0, s>>>(c, st, nrow, tn, sn); };
-        auto cols = [&](auto kernel) { kernel<<<(unsigned)((ncol + 255) / 256), 256, 0, s>>>(c, st, ncol, tn, sn); };
-        auto launch_rows = [&]() {
-            if (H.kind == RTE_VOLUME) {
-                if (wm == kNoWall) rows(k_aca_rows<T, RTE_VOLUME, kNoWall>);
-                else if (wm == kOneWall) rows(k_aca_rows<T, RTE_VOLUME, kOneWall>);
-                else rows(k_aca_rows<T, RTE_VOLUME, kAnyWalls>);
-            } else {
-                if (wm == kNoWall) rows(k_aca_rows<T, RTE_SURFACE, kNoWall>);
-                else if (wm == kOneWall) rows(k_aca_rows<T, RTE_SURFACE, kOneWall>);
-                else rows(k_aca_rows<T, RTE_SURFACE, kAnyWalls>);
-            }
+        std::function<void()> launch_rows, launch_cols;
+        // the entry launches, compiled for the operator's kind and the mesh's wall mode (no wall, one, several)
+        auto entries = [&](auto kind, auto nw) {
+            constexpr int KIND = decltype(kind)::value, NW = decltype(nw)::value;
+            auto rows = [=]() {
+                if (Pr > 1) k_aca_wide<T, KIND, NW, false><<<(unsigned)wr, 256, 0, s>>>(c, st, nrow, Pr, tn, sn);
+                else k_aca_rows<T, KIND, NW><<<(unsigned)wr, 256, 0, s>>>(c, st, nrow, tn, sn);
+            };
+            auto cols = [=]() {
+                if (Pc > 1) k_aca_wide<T, KIND, NW, true><<<(unsigned)wc, 256, 0, s>>>(c, st, ncol, Pc, tn, sn);
+                else k_aca_cols<T, KIND, NW><<<(unsigned)wc, 256, 0, s>>>(c, st, ncol, tn, sn);
+            };
+            launch_rows = rows;
+            launch_cols = cols;
         };
-        auto launch_cols = [&]() {
-            if (H.kind == RTE_VOLUME) {
-                if (wm == kNoWall) cols(k_aca_cols<T, RTE_VOLUME, kNoWall>);
-                else if (wm == kOneWall) cols(k_aca_cols<T, RTE_VOLUME, kOneWall>);
-                else cols(k_aca_cols<T, RTE_VOLUME, kAnyWalls>);
-            } else {
-                if (wm == kNoWall) cols(k_aca_cols<T, RTE_SURFACE, kNoWall>);
-                else if (wm == kOneWall) cols(k_aca_cols<T, RTE_SURFACE, kOneWall>);
-                else cols(k_aca_cols<T, RTE_SURFACE, kAnyWalls>);
-            }
+        auto by_walls = [&](auto kind) {
+            if (wm == kNoWall) entries(kind, std::integral_constant<int, kNoWall>());
+            else if (wm == kOneWall) entries(kind, std::integral_constant<int, kOneWall>());
+            else entries(kind, std::integral_constant<int, kAnyWalls>());
         };
+        if (H.kind == RTE_VOLUME) by_walls(std::integral_constant<int, RTE_VOLUME>());
+        else by_walls(std::integral_constant<int, RTE_SURFACE>());
         for (int r = 0; r < kCompact && step <= max_steps; ++r, ++step) {
             mark();
             launch_rows();
@@ -838,8 +918,8 @@ void aca_batch(HMat &H, BandStore &B, BandKappa<T> kap, const std::vector<AcaTas
             launch_cols();
             HIP_LAUNCH_CHECK();
             mark();
-            k_aca_dots<T><<<(unsigned)nchunk, 256, 0, s>>>(st);
-            k_aca_finish<T><<<(unsigned)nact, 64, 0, s>>>(st, eps, std::max(1, H.opts.aca_hits));
+            k_aca_dots<T><<<(unsigned)(nchunk * split), 256, 0, s>>>(st, split);
+            k_aca_finish<T><<<(unsigned)nact, 256, 0, s>>>(st, eps, std::max(1, H.opts.aca_hits));
             HIP_LAUNCH_CHECK();
             launches += 2;
         }

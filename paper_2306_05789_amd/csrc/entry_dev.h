@@ -134,15 +134,20 @@ __device__ __forceinline__ WallInfo wall_info(const GridDev &g, int w) {
     return r;
 }
 
-// optical depth of the path from x (grid index P) to wall w and on to y (Q)
-__device__ __forceinline__ double tau_mirror(const GridDev &g, int w, const KinkTab &kt, const int P[3],
-                                             const int Q[3]) {
-    const WallInfo wi = wall_info(g, w);
+// grid index of the wall's plane along its axis
+__device__ __forceinline__ int wall_plane(const GridDev &g, const WallInfo &wi) {
     int C = 0;
 #pragma unroll
     for (int b = 0; b < 3; ++b)
         if (b == wi.axis && wi.side) C = g.n[b] - 1;
-    return tau_reflected(g, kt, wi.axis, C, P, Q);
+    return C;
+}
+
+// optical depth of the path from x (grid index P) to wall w and on to y (Q)
+__device__ __forceinline__ double tau_mirror(const GridDev &g, int w, const KinkTab &kt, const int P[3],
+                                             const int Q[3]) {
+    const WallInfo wi = wall_info(g, w);
+    return tau_reflected(g, kt, wi.axis, wall_plane(g, wi), P, Q);
 }
 
 // grid index of the mirror image of vertex xi in wall w
@@ -350,7 +355,7 @@ __device__ __forceinline__ T vol_points(const EntryCtx<T> &c, int64_t v, int cel
 template <typename T, int o, int... es>
 __device__ __forceinline__ void cell_corners(std::integer_sequence<int, es...>, const EntryCtx<T> &c, int64_t v,
                                              const T *__restrict__ row, T &acc) {
-    ((corner_used(es, o) ? (void)(acc += row[o * 8 + es] * kappa_slot(c, v, slot_of(es, o))) : (void)0), ...);
+    ((corner_used(es, o) ? (void)(acc = fma(row[o * 8 + es], kappa_slot(c, v, slot_of(es, o)), acc)) : (void)0), ...);
 }
 template <typename T, int... os>
 __device__ __forceinline__ T vol_cells(std::integer_sequence<int, os...>, const EntryCtx<T> &c, int64_t v, int cellmask,
@@ -384,9 +389,9 @@ __device__ __forceinline__ T vol_quad(const EntryCtx<T> &c, const Star<T> &s, co
         return vol_cells(std::make_integer_sequence<int, 8>{}, c, s.v, s.cellmask,
                          static_cast<const T *>(c.star.cell) + row * 64);
     const T *w = static_cast<const T *>(__builtin_assume_aligned(static_cast<const T *>(c.star.w) + row * kStarWeights, 64));
-    T acc = w[0] * s.k[0];
+    T acc = (T)0;   // explicit fma: the same sum wherever it is inlined
 #pragma unroll
-    for (int v = 1; v < 15; ++v) acc += w[v] * s.k[v];
+    for (int v = 0; v < 15; ++v) acc = fma(w[v], s.k[v], acc);
     return acc;
 }
 
@@ -423,7 +428,7 @@ __device__ __forceinline__ T vol_sum(const EntryCtx<T> &c, T att, const T att_w[
         if (g.has_hole) cellmask &= ~hole_cells(g, ss);   // the hole's cells are in no star
     const Star<T> star = load_star(c, ss, cellmask);
     const int dg[3] = {tt[0] - ss[0], tt[1] - ss[1], tt[2] - ss[2]};
-    T G = att * vol_quad(c, star, dg);
+    T G = rounded_product(att, vol_quad(c, star, dg));
     if constexpr (NW != kNoWall) {
         const int nw = NW == kOneWall ? 1 : g.n_walls;
         for (int w = 0; w < nw; ++w) {
@@ -455,6 +460,57 @@ __device__ __forceinline__ T attenuations(const GridDev &g, const KinkTab &kt, c
         if constexpr (NW == kOneWall) att_w[0] = (T)g.R[0] * exp(-(T)tau_mirror(g, 0, kt, Pi, Qi));
         return att;
     }
+}
+
+// The same for a group of P lanes of one wavefront (P a power of two, lane
+// number `sub`) that share the pair: the families of every leg of every path
+// are dealt to the lanes and added in the order of kink_sum, so that the
+// attenuations are those of a single lane bit for bit.  buf: LDS of the group,
+// kGroupTasks<NW> values.
+template <int NW>
+constexpr int kGroupTasks = 6 * (1 + 2 * NW);
+__device__ __forceinline__ void group_sync() {   // orders the LDS accesses of a wavefront
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+template <typename T, int NW>
+__device__ __forceinline__ T group_attenuations(const GridDev &g, const KinkTab &kt, const int Pi[3], const int Qi[3],
+                                                T att_w[6], int P, int sub, double *buf) {
+    const int nw = NW == kAnyWalls ? g.n_walls : NW;
+    for (int t = sub; t < 6 * (1 + 2 * nw); t += P) {
+        const int leg = t / 6, f = t - 6 * leg;
+        int V[3] = {Pi[0], Pi[1], Pi[2]}, D[3] = {Qi[0] - Pi[0], Qi[1] - Pi[1], Qi[2] - Pi[2]}, p = 1, M = 1;
+        if (NW != kNoWall && leg > 0) {
+            const WallInfo wi = wall_info(g, (leg - 1) >> 1);
+            const Legs l = reflect_legs(wi.axis, wall_plane(g, wi), Pi, Qi);
+            const bool from_q = (leg & 1) == 0;
+            M = l.p + l.q;
+            p = from_q ? l.q : l.p;
+#pragma unroll
+            for (int b = 0; b < 3; ++b) {
+                V[b] = from_q ? Qi[b] : Pi[b];
+                D[b] = from_q ? l.D2[b] : l.D1[b];
+            }
+            if (M == 0) p = M = 1;   // both on the wall: the direct depth is taken below
+        }
+        buf[t] = kink_one(g, kt.tab, V, D, p, M, f);
+    }
+    group_sync();
+    const double direct = direct_depth(g, kt, Pi, Qi, add_families(buf));
+    const bool hole = NW == kAnyWalls && g.has_hole;
+    const T att = hole && hole_blocks(g, Pi, Qi) ? (T)0 : exp(-(T)direct);
+    if constexpr (NW != kNoWall) {
+        for (int w = 0; w < nw; ++w) {
+            const WallInfo wi = wall_info(g, w);
+            const int C = wall_plane(g, wi);
+            const Legs l = reflect_legs(wi.axis, C, Pi, Qi);
+            const double *b = buf + 6 + 12 * w;
+            const double tau = l.p + l.q == 0 ? direct
+                                              : reflected_depth(g, kt, wi.axis, C, Pi, Qi, l, add_families(b) + add_families(b + 6));
+            att_w[w] = hole && hole_blocks_mirror(g, w, Pi, Qi) ? (T)0 : (T)wi.R * exp(-(T)tau);
+        }
+    }
+    return att;
 }
 
 // G(i, j).  Every wall adds its own mirror-image term (one reflection per
@@ -534,46 +590,47 @@ template <typename T>
 __device__ T surf_quad(const EntryCtx<T> &c, const int xi[3], const int ll[3], bool near) {
     const GridDev &g = c.g;
     T acc = (T)0;
-#pragma unroll
+#pragma nounroll
     for (int f = 0; f < 6; ++f) {
         if (!((g.emit_faces >> f) & 1u)) continue;
-        const int a = f / 2;
-        const int pf = (f & 1) ? g.n[a] - 1 : 0;
-        if (ll[a] != pf) continue;
-        const int b = (a == 0) ? 1 : 0;
-        const int cc = (a == 2) ? 1 : 2;
-        if (xi[a] == pf) {
+        // the face's axis a and its other axes b < cc, by selects (an index into the grid's
+        // arrays that is not a compile-time constant copies the kernel argument to scratch)
+        const bool a0 = f < 2, a2 = f >= 4;
+        const int na = a0 ? g.n[0] : (a2 ? g.n[2] : g.n[1]), nb = a0 ? g.n[1] : g.n[0], nc = a2 ? g.n[1] : g.n[2];
+        const int la = a0 ? ll[0] : (a2 ? ll[2] : ll[1]), lb = a0 ? ll[1] : ll[0], lc = a2 ? ll[1] : ll[2];
+        const int xa = a0 ? xi[0] : (a2 ? xi[2] : xi[1]), xb = a0 ? xi[1] : xi[0], xc = a2 ? xi[1] : xi[2];
+        const int pf = (f & 1) ? na - 1 : 0;
+        if (la != pf) continue;
+        if (xa == pf) {
             // coplanar limit: theta_F(x)/(4 pi) on the diagonal (isotropic), half
             // that for the cosine-weighted source
-            if (xi[0] == ll[0] && xi[1] == ll[1] && xi[2] == ll[2]) {
+            if (xb == lb && xc == lc) {
                 T frac = (T)1;
-                const int axes[2] = {b, cc};
-#pragma unroll
-                for (int k = 0; k < 2; ++k) {
-                    const int p = xi[axes[k]];
-                    if (p < 0 || p > g.n[axes[k]] - 1) frac = (T)0;
-                    else if (p == 0 || p == g.n[axes[k]] - 1) frac *= (T)0.5;
-                }
+                if (xb < 0 || xb > nb - 1) frac = (T)0;
+                else if (xb == 0 || xb == nb - 1) frac *= (T)0.5;
+                if (xc < 0 || xc > nc - 1) frac = (T)0;
+                else if (xc == 0 || xc == nc - 1) frac *= (T)0.5;
                 acc += (g.emission ? (T)0.25 : (T)0.5) * frac;
             }
             continue;
         }
-        const T da = (T)(xi[a] - pf) * (T)g.h[a];
+        const double ha = a0 ? g.h[0] : (a2 ? g.h[2] : g.h[1]), hb = a0 ? g.h[1] : g.h[0], hc = a2 ? g.h[1] : g.h[2];
+        const T da = (T)(xa - pf) * (T)ha;
         const T da2 = da * da;
-        const T hb2 = (T)(g.h[b] * g.h[b]), hc2 = (T)(g.h[cc] * g.h[cc]);
-        const T db = (T)(xi[b] - ll[b]), dc = (T)(xi[cc] - ll[cc]);
+        const T hb2 = (T)(hb * hb), hc2 = (T)(hc * hc);
+        const T db = (T)(xb - lb), dc = (T)(xc - lc);
         constexpr auto seq = std::make_integer_sequence<int, kTris>{};
         T s;
         if (g.emission) {
-            s = near ? tri_all<T, 7, true>(seq, c.st.tri_near, ll[b], ll[cc], g.n[b], g.n[cc], db, dc, da2, hb2, hc2)
-                     : tri_all<T, 3, true>(seq, c.st.tri_far, ll[b], ll[cc], g.n[b], g.n[cc], db, dc, da2, hb2, hc2);
+            s = near ? tri_all<T, 7, true>(seq, c.st.tri_near, lb, lc, nb, nc, db, dc, da2, hb2, hc2)
+                     : tri_all<T, 3, true>(seq, c.st.tri_far, lb, lc, nb, nc, db, dc, da2, hb2, hc2);
             s *= da2;
         } else {
-            s = near ? tri_all<T, 7, false>(seq, c.st.tri_near, ll[b], ll[cc], g.n[b], g.n[cc], db, dc, da2, hb2, hc2)
-                     : tri_all<T, 3, false>(seq, c.st.tri_far, ll[b], ll[cc], g.n[b], g.n[cc], db, dc, da2, hb2, hc2);
+            s = near ? tri_all<T, 7, false>(seq, c.st.tri_near, lb, lc, nb, nc, db, dc, da2, hb2, hc2)
+                     : tri_all<T, 3, false>(seq, c.st.tri_far, lb, lc, nb, nc, db, dc, da2, hb2, hc2);
             s *= fabs(da);
         }
-        acc += s * (T)g.area_scale[a];
+        acc += s * (T)(a0 ? g.area_scale[0] : (a2 ? g.area_scale[2] : g.area_scale[1]));
     }
     return acc;
 }
@@ -682,17 +739,12 @@ __device__ T surf_quad_rects(const EntryCtx<T> &c, const int xi[3], const int ll
     return acc;
 }
 
-template <typename T, int NW = kAnyWalls>
-__device__ T surface_entry(const EntryCtx<T> &c, int64_t i, int64_t l) {
+// S(i, l) from the attenuations of the pair
+template <typename T, int NW>
+__device__ __forceinline__ T surf_sum(const EntryCtx<T> &c, T att, const T att_w[6], const int ii[3], const int ll[3]) {
     const GridDev &g = c.g;
-    int ii[3], ll[3];
-    vtx_index(g, i, ii);
-    vtx_index(g, l, ll);
     if constexpr (NW == kAnyWalls) {
-        if (!vertex_active(g, ii)) return (T)0;   // a removed vertex
-        T att_w[6];
-        const T att = attenuations<T, NW>(g, c.kink, ii, ll, att_w);
-        T S = att == (T)0 ? (T)0 : att * surf_quad_rects(c, ii, ll, cheb3(ii, ll) <= kNearCheb);
+        T S = att == (T)0 ? (T)0 : rounded_product(att, surf_quad_rects(c, ii, ll, cheb3(ii, ll) <= kNearCheb));
         for (int w = 0; w < g.n_walls; ++w) {
             if (att_w[w] == (T)0) continue;
             int mi[3];
@@ -701,8 +753,7 @@ __device__ T surface_entry(const EntryCtx<T> &c, int64_t i, int64_t l) {
         }
         return S;
     } else {
-        T att_w[6];
-        T S = attenuations<T, NW>(g, c.kink, ii, ll, att_w) * surf_quad(c, ii, ll, cheb3(ii, ll) <= kNearCheb);
+        T S = rounded_product(att, surf_quad(c, ii, ll, cheb3(ii, ll) <= kNearCheb));
         if constexpr (NW == kOneWall) {
             int mi[3];
             mirror_index(g, 0, ii, mi);
@@ -712,10 +763,39 @@ __device__ T surface_entry(const EntryCtx<T> &c, int64_t i, int64_t l) {
     }
 }
 
+template <typename T, int NW = kAnyWalls>
+__device__ T surface_entry(const EntryCtx<T> &c, int64_t i, int64_t l) {
+    const GridDev &g = c.g;
+    int ii[3], ll[3];
+    vtx_index(g, i, ii);
+    vtx_index(g, l, ll);
+    if constexpr (NW == kAnyWalls)
+        if (!vertex_active(g, ii)) return (T)0;   // a removed vertex
+    T att_w[6];
+    const T att = attenuations<T, NW>(g, c.kink, ii, ll, att_w);
+    return surf_sum<T, NW>(c, att, att_w, ii, ll);
+}
+
 template <typename T, int KIND, int NW = kAnyWalls>
 __device__ __forceinline__ T entry(const EntryCtx<T> &c, int64_t i, int64_t j) {
     if constexpr (KIND == RTE_VOLUME) return volume_entry<T, NW>(c, i, j);
     else return surface_entry<T, NW>(c, i, j);
+}
+
+// The entry of a pair shared by a group of P lanes (group_attenuations); every
+// lane returns it.
+template <typename T, int KIND, int NW>
+__device__ __forceinline__ T group_entry(const EntryCtx<T> &c, int64_t i, int64_t j, int P, int sub, double *buf) {
+    const GridDev &g = c.g;
+    int ii[3], jj[3];
+    vtx_index(g, i, ii);
+    vtx_index(g, j, jj);
+    if constexpr (NW == kAnyWalls)
+        if (!vertex_active(g, ii)) return (T)0;   // a removed vertex
+    T att_w[6];
+    const T att = group_attenuations<T, NW>(g, c.kink, ii, jj, att_w, P, sub, buf);
+    if constexpr (KIND == RTE_VOLUME) return vol_sum<T, NW>(c, att, att_w, ii, jj);
+    else return surf_sum<T, NW>(c, att, att_w, ii, jj);
 }
 
 }  // namespace rte

@@ -47,12 +47,22 @@ struct KinkTab {
 
 // Crossings in flight per loop step of a family: their loads are independent
 // (the indices need no loaded value), so this many are issued before the first
-// is used.
-constexpr int kMarchAhead = 4;
+// is used.  A lane that walks one family of a ray for a group (kink_one) takes
+// more: there the latency of a launch counts, not its issue slots.  The depth
+// does not depend on it.
+constexpr int kMarchAhead = 4, kMarchAheadOne = 8;
+
+// a b rounded before it is added to anything: the same wherever the sum is formed
+template <typename T>
+__device__ __forceinline__ T rounded_product(T a, T b) {
+#pragma clang fp contract(off)
+    return a * b;
+}
 
 // (1/N) sum_{k < c} J(v_k) k (c - k) of one family.  Flat index of v_k: idx0 + k K0 + floor1 S1 + floor2 S2, floor_i
 // the floor of k d_i / N, of the value just below when neg_i (the moved ray is
 // on the lower side of a lattice plane that the ray itself touches).
+template <int AHEAD>
 __device__ __forceinline__ double kink_family(const double *__restrict__ tab, uint32_t idx, int N, int K0, int d1,
                                               int S1, bool neg1, int d2, int S2, bool neg2, double c, int last) {
     const double Nd = (double)N, rN = N > 0 ? recip(Nd) : 0.0;
@@ -64,10 +74,10 @@ __device__ __forceinline__ double kink_family(const double *__restrict__ tab, ui
     int r1 = neg1 ? -1 : -N, r2 = neg2 ? -1 : -N;
     idx -= (uint32_t)((neg1 ? S1 : 0) + (neg2 ? S2 : 0));
     double acc = 0.0, kd = 0.0;
-    for (int k = 1; k <= last; k += kMarchAhead) {
-        double J[kMarchAhead];
+    for (int k = 1; k <= last; k += AHEAD) {
+        double J[AHEAD];
 #pragma unroll
-        for (int u = 0; u < kMarchAhead; ++u) {
+        for (int u = 0; u < AHEAD; ++u) {
             r1 += s1;
             r2 += s2;
             const bool c1 = r1 >= 0, c2 = r2 >= 0;
@@ -78,17 +88,18 @@ __device__ __forceinline__ double kink_family(const double *__restrict__ tab, ui
             J[u] = tab[k + u <= last ? idx : 0u];
         }
 #pragma unroll
-        for (int u = 0; u < kMarchAhead; ++u) {
+        for (int u = 0; u < AHEAD; ++u) {
             kd += 1.0;
             acc = fma(J[u], fmax(kd * (c - kd), 0.0), acc);
         }
     }
-    return acc * rN;
+    return rounded_product(acc, rN);
 }
 
 // One family with slope dG and offset oG of the moved ray along its
 // coordinate, up to s = p / M (p = M: the whole segment); the companion
 // coordinates have slopes d and offsets o.
+template <int AHEAD>
 __device__ __forceinline__ double kink_plane(const double *__restrict__ tab, uint32_t idx, int dG, double oG, int K,
                                              int d1, double o1, int S1, int d2, double o2, int S2, int p, int M) {
     const int N = dG < 0 ? -dG : dG;
@@ -99,7 +110,7 @@ __device__ __forceinline__ double kink_plane(const double *__restrict__ tab, uin
     // a companion coordinate meets the family's plane at the offset o - oG d / dG
     const double gd = (double)dG, sg = dG < 0 ? -1.0 : 1.0;
     const bool neg1 = (o1 * gd - oG * (double)d1) * sg < 0.0, neg2 = (o2 * gd - oG * (double)d2) * sg < 0.0;
-    return kink_family(tab, idx, N, dG < 0 ? -K : K, d1, S1, neg1, d2, S2, neg2, c, last);
+    return kink_family<AHEAD>(tab, idx, N, dG < 0 ? -K : K, d1, S1, neg1, d2, S2, neg2, c, last);
 }
 
 // the moved ray's offsets along the axes, with no integer relation (1, 1/sqrt 2, 1/sqrt 3)
@@ -120,9 +131,9 @@ __device__ __forceinline__ double kink_sum(const GridDev &g, const double *__res
     double sum = 0.0;
 #pragma nounroll
     for (int f = 0; f < 3; ++f) {
-        sum += kink_plane(tab, (uint32_t)base, Da, oa, Sa, Db, ob, Sb, Dc, oc, Sc, p, M);
-        sum += kink_plane(tab + 3 * fam, (uint32_t)(base + Sc), Da - Db, oa - ob, -Sb, Da, oa, T, Dc - Da, oc - oa, Sc,
-                          p, M);
+        sum += kink_plane<kMarchAhead>(tab, (uint32_t)base, Da, oa, Sa, Db, ob, Sb, Dc, oc, Sc, p, M);
+        sum += kink_plane<kMarchAhead>(tab + 3 * fam, (uint32_t)(base + Sc), Da - Db, oa - ob, -Sb, Da, oa, T, Dc - Da,
+                                       oc - oa, Sc, p, M);
         tab += fam;
         const int s0 = Sa, d0 = Da;
         const double o0 = oa;
@@ -136,18 +147,24 @@ __device__ __forceinline__ double kink_sum(const GridDev &g, const double *__res
 // length of the grid vector D
 __device__ __forceinline__ double grid_length(const GridDev &g, double d0, double d1, double d2) {
     const double x = d0 * g.h[0], y = d1 * g.h[1], z = d2 * g.h[2];
-    return sqrt(x * x + y * y + z * z);
+    return sqrt(fma(x, x, fma(y, y, rounded_product(z, z))));
 }
 
 __device__ __forceinline__ double vertex_kappa(const GridDev &g, const KinkTab &kt, const int V[3]) {
     return kt.kappa[(int64_t)V[0] * g.stride[0] + V[1] * g.stride[1] + V[2]];
 }
 
+// the depth of the segment between vertices P and Q from its kinks
+__device__ __forceinline__ double direct_depth(const GridDev &g, const KinkTab &kt, const int P[3], const int Q[3],
+                                               double kinks) {
+    const double ends = vertex_kappa(g, kt, P) + vertex_kappa(g, kt, Q);
+    return 0.5 * grid_length(g, Q[0] - P[0], Q[1] - P[1], Q[2] - P[2]) * (ends - kinks);
+}
+
 // optical depth of the segment between vertices P and Q
 __device__ __forceinline__ double tau_direct(const GridDev &g, const KinkTab &kt, const int P[3], const int Q[3]) {
     const int D[3] = {Q[0] - P[0], Q[1] - P[1], Q[2] - P[2]};
-    const double ends = vertex_kappa(g, kt, P) + vertex_kappa(g, kt, Q);
-    return 0.5 * grid_length(g, D[0], D[1], D[2]) * (ends - kink_sum(g, kt.tab, P, D, 1, 1));
+    return direct_depth(g, kt, P, Q, kink_sum(g, kt.tab, P, D, 1, 1));
 }
 
 // kappa at X = P + (p / M) (Q - P) on the lattice plane x_a = C (a grid face), where P1 is linear on the
@@ -220,6 +237,30 @@ __device__ __forceinline__ double tau_reflected(const GridDev &g, const KinkTab 
     const int M = l.p + l.q;
     if (M == 0) return tau_direct(g, kt, P, Q);   // both vertices on the wall: the path lies in it
     return reflected_depth(g, kt, a, C, P, Q, l, kink_sum(g, kt.tab, P, l.D1, l.p, M) + kink_sum(g, kt.tab, Q, l.D2, l.q, M));
+}
+
+// Family f (0..5) alone of the segment V + s D, s < p / M, for one lane of a
+// group that shares a ray; add_families adds the six as kink_sum does, bit for
+// bit.
+__device__ __forceinline__ double kink_one(const GridDev &g, const double *__restrict__ tab, const int V[3],
+                                           const int D[3], int p, int M, int f) {
+    const int n1 = g.n[1] + 1, n2 = g.n[2] + 1;
+    const int64_t fam = (int64_t)(g.n[0] + 1) * n1 * n2;
+    const int S0 = n1 * n2, S1 = n2, base = V[0] * S0 + V[1] * S1 + V[2];
+    const bool diag = f >= 3;
+    const int r = diag ? f - 3 : f;
+    const int Sa = r == 0 ? S0 : (r == 1 ? S1 : 1), Sb = r == 0 ? S1 : (r == 1 ? 1 : S0), Sc = r == 0 ? 1 : (r == 1 ? S0 : S1);
+    const int Da = r == 0 ? D[0] : (r == 1 ? D[1] : D[2]), Db = r == 0 ? D[1] : (r == 1 ? D[2] : D[0]),
+              Dc = r == 0 ? D[2] : (r == 1 ? D[0] : D[1]);
+    const double oa = r == 0 ? kOff0 : (r == 1 ? kOff1 : kOff2), ob = r == 0 ? kOff1 : (r == 1 ? kOff2 : kOff0),
+                 oc = r == 0 ? kOff2 : (r == 1 ? kOff0 : kOff1);
+    return kink_plane<kMarchAheadOne>(tab + f * fam, (uint32_t)(diag ? base + Sc : base), diag ? Da - Db : Da, diag ? oa - ob : oa,
+                      diag ? -Sb : Sa, diag ? Da : Db, diag ? oa : ob, diag ? S0 + S1 + 1 : Sb, diag ? Dc - Da : Dc,
+                      diag ? oc - oa : oc, Sc, p, M);
+}
+
+__device__ __forceinline__ double add_families(const double *f) {
+    return ((((f[0] + f[3]) + f[1]) + f[4]) + f[2]) + f[5];
 }
 
 }  // namespace rte
