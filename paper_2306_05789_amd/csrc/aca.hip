@@ -350,7 +350,7 @@ __global__ __launch_bounds__(256, (entry_waves<T, KIND, NW>())) void k_aca_cols(
     T a;
     {
         const AcaTask tk = st.task[b];
-        a = entry<T, KIND, NW>(c, tgt_nat[tk.t0 + i], src_nat[tk.s0 + st.jstar[b]]);
+        a = entry<T, KIND, NW, true>(c, tgt_nat[tk.t0 + i], src_nat[tk.s0 + st.jstar[b]]);
     }
     asm volatile("" ::: "memory");   // as in k_aca_rows
     const AcaTask tk = st.task[b];
@@ -384,7 +384,7 @@ __global__ __launch_bounds__(256, 3) void k_aca_wide(EntryCtx<T> c, AcaState<T> 
     if (st.status[b] != kActive || (COLS && !st.havepiv[b])) return;
     const AcaTask tk = st.task[b];
     const int x = (int)(e - off[b]), k = st.k[b], y = COLS ? st.jstar[b] : st.istar[b];
-    T a = group_entry<T, KIND, NW>(c, tgt_nat[tk.t0 + (COLS ? x : y)], src_nat[tk.s0 + (COLS ? y : x)], P, sub,
+    T a = group_entry<T, KIND, NW, COLS>(c, tgt_nat[tk.t0 + (COLS ? x : y)], src_nat[tk.s0 + (COLS ? y : x)], P, sub,
                                    tasks + grp * kGroupTasks<NW>);
     T *U = st.Us + tk.uoff, *V = st.Vs + tk.voff;
     // row: sum_l U_l(i*) V_l(x); column: sum_l V_l(j*) U_l(x)

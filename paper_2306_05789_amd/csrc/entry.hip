@@ -56,7 +56,7 @@ __device__ __forceinline__ void fill_one(const EntryCtx<T> &c, const FillTask &t
                          tk.li0_t + (int)jl + 1),
             vt);
     } else {
-        const T v = entry<T, KIND, NW>(c, tgt_nat[tk.t0 + il], src_nat[tk.s0 + jl]);
+        const T v = entry<T, KIND, NW, true>(c, tgt_nat[tk.t0 + il], src_nat[tk.s0 + jl]);
         put(tk.out, tk.outlo,
             slice_offset(sm, tk.li0, tk.t0 + il, tk.kw, sm.src_p[tk.s0 + jl] - sm.src_p[tk.s0], tk.li0 + (int)il + 1),
             v);
@@ -108,12 +108,14 @@ __global__ void k_kink_table(GridDev g, const double *__restrict__ kap, double *
     const double v = k(0, 0, 0), all = k(1, 1, 1);
     const double x1 = k(1, 0, 0), y1 = k(0, 1, 0), z1 = k(0, 0, 1);
     const double xy = k(1, 1, 0), yz = k(0, 1, 1), xz = k(1, 0, 1);
+    // a family of rotation (a, b, c) is stored [v_a][v_b][v_c]
+    const int64_t r1 = ((int64_t)y * (g.n[2] + 1) + z) * (g.n[0] + 1) + x, r2 = ((int64_t)z * (g.n[0] + 1) + x) * (g.n[1] + 1) + y;
     out[0 * M + o] = all - yz - v + k(-1, 0, 0);
-    out[1 * M + o] = all - xz - v + k(0, -1, 0);
-    out[2 * M + o] = all - xy - v + k(0, 0, -1);
+    out[1 * M + r1] = all - xz - v + k(0, -1, 0);
+    out[2 * M + r2] = all - xy - v + k(0, 0, -1);
     out[3 * M + o] = x1 + y1 - v - xy;
-    out[4 * M + o] = y1 + z1 - v - yz;
-    out[5 * M + o] = x1 + z1 - v - xz;
+    out[4 * M + r1] = y1 + z1 - v - yz;
+    out[5 * M + r2] = x1 + z1 - v - xz;
 }
 
 DevBuf kink_table(const Mesh &m, const double *kappa, hipStream_t s) {

@@ -515,8 +515,10 @@ __device__ __forceinline__ T group_attenuations(const GridDev &g, const KinkTab 
 
 // G(i, j).  Every wall adds its own mirror-image term (one reflection per
 // ray).  The optical depths come first: the star of j is loaded after the
-// marches, so its 27 values do not stay live through them.
-template <typename T, int NW = kAnyWalls>
+// marches, so its values do not stay live through them.  FROM_J: the rays are
+// walked from j (the depth is symmetric), for launches whose lanes share the
+// source: the lanes then meet the planes in step (KinkTab).
+template <typename T, int NW = kAnyWalls, bool FROM_J = false>
 __device__ T volume_entry(const EntryCtx<T> &c, int64_t i, int64_t j) {
     const GridDev &g = c.g;
     int ii[3], jj[3];
@@ -525,11 +527,11 @@ __device__ T volume_entry(const EntryCtx<T> &c, int64_t i, int64_t j) {
     if constexpr (NW == kAnyWalls)
         if (!vertex_active(g, ii)) return (T)0;   // a removed vertex (its column: an empty star)
     T att_w[6];
-    const T att = attenuations<T, NW>(g, c.kink, ii, jj, att_w);
+    const T att = FROM_J ? attenuations<T, NW>(g, c.kink, jj, ii, att_w) : attenuations<T, NW>(g, c.kink, ii, jj, att_w);
     return vol_sum<T, NW>(c, att, att_w, ii, jj);
 }
 
-// G(i, j) and G(j, i) together: the optical depth along the segment (and along
+// G(i, j) and G(j, i) together (lanes share j): the optical depth along the segment (and along
 // each reflected path, whose wall point is the same seen from either end) is
 // shared; each entry takes its own source star and quadrature.
 template <typename T, int NW = kAnyWalls>
@@ -539,7 +541,7 @@ __device__ __forceinline__ void volume_entry_pair(const EntryCtx<T> &c, int64_t 
     vtx_index(g, i, ii);
     vtx_index(g, j, jj);
     T att_w[6];
-    const T att = attenuations<T, NW>(g, c.kink, ii, jj, att_w);
+    const T att = attenuations<T, NW>(g, c.kink, jj, ii, att_w);
     gij = vol_sum<T, NW>(c, att, att_w, ii, jj);
     gji = vol_sum<T, NW>(c, att, att_w, jj, ii);
     if constexpr (NW == kAnyWalls) {   // removed vertices have zero rows
@@ -763,7 +765,7 @@ __device__ __forceinline__ T surf_sum(const EntryCtx<T> &c, T att, const T att_w
     }
 }
 
-template <typename T, int NW = kAnyWalls>
+template <typename T, int NW = kAnyWalls, bool FROM_J = false>
 __device__ T surface_entry(const EntryCtx<T> &c, int64_t i, int64_t l) {
     const GridDev &g = c.g;
     int ii[3], ll[3];
@@ -772,19 +774,19 @@ __device__ T surface_entry(const EntryCtx<T> &c, int64_t i, int64_t l) {
     if constexpr (NW == kAnyWalls)
         if (!vertex_active(g, ii)) return (T)0;   // a removed vertex
     T att_w[6];
-    const T att = attenuations<T, NW>(g, c.kink, ii, ll, att_w);
+    const T att = FROM_J ? attenuations<T, NW>(g, c.kink, ll, ii, att_w) : attenuations<T, NW>(g, c.kink, ii, ll, att_w);
     return surf_sum<T, NW>(c, att, att_w, ii, ll);
 }
 
-template <typename T, int KIND, int NW = kAnyWalls>
+template <typename T, int KIND, int NW = kAnyWalls, bool FROM_J = false>
 __device__ __forceinline__ T entry(const EntryCtx<T> &c, int64_t i, int64_t j) {
-    if constexpr (KIND == RTE_VOLUME) return volume_entry<T, NW>(c, i, j);
-    else return surface_entry<T, NW>(c, i, j);
+    if constexpr (KIND == RTE_VOLUME) return volume_entry<T, NW, FROM_J>(c, i, j);
+    else return surface_entry<T, NW, FROM_J>(c, i, j);
 }
 
 // The entry of a pair shared by a group of P lanes (group_attenuations); every
 // lane returns it.
-template <typename T, int KIND, int NW>
+template <typename T, int KIND, int NW, bool FROM_J>
 __device__ __forceinline__ T group_entry(const EntryCtx<T> &c, int64_t i, int64_t j, int P, int sub, double *buf) {
     const GridDev &g = c.g;
     int ii[3], jj[3];
@@ -793,7 +795,8 @@ __device__ __forceinline__ T group_entry(const EntryCtx<T> &c, int64_t i, int64_
     if constexpr (NW == kAnyWalls)
         if (!vertex_active(g, ii)) return (T)0;   // a removed vertex
     T att_w[6];
-    const T att = group_attenuations<T, NW>(g, c.kink, ii, jj, att_w, P, sub, buf);
+    const T att = FROM_J ? group_attenuations<T, NW>(g, c.kink, jj, ii, att_w, P, sub, buf)
+                         : group_attenuations<T, NW>(g, c.kink, ii, jj, att_w, P, sub, buf);
     if constexpr (KIND == RTE_VOLUME) return vol_sum<T, NW>(c, att, att_w, ii, jj);
     else return surf_sum<T, NW>(c, att, att_w, ii, jj);
 }
