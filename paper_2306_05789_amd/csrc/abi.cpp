@@ -587,11 +587,14 @@ rte_status_t rte_hmat_matvec(rte_hmat_t h, int32_t band, int32_t nrhs, const dou
         check_device_pointer(y, "y");
         hipStream_t s = (hipStream_t)stream;
         const int64_t ns = H.stats.n_src, nt = H.stats.n_tgt;
-        DevBuf xc(sizeof(double) * ns * nrhs), yc(sizeof(double) * nt * nrhs);
+        DevBuf xc = DevBuf::scratch(sizeof(double) * ns * nrhs), yc = DevBuf::scratch(sizeof(double) * nt * nrhs),
+               ws = DevBuf::scratch(sizeof(double) * (size_t)matvec_ws(H, band, nrhs));
+        poison(ws, s);
         permute_gather(H.src_pos.as<int64_t>(), ns, nrhs, ns, ns, x, xc.as<double>(), s);
-        matvec_launch(H, band, nrhs, xc.as<double>(), yc.as<double>(), nullptr, s);
+        matvec_launch_ws(H, band, nrhs, xc.as<double>(), yc.as<double>(), nullptr, ws.as<double>(), s);
         permute_scatter(H.tgt_nat.as<int64_t>(), nt, nrhs, nt, nt, yc.as<double>(), y, s);
         HIP_CHECK(hipStreamSynchronize(s));
+        settle({&xc, &yc, &ws});
         return RTE_OK;
     });
 }
@@ -641,14 +644,15 @@ rte_status_t rte_hmat_matvec_batched(rte_hmat_t h, int32_t nrhs, const double *x
         check_device_pointer(y, "y");
         hipStream_t s = (hipStream_t)stream;
         const int64_t ns = H.stats.n_src, nt = H.stats.n_tgt, nv = (int64_t)nrhs * H.n_bands;
-        DevBuf xc(sizeof(double) * ns * nv), yc(sizeof(double) * nt * nv),
-            ws(sizeof(double) * (size_t)matvec_ws_all(H, nrhs));
+        DevBuf xc = DevBuf::scratch(sizeof(double) * ns * nv), yc = DevBuf::scratch(sizeof(double) * nt * nv),
+               ws = DevBuf::scratch(sizeof(double) * (size_t)matvec_ws_all(H, nrhs));
         poison(ws, s);
         permute_gather(H.src_pos.as<int64_t>(), ns, (int)nv, ns, ns, x, xc.as<double>(), s);
         matvec_launch_all(H, nrhs, xc.as<double>(), yc.as<double>(), nullptr, ws.as<double>(), s,
                           op == RTE_OP_LOW ? kMatvecLow : kMatvecAccurate);
         permute_scatter(H.tgt_nat.as<int64_t>(), nt, (int)nv, nt, nt, yc.as<double>(), y, s);
         HIP_CHECK(hipStreamSynchronize(s));
+        settle({&xc, &yc, &ws});
         return RTE_OK;
     });
 }

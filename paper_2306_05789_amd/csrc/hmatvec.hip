@@ -1392,14 +1392,6 @@ void matvec_launch_ws(const HMat &H, int band, int nrhs, const double *x_c, doub
     launch_plan(H, *H.mv[band], nrhs, x_c, y_c, y0_c, tbuf, s, mode);
 }
 
-void matvec_launch(const HMat &H, int band, int nrhs, const double *x_c, double *y_c, const double *y0_c,
-                   hipStream_t s, int mode) {
-    DevBuf tb(sizeof(double) * (size_t)matvec_ws(H, band, nrhs));
-    poison(tb, s);
-    matvec_launch_ws(H, band, nrhs, x_c, y_c, y0_c, tb.as<double>(), s, mode);
-    HIP_CHECK(hipStreamSynchronize(s));
-}
-
 void permute_gather(const int64_t *perm, int64_t n, int nrhs, int64_t ld_in, int64_t ld_out, const double *in,
                     double *out, hipStream_t s) {
     const int64_t tot = n * nrhs;

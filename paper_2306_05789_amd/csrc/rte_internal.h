@@ -5,6 +5,7 @@
 
 #include <cstdint>
 #include <cstdlib>
+#include <initializer_list>
 #include <mutex>
 #include <map>
 #include <memory>
@@ -250,6 +251,11 @@ private:
     }
 };
 
+// The stream that used these buffers has drained: they may go back to the pool.
+inline void settle(std::initializer_list<DevBuf *> bufs) {
+    for (DevBuf *b : bufs) b->settled = true;
+}
+
 // Scratch pool of the current device (pool.cpp).
 void *pool_take(size_t bytes, size_t *cap);
 void pool_give(void *p, size_t cap);
@@ -394,9 +400,8 @@ void matvec_build(HMat &H, int band, hipStream_t s);
 // accumulation (defect steps and external calls).  Other storages ignore it.
 constexpr int kMatvecLow = 0;
 constexpr int kMatvecAccurate = 1;
-void matvec_launch(const HMat &H, int band, int nrhs, const double *x_c, double *y_c, const double *y0_c,
-                   hipStream_t s, int mode = kMatvecAccurate);
-// Same with a caller-provided workspace of matvec_ws(H, band, nrhs) doubles; does not synchronise.
+// y = y0 + H_band x in cluster order, with a caller-provided workspace of matvec_ws(H, band, nrhs) doubles; does
+// not synchronise.
 void matvec_launch_ws(const HMat &H, int band, int nrhs, const double *x_c, double *y_c, const double *y0_c,
                       double *tbuf, hipStream_t s, int mode = kMatvecAccurate);
 int64_t matvec_ws(const HMat &H, int band, int nrhs);

@@ -505,7 +505,7 @@ struct Server {
             r.ops.push_back(o);
         }
         r.state_bytes = state_bytes(r);
-        r.st.alloc((size_t)r.state_bytes);
+        r.st = DevBuf::scratch((size_t)r.state_bytes);
         HIP_CHECK(hipMemsetAsync(r.st.p, 0, r.st.bytes, s));   // T = 0, J = 0
         resident += r.state_bytes;
         // S^E_b = S_hat Q_b, Q_b = B_nu(T_wall), wall values in surface cluster order
@@ -598,7 +598,7 @@ struct Server {
 
     void retire(SrvReq &r) {
         const SrvMesh &M = *meshes[r.mesh];
-        r.out.alloc(sizeof(double) * (size_t)M.mesh.N);
+        r.out = DevBuf::scratch(sizeof(double) * (size_t)M.mesh.N);
         permute_scatter(M.tgt_nat.as<int64_t>(), M.mesh.N, 1, M.mesh.N, M.mesh.N, r.T(), r.out.as<double>(), s);
         HIP_CHECK(hipStreamSynchronize(s));
         for (int l : distinct_levels(r)) {
@@ -607,7 +607,9 @@ struct Server {
             o->used = ++clock;
         }
         resident -= r.state_bytes;
+        settle({&r.st, &r.Tw, &r.out});   // the sweep stream has drained
         r.st.release();
+        r.Tw.release();
         r.state = RTE_REQ_DONE;
         stats.completed += 1;
     }
@@ -873,7 +875,7 @@ int64_t server_submit(Server &S, const rte_request_t &q) {
     }
     r->tol = q.tol;
     r->max_iter = q.max_iter;
-    r->Tw.alloc(sizeof(double) * (size_t)M.mesh.L);
+    r->Tw = DevBuf::scratch(sizeof(double) * (size_t)M.mesh.L);
     after_user(S);
     HIP_CHECK(hipMemcpyAsync(r->Tw.p, q.T_wall, r->Tw.bytes, hipMemcpyDeviceToDevice, S.s));
     HIP_CHECK(hipStreamSynchronize(S.s));
@@ -914,8 +916,10 @@ void server_fetch(Server &S, int64_t id, double *T_out) {
     SrvReq &r = *it->second;
     RTE_REQUIRE(r.state == RTE_REQ_DONE, "server: the request has not finished");
     const SrvMesh &M = *S.meshes[r.mesh];
+    r.out.settled = false;   // until the copy below has run
     HIP_CHECK(hipMemcpyAsync(T_out, r.out.p, sizeof(double) * (size_t)M.mesh.N, hipMemcpyDeviceToDevice, S.s));
     HIP_CHECK(hipStreamSynchronize(S.s));
+    r.out.settled = true;
     S.reqs.erase(it);
 }
 

@@ -264,17 +264,17 @@ rte_status_t fixed_point_solve(const Mesh &m, const HMat &G, const HMat &S, cons
     consts.insert(consts.end(), nu.begin(), nu.end());
     consts.insert(consts.end(), w.begin(), w.end());
     consts.insert(consts.end(), a.begin(), a.end());
-    DevBuf dconst = upload(consts, s);
+    DevBuf dconst = upload_scratch(consts, s);
     BandParams bp{nb, d.grey, dconst.as<double>(), dconst.as<double>() + nb, dconst.as<double>() + 2 * nb};
 
     const int64_t vecN = N * nr;
-    DevBuf Tw(sizeof(double) * L * nr), Q(sizeof(double) * L * nr * nb), SE(sizeof(double) * vecN * nb),
-        Sv(sizeof(double) * vecN * nb), J(sizeof(double) * vecN * nb), Jn(sizeof(double) * vecN * nb),
-        T(sizeof(double) * vecN), part(sizeof(double) * 2 * kResidBlocks * nb * nr),
-        res(sizeof(double) * 2 * nb * nr), viol(sizeof(unsigned long long));
+    auto words = [](int64_t n) { return DevBuf::scratch(sizeof(double) * (size_t)n); };
+    DevBuf Tw = words(L * nr), Q = words(L * nr * nb), SE = words(vecN * nb), Sv = words(vecN * nb), J = words(vecN * nb),
+           Jn = words(vecN * nb), T = words(vecN), part = words((int64_t)2 * kResidBlocks * nb * nr),
+           res = words(2 * nb * nr), viol = words(1);
     const int64_t kt = std::max<int64_t>({1, matvec_ws_all(G, nr), matvec_ws_all(S, nr)});
-    DevBuf tbuf(sizeof(double) * kt);
-    poison(tbuf, s);
+    DevBuf tbuf = words(kt);
+    for (DevBuf *d : {&Tw, &Q, &SE, &Sv, &J, &Jn, &T, &part, &res, &tbuf}) poison(*d, s);
     const unsigned gN = (unsigned)((vecN + 255) / 256), gL = (unsigned)((L * nr + 255) / 256);
 
     // boundary source: Q_b = B_b(T_wall) and S^E_b = S_hat_b Q_b
@@ -301,7 +301,7 @@ rte_status_t fixed_point_solve(const Mesh &m, const HMat &G, const HMat &S, cons
     int op_count[2] = {0, 0};
     std::vector<double> rv(2 * nb * nr);
     const bool mixed = d.precision == RTE_MIXED_BF16;
-    DevBuf Jacc(mixed ? sizeof(double) * vecN * nb : 0), Sm(mixed ? sizeof(double) * vecN * nb : 0);
+    DevBuf Jacc = words(mixed ? vecN * nb : 0), Sm = words(mixed ? vecN * nb : 0);
 
     // the parts of a sweep: before the matvec, the matvec, after it
     auto enqueue_pre = [&](const double *sub) {
@@ -455,6 +455,7 @@ rte_status_t fixed_point_solve(const Mesh &m, const HMat &G, const HMat &S, cons
     unsigned long long nviol = 0;
     HIP_CHECK(hipMemcpyAsync(&nviol, viol.p, sizeof(nviol), hipMemcpyDeviceToHost, s));
     HIP_CHECK(hipStreamSynchronize(s));
+    settle({&dconst, &Tw, &Q, &SE, &Sv, &J, &Jn, &T, &part, &res, &viol, &tbuf, &Jacc, &Sm});
     if (st) {
         st->iterations = it;
         st->outer_steps = outer;
