@@ -66,9 +66,9 @@ constexpr int kChunk = 1024;
 // Lanes per entry of k_aca_wide, and the lanes it may put on the chip: what four
 // wavefronts per SIMD hold, one round of waves (ACA entry launches of 13x21x13
 // with three walls 20.7 ms without it, 16.8 at 2^18 lanes, 18.6 at 2^17, 21.4 at
-// 2^20; of the 41^3 surface operator 20.4, 15.1, 15.3, 14.3); more than 8 lanes
-// per entry while a quarter of that holds them (33x17x17, one wall: 166 against
-// 168 ms).
+// 2^20; of the 41^3 surface operator 18.1 and 15.3; of 33x17x17 with one wall in
+// 4 bands of mixed precision 494 and 302, 309 at 2^17, its surface 82 and 53); more
+// than 8 lanes per entry while a quarter of that holds them.
 constexpr int kWideMin = 8, kWideMax = 32;
 constexpr int64_t kWideLanes = (int64_t)1 << 18;
 // Workgroups of k_aca_dots below which the rank indices of a chunk are split
@@ -366,15 +366,15 @@ __global__ __launch_bounds__(256, (entry_waves<T, KIND, NW>())) void k_aca_cols(
 // (group_entry) and the loads of the residual, whose terms are then subtracted
 // in order by every lane, so that an entry is that of the one-lane kernels bit
 // for bit and the choice between them (aca_batch) does not show in the factors.
-// Such a launch lasts as long as one entry, a chain of loads: 6 families of
-// about N / 4 batches each (13 legs of them with six walls), then k / 8 batches
-// of the residual.
+// Such a launch lasts as long as one entry, a chain of loads: in FP64 6 families
+// of about N / 4 batches each (13 legs of them with six walls), in FP32 the
+// pieces of every leg, then k / 8 batches of the residual.
 template <typename T, int KIND, int NW, bool COLS>
 __global__ __launch_bounds__(256, 3) void k_aca_wide(EntryCtx<T> c, AcaState<T> st, int64_t total, int P,
                                                      const int64_t *__restrict__ tgt_nat,
                                                      const int64_t *__restrict__ src_nat) {
     constexpr int R = 4;   // residual terms in flight per lane
-    __shared__ double tasks[256 / kWideMin * kGroupTasks<NW>];
+    __shared__ T tasks[256 / kWideMin * kGroupTasks<T, NW>];
     __shared__ T terms[256 * R][2];
     const int tid = threadIdx.x, grp = tid / P, sub = tid - grp * P;
     const int64_t e = (int64_t)blockIdx.x * (256 / P) + grp;
@@ -385,7 +385,7 @@ __global__ __launch_bounds__(256, 3) void k_aca_wide(EntryCtx<T> c, AcaState<T> 
     const AcaTask tk = st.task[b];
     const int x = (int)(e - off[b]), k = st.k[b], y = COLS ? st.jstar[b] : st.istar[b];
     T a = group_entry<T, KIND, NW, COLS>(c, tgt_nat[tk.t0 + (COLS ? x : y)], src_nat[tk.s0 + (COLS ? y : x)], P, sub,
-                                   tasks + grp * kGroupTasks<NW>);
+                                   tasks + grp * kGroupTasks<T, NW>);
     T *U = st.Us + tk.uoff, *V = st.Vs + tk.voff;
     // row: sum_l U_l(i*) V_l(x); column: sum_l V_l(j*) U_l(x)
     const T *p = COLS ? V + y : U + y, *q = COLS ? U + x : V + x;
@@ -501,8 +501,7 @@ __global__ __launch_bounds__(256) void k_aca_dots(AcaState<T> st, int split) {
 // test convergence and pick the next row.  One workgroup per pivoted block.
 template <typename T>
 __global__ __launch_bounds__(256) void k_aca_finish(AcaState<T> st, T eps, int need) {
-    __shared__ T sa[4], ss[4], sx[4];
-    __shared__ T last[2];
+    __shared__ T sa[4], ss[4], sums[2][kAcaRetryRank];   // (u_l.u_k), (v_l.v_k), l <= k < kcap
     __shared__ int si[4];
     const int b = st.act2[blockIdx.x];
     if (st.status[b] != kActive || !st.havepiv[b]) return;   // uniform over the workgroup
@@ -510,7 +509,6 @@ __global__ __launch_bounds__(256) void k_aca_finish(AcaState<T> st, T eps, int n
     const int k = st.k[b], tid = threadIdx.x;
     const int64_t c0 = st.chunkoff[b], c1 = st.chunkoff[b + 1];
     const int64_t row = 2 * (int64_t)st.half;
-    T cross = (T)0;
     for (int l = tid; l <= k; l += 256) {
         T su = (T)0, sv = (T)0;
 #pragma unroll 4
@@ -518,11 +516,9 @@ __global__ __launch_bounds__(256) void k_aca_finish(AcaState<T> st, T eps, int n
             su += st.part[c * row + l];
             sv += st.part[c * row + st.half + l];
         }
-        if (l < k) cross += su * sv;
-        else { last[0] = su; last[1] = sv; }
+        sums[0][l] = su;
+        sums[1][l] = sv;
     }
-    cross = wave_sum(cross);
-    if ((tid & 63) == 0) sx[tid >> 6] = cross;
     T bu = (T)-1, none = (T)0;
     int bi = INT_MAX;
     for (int64_t c = c0 + tid; c < c1; c += 256) {
@@ -530,11 +526,14 @@ __global__ __launch_bounds__(256) void k_aca_finish(AcaState<T> st, T eps, int n
         const int i = st.pidx[c];
         if (a > bu || (a == bu && i < bi)) { bu = a; bi = i; }
     }
-    block_argmax(bu, bi, none, sa, si, ss);   // its barriers publish sx and last
+    block_argmax(bu, bi, none, sa, si, ss);   // its barriers publish the sums
+    if (tid >= 64) return;
+    T cross = (T)0;
+    for (int l = tid; l < k; l += 64) cross += sums[0][l] * sums[1][l];
+    cross = wave_sum(cross);
     if (tid != 0) return;
     st.ents[b] += tk.m;
-    const T u2 = last[0], v2 = last[1];
-    cross = ((sx[0] + sx[1]) + sx[2]) + sx[3];
+    const T u2 = sums[0][k], v2 = sums[1][k];
     const T s2 = st.normS2[b] + u2 * v2 + (T)2 * cross;
     st.normS2[b] = s2;
     // the stopping test, met by `need` consecutive rank steps
@@ -870,11 +869,15 @@ void aca_batch(HMat &H, BandStore &B, BandKappa<T> kap, const std::vector<AcaTas
         HIP_CHECK(hipStreamSynchronize(s));
         if (ht[1] == 0) break;
         const int64_t nrow = ht[0], nact = ht[1], ncol = ht[2], nchunk = ht[4];
-        // lanes per entry: 1, or as many of 8 .. 32 as fit the chip at once (an
-        // open mesh has 6 families to share, so 8)
-        const int wm = wall_mode(c.g);
+        // lanes per entry: 1, or as many of 8 .. 32 as fit the chip at once and
+        // have a part of the rays to walk (FP64: 6 families per leg; FP32: a leg,
+        // so that an open mesh has nothing to share: 29^3 surface entry launches
+        // 77 ms at 8 lanes, 70 at one)
+        const int wm = wall_mode(c.g), parts = (sizeof(T) == 8 ? 6 : 1) * (1 + 2 * c.g.n_walls);
         auto lanes = [&](int64_t n) {
-            int P = wm == kNoWall ? kWideMin : kWideMax;
+            if (parts == 1) return 1;
+            int P = kWideMin;
+            while (P < kWideMax && P < parts) P <<= 1;
             while (P > kWideMin && n * P > kWideLanes / 4) P >>= 1;
             return wide_on && n * P <= kWideLanes ? P : 1;
         };
@@ -1106,16 +1109,18 @@ void assemble_band(HMat &H, int band, const double *kappa_band, hipStream_t s) {
     // them is queued (band_settle, which an ACA batch may call, releases what
     // B.retire holds)
     BandStore &B = H.bands[band];
-    DevBuf kt = kink_table(*H.mesh, kappa_band, s);
     if (H.precision == RTE_FP64) {
-        assemble_typed<double>(H, band, BandKappa<double>{kappa_band, kappa_band, kt.as<double>()}, s);
+        DevBuf kt = march_table(*H.mesh, kappa_band, s);
+        assemble_typed<double>(H, band, BandKappa<double>{kappa_band, kt.as<double>()}, s);
+        B.retire.push_back(std::move(kt));
     } else {
         DevBuf kf = DevBuf::scratch(sizeof(float) * (size_t)H.mesh->N);
         to_float(kappa_band, kf.as<float>(), H.mesh->N, s);
-        assemble_typed<float>(H, band, BandKappa<float>{kf.as<float>(), kappa_band, kt.as<double>()}, s);
+        DevBuf kt = march_table(*H.mesh, kf.as<float>(), s);
+        assemble_typed<float>(H, band, BandKappa<float>{kf.as<float>(), kt.as<float>()}, s);
         B.retire.push_back(std::move(kf));
+        B.retire.push_back(std::move(kt));
     }
-    B.retire.push_back(std::move(kt));
 }
 
 void band_settle(BandStore &B, hipStream_t s) {

@@ -118,7 +118,7 @@ __global__ void k_kink_table(GridDev g, const double *__restrict__ kap, double *
     out[5 * M + r2] = x1 + z1 - v - xz;
 }
 
-DevBuf kink_table(const Mesh &m, const double *kappa, hipStream_t s) {
+DevBuf march_table(const Mesh &m, const double *kappa, hipStream_t s) {
     const int64_t M = (int64_t)(m.dev.n[0] + 1) * (m.dev.n[1] + 1) * (m.dev.n[2] + 1);
     DevBuf d = DevBuf::scratch(sizeof(double) * 6 * (size_t)M);
     k_kink_table<<<(unsigned)((M + 255) / 256), 256, 0, s>>>(m.dev, kappa, d.as<double>());
@@ -126,10 +126,38 @@ DevBuf kink_table(const Mesh &m, const double *kappa, hipStream_t s) {
     return d;
 }
 
+// The four vertex values of every (cell base b, Kuhn tetrahedron t) pair, in
+// the order tet_sample reads them: b, b + s_L, b + s0 + s1 + 1 - s_S and
+// b + s0 + s1 + 1, L and S the tetrahedron's largest and smallest axes
+// (t = 2 L + (S > L ? S - 1 : S)).  A vertex past the grid (bases on the
+// upper faces) gives 0.
+__global__ void k_tet_table(GridDev g, const float *__restrict__ kap, float *__restrict__ out) {
+    const int64_t N = (int64_t)g.n[0] * g.n[1] * g.n[2];
+    const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (k >= N * 6) return;
+    const int64_t b = k / 6;
+    const int t = (int)(k - b * 6), L = t >> 1, r = t & 1, S = r < L ? r : r + 1;
+    const int64_t s0 = g.stride[0], s1 = g.stride[1];
+    const int64_t sL = L == 0 ? s0 : (L == 1 ? s1 : 1), sS = S == 0 ? s0 : (S == 1 ? s1 : 1);
+    const int64_t v3 = b + s0 + s1 + 1;
+    const int64_t v1 = b + sL, v2 = v3 - sS;
+    out[4 * k + 0] = kap[b];
+    out[4 * k + 1] = v1 < N ? kap[v1] : 0.0f;
+    out[4 * k + 2] = v2 < N ? kap[v2] : 0.0f;
+    out[4 * k + 3] = v3 < N ? kap[v3] : 0.0f;
+}
+
+DevBuf march_table(const Mesh &m, const float *kappa, hipStream_t s) {
+    DevBuf d = DevBuf::scratch(sizeof(float) * (size_t)m.N * 24);
+    const int64_t n = m.N * 6;
+    k_tet_table<<<(unsigned)((n + 255) / 256), 256, 0, s>>>(m.dev, kappa, d.as<float>());
+    HIP_LAUNCH_CHECK();
+    return d;
+}
+
 // Row d of the star table (StarTab), from the mesh's near and far tables.
-template <typename T>
 __global__ __launch_bounds__(128) void k_star_table(GridDev g, StarTab st, int64_t rows, const double *__restrict__ near,
-                                                    T *__restrict__ w, T *__restrict__ cell) {
+                                                    double *__restrict__ w, double *__restrict__ cell) {
     const int64_t row = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (row >= rows) return;
     const int d[3] = {(int)(row / st.st0) + st.lo[0], (int)(row % st.st0 / st.st1) + st.lo[1],
@@ -165,14 +193,14 @@ __global__ __launch_bounds__(128) void k_star_table(GridDev g, StarTab st, int64
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
             sum[slot_of(e, bits)] += c[e];
-            cell[row * 64 + bits * 8 + e] = (T)(c[e] * g.vol_scale);
+            cell[row * 64 + bits * 8 + e] = c[e] * g.vol_scale;
         }
     }
 #pragma unroll
-    for (int v = 0; v < kStarWeights; ++v) w[row * kStarWeights + v] = v < 15 ? (T)(sum[star_slot(v)] * g.vol_scale) : (T)0;
+    for (int v = 0; v < kStarWeights; ++v) w[row * kStarWeights + v] = v < 15 ? sum[star_slot(v)] * g.vol_scale : 0.0;
 }
 
-StarTab star_table(const Mesh &m, bool fp64, hipStream_t s) {
+StarTab star_table(const Mesh &m, hipStream_t s) {
     // checking aid: RTE_STAR_TABLE=0 in the environment sums the rules point by point
     if (const char *e = std::getenv("RTE_STAR_TABLE"))
         if (std::atoi(e) == 0) return StarTab{};
@@ -187,37 +215,33 @@ StarTab star_table(const Mesh &m, bool fp64, hipStream_t s) {
         n[a] = hi - lo + 1;
         rows *= n[a];
     }
-    const size_t esz = fp64 ? sizeof(double) : sizeof(float);
     size_t free_b = 0, total_b = 0;
     HIP_CHECK(hipMemGetInfo(&free_b, &total_b));
-    if ((double)rows * kStarRow * esz > total_b / 16.0) return StarTab{};
+    if ((double)rows * kStarRow * sizeof(double) > total_b / 16.0) return StarTab{};
     t.st0 = (int)(n[1] * n[2]);
     t.st1 = (int)n[2];
     int dev = 0;
     HIP_CHECK(hipGetDevice(&dev));
     const double *near = static_cast<const double *>(m.near_table(true));
     std::lock_guard<std::mutex> lk(m.star->mu);
-    std::shared_ptr<DevBuf> &buf = m.star->dev[{dev, fp64}];
-    char *p = buf ? buf->as<char>() : nullptr;
+    std::shared_ptr<DevBuf> &buf = m.star->dev[dev];
+    double *p = buf ? buf->as<double>() : nullptr;
     if (!p) {
         auto b = std::make_shared<DevBuf>();
         try {
-            b->alloc((size_t)rows * kStarRow * esz);
+            b->alloc((size_t)rows * kStarRow * sizeof(double));
         } catch (const Error &) {   // no room for it now
             (void)hipGetLastError();
             return StarTab{};
         }
-        p = b->as<char>();
-        const unsigned grid = (unsigned)((rows + 127) / 128);
-        if (fp64)
-            k_star_table<double><<<grid, 128, 0, s>>>(g, t, rows, near, (double *)p, (double *)p + rows * kStarWeights);
-        else k_star_table<float><<<grid, 128, 0, s>>>(g, t, rows, near, (float *)p, (float *)p + rows * kStarWeights);
+        p = b->as<double>();
+        k_star_table<<<(unsigned)((rows + 127) / 128), 128, 0, s>>>(g, t, rows, near, p, p + rows * kStarWeights);
         HIP_LAUNCH_CHECK();
         HIP_CHECK(hipStreamSynchronize(s));   // other streams read it from here on
         buf = std::move(b);
     }
     t.w = p;
-    t.cell = p + (size_t)rows * kStarWeights * esz;
+    t.cell = p + rows * kStarWeights;
     return t;
 }
 
@@ -226,11 +250,14 @@ EntryCtx<T> make_ctx(const Mesh &m, int kind, BandKappa<T> kappa, hipStream_t s)
     EntryCtx<T> c;
     c.g = m.dev;
     c.kappa = kappa.v;
-    c.kink = KinkTab{kappa.kinks, kappa.v64};
+    c.tab = kappa.tab;
     c.near = static_cast<const T *>(m.near_table(std::is_same<T, double>::value));
-    if (kind == RTE_VOLUME) c.star = star_table(m, std::is_same<T, double>::value, s);
-    if constexpr (std::is_same<T, double>::value) c.st = stencil_device().d;
-    else c.st = stencil_device().f;
+    if constexpr (std::is_same<T, double>::value) {
+        if (kind == RTE_VOLUME) c.star = star_table(m, s);
+        c.st = stencil_device().d;
+    } else {
+        c.st = stencil_device().f;
+    }
     return c;
 }
 template EntryCtx<double> make_ctx<double>(const Mesh &, int, BandKappa<double>, hipStream_t);
@@ -240,9 +267,9 @@ void entries_launch(const Mesh &m, int kind, const double *kappa, int64_t n, con
                     const int64_t *cols, double *out, int precision, hipStream_t s) {
     if (n == 0) return;
     const unsigned grid = (unsigned)((n + 255) / 256);
-    DevBuf kt = kink_table(m, kappa, s);
     if (precision == RTE_FP64) {
-        auto c = make_ctx<double>(m, kind, BandKappa<double>{kappa, kappa, kt.as<double>()}, s);
+        DevBuf kt = march_table(m, kappa, s);
+        auto c = make_ctx<double>(m, kind, BandKappa<double>{kappa, kt.as<double>()}, s);
         if (kind == RTE_VOLUME) k_entries<double, RTE_VOLUME><<<grid, 256, 0, s>>>(c, n, rows, cols, out);
         else k_entries<double, RTE_SURFACE><<<grid, 256, 0, s>>>(c, n, rows, cols, out);
         HIP_LAUNCH_CHECK();
@@ -250,7 +277,8 @@ void entries_launch(const Mesh &m, int kind, const double *kappa, int64_t n, con
     } else {
         DevBuf kf(sizeof(float) * (size_t)m.N);
         to_float(kappa, kf.as<float>(), m.N, s);
-        auto c = make_ctx<float>(m, kind, BandKappa<float>{kf.as<float>(), kappa, kt.as<double>()}, s);
+        DevBuf kt = march_table(m, kf.as<float>(), s);
+        auto c = make_ctx<float>(m, kind, BandKappa<float>{kf.as<float>(), kt.as<float>()}, s);
         if (kind == RTE_VOLUME) k_entries<float, RTE_VOLUME><<<grid, 256, 0, s>>>(c, n, rows, cols, out);
         else k_entries<float, RTE_SURFACE><<<grid, 256, 0, s>>>(c, n, rows, cols, out);
         HIP_LAUNCH_CHECK();

@@ -11,7 +11,8 @@
 // at the wall.  One optical depth per vertex pair; near rule (degree 5)
 // when the grid Chebyshev distance is <= 2, degree 2 otherwise.
 //
-// tau comes from the kinks of kappa along the ray (march.h).
+// FP64: tau from the kinks of kappa along the ray (march.h), g from a table by
+// offset; FP32: tau from a march in FP32 (march32.h), g point by point.
 #pragma once
 
 #include <type_traits>
@@ -36,6 +37,7 @@ __device__ __forceinline__ float recip(float x) { return __builtin_amdgcn_rcpf(x
 }  // namespace rte
 
 #include "march.h"
+#include "march32.h"
 
 namespace rte {
 
@@ -43,11 +45,13 @@ template <typename T>
 struct EntryCtx {
     GridDev g;
     const T *__restrict__ kappa;   // [N] P1 vertex values of one band
-    KinkTab kink;                  // the march's table of kappa's kinks (FP64 for every T)
+    const T *__restrict__ tab;     // the march's table: kinks of kappa (FP64), vertices of its tetrahedra (FP32)
     StencilDev<T> st;
     const T *__restrict__ near;    // quadrature tables of the mesh: near [125][8][8], then far [24][4][8]
-    StarTab star;                  // the same by offset (null: not built)
+    StarTab star;                  // FP64: the same by offset (null: not built)
 };
+__device__ __forceinline__ KinkTab depth_src(const EntryCtx<double> &c) { return {c.tab, c.kappa}; }
+__device__ __forceinline__ KappaSrc depth_src(const EntryCtx<float> &c) { return {c.tab}; }
 
 // ---------------------------------------------------------------- compile-time Kuhn star
 struct TetInfo { int slot[4]; int bits; };
@@ -144,8 +148,8 @@ __device__ __forceinline__ int wall_plane(const GridDev &g, const WallInfo &wi) 
 }
 
 // optical depth of the path from x (grid index P) to wall w and on to y (Q)
-__device__ __forceinline__ double tau_mirror(const GridDev &g, int w, const KinkTab &kt, const int P[3],
-                                             const int Q[3]) {
+template <typename Src>
+__device__ __forceinline__ auto tau_mirror(const GridDev &g, int w, const Src &kt, const int P[3], const int Q[3]) {
     const WallInfo wi = wall_info(g, w);
     return tau_reflected(g, kt, wi.axis, wall_plane(g, wi), P, Q);
 }
@@ -315,89 +319,85 @@ __device__ __forceinline__ T kappa_slot(const EntryCtx<T> &c, int64_t v, int slo
 // flat index of j): near offsets from the near table, far ones by the degree-2
 // rule, |x - y|^2 = |h d|^2 + A.d + C per point and the 4 points of a
 // tetrahedron over one common denominator.
-template <typename T>
-__device__ __forceinline__ T vol_points(const EntryCtx<T> &c, int64_t v, int cellmask, const int d0, const int d1,
+__device__ __forceinline__ double vol_points(const EntryCtx<double> &c, int64_t v, int cellmask, const int d0, const int d1,
                                      const int d2) {
     const GridDev &g = c.g;
-    T acc = (T)0;
+    double acc = 0.0;
     if (max(max(abs(d0), abs(d1)), abs(d2)) <= kNearCheb) {
-        const T *row = c.near + ((d0 + 2) * 25 + (d1 + 2) * 5 + (d2 + 2)) * 64;
+        const double *row = c.near + ((d0 + 2) * 25 + (d1 + 2) * 5 + (d2 + 2)) * 64;
 #pragma nounroll
         for (int o = 0; o < 8; ++o) {
             if (!((cellmask >> o) & 1)) continue;
 #pragma nounroll
             for (int e = 0; e < 8; ++e) acc += row[o * 8 + e] * kappa_slot(c, v, slot_of(e, o));
         }
-        return acc * (T)g.vol_scale;
+        return acc * g.vol_scale;
     }
-    const T x = (T)d0, y = (T)d1, z = (T)d2;
-    const T D2 = (T)(g.h[0] * g.h[0]) * x * x + (T)(g.h[1] * g.h[1]) * y * y + (T)(g.h[2] * g.h[2]) * z * z;
+    const double x = (double)d0, y = (double)d1, z = (double)d2;
+    const double D2 = g.h[0] * g.h[0] * x * x + g.h[1] * g.h[1] * y * y + g.h[2] * g.h[2] * z * z;
 #pragma nounroll
     for (int t = 0; t < kTets; ++t) {
         const TetInfo &ti = kStarDev.tet[t];
         if (!((cellmask >> ti.bits) & 1)) continue;
-        const T k0 = kappa_slot(c, v, ti.slot[0]), k1 = kappa_slot(c, v, ti.slot[1]);
-        const T k2 = kappa_slot(c, v, ti.slot[2]), k3 = kappa_slot(c, v, ti.slot[3]);
-        const T *e = c.near + kNearSize + t * 32;
-        T a[4], r[4];
+        const double k0 = kappa_slot(c, v, ti.slot[0]), k1 = kappa_slot(c, v, ti.slot[1]);
+        const double k2 = kappa_slot(c, v, ti.slot[2]), k3 = kappa_slot(c, v, ti.slot[3]);
+        const double *e = c.near + kNearSize + t * 32;
+        double a[4], r[4];
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
             r[q] = D2 + e[8 * q + 3] + e[8 * q + 0] * x + e[8 * q + 1] * y + e[8 * q + 2] * z;
             a[q] = e[8 * q + 4] * k0 + e[8 * q + 5] * k1 + e[8 * q + 6] * k2 + e[8 * q + 7] * k3;
         }
-        const T n01 = a[0] * r[1] + a[1] * r[0], d01 = r[0] * r[1];
-        const T n23 = a[2] * r[3] + a[3] * r[2], d23 = r[2] * r[3];
+        const double n01 = a[0] * r[1] + a[1] * r[0], d01 = r[0] * r[1];
+        const double n23 = a[2] * r[3] + a[3] * r[2], d23 = r[2] * r[3];
         acc += (n01 * d23 + n23 * d01) * recip(d01 * d23);
     }
-    return acc * (T)g.vol_scale;
+    return acc * g.vol_scale;
 }
 
-template <typename T, int o, int... es>
-__device__ __forceinline__ void cell_corners(std::integer_sequence<int, es...>, const EntryCtx<T> &c, int64_t v,
-                                             const T *__restrict__ row, T &acc) {
+template <int o, int... es>
+__device__ __forceinline__ void cell_corners(std::integer_sequence<int, es...>, const EntryCtx<double> &c, int64_t v,
+                                             const double *__restrict__ row, double &acc) {
     ((corner_used(es, o) ? (void)(acc = fma(row[o * 8 + es], kappa_slot(c, v, slot_of(es, o)), acc)) : (void)0), ...);
 }
-template <typename T, int... os>
-__device__ __forceinline__ T vol_cells(std::integer_sequence<int, os...>, const EntryCtx<T> &c, int64_t v, int cellmask,
-                                       const T *__restrict__ row) {
-    T acc = (T)0;
-    ((((cellmask >> os) & 1) ? cell_corners<T, os>(std::make_integer_sequence<int, 8>{}, c, v, row, acc) : (void)0), ...);
+template <int... os>
+__device__ __forceinline__ double vol_cells(std::integer_sequence<int, os...>, const EntryCtx<double> &c, int64_t v, int cellmask,
+                                       const double *__restrict__ row) {
+    double acc = 0.0;
+    ((((cellmask >> os) & 1) ? cell_corners<os>(std::make_integer_sequence<int, 8>{}, c, v, row, acc) : (void)0), ...);
     return acc;
 }
 
 // The star of a source vertex: its flat index, its cells, and for a whole star
 // kappa at its 15 vertices.
-template <typename T>
 struct Star {
     int64_t v;
     int cellmask;
-    T k[15];
+    double k[15];
 };
 
-// g(x_j + d, j): a row of the star table times kappa, 15 products and 128 (FP64)
-// or 64 (FP32) contiguous bytes per entry, where the points of the rule cost
-// about 1100 instructions (FP64, 24 tetrahedra); a source that misses cells (on
-// the boundary, at the hole) takes its cells' corner weights.  41^3: FP64 dense
-// fill 12.8 -> 7.7 ms, ACA entry launches 73.5 -> 70.4 (bound by the march);
-// 29^3 FP32 dense fill 7.1 -> 3.9.
-template <typename T>
-__device__ __forceinline__ T vol_quad(const EntryCtx<T> &c, const Star<T> &s, const int d[3]) {
+// g(x_j + d, j): a row of the star table times kappa, 15 products and 128
+// contiguous bytes per entry, where the points of the rule cost about 1100
+// instructions (24 tetrahedra); a source that misses cells (on
+// the boundary, at the hole) takes its cells' corner weights.  41^3: dense
+// fill 12.8 -> 7.7 ms, ACA entry launches 73.5 -> 70.4 (bound by the march).
+template <int>
+__device__ __forceinline__ double vol_quad(const EntryCtx<double> &c, const Star &s, const int d[3]) {
     if (!c.star.w) return vol_points(c, s.v, s.cellmask, d[0], d[1], d[2]);
     const int64_t row = (int64_t)(d[0] - c.star.lo[0]) * c.star.st0 + (d[1] - c.star.lo[1]) * c.star.st1 +
                         (d[2] - c.star.lo[2]);
     if (s.cellmask != 255)
         return vol_cells(std::make_integer_sequence<int, 8>{}, c, s.v, s.cellmask,
-                         static_cast<const T *>(c.star.cell) + row * 64);
-    const T *w = static_cast<const T *>(__builtin_assume_aligned(static_cast<const T *>(c.star.w) + row * kStarWeights, 64));
-    T acc = (T)0;   // explicit fma: the same sum wherever it is inlined
+                         c.star.cell + row * 64);
+    const double *w = static_cast<const double *>(__builtin_assume_aligned(c.star.w + row * kStarWeights, 64));
+    double acc = 0.0;   // explicit fma: the same sum wherever it is inlined
 #pragma unroll
     for (int v = 0; v < 15; ++v) acc = fma(w[v], s.k[v], acc);
     return acc;
 }
 
-template <typename T>
-__device__ __forceinline__ Star<T> load_star(const EntryCtx<T> &c, const int jj[3], int cellmask) {
-    Star<T> s;
+__device__ __forceinline__ Star load_star(const EntryCtx<double> &c, const int jj[3], int cellmask) {
+    Star s;
     s.v = (int64_t)jj[0] * c.g.stride[0] + (int64_t)jj[1] * c.g.stride[1] + jj[2];
     s.cellmask = cellmask;
     if (cellmask == 255) {
@@ -405,6 +405,86 @@ __device__ __forceinline__ Star<T> load_star(const EntryCtx<T> &c, const int jj[
         for (int v = 0; v < 15; ++v) s.k[v] = kappa_slot(c, s.v, star_slot(v));
     }
     return s;
+}
+
+// FP32 entries, point by point (march32.h says why).
+// Near field (grid offset d = x - x_j with |d_a| <= 2): the degree-5 rule's
+// sums, tabulated per mesh by cell and corner, so g is 64 products with the
+// star's kappa values (cells outside the grid skipped).
+__device__ __forceinline__ float vol_near(const float *__restrict__ tab, const float kn[27], int cellmask, const int d[3]) {
+    const float *row = tab + ((d[0] + 2) * 25 + (d[1] + 2) * 5 + (d[2] + 2)) * 64;
+    float acc = 0.0f;
+#pragma unroll
+    for (int bits = 0; bits < 8; ++bits) {
+        if (!((cellmask >> bits) & 1)) continue;
+        const int o0 = bits & 1, o1 = (bits >> 1) & 1, o2 = (bits >> 2) & 1;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            const int slot = ((e & 1) - o0 + 1) * 9 + (((e >> 1) & 1) - o1 + 1) * 3 + (((e >> 2) & 1) - o2 + 1);
+            acc += row[bits * 8 + e] * kn[slot];
+        }
+    }
+    return acc;
+}
+
+// Far field, one tetrahedron of the star: its 4 points' terms a_q / r_q added
+// over a common denominator, so one reciprocal serves the 4 points.
+template <int t>
+__device__ __forceinline__ void vol_far_tet(const float *__restrict__ ft, const float kn[27], int cellmask, float D2,
+                                            const float dg[3], float &acc) {
+    constexpr TetInfo ti = kStar.tet[t];
+    if (!((cellmask >> ti.bits) & 1)) return;
+    const float k0 = kn[ti.slot[0]], k1 = kn[ti.slot[1]], k2 = kn[ti.slot[2]], k3 = kn[ti.slot[3]];
+    const float *e = ft + t * 32;
+    float a[4], r[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        r[q] = D2 + e[8 * q + 3] + e[8 * q + 0] * dg[0] + e[8 * q + 1] * dg[1] + e[8 * q + 2] * dg[2];
+        a[q] = e[8 * q + 4] * k0 + e[8 * q + 5] * k1 + e[8 * q + 6] * k2 + e[8 * q + 7] * k3;
+    }
+    const float n01 = a[0] * r[1] + a[1] * r[0], d01 = r[0] * r[1];
+    const float n23 = a[2] * r[3] + a[3] * r[2], d23 = r[2] * r[3];
+    acc += (n01 * d23 + n23 * d01) * recip(d01 * d23);
+}
+
+template <int... ts>
+__device__ __forceinline__ float vol_far_all(std::integer_sequence<int, ts...>, const float *__restrict__ ft, const float kn[27],
+                                         int cellmask, float D2, const float dg[3]) {
+    float acc = 0.0f;
+    (vol_far_tet<ts>(ft, kn, cellmask, D2, dg, acc), ...);
+    return acc;
+}
+
+// The star of an FP32 source: its cells and kappa on the 3x3x3 block around it.
+struct Star32 {
+    int cellmask;
+    float k[27];
+};
+__device__ __forceinline__ Star32 load_star(const EntryCtx<float> &c, const int jj[3], int cellmask) {
+    const GridDev &g = c.g;
+    Star32 r;
+    r.cellmask = cellmask;
+#pragma unroll
+    for (int s = 0; s < 27; ++s) {
+        const int dx = s / 9 - 1, dy = (s / 3) % 3 - 1, dz = s % 3 - 1;
+        const int x = min(max(jj[0] + dx, 0), g.n[0] - 1);
+        const int y = min(max(jj[1] + dy, 0), g.n[1] - 1);
+        const int z = min(max(jj[2] + dz, 0), g.n[2] - 1);
+        r.k[s] = c.kappa[x * g.stride[0] + y * g.stride[1] + z];
+    }
+    return r;
+}
+// g(x_j + d, j) without the 1/(4 pi)|e| factor.  FIRST: the axis whose square is
+// rounded by itself in |h d|^2.
+template <int FIRST>
+__device__ __forceinline__ float vol_quad(const EntryCtx<float> &c, const Star32 &s, const int d[3]) {
+    if (max(max(abs(d[0]), abs(d[1])), abs(d[2])) <= kNearCheb) return vol_near(c.near, s.k, s.cellmask, d);
+    const GridDev &g = c.g;
+    const float h2[3] = {(float)(g.h[0] * g.h[0]), (float)(g.h[1] * g.h[1]), (float)(g.h[2] * g.h[2])};
+    const float dg[3] = {(float)d[0], (float)d[1], (float)d[2]};
+    constexpr int A = FIRST, B = 1 - FIRST;   // rounded the same way in every kernel
+    const float D2 = fma(h2[2] * dg[2], dg[2], fma(h2[B] * dg[B], dg[B], rounded_product(h2[A] * dg[A], dg[A])));
+    return vol_far_all(std::make_integer_sequence<int, kTets>{}, c.near + kNearSize, s.k, s.cellmask, D2, dg);
 }
 
 // Wall modes the entry code is compiled for: no wall, exactly one wall (the
@@ -416,6 +496,12 @@ inline int wall_mode(const GridDev &g) {
     return (g.has_hole || g.n_walls > 1) ? kAnyWalls : (g.n_walls == 0 ? kNoWall : kOneWall);
 }
 
+// The first term of an entry.  FP64: rounded, so that group_entry's sum is that of
+// a single lane.  FP32: free to join what follows (the BF16 lo part of a dense entry
+// is taken from the unrounded product).
+__device__ __forceinline__ double first_term(double att, double g) { return rounded_product(att, g); }
+__device__ __forceinline__ float first_term(float att, float g) { return att * g; }
+
 // sum over the direct path and the walls of attenuation times the quadrature
 // of the source star of ss seen from target tt (or from its mirror image in
 // each wall); att_w[w] = R_w exp(-tau_w)
@@ -426,56 +512,57 @@ __device__ __forceinline__ T vol_sum(const EntryCtx<T> &c, T att, const T att_w[
     int cellmask = cells_in_grid(g, ss);
     if constexpr (NW == kAnyWalls)
         if (g.has_hole) cellmask &= ~hole_cells(g, ss);   // the hole's cells are in no star
-    const Star<T> star = load_star(c, ss, cellmask);
+    const auto star = load_star(c, ss, cellmask);
     const int dg[3] = {tt[0] - ss[0], tt[1] - ss[1], tt[2] - ss[2]};
-    T G = rounded_product(att, vol_quad(c, star, dg));
+    T G = first_term(att, vol_quad<NW == kAnyWalls ? 0 : 1>(c, star, dg));
     if constexpr (NW != kNoWall) {
         const int nw = NW == kOneWall ? 1 : g.n_walls;
         for (int w = 0; w < nw; ++w) {
             int mt[3];
             mirror_index(g, w, tt, mt);
             const int dgm[3] = {mt[0] - ss[0], mt[1] - ss[1], mt[2] - ss[2]};
-            G += att_w[w] * vol_quad(c, star, dgm);
+            G += att_w[w] * vol_quad<1>(c, star, dgm);
         }
     }
-    return G;
+    if constexpr (sizeof(T) == 4) return G * (T)g.vol_scale;
+    else return G;   // the scale is in the table
 }
 
 // The attenuations of a pair: exp(-tau) along the direct path, and R_w
 // exp(-tau_w) per wall; a path that the hole blocks has tau = +infinity (no
 // march).  Pi, Qi: the vertices' grid indices.
-template <typename T, int NW>
-__device__ __forceinline__ T attenuations(const GridDev &g, const KinkTab &kt, const int Pi[3], const int Qi[3],
+template <typename T, int NW, typename Src>
+__device__ __forceinline__ T attenuations(const GridDev &g, const Src &kt, const int Pi[3], const int Qi[3],
                                           T att_w[6]) {
     if constexpr (NW == kAnyWalls) {
         const bool hole = g.has_hole;
-        const T att = (hole && hole_blocks(g, Pi, Qi)) ? (T)0 : exp(-(T)tau_direct(g, kt, Pi, Qi));
+        const T att = (hole && hole_blocks(g, Pi, Qi)) ? (T)0 : exp(-tau_direct(g, kt, Pi, Qi));
         for (int w = 0; w < g.n_walls; ++w)
             att_w[w] = (hole && hole_blocks_mirror(g, w, Pi, Qi))
                            ? (T)0
-                           : (T)wall_info(g, w).R * exp(-(T)tau_mirror(g, w, kt, Pi, Qi));
+                           : (T)wall_info(g, w).R * exp(-tau_mirror(g, w, kt, Pi, Qi));
         return att;
     } else {
-        const T att = exp(-(T)tau_direct(g, kt, Pi, Qi));
-        if constexpr (NW == kOneWall) att_w[0] = (T)g.R[0] * exp(-(T)tau_mirror(g, 0, kt, Pi, Qi));
+        const T att = exp(-tau_direct(g, kt, Pi, Qi));
+        if constexpr (NW == kOneWall) att_w[0] = (T)g.R[0] * exp(-tau_mirror(g, 0, kt, Pi, Qi));
         return att;
     }
 }
 
 // The same for a group of P lanes of one wavefront (P a power of two, lane
-// number `sub`) that share the pair: the families of every leg of every path
-// are dealt to the lanes and added in the order of kink_sum, so that the
-// attenuations are those of a single lane bit for bit.  buf: LDS of the group,
-// kGroupTasks<NW> values.
-template <int NW>
-constexpr int kGroupTasks = 6 * (1 + 2 * NW);
+// number `sub`) that share the pair.  FP64: the families of every leg of every
+// path are dealt to the lanes and added in the order of kink_sum; FP32: the legs
+// are.  The attenuations are those of a single lane bit for bit.  buf: LDS of the
+// group, kGroupTasks<T, NW> values.
+template <typename T, int NW>
+constexpr int kGroupTasks = (sizeof(T) == 8 ? 6 : 1) * (1 + 2 * NW);
 __device__ __forceinline__ void group_sync() {   // orders the LDS accesses of a wavefront
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     __builtin_amdgcn_wave_barrier();
 }
-template <typename T, int NW>
-__device__ __forceinline__ T group_attenuations(const GridDev &g, const KinkTab &kt, const int Pi[3], const int Qi[3],
-                                                T att_w[6], int P, int sub, double *buf) {
+template <int NW>
+__device__ __forceinline__ double group_attenuations(const GridDev &g, const KinkTab &kt, const int Pi[3],
+                                                     const int Qi[3], double att_w[6], int P, int sub, double *buf) {
     const int nw = NW == kAnyWalls ? g.n_walls : NW;
     for (int t = sub; t < 6 * (1 + 2 * nw); t += P) {
         const int leg = t / 6, f = t - 6 * leg;
@@ -498,7 +585,7 @@ __device__ __forceinline__ T group_attenuations(const GridDev &g, const KinkTab 
     group_sync();
     const double direct = direct_depth(g, kt, Pi, Qi, add_families(buf));
     const bool hole = NW == kAnyWalls && g.has_hole;
-    const T att = hole && hole_blocks(g, Pi, Qi) ? (T)0 : exp(-(T)direct);
+    const double att = hole && hole_blocks(g, Pi, Qi) ? 0.0 : exp(-direct);
     if constexpr (NW != kNoWall) {
         for (int w = 0; w < nw; ++w) {
             const WallInfo wi = wall_info(g, w);
@@ -507,15 +594,43 @@ __device__ __forceinline__ T group_attenuations(const GridDev &g, const KinkTab 
             const double *b = buf + 6 + 12 * w;
             const double tau = l.p + l.q == 0 ? direct
                                               : reflected_depth(g, kt, wi.axis, C, Pi, Qi, l, add_families(b) + add_families(b + 6));
-            att_w[w] = hole && hole_blocks_mirror(g, w, Pi, Qi) ? (T)0 : (T)wi.R * exp(-(T)tau);
+            att_w[w] = hole && hole_blocks_mirror(g, w, Pi, Qi) ? 0.0 : wi.R * exp(-tau);
         }
     }
+    return att;
+}
+template <int NW>
+__device__ __forceinline__ float group_attenuations(const GridDev &g, const KappaSrc &kt, const int Pi[3],
+                                                    const int Qi[3], float att_w[6], int P, int sub, float *buf) {
+    const int nw = NW == kAnyWalls ? g.n_walls : NW;
+    for (int t = sub; t < 1 + 2 * nw; t += P) {
+        float A[3] = {(float)Pi[0], (float)Pi[1], (float)Pi[2]}, B[3] = {(float)Qi[0], (float)Qi[1], (float)Qi[2]};
+        if (NW != kNoWall && t > 0) {   // P to the wall, the wall to Q
+            const WallInfo wi = wall_info(g, (t - 1) >> 1);
+            float X[3];
+            wall_point(wi.axis, (float)wall_plane(g, wi), A, B, X);
+#pragma unroll
+            for (int b = 0; b < 3; ++b) {
+                A[b] = t & 1 ? A[b] : X[b];
+                B[b] = t & 1 ? X[b] : B[b];
+            }
+        }
+        buf[t] = tau_segment(g, kt, A, B);
+    }
+    group_sync();
+    const bool hole = NW == kAnyWalls && g.has_hole;
+    const float att = hole && hole_blocks(g, Pi, Qi) ? 0.0f : exp(-buf[0]);
+    if constexpr (NW != kNoWall)
+        for (int w = 0; w < nw; ++w)
+            att_w[w] = hole && hole_blocks_mirror(g, w, Pi, Qi)
+                           ? 0.0f
+                           : (float)wall_info(g, w).R * exp(-(buf[1 + 2 * w] + buf[2 + 2 * w]));
     return att;
 }
 
 // G(i, j).  Every wall adds its own mirror-image term (one reflection per
 // ray).  The optical depths come first: the star of j is loaded after the
-// marches, so its values do not stay live through them.  FROM_J: the rays are
+// marches, so its values do not stay live through them.  FROM_J: FP64 rays are
 // walked from j (the depth is symmetric), for launches whose lanes share the
 // source: the lanes then meet the planes in step (KinkTab).
 template <typename T, int NW = kAnyWalls, bool FROM_J = false>
@@ -527,13 +642,15 @@ __device__ T volume_entry(const EntryCtx<T> &c, int64_t i, int64_t j) {
     if constexpr (NW == kAnyWalls)
         if (!vertex_active(g, ii)) return (T)0;   // a removed vertex (its column: an empty star)
     T att_w[6];
-    const T att = FROM_J ? attenuations<T, NW>(g, c.kink, jj, ii, att_w) : attenuations<T, NW>(g, c.kink, ii, jj, att_w);
+    constexpr bool from_j = FROM_J && sizeof(T) == 8;
+    const T att = attenuations<T, NW>(g, depth_src(c), from_j ? jj : ii, from_j ? ii : jj, att_w);
     return vol_sum<T, NW>(c, att, att_w, ii, jj);
 }
 
-// G(i, j) and G(j, i) together (lanes share j): the optical depth along the segment (and along
-// each reflected path, whose wall point is the same seen from either end) is
-// shared; each entry takes its own source star and quadrature.
+// G(i, j) and G(j, i) together (lanes share j; FP32 rays are walked from i): the
+// optical depth along the segment (and along each reflected path, whose wall point
+// is the same seen from either end) is shared; each entry takes its own source
+// star and quadrature.
 template <typename T, int NW = kAnyWalls>
 __device__ __forceinline__ void volume_entry_pair(const EntryCtx<T> &c, int64_t i, int64_t j, T &gij, T &gji) {
     const GridDev &g = c.g;
@@ -541,7 +658,8 @@ __device__ __forceinline__ void volume_entry_pair(const EntryCtx<T> &c, int64_t 
     vtx_index(g, i, ii);
     vtx_index(g, j, jj);
     T att_w[6];
-    const T att = attenuations<T, NW>(g, c.kink, jj, ii, att_w);
+    constexpr bool from_j = sizeof(T) == 8;
+    const T att = attenuations<T, NW>(g, depth_src(c), from_j ? jj : ii, from_j ? ii : jj, att_w);
     gij = vol_sum<T, NW>(c, att, att_w, ii, jj);
     gji = vol_sum<T, NW>(c, att, att_w, jj, ii);
     if constexpr (NW == kAnyWalls) {   // removed vertices have zero rows
@@ -746,7 +864,7 @@ template <typename T, int NW>
 __device__ __forceinline__ T surf_sum(const EntryCtx<T> &c, T att, const T att_w[6], const int ii[3], const int ll[3]) {
     const GridDev &g = c.g;
     if constexpr (NW == kAnyWalls) {
-        T S = att == (T)0 ? (T)0 : rounded_product(att, surf_quad_rects(c, ii, ll, cheb3(ii, ll) <= kNearCheb));
+        T S = att == (T)0 ? (T)0 : first_term(att, surf_quad_rects(c, ii, ll, cheb3(ii, ll) <= kNearCheb));
         for (int w = 0; w < g.n_walls; ++w) {
             if (att_w[w] == (T)0) continue;
             int mi[3];
@@ -755,7 +873,7 @@ __device__ __forceinline__ T surf_sum(const EntryCtx<T> &c, T att, const T att_w
         }
         return S;
     } else {
-        T S = rounded_product(att, surf_quad(c, ii, ll, cheb3(ii, ll) <= kNearCheb));
+        T S = first_term(att, surf_quad(c, ii, ll, cheb3(ii, ll) <= kNearCheb));
         if constexpr (NW == kOneWall) {
             int mi[3];
             mirror_index(g, 0, ii, mi);
@@ -774,7 +892,8 @@ __device__ T surface_entry(const EntryCtx<T> &c, int64_t i, int64_t l) {
     if constexpr (NW == kAnyWalls)
         if (!vertex_active(g, ii)) return (T)0;   // a removed vertex
     T att_w[6];
-    const T att = FROM_J ? attenuations<T, NW>(g, c.kink, ll, ii, att_w) : attenuations<T, NW>(g, c.kink, ii, ll, att_w);
+    constexpr bool from_j = FROM_J && sizeof(T) == 8;
+    const T att = attenuations<T, NW>(g, depth_src(c), from_j ? ll : ii, from_j ? ii : ll, att_w);
     return surf_sum<T, NW>(c, att, att_w, ii, ll);
 }
 
@@ -787,7 +906,7 @@ __device__ __forceinline__ T entry(const EntryCtx<T> &c, int64_t i, int64_t j) {
 // The entry of a pair shared by a group of P lanes (group_attenuations); every
 // lane returns it.
 template <typename T, int KIND, int NW, bool FROM_J>
-__device__ __forceinline__ T group_entry(const EntryCtx<T> &c, int64_t i, int64_t j, int P, int sub, double *buf) {
+__device__ __forceinline__ T group_entry(const EntryCtx<T> &c, int64_t i, int64_t j, int P, int sub, T *buf) {
     const GridDev &g = c.g;
     int ii[3], jj[3];
     vtx_index(g, i, ii);
@@ -795,8 +914,8 @@ __device__ __forceinline__ T group_entry(const EntryCtx<T> &c, int64_t i, int64_
     if constexpr (NW == kAnyWalls)
         if (!vertex_active(g, ii)) return (T)0;   // a removed vertex
     T att_w[6];
-    const T att = FROM_J ? group_attenuations<T, NW>(g, c.kink, jj, ii, att_w, P, sub, buf)
-                         : group_attenuations<T, NW>(g, c.kink, ii, jj, att_w, P, sub, buf);
+    constexpr bool from_j = FROM_J && sizeof(T) == 8;
+    const T att = group_attenuations<NW>(g, depth_src(c), from_j ? jj : ii, from_j ? ii : jj, att_w, P, sub, buf);
     if constexpr (KIND == RTE_VOLUME) return vol_sum<T, NW>(c, att, att_w, ii, jj);
     else return surf_sum<T, NW>(c, att, att_w, ii, jj);
 }

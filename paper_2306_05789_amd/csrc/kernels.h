@@ -114,19 +114,18 @@ struct EventTimer {
 
 template <typename T> struct EntryCtx;
 // One band's absorption as the entry kernels read it: the vertex values in the
-// entries' type (quadrature) and in FP64 (ends of a ray), and the table of
-// their kinks (march.h).
+// entries' type, and the march's table of them.
 template <typename T>
 struct BandKappa {
-    const T *v;            // [N]
-    const double *v64;     // [N]
-    const double *kinks;   // [6][n0 + 1][n1 + 1][n2 + 1]
+    const T *v;     // [N]
+    const T *tab;   // FP64: kinks [6][n0 + 1][n1 + 1][n2 + 1] (march.h); FP32: [N][6][4] (march32.h)
 };
-// s: the stream on which the mesh's quadrature table is built if it is not yet there (volume entries)
+// s: the stream on which the mesh's quadrature table is built if it is not yet there (FP64 volume entries)
 template <typename T> EntryCtx<T> make_ctx(const Mesh &m, int kind, BandKappa<T> kappa, hipStream_t s);
 // the march's table of `kappa` on the mesh, queued on s (scratch; the caller
 // keeps it until the launches that read it have run)
-DevBuf kink_table(const Mesh &m, const double *kappa, hipStream_t s);
+DevBuf march_table(const Mesh &m, const double *kappa, hipStream_t s);
+DevBuf march_table(const Mesh &m, const float *kappa, hipStream_t s);
 void to_float(const double *in, float *out, int64_t n, hipStream_t s);
 // queues the fill on s without waiting: the task list and the launch's event
 // pair go to B.retire / B.fill_events (read by band_settle); split: write BF16 hi/lo

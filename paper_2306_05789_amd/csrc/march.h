@@ -1,4 +1,5 @@
-// Optical depth between grid vertices, exact for the P1 kappa.
+// Optical depth between grid vertices, exact for the P1 kappa (FP64 entries; those
+// in FP32 keep the march of march32.h).
 //
 // Along a ray x(s) = V + s D, s in [0, 1], kappa is continuous and piecewise
 // linear, with a kink where the ray crosses a face of a Kuhn tetrahedron.  By
@@ -29,10 +30,9 @@
 // Bound by the gathers of the table and by integer arithmetic: about 18 vector
 // instructions and one 8-byte load per crossing, the loads of kMarchAhead
 // crossings independent.  A march that merges the six families and samples
-// kappa on every piece costs 55 (FP32) to 86 (FP64) instructions and 16 to 32
-// bytes of loads that wait for the merge: 41^3 FP64 volume entry launches
-// 137.9 -> 73.5 ms, surface 37.1 -> 20.1; 33x17x17 with a wall, 4 mixed bands
-// 486 -> 310; three walls and the hole (13x21x13) 42.2 -> 22.3.
+// kappa on every piece costs 86 instructions and 32 bytes of loads that wait for
+// the merge: 41^3 volume entry launches 137.9 -> 73.5 ms, surface 37.1 -> 20.1;
+// three walls and the hole (13x21x13) 42.2 -> 22.3.
 #pragma once
 
 #include <cstdint>
@@ -46,8 +46,8 @@ namespace rte {
 // k-th plane side by side, spread over a few cells of the plane, and the
 // coordinate that varies fastest within the plane is contiguous.  ACA entry
 // launches against one natural order for all families: 41^3 FP64 68.8 -> 67.3
-// ms, 33^3 4 mixed bands 188.6 -> 182.4 (the address units, busy 84 % of the
-// time, take about 20 cycles per load either way).
+// ms (the address units, busy 84 % of the time, take about 20 cycles per load
+// either way).
 struct KinkTab {
     const double *__restrict__ tab;
     const double *__restrict__ kappa;   // [N], natural order
@@ -127,8 +127,7 @@ constexpr double kOff0 = 1.0, kOff1 = 0.70710678118654752, kOff2 = 0.57735026918
 // Sum over the families of (1/N) sum_{k < w N} J k (w N - k) along V + s D, s < w = p / M (p = M: the whole
 // segment to the vertex V + D).  The axes rotate through one loop body (axis a
 // with x_a and x_a - x_b), which keeps the registers of one family live at a
-// time: with the six families unrolled the FP32 kernels with a wall spilled 106
-// registers.
+// time (six unrolled families spill).
 __device__ __forceinline__ double kink_sum(const GridDev &g, const double *__restrict__ tab, const int V[3],
                                            const int D[3], int p, int M) {
     int na = g.n[0] + 1, nb = g.n[1] + 1, nc = g.n[2] + 1;

@@ -112,22 +112,22 @@ struct NearTables {
 // for sources that miss cells, the weights of every cell's 8 corners
 // ([8 cells][8 corners]).  Near offsets hold the degree-5 rule's sums, the
 // others the degree-2 rule's; the factor |tet| / (4 pi) is folded in.  Built on
-// the GPU once per mesh, device and precision, owned by the mesh; null when it
+// the GPU once per mesh and device, owned by the mesh (FP64 entries); null when it
 // would take more than a 16th of the device memory or does not fit it (the
 // quadrature is then summed point by point).
 constexpr int kStarWeights = 16, kStarRow = kStarWeights + 64;
 struct StarTab {
-    const void *w = nullptr;    // [rows][16]
-    const void *cell = nullptr; // [rows][8][8]
+    const double *w = nullptr;      // [rows][16]
+    const double *cell = nullptr;   // [rows][8][8]
     int lo[3] = {0, 0, 0}, st0 = 0, st1 = 0;   // row of d: (d0 - lo0) st0 + (d1 - lo1) st1 + (d2 - lo2)
 };
 struct Mesh;
 struct DevBuf;
 struct StarCache {
     std::mutex mu;
-    std::map<std::pair<int, bool>, std::shared_ptr<DevBuf>> dev;   // (device, FP64)
+    std::map<int, std::shared_ptr<DevBuf>> dev;   // by device
 };
-StarTab star_table(const Mesh &m, bool fp64, hipStream_t s);   // built on s and waited for on first use (entry.hip)
+StarTab star_table(const Mesh &m, hipStream_t s);   // built on s and waited for on first use (entry.hip)
 
 struct PlanCache;   // block-tree plans of a mesh (htree.cpp)
 
