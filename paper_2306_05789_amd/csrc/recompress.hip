@@ -14,18 +14,21 @@
 //      Ru = L_u^T D_u and Qu = U Ru^-1 (the scaling keeps the Cholesky away
 //      from the spread of the ACA columns' norms);
 //   3. the core M = Ru Rv^T (U V^T = Qu M Qv^T) and its SVD by one-sided
-//      Jacobi rotations of M's columns, accumulated in Z: M Z = B with
-//      orthogonal columns of norms sigma_j;
+//      Jacobi rotations of M's columns: M Z = B with orthogonal columns of
+//      norms sigma_j (the rotations themselves are not kept, Z = M^T B S^-2, S
+//      the diagonal of sigma);
 //   4. r = the fewest columns of B, by decreasing sigma, whose dropped sigmas
 //      have a norm <= eps ||sigma||;
-//   5. U' = U Ru^-1 B_r, V' = V Rv^-1 Z_r (triangular solves on the small
-//      matrices, then one product per factor, written in place).
+//   5. U' = U Ru^-1 B_r, V' = V Rv^-1 Z_r = V Ru^T B_r S_r^-2 (a triangular
+//      solve and a triangular product on the small matrices, then one product
+//      per factor, written in place).
 //
 // A block whose scaled Gram is numerically singular, or that would not get
 // shorter, keeps its ACA factors.  The Gram matrices and the core are FP64
 // whatever the storage type; every reduction has a fixed order, so results
 // are bitwise reproducible.
 #include <cmath>
+#include <type_traits>
 
 #include "kernels.h"
 
@@ -38,20 +41,19 @@ constexpr int kRcMax = 96;   // recompressed ranks: up to 96 (larger blocks, a f
 struct RcTask {
     int64_t uoff, voff;   // U^T [kcap][m] and V^T [kcap][n] in the ACA scratch (elements)
     int64_t woff;         // FP64 workspace of the block: Gu, Gv, Mt, Zt (k x k each)
-    int32_t m, n, k, idx; // idx: the block's slot in the rank and order outputs
+    int32_t m, n, k, idx; // idx: the block's slot in the rank output
 };
 
 struct RcApply {
     int32_t task, side, i0, i1;   // rows [i0, i1) of U (side 0) or V (side 1)
 };
 
-// Launches go by rank bucket, each with the LDS its largest rank needs: the
-// factor tiles of k_rc_gram and k_rc_apply take kb x 33 doubles, the core of
-// k_rc_core (ranks up to kRcShared) 4 kb^2; small ranks then keep many
-// workgroups per CU.
-constexpr int kRcShared = 64;
-constexpr int kRcBuckets[] = {16, 32, 48, 64, 96};
-constexpr int kRcStaticLds = 6144;   // k_rc_core's fixed LDS (per-rank vectors, flags), rounded up
+// Launches go by rank bucket, each with the threads and the LDS its largest rank
+// needs (k_rc_gram and k_rc_apply: factor tiles of kb x 33 doubles), so that small
+// ranks keep many workgroups per CU.
+
+constexpr int kRcBuckets[] = {16, 32, 48, 64, kRcMax};
+constexpr int kRcStaticLds = 7168;   // k_rc_core's fixed LDS (per-rank vectors, flags), rounded up
 
 // Step 1: one workgroup per (block, factor).  The factor's rows are staged
 // 32 columns at a time in LDS (FP64); a thread accumulates a 4 x 4 tile of
@@ -117,75 +119,118 @@ __global__ __launch_bounds__(256) void k_rc_gram(const RcTask *__restrict__ task
     }
 }
 
-// Steps 2 to 5 (small matrices): one workgroup per block.  Output: the new
-// rank (-1: keep the ACA factors) and the order of B's columns; the
-// transforms Ru^-1 B and Rv^-1 Z are written over the columns of the global
-// Mt and Zt, where k_rc_apply reads them.  Where the working matrices live:
-// SH = kRcAllLds (ranks up to kRcShared): the scaled Grams, their factors, the
-// core and Z in LDS; SH = kRcJacobiLds: the core and Z in LDS (the Jacobi
-// sweeps), the factors in the global workspace; SH = kRcGlobal: all global.
-enum { kRcGlobal = 0, kRcAllLds = 1, kRcJacobiLds = 2 };
-template <int SH>
-__global__ __launch_bounds__(256) void k_rc_core(const RcTask *__restrict__ tasks, double *__restrict__ W,
-                                                 int *__restrict__ ord, int *__restrict__ rnew, double eps) {
-    extern __shared__ double smem[];   // the working matrices kept in LDS
-    __shared__ double du[kRcMax], dv[kRcMax], sig[kRcMax];
-    __shared__ int order[kRcMax];
+// Steps 2 to 5 (small matrices): one workgroup of 4 KB lanes per block of rank
+// k <= KB.  Output: the new rank (-1: keep the ACA factors), and over the global
+// Mt and Zt the transforms of U and V, where k_rc_apply reads them.
+//
+// Bound by the latency of the Jacobi rounds (k - 1 per sweep, about 8 sweeps, a
+// barrier each).  8 lanes hold a pair of columns in registers from its dot products
+// to its rotation, so a round is one pass over all pairs: a read and a write of M,
+// three sums over 8 lanes, one square root, one quotient and one reciprocal root.
+// Two matrices in LDS: the core M, and both Cholesky factors in the triangles of
+// one square; M's columns lie 8 doubles apart (mod 16), so that the 4 groups that
+// an LDS access serves at a time meet different banks.
+// 29^3 in 2 bands of mixed precision, recompression in all: 72 -> 20 ms (the Jacobi
+// with its rotations accumulated, 16 lanes per pair and 4 matrices in LDS: 280 ms of
+// kernels in 4 steps).  U' V'^T against the truncated SVD of 20x18x22 at eps 1e-5:
+// 1.1e-14 of the block's norm at most, 5.5e-14 with accumulated rotations.
+template <int KB>
+struct RcCore {
+    static constexpr int E = KB / 8;               // elements of a column per lane
+    static constexpr int LD = (KB / 16) * 16 + 8;  // stride of M's columns (KB a multiple of 16)
+    static constexpr int LS = KB + 1;              // stride of the factors' square
+    static constexpr size_t lds = sizeof(double) * KB * (LD + LS);
+};
+
+// sum over a group of 8 lanes (every lane gets it)
+template <int CTRL>
+__device__ __forceinline__ double dpp_add(double v) {
+    const uint64_t b = __builtin_bit_cast(uint64_t, v);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_mov_dpp((int)(uint32_t)b, CTRL, 0xF, 0xF, true);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_mov_dpp((int)(uint32_t)(b >> 32), CTRL, 0xF, 0xF, true);
+    return v + __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
+__device__ __forceinline__ double sum8(double v) {
+    v = dpp_add<0xB1>(v);     // quad_perm [1, 0, 3, 2]
+    v = dpp_add<0x4E>(v);     // quad_perm [2, 3, 0, 1]
+    return dpp_add<0x141>(v); // row_half_mirror: the other quad of the 8
+}
+
+// 1 / sqrt(x) and 1 / x for normal x far from the ends of the range, to about one ulp
+__device__ __forceinline__ double rsqrt_n(double x) {
+    double y = __builtin_amdgcn_rsq(x);
+#pragma unroll
+    for (int i = 0; i < 2; ++i) y = fma(0.5 * y, fma(-x * y, y, 1.0), y);
+    return y;
+}
+__device__ __forceinline__ double recip_n(double x) {
+    double y = __builtin_amdgcn_rcp(x);
+#pragma unroll
+    for (int i = 0; i < 2; ++i) y = fma(fma(-x, y, 1.0), y, y);
+    return y;
+}
+
+template <int KB>
+__global__ __launch_bounds__(4 * KB) void k_rc_core(const RcTask *__restrict__ tasks, double *__restrict__ W,
+                                                    int *__restrict__ rnew, double eps) {
+    constexpr int NT = 4 * KB, E = RcCore<KB>::E, LD = RcCore<KB>::LD, LS = RcCore<KB>::LS;
+    extern __shared__ double smem[];
+    __shared__ double du[KB], dv[KB], dw[KB], dl[2][KB], run[2][KB], sig[KB], wmax[NT / 64];
+    __shared__ int order[KB];
     __shared__ int fail, rotated, rk;
+    double *const M = smem;            // M[j * LD + i] = M(i, j), zero for k <= i < KB
+    double *const S = smem + KB * LD;  // S[p * LS + i] = L_u(p, i), S[i * LS + p] = L_v(p, i), p > i; diagonals in dl
     const RcTask t = tasks[blockIdx.x];
-    const int k = t.k, tid = threadIdx.x;
+    const int k = t.k, tid = threadIdx.x, grp = tid >> 3, sl = tid & 7;
     const int64_t kk = (int64_t)k * k;
-    double *const Gg = W + t.woff;        // global: Gu, Gv, Mt, Zt (row stride k)
-    double *const Mg = Gg + 2 * kk;       // Mt[j * k + i] = M(i, j): column j contiguous
-    double *const Zg = Gg + 3 * kk;
-    // working copies: row strides ldl (factors) and ld (core, Z), odd in LDS so
-    // that a column's elements (stride ld doubles) fall in different banks
-    const int ldl = SH == kRcAllLds ? (k | 1) : k;
-    const int ld = SH != kRcGlobal ? (k | 1) : k;
-    const int64_t kl = (int64_t)k * ldl, km = (int64_t)k * ld;
-    double *Lu = SH == kRcAllLds ? smem : Gg;
-    double *Lv = Lu + kl;
-    double *Mt = SH == kRcAllLds ? smem + 2 * kl : (SH == kRcJacobiLds ? smem : Mg);
-    double *Zt = SH == kRcGlobal ? Zg : Mt + km;
-    if (tid == 0) fail = 0;
+    const double *const Gu = W + t.woff, *const Gv = Gu + kk;
+    double *const Tu = W + t.woff + 2 * kk, *const Tv = Tu + kk;   // transforms, column c at c * k
+    if (tid == 0) {
+        fail = 0;
+        rk = k;
+    }
     __syncthreads();
-    for (int l = tid; l < k; l += 256) {
-        du[l] = sqrt(Gg[(int64_t)l * k + l]);
-        dv[l] = sqrt(Gg[kk + (int64_t)l * k + l]);
+    for (int l = tid; l < k; l += NT) {
+        du[l] = sqrt(Gu[(int64_t)l * k + l]);
+        dv[l] = sqrt(Gv[(int64_t)l * k + l]);
         if (!(du[l] > 0.0) || !(dv[l] > 0.0)) fail = 1;
+        dw[l] = du[l] * dv[l];
     }
     __syncthreads();
     if (fail) {
         if (tid == 0) rnew[t.idx] = -1;
         return;
     }
-    for (int e = tid; e < k * k; e += 256) {
+    for (int e = tid; e < k * k; e += NT) {
         const int i = e / k, j = e - i * k;
-        Lu[(int64_t)i * ldl + j] = Gg[e] / (du[i] * du[j]);
-        Lv[(int64_t)i * ldl + j] = Gg[kk + e] / (dv[i] * dv[j]);
+        // the Grams are symmetric: the lower triangle from Gu, the upper one from Gv
+        const double gu = Gu[e] / (du[i] * du[j]), gv = Gv[e] / (dv[i] * dv[j]);
+        S[i * LS + j] = i > j ? gu : gv;
+        if (i == j) {
+            run[0][i] = gu;
+            run[1][i] = gv;
+        }
     }
     __syncthreads();
-    // Cholesky of both scaled Grams at once (threads 0-127: Lu, 128-255: Lv),
-    // lower factor in place, column by column
+    // Cholesky of both scaled Grams at once, column by column, a thread per row
+    // (threads 0 .. 2 KB - 1: L_u, the others: L_v); run: the diagonal left
     {
-        const int half = tid >> 7, lt = tid & 127;
-        double *G = half ? Lv : Lu;
+        const int half = tid >= NT / 2 ? 1 : 0, i = tid - half * (NT / 2);
+        const int si = half ? 1 : LS, sj = half ? LS : 1;
         for (int j = 0; j < k; ++j) {
-            if (lt == 0) {
-                double d = G[(int64_t)j * ldl + j];
-                for (int p = 0; p < j; ++p) d -= G[(int64_t)j * ldl + p] * G[(int64_t)j * ldl + p];
-                if (!(d > 1e-13)) {   // numerically dependent columns
-                    fail = 1;
-                    d = 1.0;
-                }
-                G[(int64_t)j * ldl + j] = sqrt(d);
-            }
-            __syncthreads();
-            const double piv = G[(int64_t)j * ldl + j];
-            for (int i = j + 1 + lt; i < k; i += 128) {
-                double s = G[(int64_t)i * ldl + j];
-                for (int p = 0; p < j; ++p) s -= G[(int64_t)i * ldl + p] * G[(int64_t)j * ldl + p];
-                G[(int64_t)i * ldl + j] = s / piv;
+            double d = run[half][j];
+            const bool bad = !(d > 1e-13);   // numerically dependent columns
+            d = bad ? 1.0 : d;
+            if (i > j && i < k) {
+                double s = S[i * si + j * sj];
+#pragma unroll 4
+                for (int p = 0; p < j; ++p) s = fma(-S[i * si + p * sj], S[j * si + p * sj], s);
+                s *= rsqrt_n(d);
+                S[i * si + j * sj] = s;
+                run[half][i] = fma(-s, s, run[half][i]);
+            } else if (i == j) {
+                dl[half][j] = sqrt(d);
+                if (bad) fail = 1;
             }
             __syncthreads();
         }
@@ -194,69 +239,98 @@ __global__ __launch_bounds__(256) void k_rc_core(const RcTask *__restrict__ task
         if (tid == 0) rnew[t.idx] = -1;
         return;
     }
-    // core M = Ru Rv^T, Ru(i, p) = L_u(p, i) du(p) for p >= i; Z = I
-    for (int e = tid; e < k * k; e += 256) {
-        const int j = e / k, i = e - j * k;
+    // core M = Ru Rv^T, Ru(i, p) = L_u(p, i) du(p) for p >= i, times a power of two
+    // that brings its largest element to [1/2, 1)
+    double mx = 0.0;
+    for (int e = tid; e < k * KB; e += NT) {
+        const int j = e / KB, i = e - j * KB, p0 = i > j ? i : j;
         double s = 0.0;
-        for (int p = i > j ? i : j; p < k; ++p)
-            s += (Lu[(int64_t)p * ldl + i] * du[p]) * (Lv[(int64_t)p * ldl + j] * dv[p]);
-        Mt[(int64_t)j * ld + i] = s;
-        Zt[(int64_t)j * ld + i] = i == j ? 1.0 : 0.0;
+        if (i < k) {
+            s = (p0 == i ? dl[0][i] : S[p0 * LS + i]) * (p0 == j ? dl[1][j] : S[j * LS + p0]) * dw[p0];
+#pragma unroll 4
+            for (int p = p0 + 1; p < k; ++p) s = fma(S[p * LS + i] * S[j * LS + p], dw[p], s);
+        }
+        M[j * LD + i] = s;
+        mx = fmax(mx, fabs(s));
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) mx = fmax(mx, __shfl_xor(mx, o, 64));
+    if ((tid & 63) == 0) wmax[tid >> 6] = mx;
+    __syncthreads();
+    mx = wmax[0];
+#pragma unroll
+    for (int w = 1; w < NT / 64; ++w) mx = fmax(mx, wmax[w]);
+    if (!(mx > 0.0 && mx < HUGE_VAL)) {   // underflow or overflow of the core
+        if (tid == 0) rnew[t.idx] = -1;
+        return;
+    }
+    int ex;
+    (void)frexp(mx, &ex);
+    for (int e = tid; e < k * KB; e += NT) {
+        const int j = e / KB, i = e - j * KB;
+        M[j * LD + i] = ldexp(M[j * LD + i], -ex);
     }
     __syncthreads();
     // one-sided Jacobi: sweeps of the round-robin pairing of the columns (a
-    // dummy column when k is odd), 16 lanes per pair (16 pairs at a time),
-    // until a sweep rotates nothing.  A pair is rotated when its columns are
-    // not orthogonal to 1e-12 of their norms, far below the truncation
-    // tolerance; couplings below (1e-12 s)^2, s the largest column norm of M,
-    // are left: such columns are far beyond any truncation and would only
-    // trade rounding noise with the large ones.
-    for (int j = tid; j < k; j += 256) {
-        double c2 = 0.0;
-        for (int i = 0; i < k; ++i) c2 = fma(Mt[(int64_t)j * ld + i], Mt[(int64_t)j * ld + i], c2);
-        sig[j] = c2;
-    }
-    __syncthreads();
+    // dummy column when k is odd) until a sweep rotates nothing.  A pair is
+    // rotated when its columns are not orthogonal to 3e-15 of their norms (V' takes
+    // up sigma_1 / sigma_j times what is left; 1e-12 costs 4 % less and leaves 230
+    // times as much); couplings below (1e-12 s)^2, s the largest column norm of M,
+    // are left: such columns are far beyond any truncation and would only trade
+    // rounding noise with the large ones.
+    auto column_norms = [&]() {
+        for (int j = grp; j < k; j += NT / 8) {
+            double c2 = 0.0;
+#pragma unroll
+            for (int u = 0; u < E; ++u) c2 = fma(M[j * LD + sl + 8 * u], M[j * LD + sl + 8 * u], c2);
+            c2 = sum8(c2);
+            if (sl == 0) sig[j] = c2;
+        }
+        __syncthreads();
+    };
+    column_norms();
     double s2 = 0.0;
-    for (int j = 0; j < k; ++j) s2 = sig[j] > s2 ? sig[j] : s2;
+    for (int j = 0; j < k; ++j) s2 = fmax(s2, sig[j]);
     const double floor2 = 1e-24 * s2;
-    const int n = k + (k & 1), grp = tid >> 4, sl = tid & 15;
+    const int n = k + (k & 1);
     for (int sweep = 0; sweep < 30; ++sweep) {
         __syncthreads();
         if (tid == 0) rotated = 0;
         __syncthreads();
         for (int r = 0; r < n - 1; ++r) {
-            for (int pi = grp; pi < n / 2; pi += 16) {
-                const int qa = pi, qb = n - 1 - pi;
-                const int a = qa == 0 ? 0 : (qa - 1 + r) % (n - 1) + 1;
-                const int b = qb == 0 ? 0 : (qb - 1 + r) % (n - 1) + 1;
-                if (a >= k || b >= k) continue;   // the dummy column (the whole group)
-                double al = 0.0, be = 0.0, ga = 0.0;
-                for (int i = sl; i < k; i += 16) {
-                    const double x = Mt[(int64_t)a * ld + i], y = Mt[(int64_t)b * ld + i];
-                    al = fma(x, x, al);
-                    be = fma(y, y, be);
-                    ga = fma(x, y, ga);
-                }
+            if (grp < n / 2) {
+                int a = grp - 1 + r, b = n - 2 - grp + r;
+                a = grp == 0 ? 0 : (a >= n - 1 ? a - (n - 1) : a) + 1;
+                b = (b >= n - 1 ? b - (n - 1) : b) + 1;
+                if (a < k && b < k) {   // not the dummy column
+                    double *const ca = M + a * LD + sl, *const cb = M + b * LD + sl;
+                    double x[E], y[E], al = 0.0, be = 0.0, ga = 0.0;
 #pragma unroll
-                for (int o = 8; o > 0; o >>= 1) {
-                    al += __shfl_xor(al, o, 16);
-                    be += __shfl_xor(be, o, 16);
-                    ga += __shfl_xor(ga, o, 16);
-                }
-                if (fabs(ga) > 1e-12 * sqrt(al * be) && fabs(ga) > floor2) {
-                    const double zeta = (be - al) / (2.0 * ga);
-                    const double tt = (zeta >= 0.0 ? 1.0 : -1.0) / (fabs(zeta) + sqrt(1.0 + zeta * zeta));
-                    const double c = 1.0 / sqrt(1.0 + tt * tt), s = c * tt;
-                    for (int i = sl; i < k; i += 16) {
-                        const double x = Mt[(int64_t)a * ld + i], y = Mt[(int64_t)b * ld + i];
-                        Mt[(int64_t)a * ld + i] = c * x - s * y;
-                        Mt[(int64_t)b * ld + i] = s * x + c * y;
-                        const double zx = Zt[(int64_t)a * ld + i], zy = Zt[(int64_t)b * ld + i];
-                        Zt[(int64_t)a * ld + i] = c * zx - s * zy;
-                        Zt[(int64_t)b * ld + i] = s * zx + c * zy;
+                    for (int u = 0; u < E; ++u) {
+                        x[u] = ca[8 * u];
+                        y[u] = cb[8 * u];
                     }
-                    if (sl == 0) rotated = 1;
+#pragma unroll
+                    for (int u = 0; u < E; ++u) {
+                        al = fma(x[u], x[u], al);
+                        be = fma(y[u], y[u], be);
+                        ga = fma(x[u], y[u], ga);
+                    }
+                    al = sum8(al);
+                    be = sum8(be);
+                    ga = sum8(ga);
+                    if (ga * ga > 9e-30 * (al * be) && fabs(ga) > floor2) {
+                        // t = tan of the angle: the smaller root of t^2 + 2 z t - 1, z = (be - al) / (2 ga)
+                        const double d = be - al, h2 = fma(d, d, 4.0 * (ga * ga)), h = h2 * rsqrt_n(h2);
+                        const double tt = 2.0 * ga * recip_n(d + copysign(h, d));
+                        const double c = rsqrt_n(fma(tt, tt, 1.0)), s = c * tt;
+#pragma unroll
+                        for (int u = 0; u < E; ++u) {
+                            ca[8 * u] = c * x[u] - s * y[u];
+                            cb[8 * u] = s * x[u] + c * y[u];
+                        }
+                        if (sl == 0) rotated = 1;
+                    }
                 }
             }
             __syncthreads();
@@ -264,30 +338,20 @@ __global__ __launch_bounds__(256) void k_rc_core(const RcTask *__restrict__ task
         if (!rotated) break;   // read by every thread after the round's barrier
     }
     __syncthreads();
-    // singular values, their decreasing order, the truncation rank
-    for (int j = tid; j < k; j += 256) {
-        double s = 0.0;
-        for (int i = 0; i < k; ++i) s = fma(Mt[(int64_t)j * ld + i], Mt[(int64_t)j * ld + i], s);
-        sig[j] = sqrt(s);
-    }
-    __syncthreads();
-    for (int j = tid; j < k; j += 256) {
+    // singular values (sig: their squares), their decreasing order, the truncation
+    // rank: the first c >= 1 whose tail c .. k - 1 is within eps
+    column_norms();
+    for (int j = tid; j < k; j += NT) {
         int pos = 0;
         for (int i = 0; i < k; ++i) pos += (sig[i] > sig[j] || (sig[i] == sig[j] && i < j)) ? 1 : 0;
         order[pos] = j;
     }
     __syncthreads();
-    if (tid == 0) {
-        double total = 0.0;
-        for (int c = 0; c < k; ++c) total += sig[order[c]] * sig[order[c]];
-        int r = k;
-        double tail = 0.0;
-        for (int c = k - 1; c >= 1; --c) {
-            tail += sig[order[c]] * sig[order[c]];
-            if (tail <= eps * eps * total) r = c;
-            else break;
-        }
-        rk = r;
+    if (tid < k) {
+        double total = 0.0, tail = 0.0;
+        for (int c = 0; c < k; ++c) total += sig[order[c]];
+        for (int c = k - 1; c >= tid; --c) tail += sig[order[c]];
+        if (tid >= 1 && tail <= eps * eps * total) atomicMin(&rk, tid);
     }
     __syncthreads();
     const int r = rk;
@@ -295,22 +359,27 @@ __global__ __launch_bounds__(256) void k_rc_core(const RcTask *__restrict__ task
         if (tid == 0) rnew[t.idx] = -1;
         return;
     }
-    // transforms: column ord[c] of Mt becomes Ru^-1 B(:, ord[c]) = D_u^-1 L_u^-T b,
-    // the same column of Zt Rv^-1 Z(:, ord[c]); a thread per (kept column, side),
-    // solved in place, then written to the global columns
-    for (int q = tid; q < 2 * r; q += 256) {
-        const int c = q >> 1, side = q & 1, j = order[c];
-        const double *Lf = side ? Lv : Lu;
-        const double *d = side ? dv : du;
-        double *y = (side ? Zt : Mt) + (int64_t)j * ld;
-        double *out = (side ? Zg : Mg) + (int64_t)j * k;
+    // transforms, columns c < r by decreasing sigma, b = B(:, order[c]):
+    // V: Ru^T b / sigma^2
+    for (int e = tid; e < r * k; e += NT) {
+        const int c = e / k, p = e - c * k;
+        const double *b = M + order[c] * LD;
+        double s = dl[0][p] * b[p];
+#pragma unroll 4
+        for (int i = 0; i < p; ++i) s = fma(S[p * LS + i], b[i], s);
+        Tv[(int64_t)c * k + p] = ldexp(du[p] * s / sig[order[c]], -ex);
+    }
+    __syncthreads();
+    // U: Ru^-1 b = D_u^-1 L_u^-T b, solved in place by a group of 8 lanes per column
+    for (int c = grp; c < r; c += NT / 8) {
+        double *y = M + order[c] * LD;
         for (int i = k - 1; i >= 0; --i) {
-            double s = y[i];
-            for (int p = i + 1; p < k; ++p) s -= Lf[(int64_t)p * ldl + i] * y[p];
-            y[i] = s / Lf[(int64_t)i * ldl + i];
+            const double v = y[i] * recip_n(dl[0][i]);
+            for (int p = sl; p < i; p += 8) y[p] = fma(-S[i * LS + p], v, y[p]);
+            if (sl == 0) Tu[(int64_t)c * k + i] = ldexp(v / du[i], ex);
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");   // the group's next read of y
+            __builtin_amdgcn_wave_barrier();
         }
-        for (int i = 0; i < k; ++i) out[i] = y[i] / d[i];
-        if (side == 0) ord[(int64_t)t.idx * kRcMax + c] = j;
     }
     if (tid == 0) rnew[t.idx] = r;
 }
@@ -321,7 +390,7 @@ __global__ __launch_bounds__(256) void k_rc_core(const RcTask *__restrict__ task
 template <typename T>
 __global__ __launch_bounds__(256) void k_rc_apply(const RcApply *__restrict__ ap, const RcTask *__restrict__ tasks,
                                                   T *__restrict__ Us, T *__restrict__ Vs, const double *__restrict__ W,
-                                                  const int *__restrict__ ord, const int *__restrict__ rnew) {
+                                                  const int *__restrict__ rnew) {
     extern __shared__ double sx[];   // [k][33]
     const RcApply a = ap[blockIdx.x];
     const RcTask t = tasks[a.task];
@@ -338,7 +407,7 @@ __global__ __launch_bounds__(256) void k_rc_apply(const RcApply *__restrict__ ap
     const int i = threadIdx.x & 31, g = threadIdx.x >> 5;
     if (i >= w) return;
     for (int c = g; c < r; c += 8) {
-        const double *__restrict__ col = Tm + (int64_t)ord[(int64_t)t.idx * kRcMax + c] * k;
+        const double *__restrict__ col = Tm + (int64_t)c * k;
         double s = 0.0;
         for (int l = 0; l < k; ++l) s = fma(sx[l * 33 + i], col[l], s);
         X[(int64_t)c * L + a.i0 + i] = (T)s;
@@ -361,7 +430,7 @@ void recompress_batch(const std::vector<AcaTask> &tasks, std::vector<int> &rk, T
     if (cand.empty()) return;
     EventTimer timer(s);
     timer.start();
-    // the LDS a workgroup may ask for (the cores of the larger buckets go global beyond it)
+    // the LDS a workgroup may ask for (the core of the largest bucket takes 158 KiB of the 160)
     int dev = 0, lds_max = 0;
     HIP_CHECK(hipGetDevice(&dev));
     HIP_CHECK(hipDeviceGetAttribute(&lds_max, hipDeviceAttributeMaxSharedMemoryPerBlock, dev));
@@ -395,7 +464,7 @@ void recompress_batch(const std::vector<AcaTask> &tasks, std::vector<int> &rk, T
         const int nt = (int)rt.size();
         DevBuf dt = upload_scratch(rt, s), dap = upload_scratch(ap, s);
         DevBuf W = DevBuf::scratch(sizeof(double) * (size_t)words);
-        DevBuf dord = DevBuf::scratch(sizeof(int) * (size_t)nt * kRcMax), dr = DevBuf::scratch(sizeof(int) * (size_t)nt);
+        DevBuf dr = DevBuf::scratch(sizeof(int) * (size_t)nt);
         const RcTask *tp = dt.as<RcTask>();
         const RcApply *app = dap.as<RcApply>();
         int t0 = 0, a0 = 0;
@@ -404,20 +473,21 @@ void recompress_batch(const std::vector<AcaTask> &tasks, std::vector<int> &rk, T
             if (t1 > t0) {
                 const size_t tile = sizeof(double) * (size_t)((kb + 3) / 4 * 4) * 33;
                 k_rc_gram<T><<<dim3((unsigned)(t1 - t0), 2), 256, tile, s>>>(tp + t0, Us, Vs, W.as<double>());
-                // LDS for the working matrices: all four, or the core and Z only, or none
-                const size_t all_lds = sizeof(double) * 4 * kb * (kb | 1), jac_lds = all_lds / 2;
-                const size_t room = (size_t)lds_max - kRcStaticLds;
-                if (kb <= kRcShared && all_lds <= room)
-                    k_rc_core<kRcAllLds><<<(unsigned)(t1 - t0), 256, all_lds, s>>>(
-                        tp + t0, W.as<double>(), dord.as<int>(), dr.as<int>(), eps);
-                else if (jac_lds <= room)
-                    k_rc_core<kRcJacobiLds><<<(unsigned)(t1 - t0), 256, jac_lds, s>>>(
-                        tp + t0, W.as<double>(), dord.as<int>(), dr.as<int>(), eps);
-                else
-                    k_rc_core<kRcGlobal><<<(unsigned)(t1 - t0), 256, 0, s>>>(tp + t0, W.as<double>(), dord.as<int>(),
-                                                                             dr.as<int>(), eps);
+                auto core = [&](auto kb_c) {
+                    constexpr int KB = decltype(kb_c)::value;
+                    RTE_REQUIRE(RcCore<KB>::lds + kRcStaticLds <= (size_t)lds_max, "recompression: LDS of the device");
+                    k_rc_core<KB><<<(unsigned)(t1 - t0), 4 * KB, RcCore<KB>::lds, s>>>(tp + t0, W.as<double>(),
+                                                                                       dr.as<int>(), eps);
+                };
+                switch (bk) {
+                    case 0: core(std::integral_constant<int, kRcBuckets[0]>()); break;
+                    case 1: core(std::integral_constant<int, kRcBuckets[1]>()); break;
+                    case 2: core(std::integral_constant<int, kRcBuckets[2]>()); break;
+                    case 3: core(std::integral_constant<int, kRcBuckets[3]>()); break;
+                    default: core(std::integral_constant<int, kRcBuckets[4]>()); break;
+                }
                 k_rc_apply<T><<<(unsigned)(a1 - a0), 256, sizeof(double) * kb * 33, s>>>(
-                    app + a0, tp, Us, Vs, W.as<double>(), dord.as<int>(), dr.as<int>());
+                    app + a0, tp, Us, Vs, W.as<double>(), dr.as<int>());
                 HIP_LAUNCH_CHECK();
             }
             t0 = std::max(t0, t1);
@@ -433,7 +503,7 @@ void recompress_batch(const std::vector<AcaTask> &tasks, std::vector<int> &rk, T
             if (rn[q] > 0) rk[t] = rn[q];
             B.rc_after += rk[t] * mn;
         }
-        for (DevBuf *d : {&dt, &dap, &W, &dord, &dr}) B.retire.push_back(std::move(*d));
+        for (DevBuf *d : {&dt, &dap, &W, &dr}) B.retire.push_back(std::move(*d));
         c0 = c1;
     }
     timer.stop();
