@@ -336,6 +336,55 @@ __device__ __forceinline__ f64x4 mfma64(double a, double b, f64x4 c) {
     return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
 }
 
+// Both phases are bound by the operator's bytes, a wavefront by the loads it has in
+// flight: kMf64Steps steps of 4 k indices are loaded before the first is used,
+// without a branch on the lane (a row of A and a column of B that the block or the
+// call does not have touch only results that are not stored, so they read a valid
+// one; past the last index both are zero).  29^3, 16 right-hand sides (1.38 GB):
+// phase A 300 -> 150 us, phase B 343 -> 212; with 8 steps 150 and 229, with a
+// register budget of 4 wavefronts per SIMD 152 and 228.
+constexpr int kMf64Steps = 4;
+typedef double f64x2 __attribute__((ext_vector_type(2)));
+typedef const f64x2 __attribute__((address_space(1))) *pair_ptr;   // global memory: no flat loads
+
+// acc += A B over k < n: a lane's pair of rows of A at p0 (tiles 0 and 1) and p1 (tiles
+// 2 and 3, if TWO), `ld` pairs from one k to the next, its column of B at q.  Within a
+// chunk or a block, so offsets fit 32 bits.
+template <bool TWO>
+__device__ __forceinline__ void mf64_sum(f64x4 (&acc)[4], int n, int sub, const double *p0, const double *p1, int ld,
+                                         const double *q) {
+    constexpr int U = kMf64Steps;
+    n = __builtin_amdgcn_readfirstlane(n);
+    ld = __builtin_amdgcn_readfirstlane(ld);
+    const pair_ptr a0 = (pair_ptr)p0, a1 = (pair_ptr)p1;
+    auto batch = [&](int k0, auto tail) {
+        f64x2 x0[U], x1[U];
+        double y[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int k = tail.value ? min(k0 + 4 * u + sub, n - 1) : k0 + 4 * u + sub;
+            x0[u] = a0[(uint32_t)(k * ld)];
+            if constexpr (TWO) x1[u] = a1[(uint32_t)(k * ld)];
+            y[u] = q[(uint32_t)k];
+        }
+        __builtin_amdgcn_sched_barrier(0);   // the loads stay together
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const bool in = !tail.value || k0 + 4 * u + sub < n;
+            const double b = in ? y[u] : 0.0;
+            acc[0] = mfma64(in ? x0[u].x : 0.0, b, acc[0]);
+            acc[1] = mfma64(in ? x0[u].y : 0.0, b, acc[1]);
+            if constexpr (TWO) {
+                acc[2] = mfma64(in ? x1[u].x : 0.0, b, acc[2]);
+                acc[3] = mfma64(in ? x1[u].y : 0.0, b, acc[3]);
+            }
+        }
+    };
+    int k0 = 0;
+    for (; k0 + 4 * U <= n; k0 += 4 * U) batch(k0, std::false_type());
+    if (k0 < n) batch(k0, std::true_type());
+}
+
 // Phase A: one wavefront per task (a chunk of V [nj][kp] rows), ranks in
 // slices of 64 = 4 tiles of 16.  A lane loads 2 consecutive ranks of a row in
 // one 16-byte load: the even one feeds tile 0 (2) and the odd one tile 1
@@ -363,21 +412,9 @@ __global__ __launch_bounds__(256) void k_phase_a_mf64(const VtTask *__restrict__
         f64x4 acc[4];
 #pragma unroll
         for (int tl = 0; tl < 4; ++tl) acc[tl] = f64x4{0.0, 0.0, 0.0, 0.0};
-        for (int jj = 0; jj < tk.nj; jj += 4) {
-            const int j = jj + sub;
-            const bool jl = j < tk.nj;
-            const double b = xl && jl ? xr[j] : 0.0;
-            const double2 *vr = reinterpret_cast<const double2 *>(V + (int64_t)j * kp + L0) + col;
-            const double2 z{0.0, 0.0};
-            const double2 a0 = jl && h0 ? vr[0] : z;
-            acc[0] = mfma64(a0.x, b, acc[0]);
-            acc[1] = mfma64(a0.y, b, acc[1]);
-            if (two) {
-                const double2 a1 = jl && h1 ? vr[16] : z;
-                acc[2] = mfma64(a1.x, b, acc[2]);
-                acc[3] = mfma64(a1.y, b, acc[3]);
-            }
-        }
+        const double *v0 = V + L0 + (h0 ? 2 * col : 0), *v1 = V + L0 + (h1 ? 32 + 2 * col : 0);
+        if (two) mf64_sum<true>(acc, tk.nj, sub, v0, v1, kp / 2, xr);
+        else mf64_sum<false>(acc, tk.nj, sub, v0, v1, kp / 2, xr);
         if (xl) {
 #pragma unroll
             for (int tl = 0; tl < 4; ++tl)
@@ -426,21 +463,9 @@ __global__ __launch_bounds__(64 * W) void k_phase_b_mf64(const LeafWork *__restr
             if (s + W < lw.seg1) nxt = segs[s + W];
             const double *cr = (cur.is_lr ? t + (int64_t)rc * ldt : x + (int64_t)rc * ldx) + cur.coef_off;
             const double *D = static_cast<const double *>(cur.data) + rb;
-            for (int c0 = 0; c0 < cur.K; c0 += 4) {
-                const int c = c0 + sub;
-                const bool cl = c < cur.K;
-                const double b = xl && cl ? cr[c] : 0.0;
-                const double2 *dc = reinterpret_cast<const double2 *>(D + (int64_t)c * cur.ld) + col;
-                const double2 z{0.0, 0.0};
-                const double2 a0 = cl && h0 ? dc[0] : z;
-                acc[0] = mfma64(a0.x, b, acc[0]);
-                acc[1] = mfma64(a0.y, b, acc[1]);
-                if (two) {
-                    const double2 a1 = cl && h1 ? dc[16] : z;
-                    acc[2] = mfma64(a1.x, b, acc[2]);
-                    acc[3] = mfma64(a1.y, b, acc[3]);
-                }
-            }
+            const double *d0 = D + (h0 ? 2 * col : 0), *d1 = D + (h1 ? 32 + 2 * col : 0);
+            if (two) mf64_sum<true>(acc, cur.K, sub, d0, d1, cur.ld / 2, cr);
+            else mf64_sum<false>(acc, cur.K, sub, d0, d1, cur.ld / 2, cr);
         }
 #pragma unroll
         for (int tl = 0; tl < 4; ++tl)
