@@ -118,17 +118,68 @@ namespace {
 // factor storage of the vector-ALU path: FP64 or FP32
 enum : int { ST_F64 = 0, ST_F32 = 1 };
 
+typedef double f64x2 __attribute__((ext_vector_type(2)));
+typedef float f32q __attribute__((ext_vector_type(4)));
+typedef const f64x2 __attribute__((address_space(1))) *pair_ptr;   // global memory: no flat loads
+typedef const f32q __attribute__((address_space(1))) *quad_ptr;
+
 // 4 consecutive elements starting at element i (i a multiple of 4, rows aligned)
-template <int ST, int MODE, typename A>
-__device__ __forceinline__ void load4(const void *p, const void *, int64_t i, A v[4]) {
+template <int ST, typename A>
+__device__ __forceinline__ void load4(const void *p, uint32_t i, A v[4]) {
     if constexpr (ST == ST_F64) {
-        const double2 *q = reinterpret_cast<const double2 *>(static_cast<const double *>(p) + i);
-        const double2 a = q[0], b = q[1];
+        const pair_ptr q = (pair_ptr)(static_cast<const double *>(p) + i);
+        const f64x2 a = q[0], b = q[1];
         v[0] = (A)a.x; v[1] = (A)a.y; v[2] = (A)b.x; v[3] = (A)b.y;
     } else {
-        const float4 a = *reinterpret_cast<const float4 *>(static_cast<const float *>(p) + i);
+        const f32q a = *(quad_ptr)(static_cast<const float *>(p) + i);
         v[0] = (A)a.x; v[1] = (A)a.y; v[2] = (A)a.z; v[3] = (A)a.w;
     }
+}
+
+// acc[r] += v(k) c(k, r), a lane's elements k = first, first + stride, ... < n of one
+// chunk or block (first < stride), two products at a time: v(k) the 4 elements at
+// p + at + k ld, c(k, r) at q + r ldq + k.  A wavefront is bound by the loads it has in
+// flight, so U elements are loaded together and without a branch on the lane (past
+// the end the last one, with c = 0); fewer when half of them reach the end.  FP64, one
+// right-hand side, against two at a time under a condition: 27x18x22 in 2 bands
+// phase A 93 -> 75 us, phase B 135 -> 123 (U = 4: 81 and 128; U = 8 held to 4
+// wavefronts per SIMD: 79 and 127); 41^3 388 -> 385 and 531 -> 507, near the rate of a
+// large read.
+template <int U, bool TAIL, int ST, typename A, int NR>
+__device__ __forceinline__ void valu_batch(A (&acc)[NR][4], int k0, int stride, int n, const void *p, uint32_t at,
+                                           int ld, const double *q, int64_t ldq, int nr) {
+    A v[U][4], c[U][NR];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const int k = TAIL ? min(k0 + u * stride, n - 1) : k0 + u * stride;
+        load4<ST>(p, at + (uint32_t)(k * ld), v[u]);
+#pragma unroll
+        for (int r = 0; r < NR; ++r) c[u][r] = (A)q[(int64_t)min(r, nr - 1) * ldq + k];
+    }
+    __builtin_amdgcn_sched_barrier(0);   // the loads stay together
+#pragma unroll
+    for (int u = 0; u < U; u += 2) {
+        const bool one = !TAIL || k0 + u * stride < n, two = !TAIL || k0 + (u + 1) * stride < n;
+#pragma unroll
+        for (int r = 0; r < NR; ++r) {
+            const A c0 = one ? c[u][r] : (A)0, c1 = two ? c[u + 1][r] : (A)0;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) acc[r][e] += v[u][e] * c0 + v[u + 1][e] * c1;
+        }
+    }
+}
+
+template <int ST, typename A, int NR>
+__device__ __forceinline__ void valu_sum(A (&acc)[NR][4], int first, int stride, int n, const void *p, uint32_t at,
+                                         int ld, const double *q, int64_t ldq, int nr) {
+    constexpr int U = NR == 1 ? 8 : 4;
+    n = __builtin_amdgcn_readfirstlane(n);
+    ld = __builtin_amdgcn_readfirstlane(ld);
+    int k0 = 0;
+    for (; k0 + U * stride <= n; k0 += U * stride)
+        valu_batch<U, false, ST>(acc, k0 + first, stride, n, p, at, ld, q, ldq, nr);
+    if (n - k0 > U / 2 * stride) valu_batch<U, true, ST>(acc, k0 + first, stride, n, p, at, ld, q, ldq, nr);
+    else if (n > k0) valu_batch<U / 2, true, ST>(acc, k0 + first, stride, n, p, at, ld, q, ldq, nr);
 }
 
 template <int ST, int MODE, typename A, int NR>
@@ -157,35 +208,7 @@ __global__ __launch_bounds__(256) void k_phase_a(const VtTask *__restrict__ task
         for (int r = 0; r < NR; ++r)
 #pragma unroll
             for (int u = 0; u < 4; ++u) acc[r][u] = (A)0;
-        int jj = g;
-        for (; jj + G < tk.nj; jj += 2 * G) {
-            A v0[4] = {(A)0, (A)0, (A)0, (A)0}, v1[4] = {(A)0, (A)0, (A)0, (A)0};
-            if (live) {
-                load4<ST, MODE, A>(tk.V, tk.Vlo, (int64_t)jj * kp + l, v0);
-                load4<ST, MODE, A>(tk.V, tk.Vlo, (int64_t)(jj + G) * kp + l, v1);
-            }
-#pragma unroll
-            for (int r = 0; r < NR; ++r) {
-                if (r < nr) {
-                    const double *xr = x + (int64_t)(r0 + r) * ldx + tk.s0 + jj;
-                    const A x0 = (A)xr[0], x1 = (A)xr[G];
-#pragma unroll
-                    for (int u = 0; u < 4; ++u) acc[r][u] += v0[u] * x0 + v1[u] * x1;
-                }
-            }
-        }
-        if (jj < tk.nj) {
-            A v0[4] = {(A)0, (A)0, (A)0, (A)0};
-            if (live) load4<ST, MODE, A>(tk.V, tk.Vlo, (int64_t)jj * kp + l, v0);
-#pragma unroll
-            for (int r = 0; r < NR; ++r) {
-                if (r < nr) {
-                    const A x0 = (A)x[(int64_t)(r0 + r) * ldx + tk.s0 + jj];
-#pragma unroll
-                    for (int u = 0; u < 4; ++u) acc[r][u] += v0[u] * x0;
-                }
-            }
-        }
+        valu_sum<ST>(acc, g, G, tk.nj, tk.V, live ? l : l0, kp, x + (int64_t)r0 * ldx + tk.s0, ldx, nr);
         // add the G row groups (lanes q, q + LQ, ...) in a fixed order
 #pragma unroll
         for (int r = 0; r < NR; ++r) {
@@ -218,21 +241,13 @@ __global__ __launch_bounds__(256) void k_phase_a_reduce(const VtReduce *__restri
 
 // a lane reads RPL = 4 consecutive rows of one column per load (16 or 32
 // bytes); 16 lanes cover a 64-row tile and 4 column groups run side by side
-template <int ST, int MODE, typename A, int RPL>
-__device__ __forceinline__ void load_rows(const void *p, const void *lo, int64_t i, A v[RPL]) {
-    static_assert(RPL == 4, "4 rows per lane");
-    load4<ST, MODE, A>(p, lo, i, v);
-}
-
-template <int ST> constexpr int rows_per_lane() { return 4; }
-
 template <int ST, int MODE, typename A, int NR, int W>
 __global__ __launch_bounds__(64 * W) void k_phase_b(const LeafWork *__restrict__ leaves, const Seg *__restrict__ segs,
                                                     const double *__restrict__ x, int64_t ldx, int64_t xbs,
                                                     const double *__restrict__ t, int64_t ldt,
                                                     const double *__restrict__ y0, double *__restrict__ y,
                                                     int64_t ldy, int64_t ybs, int r0, int nr) {
-    constexpr int RPL = rows_per_lane<ST>();
+    constexpr int RPL = 4;
     constexpr int LPC = 64 / RPL;   // lanes per column (a 64-row tile)
     constexpr int CG = RPL;         // column groups
     __shared__ A part[W][NR][64];
@@ -244,12 +259,12 @@ __global__ __launch_bounds__(64 * W) void k_phase_b(const LeafWork *__restrict__
     if (y0) y0 += (int64_t)lw.band * ybs;
     for (int rb = 0; rb < lw.rows; rb += 64) {
         const bool rlive = rb + RPL * rq < lw.rows;
-        const int64_t cb = rb + RPL * rq;   // first row of this lane within a column
-        A acc[RPL][NR];
+        const uint32_t cb = rlive ? rb + RPL * rq : rb;   // first row of this lane within a column
+        A acc[NR][RPL];
 #pragma unroll
-        for (int u = 0; u < RPL; ++u)
+        for (int r = 0; r < NR; ++r)
 #pragma unroll
-            for (int r = 0; r < NR; ++r) acc[u][r] = (A)0;
+            for (int u = 0; u < RPL; ++u) acc[r][u] = (A)0;
         int s = lw.seg0 + wid;
         Seg sg;
         if (s < lw.seg1) sg = segs[s];
@@ -257,56 +272,25 @@ __global__ __launch_bounds__(64 * W) void k_phase_b(const LeafWork *__restrict__
             // the next descriptor is fetched while this segment streams
             const Seg cur = sg;
             if (s + W < lw.seg1) sg = segs[s + W];
-            const double *cf = (cur.is_lr ? t : x) + cur.coef_off;
             const int64_t ldc = cur.is_lr ? ldt : ldx;
-            int l = cg;
-            for (; l + CG < cur.K; l += 2 * CG) {
-                A d0[RPL], d1[RPL];
-#pragma unroll
-                for (int u = 0; u < RPL; ++u) d0[u] = d1[u] = (A)0;
-                if (rlive) {
-                    load_rows<ST, MODE, A, RPL>(cur.data, cur.lo, (int64_t)l * cur.ld + cb, d0);
-                    load_rows<ST, MODE, A, RPL>(cur.data, cur.lo, (int64_t)(l + CG) * cur.ld + cb, d1);
-                }
-#pragma unroll
-                for (int r = 0; r < NR; ++r) {
-                    if (r < nr) {
-                        const A c0 = (A)cf[(int64_t)(r0 + r) * ldc + l], c1 = (A)cf[(int64_t)(r0 + r) * ldc + l + CG];
-#pragma unroll
-                        for (int u = 0; u < RPL; ++u) acc[u][r] += d0[u] * c0 + d1[u] * c1;
-                    }
-                }
-            }
-            if (l < cur.K) {
-                A d0[RPL];
-#pragma unroll
-                for (int u = 0; u < RPL; ++u) d0[u] = (A)0;
-                if (rlive) load_rows<ST, MODE, A, RPL>(cur.data, cur.lo, (int64_t)l * cur.ld + cb, d0);
-#pragma unroll
-                for (int r = 0; r < NR; ++r) {
-                    if (r < nr) {
-                        const A c0 = (A)cf[(int64_t)(r0 + r) * ldc + l];
-#pragma unroll
-                        for (int u = 0; u < RPL; ++u) acc[u][r] += d0[u] * c0;
-                    }
-                }
-            }
+            valu_sum<ST>(acc, cg, CG, cur.K, cur.data, cb, cur.ld, (cur.is_lr ? t : x) + (int64_t)r0 * ldc + cur.coef_off,
+                         ldc, nr);
         }
         // sum over the column groups (same order on every lane)
 #pragma unroll
         for (int u = 0; u < RPL; ++u)
 #pragma unroll
             for (int r = 0; r < NR; ++r) {
-                A a = acc[u][r];
+                A a = acc[r][u];
 #pragma unroll
                 for (int o = LPC; o < 64; o <<= 1) a += __shfl_xor(a, o, 64);
-                acc[u][r] = a;
+                acc[r][u] = a;
             }
         if (cg == 0) {
 #pragma unroll
             for (int u = 0; u < RPL; ++u)
 #pragma unroll
-                for (int r = 0; r < NR; ++r) part[wid][r][RPL * rq + u] = acc[u][r];
+                for (int r = 0; r < NR; ++r) part[wid][r][RPL * rq + u] = acc[r][u];
         }
         __syncthreads();
         const int row = rb + lane;
@@ -344,8 +328,6 @@ __device__ __forceinline__ f64x4 mfma64(double a, double b, f64x4 c) {
 // phase A 300 -> 150 us, phase B 343 -> 212; with 8 steps 150 and 229, with a
 // register budget of 4 wavefronts per SIMD 152 and 228.
 constexpr int kMf64Steps = 4;
-typedef double f64x2 __attribute__((ext_vector_type(2)));
-typedef const f64x2 __attribute__((address_space(1))) *pair_ptr;   // global memory: no flat loads
 
 // acc += A B over k < n: a lane's pair of rows of A at p0 (tiles 0 and 1) and p1 (tiles
 // 2 and 3, if TWO), `ld` pairs from one k to the next, its column of B at q.  Within a
