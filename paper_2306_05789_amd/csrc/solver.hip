@@ -13,6 +13,7 @@
 #include <chrono>
 #include <cmath>
 #include <mutex>
+#include <type_traits>
 
 #include "kernels.h"
 #include "physics.h"
@@ -103,10 +104,9 @@ __global__ void k_resid_final(const double *__restrict__ part, int nvec, double 
 // registers, and the Newton evaluations (every one a pass over the bands) run
 // on them; NB = 0 reads them from memory at each evaluation, for any nb.
 template <int NB>
-__global__ __launch_bounds__(256) void k_newton(BandParams bp, const double *__restrict__ J,
-                                                const double *__restrict__ kap, int64_t N, int nrhs,
-                                                double *__restrict__ T, unsigned long long *__restrict__ viol) {
-    const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+__device__ __forceinline__ void newton_vertex(const BandParams &bp, int64_t k, const double *__restrict__ J,
+                                              const double *__restrict__ kap, int64_t N, int nrhs,
+                                              double *__restrict__ T, unsigned long long *__restrict__ viol) {
     const int64_t tot = N * nrhs;
     if (k >= tot) return;
     const int64_t i = k % N;
@@ -137,6 +137,54 @@ __global__ __launch_bounds__(256) void k_newton(BandParams bp, const double *__r
     // converged state two sweeps' roots may differ in their last bits
     if (Tn < Told * (1.0 - 8.0 * 2.220446049250313e-16)) atomicAdd(viol, 1ull);
     T[k] = Tn;
+}
+
+template <int NB>
+__global__ __launch_bounds__(256) void k_newton(BandParams bp, const double *__restrict__ J,
+                                                const double *__restrict__ kap, int64_t N, int nrhs,
+                                                double *__restrict__ T, unsigned long long *__restrict__ viol) {
+    newton_vertex<NB>(bp, (int64_t)blockIdx.x * blockDim.x + threadIdx.x, J, kap, N, nrhs, T, viol);
+}
+
+// After the product of a small mesh, in one launch: the residual sums of the nvec
+// (band, rhs) vectors, a workgroup each, then the Newton workgroups (none: the first
+// nvec alone are launched).  A sweep of such a mesh is bound by its launches: three
+// (partial sums, their sum, Newton) took 12.5 us of the 30 us that the kernels of a
+// sweep of 11^3 run, this 3.9.  The workgroup walks its vector in N / 256 steps,
+// which pays up to kPostSmall vertices.
+constexpr int64_t kPostSmall = 8192;
+template <int NB>
+__global__ __launch_bounds__(256) void k_post(BandParams bp, int nvec, const double *__restrict__ Jold,
+                                              const double *__restrict__ J, const double *__restrict__ kap, int64_t N,
+                                              int nrhs, double *__restrict__ T, unsigned long long *__restrict__ viol,
+                                              double *__restrict__ out) {
+    if ((int)blockIdx.x >= nvec) {
+        newton_vertex<NB>(bp, (int64_t)(blockIdx.x - nvec) * 256 + threadIdx.x, J, kap, N, nrhs, T, viol);
+        return;
+    }
+    __shared__ double s1[4], s2[4];
+    const double *a = Jold + (int64_t)blockIdx.x * N, *b = J + (int64_t)blockIdx.x * N;
+    double d2 = 0.0, n2 = 0.0;
+#pragma unroll 4
+    for (int i = threadIdx.x; i < (int)N; i += 256) {
+        const double d = b[i] - a[i];
+        d2 += d * d;
+        n2 += b[i] * b[i];
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+        d2 += __shfl_xor(d2, o, 64);
+        n2 += __shfl_xor(n2, o, 64);
+    }
+    if ((threadIdx.x & 63) == 0) {
+        s1[threadIdx.x >> 6] = d2;
+        s2[threadIdx.x >> 6] = n2;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        out[2 * blockIdx.x] = ((s1[0] + s1[1]) + s1[2]) + s1[3];
+        out[2 * blockIdx.x + 1] = ((s2[0] + s2[1]) + s2[2]) + s2[3];
+    }
 }
 
 void newton_launch(const BandParams &bp, const double *J, const double *kap, int64_t N, int nrhs, double *T,
@@ -312,6 +360,19 @@ rte_status_t fixed_point_solve(const Mesh &m, const HMat &G, const HMat &S, cons
         matvec_launch_all(G, nr, Sv.as<double>(), Jn.as<double>(), y0, tbuf.as<double>(), s, mode);
     };
     auto enqueue_post = [&](bool newton) {
+        if (N <= kPostSmall) {
+            const unsigned g = (unsigned)(nb * nr) + (newton ? gN : 0u);
+            auto post = [&](auto nbc) {
+                k_post<decltype(nbc)::value><<<g, 256, 0, s>>>(bp, nb * nr, J.as<double>(), Jn.as<double>(),
+                                                               G.kappa_c.as<double>(), N, nr, T.as<double>(),
+                                                               viol.as<unsigned long long>(), res.as<double>());
+            };
+            if (!bp.grey && bp.nb <= 8) post(std::integral_constant<int, 8>());
+            else if (!bp.grey && bp.nb <= 32) post(std::integral_constant<int, 32>());
+            else post(std::integral_constant<int, 0>());
+            HIP_LAUNCH_CHECK();
+            return;
+        }
         k_resid_partial<<<dim3(kResidBlocks, nb * nr), 256, 0, s>>>(J.as<double>(), Jn.as<double>(), N,
                                                                      part.as<double>());
         k_resid_final<<<(nb * nr + 63) / 64, 64, 0, s>>>(part.as<double>(), nb * nr, res.as<double>());
