@@ -61,31 +61,37 @@ struct SrvCol {
     double *Jacc;        // J_acc, written on defect steps (mixed), else null
     int32_t inner;       // inner sweep: the operand is S(T) - S_m
     int32_t save;        // defect step of the mixed iteration: keep S(T) and J_acc
+    double *x;           // the product's operand [N] and result [N]
+    const double *y;
+    int64_t N;
 };
+// Columns whose operands and results lie side by side, in bytes of x: one launch
+// forms all their operands before the groups' products and one takes all results
+// after them, instead of two per group, each 3 us long on a small mesh (4 bands of
+// 15^3: a request mix 2.50 -> 2.29 ms).  Above it a launch is long enough by itself.
+constexpr int64_t kSrvPart = (int64_t)32 << 20;
 
 // x[c] = S = (1 - a) B_nu(T) + a J (minus S_m on inner sweeps); a defect step
 // keeps S in S_m
-__global__ void k_srv_x(const SrvCol *__restrict__ cols, int64_t N, double *__restrict__ x) {
-    const int c = blockIdx.y;
+__global__ void k_srv_x(const SrvCol *__restrict__ cols) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= N) return;
-    const SrvCol col = cols[c];
+    const SrvCol col = cols[blockIdx.y];
+    if (i >= col.N) return;
     const double e = planck(col.nu, col.T[i]);
     const double s = col.a != 0.0 ? (1.0 - col.a) * e + col.a * col.J[i] : e;
-    x[(int64_t)c * N + i] = col.inner ? s - col.Sm[i] : s;
+    col.x[i] = col.inner ? s - col.Sm[i] : s;
     if (col.save) col.Sm[i] = s;
 }
 
 // J_new = y0 + y; fixed-order partial sums of |J_new - J|^2 and |J_new|^2;
 // J <- J_new (and J_acc <- J_new on defect steps)
-__global__ __launch_bounds__(256) void k_srv_update(const SrvCol *__restrict__ cols, int64_t N,
-                                                    const double *__restrict__ y, double *__restrict__ part) {
+__global__ __launch_bounds__(256) void k_srv_update(const SrvCol *__restrict__ cols, double *__restrict__ part) {
     __shared__ double s1[4], s2[4];
     const int c = blockIdx.y;
     const SrvCol col = cols[c];
     double d2 = 0.0, n2 = 0.0;
-    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < N; i += (int64_t)kSrvResidBlocks * 256) {
-        const double jn = col.y0[i] + y[(int64_t)c * N + i];
+    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < col.N; i += (int64_t)kSrvResidBlocks * 256) {
+        const double jn = col.y0[i] + col.y[i];
         const double d = jn - col.J[i];
         d2 += d * d;
         n2 += jn * jn;
@@ -626,7 +632,7 @@ struct Server {
             for (int b = 0; b < (int)r->bands.size(); ++b) {
                 SrvCol c{nu[r->bands[b]], r->a[b], r->T(), mixed() ? r->Sm(N, b) : nullptr,
                          inner ? r->Jacc(N, b) : r->SE(N, b), r->J(N, b), mixed() ? r->Jacc(N, b) : nullptr,
-                         inner ? 1 : 0, save ? 1 : 0};
+                         inner ? 1 : 0, save ? 1 : 0, nullptr, nullptr, N};
                 auto it = std::find_if(groups.begin(), groups.end(),
                                        [&](const Group &g) { return g.op == r->ops[b] && g.inner == (int)inner; });
                 if (it == groups.end()) {
@@ -656,6 +662,31 @@ struct Server {
                 }
             }
         }
+        // parts: groups [pgrp[p], pgrp[p + 1]) of at most kSrvPart of operands (or one
+        // group), their columns' x and y side by side
+        std::vector<size_t> pgrp{0};
+        int64_t room = 0, used = 0;
+        for (size_t gi = 0; gi < groups.size(); ++gi) {
+            const int64_t n = (int64_t)groups[gi].cols.size() * groups[gi].cols[0].N;
+            if (used > 0 && (used + n) * (int64_t)sizeof(double) > kSrvPart) {
+                pgrp.push_back(gi);
+                used = 0;
+            }
+            used += n;
+            room = std::max(room, used);
+        }
+        pgrp.push_back(groups.size());
+        grow<double>(x, room, s);
+        grow<double>(y, room, s);
+        for (size_t p = 0; p + 1 < pgrp.size(); ++p) {
+            int64_t o = 0;
+            const int64_t c1 = pgrp[p + 1] < groups.size() ? goff[pgrp[p + 1]] : ncol;
+            for (int64_t c = goff[pgrp[p]]; c < c1; ++c) {
+                all[c].x = x.as<double>() + o;
+                all[c].y = y.as<double>() + o;
+                o += all[c].N;
+            }
+        }
         hcols.reserve(sizeof(SrvCol) * ncol);
         std::memcpy(hcols.p, all.data(), sizeof(SrvCol) * ncol);
         grow<SrvCol>(cols, ncol, s);
@@ -663,23 +694,25 @@ struct Server {
         grow<double>(part, (int64_t)ncol * kSrvResidBlocks * 2, s);
         grow<double>(res, 2 * (int64_t)ncol, s);
         const auto t0 = std::chrono::steady_clock::now();
-        for (size_t gi = 0; gi < groups.size(); ++gi) {
-            const Group &g = groups[gi];
-            const HMat &G = g.op->G->h;
-            const int64_t N = meshes[g.op->mesh]->mesh.N;
-            const int nc = (int)g.cols.size();
-            grow<double>(x, (int64_t)nc * N, s);
-            grow<double>(y, (int64_t)nc * N, s);
-            grow<double>(ws, matvec_ws_all(G, nc), s);
-            const SrvCol *dc = cols.as<SrvCol>() + goff[gi];
-            k_srv_x<<<dim3((unsigned)((N + 255) / 256), (unsigned)nc), 256, 0, s>>>(dc, N, x.as<double>());
+        for (size_t p = 0; p + 1 < pgrp.size(); ++p) {
+            const int64_t c0 = goff[pgrp[p]], c1 = pgrp[p + 1] < groups.size() ? goff[pgrp[p + 1]] : ncol;
+            int64_t maxn = 0;
+            for (int64_t c = c0; c < c1; ++c) maxn = std::max(maxn, all[c].N);
+            const SrvCol *dc = cols.as<SrvCol>() + c0;
+            k_srv_x<<<dim3((unsigned)((maxn + 255) / 256), (unsigned)(c1 - c0)), 256, 0, s>>>(dc);
             HIP_LAUNCH_CHECK();
-            matvec_launch_all(G, nc, x.as<double>(), y.as<double>(), nullptr, ws.as<double>(), s,
-                              g.inner ? kMatvecLow : kMatvecAccurate);
-            k_srv_update<<<dim3(kSrvResidBlocks, (unsigned)nc), 256, 0, s>>>(
-                dc, N, y.as<double>(), part.as<double>() + goff[gi] * kSrvResidBlocks * 2);
+            for (size_t gi = pgrp[p]; gi < pgrp[p + 1]; ++gi) {
+                const Group &g = groups[gi];
+                const HMat &G = g.op->G->h;
+                const int nc = (int)g.cols.size();
+                grow<double>(ws, matvec_ws_all(G, nc), s);
+                matvec_launch_all(G, nc, all[goff[gi]].x, const_cast<double *>(all[goff[gi]].y), nullptr,
+                                  ws.as<double>(), s, g.inner ? kMatvecLow : kMatvecAccurate);
+                g.op->used = ++clock;
+            }
+            k_srv_update<<<dim3(kSrvResidBlocks, (unsigned)(c1 - c0)), 256, 0, s>>>(
+                dc, part.as<double>() + c0 * kSrvResidBlocks * 2);
             HIP_LAUNCH_CHECK();
-            g.op->used = ++clock;
         }
         k_srv_resid<<<(ncol + 63) / 64, 64, 0, s>>>(part.as<double>(), ncol, res.as<double>());
         HIP_LAUNCH_CHECK();
