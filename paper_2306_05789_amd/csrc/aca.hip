@@ -71,6 +71,12 @@ constexpr int kChunk = 1024;
 // than 8 lanes per entry while a quarter of that holds them.
 constexpr int kWideMin = 8, kWideMax = 32;
 constexpr int64_t kWideLanes = (int64_t)1 << 18;
+// Active blocks from which k_aca_pivot and k_aca_finish give a block one wavefront
+// instead of a workgroup: a batch starts with thousands of blocks of a hundred
+// columns, of which four wavefronts read one pass and then wait at two barriers
+// (29^3, 2 mixed bands, kernels of 4 steps: pivot 66 -> 49 ms, finish 47 -> 37; 41^3
+// assembly 129 -> 126); its last few hundred are the long ones.
+constexpr int64_t kWaveBlocks = 1024;
 // Workgroups of k_aca_dots below which the rank indices of a chunk are split
 // over several (two per CU).
 constexpr int64_t kDotsFill = 512;
@@ -291,46 +297,53 @@ __global__ __launch_bounds__(256, (entry_waves<T, KIND, NW>())) void k_aca_rows(
 }
 
 // Step 2: pivot column of each active block and the scaled row v_k = r / r_{j*},
-// or the next row after a zero row.
-template <typename T>
-__global__ __launch_bounds__(256) void k_aca_pivot(AcaState<T> st) {
+// or the next row after a zero row.  WAVE: a wavefront per block, else a workgroup.
+template <typename T, bool WAVE>
+__global__ __launch_bounds__(256) void k_aca_pivot(AcaState<T> st, int nact) {
+    constexpr int NT = WAVE ? 64 : 256;
     __shared__ T sa[4], ss[4];
     __shared__ int si[4];
-    const int b = st.act[blockIdx.x];
+    const int slot = WAVE ? (int)blockIdx.x * 4 + (threadIdx.x >> 6) : (int)blockIdx.x;
+    const int tid = WAVE ? threadIdx.x & 63 : threadIdx.x;
+    if (slot >= nact) return;
+    const int b = st.act[slot];
     if (st.status[b] != kActive) return;
+    auto argmax = [&](T &a, int &idx, T &sv) {
+        if constexpr (WAVE) wave_argmax(a, idx, sv);
+        else block_argmax(a, idx, sv, sa, si, ss);
+    };
     const AcaTask tk = st.task[b];
     const int k = st.k[b];
     T *V = st.Vs + tk.voff + (int64_t)k * tk.n;
-    if (threadIdx.x == 0) st.ents[b] += tk.n;
+    if (tid == 0) st.ents[b] += tk.n;
     unsigned *bits = st.used + st.ubase[b];
     T best = (T)-1, sv = (T)0;
     int bj = INT_MAX;
-    for (int j = threadIdx.x; j < tk.n; j += 256) {
+#pragma unroll 4
+    for (int j = tid; j < tk.n; j += NT) {
         const T v = V[j], av = fabs(v);
         if (av > best) { best = av; bj = j; sv = v; }
     }
-    block_argmax(best, bj, sv, sa, si, ss);
-    if (threadIdx.x == 0) {
-        const int is = st.istar[b];
-        bits[is >> 5] |= 1u << (is & 31);
-    }
+    argmax(best, bj, sv);
+    const int is = st.istar[b];
+    if (tid == 0) bits[is >> 5] |= 1u << (is & 31);
     if (best > (T)0) {
         const T inv = (T)1 / sv;
-        for (int j = threadIdx.x; j < tk.n; j += 256) V[j] *= inv;
-        if (threadIdx.x == 0) {
+#pragma unroll 4
+        for (int j = tid; j < tk.n; j += NT) V[j] *= inv;
+        if (tid == 0) {
             st.jstar[b] = bj;
             st.havepiv[b] = 1;
         }
         return;
     }
-    // zero residual row: the lowest unused row is next
-    __syncthreads();   // the bit of i* is visible
+    // zero residual row: the lowest unused row is next (i*, whose bit may not be visible yet, is used)
     int cand = INT_MAX;
-    for (int r = threadIdx.x; r < tk.m; r += 256)
-        if (!is_used(bits, r)) { cand = r; break; }
+    for (int r = tid; r < tk.m; r += NT)
+        if (r != is && !is_used(bits, r)) { cand = r; break; }
     T key = cand == INT_MAX ? (T)-1 : (T)1, dv = (T)0;
-    block_argmax(key, cand, dv, sa, si, ss);
-    if (threadIdx.x == 0) {
+    argmax(key, cand, dv);
+    if (tid == 0) {
         st.havepiv[b] = 0;
         if (key < (T)0) st.status[b] = kConverged;   // every row used: the residual is zero
         else st.istar[b] = cand;
@@ -498,42 +511,61 @@ __global__ __launch_bounds__(256) void k_aca_dots(AcaState<T> st, int split) {
 }
 
 // Steps 4-5, second part: add the chunk partials in order, update ||S_k||,
-// test convergence and pick the next row.  One workgroup per pivoted block.
-template <typename T>
-__global__ __launch_bounds__(256) void k_aca_finish(AcaState<T> st, T eps, int need) {
-    __shared__ T sa[4], ss[4], sums[2][kAcaRetryRank];   // (u_l.u_k), (v_l.v_k), l <= k < kcap
+// test convergence and pick the next row.  WAVE: a wavefront per pivoted block,
+// else a workgroup, whose first wavefront adds the products in the same order.
+template <typename T, bool WAVE>
+__global__ __launch_bounds__(256) void k_aca_finish(AcaState<T> st, int nact, T eps, int need) {
+    constexpr int NT = WAVE ? 64 : 256, LS = WAVE ? 1 : kAcaRetryRank;
+    __shared__ T sa[4], ss[4], sums[2][LS];   // (u_l.u_k), (v_l.v_k), l <= k < kcap
     __shared__ int si[4];
-    const int b = st.act2[blockIdx.x];
-    if (st.status[b] != kActive || !st.havepiv[b]) return;   // uniform over the workgroup
+    const int slot = WAVE ? (int)blockIdx.x * 4 + (threadIdx.x >> 6) : (int)blockIdx.x;
+    const int tid = WAVE ? threadIdx.x & 63 : threadIdx.x;
+    if (slot >= nact) return;
+    const int b = st.act2[slot];
+    if (st.status[b] != kActive || !st.havepiv[b]) return;   // uniform over the block's threads
     const AcaTask tk = st.task[b];
-    const int k = st.k[b], tid = threadIdx.x;
+    const int k = st.k[b];
     const int64_t c0 = st.chunkoff[b], c1 = st.chunkoff[b + 1];
     const int64_t row = 2 * (int64_t)st.half;
-    for (int l = tid; l <= k; l += 256) {
+    T cross = (T)0, u2 = (T)0, v2 = (T)0;
+    for (int l = tid; l <= k; l += NT) {
         T su = (T)0, sv = (T)0;
 #pragma unroll 4
         for (int64_t c = c0; c < c1; ++c) {
             su += st.part[c * row + l];
             sv += st.part[c * row + st.half + l];
         }
-        sums[0][l] = su;
-        sums[1][l] = sv;
+        if constexpr (!WAVE) {
+            sums[0][l] = su;
+            sums[1][l] = sv;
+        } else if (l < k) {
+            cross += su * sv;
+        } else {
+            u2 = su;
+            v2 = sv;
+        }
     }
     T bu = (T)-1, none = (T)0;
     int bi = INT_MAX;
-    for (int64_t c = c0 + tid; c < c1; c += 256) {
+    for (int64_t c = c0 + tid; c < c1; c += NT) {
         const T a = st.pmax[c];
         const int i = st.pidx[c];
         if (a > bu || (a == bu && i < bi)) { bu = a; bi = i; }
     }
-    block_argmax(bu, bi, none, sa, si, ss);   // its barriers publish the sums
-    if (tid >= 64) return;
-    T cross = (T)0;
-    for (int l = tid; l < k; l += 64) cross += sums[0][l] * sums[1][l];
+    if constexpr (WAVE) {
+        wave_argmax(bu, bi, none);
+        u2 = wave_sum(u2);   // one lane's value and zeros
+        v2 = wave_sum(v2);
+    } else {
+        block_argmax(bu, bi, none, sa, si, ss);   // its barriers publish the sums
+        if (tid >= 64) return;
+        for (int l = tid; l < k; l += 64) cross += sums[0][l] * sums[1][l];
+        u2 = sums[0][k];
+        v2 = sums[1][k];
+    }
     cross = wave_sum(cross);
     if (tid != 0) return;
     st.ents[b] += tk.m;
-    const T u2 = sums[0][k], v2 = sums[1][k];
     const T s2 = st.normS2[b] + u2 * v2 + (T)2 * cross;
     st.normS2[b] = s2;
     // the stopping test, met by `need` consecutive rank steps
@@ -915,14 +947,18 @@ void aca_batch(HMat &H, BandStore &B, BandKappa<T> kap, const std::vector<AcaTas
             launch_rows();
             HIP_LAUNCH_CHECK();
             mark();
-            k_aca_pivot<T><<<(unsigned)nact, 256, 0, s>>>(st);
+            if (nact >= kWaveBlocks) k_aca_pivot<T, true><<<(unsigned)((nact + 3) / 4), 256, 0, s>>>(st, (int)nact);
+            else k_aca_pivot<T, false><<<(unsigned)nact, 256, 0, s>>>(st, (int)nact);
             HIP_LAUNCH_CHECK();
             mark();
             launch_cols();
             HIP_LAUNCH_CHECK();
             mark();
             k_aca_dots<T><<<(unsigned)(nchunk * split), 256, 0, s>>>(st, split);
-            k_aca_finish<T><<<(unsigned)nact, 256, 0, s>>>(st, eps, std::max(1, H.opts.aca_hits));
+            const int need = std::max(1, H.opts.aca_hits);
+            if (nact >= kWaveBlocks)
+                k_aca_finish<T, true><<<(unsigned)((nact + 3) / 4), 256, 0, s>>>(st, (int)nact, eps, need);
+            else k_aca_finish<T, false><<<(unsigned)nact, 256, 0, s>>>(st, (int)nact, eps, need);
             HIP_LAUNCH_CHECK();
             launches += 2;
         }
