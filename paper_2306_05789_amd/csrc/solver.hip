@@ -316,7 +316,14 @@ rte_status_t fixed_point_solve(const Mesh &m, const HMat &G, const HMat &S, cons
     BandParams bp{nb, d.grey, dconst.as<double>(), dconst.as<double>() + nb, dconst.as<double>() + 2 * nb};
 
     const int64_t vecN = N * nr;
-    auto words = [](int64_t n) { return DevBuf::scratch(sizeof(double) * (size_t)n); };
+    // Buffers above 64 MiB are allocated for the solve: the pool settles on one
+    // placement of them, and on 49^3 with 32 bands and 16 right-hand sides (0.5 GB each)
+    // it is the slow one (low product 15.17 ms, 307 ms per solve; allocated 14.64 and
+    // 301); below, the allocation costs more than any placement.
+    auto words = [](int64_t n) {
+        const size_t bytes = sizeof(double) * (size_t)n;
+        return bytes > ((size_t)64 << 20) ? DevBuf(bytes) : DevBuf::scratch(bytes);
+    };
     DevBuf Tw = words(L * nr), Q = words(L * nr * nb), SE = words(vecN * nb), Sv = words(vecN * nb), J = words(vecN * nb),
            Jn = words(vecN * nb), T = words(vecN), part = words((int64_t)2 * kResidBlocks * nb * nr),
            res = words(2 * nb * nr), viol = words(1);
