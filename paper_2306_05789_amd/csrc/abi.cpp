@@ -88,10 +88,18 @@ void check_device_pointer(const void *p, const char *what) {
                 std::string(what) + " is not device memory");
 }
 
-void check_kappa(const double *kappa, int64_t n, hipStream_t s) {
+// kappa [n_bands][N]; returns each band's largest value
+std::vector<double> check_kappa(const double *kappa, int64_t N, int n_bands, hipStream_t s) {
     check_device_pointer(kappa, "kappa");
-    auto h = to_host(kappa, n, s);
-    for (double v : h) RTE_REQUIRE(std::isfinite(v) && v >= 0.0, "kappa must be finite and >= 0");
+    auto h = to_host(kappa, N * n_bands, s);
+    std::vector<double> kmax((size_t)n_bands, 0.0);
+    for (int b = 0; b < n_bands; ++b)
+        for (int64_t i = 0; i < N; ++i) {
+            const double v = h[(size_t)(b * N + i)];
+            RTE_REQUIRE(std::isfinite(v) && v >= 0.0, "kappa must be finite and >= 0");
+            kmax[b] = std::max(kmax[b], v);
+        }
+    return kmax;
 }
 
 // Stored elements [0, count) of one array of band storage as FP64: FP64 as is,
@@ -172,10 +180,10 @@ void block_factors(const HMat &H, int band, int64_t block, int op, int32_t *rank
 namespace rte {
 
 // Assembly of one H-matrix per band on a validated plan and kappa (device,
-// [n_bands][N], natural order); see rte_hmat_assemble.
+// [n_bands][N], natural order, kmax the bands' largest values); see rte_hmat_assemble.
 std::unique_ptr<rte_hmat> assemble_hmat(const Mesh &m, std::shared_ptr<const Plan> plan,
                                         const rte_hmat_opts_t &o, int n_bands, const double *kappa,
-                                        hipStream_t s) {
+                                        const std::vector<double> &kmax, hipStream_t s) {
     const auto t0 = std::chrono::steady_clock::now();
     const double alloc0 = alloc_ms_this_thread();
     double alloc_other = 0.0;   // allocation time of the second band thread
@@ -250,7 +258,7 @@ std::unique_ptr<rte_hmat> assemble_hmat(const Mesh &m, std::shared_ptr<const Pla
         std::atomic<int> next{0};
         auto run = [&](hipStream_t st) {
             for (int b; (b = next.fetch_add(1)) < n_bands;) {
-                assemble_band(H, b, kappa + (int64_t)b * m.N, st);
+                assemble_band(H, b, kappa + (int64_t)b * m.N, kmax[b], st);
                 matvec_build(H, b, st);   // host work while the band's last kernels run
                 band_settle(H.bands[b], st);
             }
@@ -371,8 +379,8 @@ rte_status_t rte_server_add_mesh(rte_server_t s, const rte_mesh_desc_t *mesh, co
         RTE_REQUIRE(s && mesh && mesh_id, "rte_server_add_mesh: NULL argument");
         Mesh probe;
         mesh_init(probe, *mesh);
-        check_kappa(kappa, probe.N, nullptr);
-        *mesh_id = server_add_mesh(*s->srv, *mesh, kappa);
+        const double kmax = check_kappa(kappa, probe.N, 1, nullptr)[0];
+        *mesh_id = server_add_mesh(*s->srv, *mesh, kappa, kmax);
         return RTE_OK;
     });
 }
@@ -544,7 +552,7 @@ rte_status_t rte_entries(rte_mesh_t mesh, int32_t kind, const double *kappa, int
         if (n == 0) return RTE_OK;
         hipStream_t s = (hipStream_t)stream;
         const Mesh &m = mesh->m;
-        check_kappa(kappa, m.N, s);
+        const double kmax = check_kappa(kappa, m.N, 1, s)[0];
         check_device_pointer(rows, "rows");
         check_device_pointer(cols, "cols");
         check_device_pointer(out, "out");
@@ -556,7 +564,7 @@ rte_status_t rte_entries(rte_mesh_t mesh, int32_t kind, const double *kappa, int
             std::unordered_set<int64_t> em(m.emitting.begin(), m.emitting.end());
             for (int64_t v : hc) RTE_REQUIRE(em.count(v), "rte_entries: column is not an emitting vertex");
         }
-        entries_launch(m, kind, kappa, n, rows, cols, out, precision, s);
+        entries_launch(m, kind, kappa, kmax, n, rows, cols, out, precision, s);
         HIP_CHECK(hipStreamSynchronize(s));
         return RTE_OK;
     });
@@ -571,8 +579,8 @@ rte_status_t rte_hmat_assemble(rte_mesh_t mesh, int32_t n_bands, const double *k
         hipStream_t s = (hipStream_t)stream;
         const Mesh &m = mesh->m;
         auto plan = mesh_plan(m, *opts);
-        check_kappa(kappa, m.N * n_bands, s);
-        *out = assemble_hmat(m, std::move(plan), *opts, n_bands, kappa, s).release();
+        const std::vector<double> kmax = check_kappa(kappa, m.N, n_bands, s);
+        *out = assemble_hmat(m, std::move(plan), *opts, n_bands, kappa, kmax, s).release();
         return RTE_OK;
     });
 }

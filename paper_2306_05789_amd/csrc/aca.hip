@@ -27,7 +27,6 @@
 #include <numeric>
 
 #include "entry_dev.h"
-#include "kernels.h"
 
 namespace rte {
 
@@ -240,7 +239,7 @@ __device__ __forceinline__ int hinted_block(const int64_t *__restrict__ off, con
 }
 
 // Waves per SIMD the entry launches are compiled for: the register budget
-// that keeps the march free of spills (the surface entry needs more
+// that keeps the depths free of spills (the surface entry needs more
 // registers than the volume one; measured per kind and precision).
 template <typename T, int KIND, int NW>
 constexpr int entry_waves() {
@@ -271,8 +270,8 @@ __device__ __forceinline__ T residual(T a, const T *p, int64_t sp, const T *q, i
 }
 
 // Step 1: residual rows of every active block, one lane per entry.
-template <typename T, int KIND, int NW>
-__global__ __launch_bounds__(256, (entry_waves<T, KIND, NW>())) void k_aca_rows(EntryCtx<T> c, AcaState<T> st, int64_t total,
+template <typename T, bool K, int KIND, int NW>
+__global__ __launch_bounds__(256, (entry_waves<T, KIND, NW>())) void k_aca_rows(EntryCtx<T, K> c, AcaState<T> st, int64_t total,
                                                   const int64_t *__restrict__ tgt_nat,
                                                   const int64_t *__restrict__ src_nat) {
     const int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x;
@@ -283,7 +282,7 @@ __global__ __launch_bounds__(256, (entry_waves<T, KIND, NW>())) void k_aca_rows(
     T a;
     {
         const AcaTask tk = st.task[b];
-        a = entry<T, KIND, NW>(c, tgt_nat[tk.t0 + st.istar[b]], src_nat[tk.s0 + j]);
+        a = entry<KIND, NW>(c, tgt_nat[tk.t0 + st.istar[b]], src_nat[tk.s0 + j]);
     }
     // the block's state is read again after the march (only b and j stay
     // live through it; the barrier keeps the compiler from reusing the loads)
@@ -351,8 +350,8 @@ __global__ __launch_bounds__(256) void k_aca_pivot(AcaState<T> st, int nact) {
 }
 
 // Step 3: residual columns of the pivoted blocks, one lane per entry.
-template <typename T, int KIND, int NW>
-__global__ __launch_bounds__(256, (entry_waves<T, KIND, NW>())) void k_aca_cols(EntryCtx<T> c, AcaState<T> st, int64_t total,
+template <typename T, bool K, int KIND, int NW>
+__global__ __launch_bounds__(256, (entry_waves<T, KIND, NW>())) void k_aca_cols(EntryCtx<T, K> c, AcaState<T> st, int64_t total,
                                                   const int64_t *__restrict__ tgt_nat,
                                                   const int64_t *__restrict__ src_nat) {
     const int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x;
@@ -363,7 +362,7 @@ __global__ __launch_bounds__(256, (entry_waves<T, KIND, NW>())) void k_aca_cols(
     T a;
     {
         const AcaTask tk = st.task[b];
-        a = entry<T, KIND, NW, true>(c, tgt_nat[tk.t0 + i], src_nat[tk.s0 + st.jstar[b]]);
+        a = entry<KIND, NW, true>(c, tgt_nat[tk.t0 + i], src_nat[tk.s0 + st.jstar[b]]);
     }
     asm volatile("" ::: "memory");   // as in k_aca_rows
     const AcaTask tk = st.task[b];
@@ -379,15 +378,16 @@ __global__ __launch_bounds__(256, (entry_waves<T, KIND, NW>())) void k_aca_cols(
 // (group_entry) and the loads of the residual, whose terms are then subtracted
 // in order by every lane, so that an entry is that of the one-lane kernels bit
 // for bit and the choice between them (aca_batch) does not show in the factors.
-// Such a launch lasts as long as one entry, a chain of loads: in FP64 6 families
-// of about N / 4 batches each (13 legs of them with six walls), in FP32 the
-// pieces of every leg, then k / 8 batches of the residual.
-template <typename T, int KIND, int NW, bool COLS>
-__global__ __launch_bounds__(256, 3) void k_aca_wide(EntryCtx<T> c, AcaState<T> st, int64_t total, int P,
+// Such a launch lasts as long as one entry, a chain of loads: by kinks 6 families
+// of about N / 4 batches each (13 legs of them with six walls), by the march the
+// pieces of every leg, then k / 8 batches of the residual.  Dynamic LDS: the groups'
+// tasks.
+template <typename T, bool K, int KIND, int NW, bool COLS>
+__global__ __launch_bounds__(256, 3) void k_aca_wide(EntryCtx<T, K> c, AcaState<T> st, int64_t total, int P,
                                                      const int64_t *__restrict__ tgt_nat,
                                                      const int64_t *__restrict__ src_nat) {
     constexpr int R = 4;   // residual terms in flight per lane
-    __shared__ T tasks[256 / kWideMin * kGroupTasks<T, NW>];
+    extern __shared__ __align__(16) unsigned char wide_lds[];
     __shared__ T terms[256 * R][2];
     const int tid = threadIdx.x, grp = tid / P, sub = tid - grp * P;
     const int64_t e = (int64_t)blockIdx.x * (256 / P) + grp;
@@ -397,8 +397,8 @@ __global__ __launch_bounds__(256, 3) void k_aca_wide(EntryCtx<T> c, AcaState<T> 
     if (st.status[b] != kActive || (COLS && !st.havepiv[b])) return;
     const AcaTask tk = st.task[b];
     const int x = (int)(e - off[b]), k = st.k[b], y = COLS ? st.jstar[b] : st.istar[b];
-    T a = group_entry<T, KIND, NW, COLS>(c, tgt_nat[tk.t0 + (COLS ? x : y)], src_nat[tk.s0 + (COLS ? y : x)], P, sub,
-                                   tasks + grp * kGroupTasks<T, NW>);
+    T a = group_entry<KIND, NW, COLS>(c, tgt_nat[tk.t0 + (COLS ? x : y)], src_nat[tk.s0 + (COLS ? y : x)], P, sub,
+                                      reinterpret_cast<GroupTask<T, K> *>(wide_lds) + grp * group_tasks<K>(c.g.n_walls));
     T *U = st.Us + tk.uoff, *V = st.Vs + tk.voff;
     // row: sum_l U_l(i*) V_l(x); column: sum_l V_l(j*) U_l(x)
     const T *p = COLS ? V + y : U + y, *q = COLS ? U + x : V + x;
@@ -759,8 +759,8 @@ int64_t stored_v(const HMat &H, int64_t s0, int64_t s1, int64_t k) {
     return H.kgroup > 1 ? H.pwidth(s0, s1) * k : (s1 - s0) * pad4(k);
 }
 
-template <typename T>
-void fill_dense_blocks(HMat &H, BandStore &B, BandKappa<T> kap, const std::vector<Block> &blocks, bool pair,
+template <typename T, bool K>
+void fill_dense_blocks(HMat &H, BandStore &B, BandKappa<T, K> kap, const std::vector<Block> &blocks, bool pair,
                        hipStream_t s) {
     if (blocks.empty()) return;
     const Plan &P = *H.plan;
@@ -811,7 +811,7 @@ void fill_dense_blocks(HMat &H, BandStore &B, BandKappa<T> kap, const std::vecto
             tasks.push_back(t);
         }
     }
-    dense_fill_launch<T>(*H.mesh, H.kind, kap, tasks, H.tgt_nat.as<int64_t>(), H.src_nat.as<int64_t>(), slice_map(H),
+    dense_fill_launch(*H.mesh, H.kind, kap, tasks, H.tgt_nat.as<int64_t>(), H.src_nat.as<int64_t>(), slice_map(H),
                          split, B, s);
     B.fill_launches += 1;
     B.dense_entries += total;
@@ -831,8 +831,8 @@ struct AcaCarry {
 // One batch of blocks through the step-synchronous ACA.  A block that stops
 // at its cap goes to `retry` when its storage break-even rank exceeds the cap
 // (the next pass takes it up with a larger one), else to `fallback` (dense).
-template <typename T>
-void aca_batch(HMat &H, BandStore &B, BandKappa<T> kap, const std::vector<AcaTask> &tasks, const std::vector<size_t> &ids,
+template <typename T, bool K>
+void aca_batch(HMat &H, BandStore &B, BandKappa<T, K> kap, const std::vector<AcaTask> &tasks, const std::vector<size_t> &ids,
                int64_t uo, int64_t vo, std::vector<Block> &fallback, std::vector<size_t> &retry, AcaCarry<T> &carry,
                hipStream_t s) {
     {   // an earlier batch's scratch is freed first (a fill's task list may stay queued)
@@ -904,7 +904,7 @@ void aca_batch(HMat &H, BandStore &B, BandKappa<T> kap, const std::vector<AcaTas
     st.cblock = cblock.as<int>();
     st.Us = Us.as<T>();
     st.Vs = Vs.as<T>();
-    auto c = make_ctx<T>(*H.mesh, H.kind, kap, s);
+    auto c = make_ctx(*H.mesh, H.kind, kap, s);
     const T eps = (T)H.opts.aca_eps;
     const int64_t *tn = H.tgt_nat.as<int64_t>(), *sn = H.src_nat.as<int64_t>();
     // every step raises a rank or consumes a zero row, so this bounds the steps
@@ -961,10 +961,10 @@ void aca_batch(HMat &H, BandStore &B, BandKappa<T> kap, const std::vector<AcaTas
         if (ht[1] == 0) break;
         const int64_t nrow = ht[0], nact = ht[1], ncol = ht[2], nchunk = ht[4];
         // lanes per entry: 1, or as many of 8 .. 32 as fit the chip at once and
-        // have a part of the rays to walk (FP64: 6 families per leg; FP32: a leg,
-        // so that an open mesh has nothing to share: 29^3 surface entry launches
+        // have a part of the rays to walk (kinks: 6 families per leg; march: a leg,
+        // so that an open mesh has nothing to share: FP32 29^3 surface entry launches
         // 77 ms at 8 lanes, 70 at one)
-        const int wm = wall_mode(c.g), parts = (sizeof(T) == 8 ? 6 : 1) * (1 + 2 * c.g.n_walls);
+        const int wm = wall_mode(c.g), parts = group_tasks<K>(c.g.n_walls);
         auto lanes = [&](int64_t n) {
             if (parts == 1) return 1;
             int P = kWideMin;
@@ -973,6 +973,7 @@ void aca_batch(HMat &H, BandStore &B, BandKappa<T> kap, const std::vector<AcaTas
             return wide_on && n * P <= kWideLanes ? P : 1;
         };
         const int Pr = lanes(nrow), Pc = lanes(ncol);
+        auto lds = [parts](int P) { return (unsigned)(256 / P * parts * sizeof(GroupTask<T, K>)); };
         const int64_t wr = (nrow * Pr + 255) / 256, wc = (ncol * Pc + 255) / 256;
         const int split = (int)std::max<int64_t>(1, std::min<int64_t>(16, kDotsFill / std::max<int64_t>(nchunk, 1)));
         k_aca_hint<T, false><<<(unsigned)((wr + 255) / 256), 256, 0, s>>>(st, wr, (int)nact, 256 / Pr);
@@ -984,12 +985,12 @@ void aca_batch(HMat &H, BandStore &B, BandKappa<T> kap, const std::vector<AcaTas
         auto entries = [&](auto kind, auto nw) {
             constexpr int KIND = decltype(kind)::value, NW = decltype(nw)::value;
             auto rows = [=]() {
-                if (Pr > 1) k_aca_wide<T, KIND, NW, false><<<(unsigned)wr, 256, 0, s>>>(c, st, nrow, Pr, tn, sn);
-                else k_aca_rows<T, KIND, NW><<<(unsigned)wr, 256, 0, s>>>(c, st, nrow, tn, sn);
+                if (Pr > 1) k_aca_wide<T, K, KIND, NW, false><<<(unsigned)wr, 256, lds(Pr), s>>>(c, st, nrow, Pr, tn, sn);
+                else k_aca_rows<T, K, KIND, NW><<<(unsigned)wr, 256, 0, s>>>(c, st, nrow, tn, sn);
             };
             auto cols = [=]() {
-                if (Pc > 1) k_aca_wide<T, KIND, NW, true><<<(unsigned)wc, 256, 0, s>>>(c, st, ncol, Pc, tn, sn);
-                else k_aca_cols<T, KIND, NW><<<(unsigned)wc, 256, 0, s>>>(c, st, ncol, tn, sn);
+                if (Pc > 1) k_aca_wide<T, K, KIND, NW, true><<<(unsigned)wc, 256, lds(Pc), s>>>(c, st, ncol, Pc, tn, sn);
+                else k_aca_cols<T, K, KIND, NW><<<(unsigned)wc, 256, 0, s>>>(c, st, ncol, tn, sn);
             };
             launch_rows = rows;
             launch_cols = cols;
@@ -1152,8 +1153,8 @@ void aca_batch(HMat &H, BandStore &B, BandKappa<T> kap, const std::vector<AcaTas
     if (split) B.bufs.push_back(std::move(outlo));
 }
 
-template <typename T>
-void run_aca(HMat &H, BandStore &B, BandKappa<T> kap, hipStream_t s) {
+template <typename T, bool K>
+void run_aca(HMat &H, BandStore &B, BandKappa<T, K> kap, hipStream_t s) {
     const Plan &P = *H.plan;
     const size_t nlr = P.lowrank.size();
     B.rank.assign(nlr, -1);
@@ -1201,7 +1202,7 @@ void run_aca(HMat &H, BandStore &B, BandKappa<T> kap, hipStream_t s) {
             }
             const int64_t need = (int64_t)kcap * (m + n);
             if (!tasks.empty() && (size_t)(uo + vo + need) * sizeof(T) > scratch_limit) {
-                aca_batch<T>(H, B, kap, tasks, ids, uo, vo, fallback, retry, carry, s);
+                aca_batch(H, B, kap, tasks, ids, uo, vo, fallback, retry, carry, s);
                 tasks.clear();
                 ids.clear();
                 uo = vo = 0;
@@ -1211,38 +1212,40 @@ void run_aca(HMat &H, BandStore &B, BandKappa<T> kap, hipStream_t s) {
             uo += (int64_t)kcap * m;
             vo += (int64_t)kcap * n;
         }
-        if (!tasks.empty()) aca_batch<T>(H, B, kap, tasks, ids, uo, vo, fallback, retry, carry, s);
+        if (!tasks.empty()) aca_batch(H, B, kap, tasks, ids, uo, vo, fallback, retry, carry, s);
         todo.swap(retry);
         retry.clear();
     }
     for (DevBuf &d : carry.bufs) B.retire.push_back(std::move(d));   // the second pass has been queued
     for (size_t b : todo) fallback.push_back(P.lowrank[b]);
-    fill_dense_blocks<T>(H, B, kap, fallback, false, s);
+    fill_dense_blocks(H, B, kap, fallback, false, s);
 }
 
-template <typename T>
-void assemble_typed(HMat &H, int band, BandKappa<T> kap, hipStream_t s) {
+template <typename T, bool K>
+void assemble_typed(HMat &H, int band, BandKappa<T, K> kap, hipStream_t s) {
     BandStore &B = H.bands[band];
-    fill_dense_blocks<T>(H, B, kap, H.plan->dense, H.kind == RTE_VOLUME, s);
-    run_aca<T>(H, B, kap, s);
+    fill_dense_blocks(H, B, kap, H.plan->dense, H.kind == RTE_VOLUME, s);
+    run_aca(H, B, kap, s);
 }
 
 }  // namespace
 
-void assemble_band(HMat &H, int band, const double *kappa_band, hipStream_t s) {
+void assemble_band(HMat &H, int band, const double *kappa_band, double kmax, hipStream_t s) {
     // the band's kappa buffers go to B.retire only after every launch reading
     // them is queued (band_settle, which an ACA batch may call, releases what
     // B.retire holds)
     BandStore &B = H.bands[band];
     if (H.precision == RTE_FP64) {
-        DevBuf kt = march_table(*H.mesh, kappa_band, s);
-        assemble_typed<double>(H, band, BandKappa<double>{kappa_band, kt.as<double>()}, s);
+        const double q = kink_quantum(H.mesh->dev, kmax);
+        DevBuf kt = q > 0.0 ? kink_table(*H.mesh, kappa_band, q, s) : march_table(*H.mesh, kappa_band, s);
+        if (q > 0.0) assemble_typed(H, band, BandKappa<double, true>{kappa_band, kt.as<int64_t>(), q}, s);
+        else assemble_typed(H, band, BandKappa<double, false>{kappa_band, kt.as<double>()}, s);
         B.retire.push_back(std::move(kt));
     } else {
         DevBuf kf = DevBuf::scratch(sizeof(float) * (size_t)H.mesh->N);
         to_float(kappa_band, kf.as<float>(), H.mesh->N, s);
         DevBuf kt = march_table(*H.mesh, kf.as<float>(), s);
-        assemble_typed<float>(H, band, BandKappa<float>{kf.as<float>(), kt.as<float>()}, s);
+        assemble_typed(H, band, BandKappa<float, false>{kf.as<float>(), kt.as<float>()}, s);
         B.retire.push_back(std::move(kf));
         B.retire.push_back(std::move(kt));
     }

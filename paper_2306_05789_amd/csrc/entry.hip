@@ -1,17 +1,18 @@
 // Kernels that evaluate kernel entries directly: arbitrary (row, col) pairs,
 // and the dense near-field leaves of the H-matrix (Section "Compression": a
 // block that reaches the leaves without being admissible is computed in full).
+#include <cmath>
+
 #include "entry_dev.h"
-#include "kernels.h"
 
 namespace rte {
 
-template <typename T, int KIND>
-__global__ __launch_bounds__(256) void k_entries(EntryCtx<T> c, int64_t n, const int64_t *__restrict__ rows,
+template <typename T, bool K, int KIND>
+__global__ __launch_bounds__(256) void k_entries(EntryCtx<T, K> c, int64_t n, const int64_t *__restrict__ rows,
                                                  const int64_t *__restrict__ cols, double *__restrict__ out) {
     const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (k >= n) return;
-    out[k] = (double)entry<T, KIND>(c, rows[k], cols[k]);
+    out[k] = (double)entry<KIND>(c, rows[k], cols[k]);
 }
 
 // One task = up to kFillChunk consecutive entries (column-major) of one
@@ -29,8 +30,8 @@ static_assert(kFillChunk % 256 == 0, "fill tasks are whole workgroups");
 // KIND of the tasks that fill a volume block and its transpose together
 constexpr int kPairedVolume = 2;
 
-template <typename T, int KIND, bool SPLIT, int NW>
-__device__ __forceinline__ void fill_one(const EntryCtx<T> &c, const FillTask &tk, int64_t e,
+template <typename T, bool K, int KIND, bool SPLIT, int NW>
+__device__ __forceinline__ void fill_one(const EntryCtx<T, K> &c, const FillTask &tk, int64_t e,
                                          const int64_t *__restrict__ tgt_nat, const int64_t *__restrict__ src_nat,
                                          const SliceMap &sm) {
     const int64_t jl = e / tk.m, il = e - jl * tk.m;
@@ -47,7 +48,7 @@ __device__ __forceinline__ void fill_one(const EntryCtx<T> &c, const FillTask &t
     if constexpr (KIND == kPairedVolume) {
         // this entry and its transpose (the volume tree's targets and sources coincide)
         T v, vt;
-        volume_entry_pair<T, NW>(c, tgt_nat[tk.t0 + il], tgt_nat[tk.s0 + jl], v, vt);
+        volume_entry_pair<T, K, NW>(c, tgt_nat[tk.t0 + il], tgt_nat[tk.s0 + jl], v, vt);
         put(tk.out, tk.outlo,
             slice_offset(sm, tk.li0, tk.t0 + il, tk.kw, sm.src_p[tk.s0 + jl] - sm.src_p[tk.s0], tk.li0 + (int)il + 1),
             v);
@@ -56,15 +57,15 @@ __device__ __forceinline__ void fill_one(const EntryCtx<T> &c, const FillTask &t
                          tk.li0_t + (int)jl + 1),
             vt);
     } else {
-        const T v = entry<T, KIND, NW, true>(c, tgt_nat[tk.t0 + il], src_nat[tk.s0 + jl]);
+        const T v = entry<KIND, NW, true>(c, tgt_nat[tk.t0 + il], src_nat[tk.s0 + jl]);
         put(tk.out, tk.outlo,
             slice_offset(sm, tk.li0, tk.t0 + il, tk.kw, sm.src_p[tk.s0 + jl] - sm.src_p[tk.s0], tk.li0 + (int)il + 1),
             v);
     }
 }
 
-template <typename T, int KIND, bool SPLIT, int NW>
-__global__ __launch_bounds__(256, sizeof(T) == 8 ? 4 : 3) void k_dense_fill(EntryCtx<T> c,
+template <typename T, bool K, int KIND, bool SPLIT, int NW>
+__global__ __launch_bounds__(256, sizeof(T) == 8 ? 4 : 3) void k_dense_fill(EntryCtx<T, K> c,
                                                                         const FillTask *__restrict__ tasks,
                                                                         const int64_t *__restrict__ tgt_nat,
                                                                         const int64_t *__restrict__ src_nat,
@@ -74,11 +75,11 @@ __global__ __launch_bounds__(256, sizeof(T) == 8 ? 4 : 3) void k_dense_fill(Entr
     const int64_t total = (int64_t)tk.m * tk.n;
     if constexpr (split == kFillChunk / 256) {
         const int64_t e = tk.first + (int64_t)(blockIdx.x % split) * 256 + threadIdx.x;
-        if (e < total) fill_one<T, KIND, SPLIT, NW>(c, tk, e, tgt_nat, src_nat, sm);
+        if (e < total) fill_one<T, K, KIND, SPLIT, NW>(c, tk, e, tgt_nat, src_nat, sm);
     } else {
         const int64_t end = min(total, tk.first + (int64_t)kFillChunk);
         for (int64_t e = tk.first + threadIdx.x; e < end; e += blockDim.x)
-            fill_one<T, KIND, SPLIT, NW>(c, tk, e, tgt_nat, src_nat, sm);
+            fill_one<T, K, KIND, SPLIT, NW>(c, tk, e, tgt_nat, src_nat, sm);
     }
 }
 
@@ -93,9 +94,46 @@ void to_float(const double *in, float *out, int64_t n, hipStream_t s) {
     HIP_LAUNCH_CHECK();
 }
 
+// The bounds that kink_family's integers need and the quantum's error, over every
+// path of the mesh: the straight ones and those reflected at each wall (two legs of the
+// unfolded segment, cut at p / M with M = twice the wall axis' cells at most; N, the
+// slope of a family, at most the two largest extents together).
+//   q / 2 per unit of length is at most 2^-53 on the longest path, half a unit in the
+//   last place of 1: exp(-depth) cannot show it;
+//   kappa / q <= 2^61, so a jump's upper 32 bits are below 2^30, and the weights
+//   k (A - k M), each below N^2 M / 4, sum to at most N^3 M / 6 < 2^32: both halves of a
+//   family's sum fit 64 bits.
+// On the unit cube this holds below kappa = 256 (128 with a wall) and to 1400 vertices
+// per axis (146 with a wall).  Largest error of the depth at 41^3 by kinks and by the march: 1.1e-16
+// and 5.6e-16 on a field in [0.3, 0.6], 9e-16 and 7e-15 beside a block of 100; at 1e4,
+// where the quantum's bound is 6e-15, still 4e-15 and 4e-14; at 1e8 3e-11 and 3e-16.
+double kink_quantum(const GridDev &g, double kmax) {
+    int e = 0;
+    (void)std::frexp(kmax, &e);   // kmax < 2^e
+    if (!std::isfinite(kmax) || e < -900) return 0.0;
+    for (int w = -1; w < g.n_walls; ++w) {
+        double ext[3], len2 = 0.0, M = 1.0, big = 0.0, next = 0.0;
+        for (int a = 0; a < 3; ++a) {
+            ext[a] = g.n[a] - 1;
+            if (w >= 0 && g.wall_axis[w] == a) {
+                ext[a] *= 2.0;
+                M = ext[a];
+            }
+            len2 += ext[a] * ext[a] * g.h[a] * g.h[a];
+            next = std::fmax(next, std::fmin(big, ext[a]));
+            big = std::fmax(big, ext[a]);
+        }
+        const double N = big + next;
+        if (N * N * N * M / 6.0 >= 4294967296.0 || N * N * M / 4.0 >= 2147483648.0) return 0.0;
+        if (!(std::ldexp(std::sqrt(len2), e) <= 512.0)) return 0.0;
+    }
+    return std::ldexp(1.0, e - 61);
+}
+
 // The kinks of kappa (march.h): per family and vertex v of the grid extended by
 // one plane on its upper sides, where kappa continues by its nearest value.
-__global__ void k_kink_table(GridDev g, const double *__restrict__ kap, double *__restrict__ out) {
+// per_q: 1 / q, a power of two.
+__global__ void k_kink_table(GridDev g, const double *__restrict__ kap, double per_q, int64_t *__restrict__ out) {
     const int64_t S0 = (int64_t)(g.n[1] + 1) * (g.n[2] + 1), S1 = g.n[2] + 1, M = (g.n[0] + 1) * S0;
     const int64_t o = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (o >= M) return;
@@ -103,11 +141,11 @@ __global__ void k_kink_table(GridDev g, const double *__restrict__ kap, double *
     auto k = [&](int dx, int dy, int dz) {
         const int i = min(max(x + dx, 0), g.n[0] - 1), j = min(max(y + dy, 0), g.n[1] - 1),
                   l = min(max(z + dz, 0), g.n[2] - 1);
-        return kap[(int64_t)i * g.stride[0] + (int64_t)j * g.stride[1] + l];
+        return (int64_t)__double2ll_rn(kap[(int64_t)i * g.stride[0] + (int64_t)j * g.stride[1] + l] * per_q);
     };
-    const double v = k(0, 0, 0), all = k(1, 1, 1);
-    const double x1 = k(1, 0, 0), y1 = k(0, 1, 0), z1 = k(0, 0, 1);
-    const double xy = k(1, 1, 0), yz = k(0, 1, 1), xz = k(1, 0, 1);
+    const int64_t v = k(0, 0, 0), all = k(1, 1, 1);
+    const int64_t x1 = k(1, 0, 0), y1 = k(0, 1, 0), z1 = k(0, 0, 1);
+    const int64_t xy = k(1, 1, 0), yz = k(0, 1, 1), xz = k(1, 0, 1);
     // a family of rotation (a, b, c) is stored [v_a][v_b][v_c]
     const int64_t r1 = ((int64_t)y * (g.n[2] + 1) + z) * (g.n[0] + 1) + x, r2 = ((int64_t)z * (g.n[0] + 1) + x) * (g.n[1] + 1) + y;
     out[0 * M + o] = all - yz - v + k(-1, 0, 0);
@@ -118,10 +156,10 @@ __global__ void k_kink_table(GridDev g, const double *__restrict__ kap, double *
     out[5 * M + r2] = x1 + z1 - v - xz;
 }
 
-DevBuf march_table(const Mesh &m, const double *kappa, hipStream_t s) {
+DevBuf kink_table(const Mesh &m, const double *kappa, double q, hipStream_t s) {
     const int64_t M = (int64_t)(m.dev.n[0] + 1) * (m.dev.n[1] + 1) * (m.dev.n[2] + 1);
-    DevBuf d = DevBuf::scratch(sizeof(double) * 6 * (size_t)M);
-    k_kink_table<<<(unsigned)((M + 255) / 256), 256, 0, s>>>(m.dev, kappa, d.as<double>());
+    DevBuf d = DevBuf::scratch(sizeof(int64_t) * 6 * (size_t)M);
+    k_kink_table<<<(unsigned)((M + 255) / 256), 256, 0, s>>>(m.dev, kappa, 1.0 / q, d.as<int64_t>());
     HIP_LAUNCH_CHECK();
     return d;
 }
@@ -147,13 +185,35 @@ __global__ void k_tet_table(GridDev g, const float *__restrict__ kap, float *__r
     out[4 * k + 3] = v3 < N ? kap[v3] : 0.0f;
 }
 
-DevBuf march_table(const Mesh &m, const float *kappa, hipStream_t s) {
-    DevBuf d = DevBuf::scratch(sizeof(float) * (size_t)m.N * 24);
-    const int64_t n = m.N * 6;
-    k_tet_table<<<(unsigned)((n + 255) / 256), 256, 0, s>>>(m.dev, kappa, d.as<float>());
-    HIP_LAUNCH_CHECK();
-    return d;
+// FP64: the eight corner values of every cell base b, in the order of tet_sample (a
+// vertex past the grid gives 0)
+__global__ void k_cell_table(GridDev g, const double *__restrict__ kap, double *__restrict__ out) {
+    const int64_t N = (int64_t)g.n[0] * g.n[1] * g.n[2];
+    const int64_t b = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (b >= N) return;
+    const int64_t s0 = g.stride[0], s1 = g.stride[1];
+    const int64_t v[8] = {b, b + s0 + s1 + 1, b + s0, b + s1, b + 1, b + s0 + s1, b + s1 + 1, b + s0 + 1};
+#pragma unroll
+    for (int q = 0; q < 8; ++q) out[8 * b + q] = v[q] < N ? kap[v[q]] : 0.0;
 }
+
+template <typename T>
+DevBuf march_table(const Mesh &m, const T *kappa, hipStream_t s) {
+    if constexpr (std::is_same<T, float>::value) {
+        DevBuf d = DevBuf::scratch(sizeof(float) * (size_t)m.N * 24);
+        const int64_t n = m.N * 6;
+        k_tet_table<<<(unsigned)((n + 255) / 256), 256, 0, s>>>(m.dev, kappa, d.as<float>());
+        HIP_LAUNCH_CHECK();
+        return d;
+    } else {
+        DevBuf d = DevBuf::scratch(sizeof(double) * (size_t)m.N * 8);
+        k_cell_table<<<(unsigned)((m.N + 255) / 256), 256, 0, s>>>(m.dev, kappa, d.as<double>());
+        HIP_LAUNCH_CHECK();
+        return d;
+    }
+}
+template DevBuf march_table<double>(const Mesh &, const double *, hipStream_t);
+template DevBuf march_table<float>(const Mesh &, const float *, hipStream_t);
 
 // Row d of the star table (StarTab), from the mesh's near and far tables.
 __global__ __launch_bounds__(128) void k_star_table(GridDev g, StarTab st, int64_t rows, const double *__restrict__ near,
@@ -245,12 +305,13 @@ StarTab star_table(const Mesh &m, hipStream_t s) {
     return t;
 }
 
-template <typename T>
-EntryCtx<T> make_ctx(const Mesh &m, int kind, BandKappa<T> kappa, hipStream_t s) {
-    EntryCtx<T> c;
+template <typename T, bool K>
+EntryCtx<T, K> make_ctx(const Mesh &m, int kind, BandKappa<T, K> kappa, hipStream_t s) {
+    EntryCtx<T, K> c;
     c.g = m.dev;
     c.kappa = kappa.v;
     c.tab = kappa.tab;
+    c.q = kappa.q;
     c.near = static_cast<const T *>(m.near_table(std::is_same<T, double>::value));
     if constexpr (std::is_same<T, double>::value) {
         if (kind == RTE_VOLUME) c.star = star_table(m, s);
@@ -260,34 +321,38 @@ EntryCtx<T> make_ctx(const Mesh &m, int kind, BandKappa<T> kappa, hipStream_t s)
     }
     return c;
 }
-template EntryCtx<double> make_ctx<double>(const Mesh &, int, BandKappa<double>, hipStream_t);
-template EntryCtx<float> make_ctx<float>(const Mesh &, int, BandKappa<float>, hipStream_t);
+template EntryCtx<double, true> make_ctx(const Mesh &, int, BandKappa<double, true>, hipStream_t);
+template EntryCtx<double, false> make_ctx(const Mesh &, int, BandKappa<double, false>, hipStream_t);
+template EntryCtx<float, false> make_ctx(const Mesh &, int, BandKappa<float, false>, hipStream_t);
 
-void entries_launch(const Mesh &m, int kind, const double *kappa, int64_t n, const int64_t *rows,
+void entries_launch(const Mesh &m, int kind, const double *kappa, double kmax, int64_t n, const int64_t *rows,
                     const int64_t *cols, double *out, int precision, hipStream_t s) {
     if (n == 0) return;
     const unsigned grid = (unsigned)((n + 255) / 256);
-    if (precision == RTE_FP64) {
-        DevBuf kt = march_table(m, kappa, s);
-        auto c = make_ctx<double>(m, kind, BandKappa<double>{kappa, kt.as<double>()}, s);
-        if (kind == RTE_VOLUME) k_entries<double, RTE_VOLUME><<<grid, 256, 0, s>>>(c, n, rows, cols, out);
-        else k_entries<double, RTE_SURFACE><<<grid, 256, 0, s>>>(c, n, rows, cols, out);
+    auto launch = [&](auto bk) {   // the band's tables are released after it
+        auto c = make_ctx(m, kind, bk, s);
+        using T = std::remove_const_t<std::remove_pointer_t<decltype(bk.v)>>;
+        constexpr bool K = std::is_same<decltype(bk), BandKappa<T, true>>::value;
+        if (kind == RTE_VOLUME) k_entries<T, K, RTE_VOLUME><<<grid, 256, 0, s>>>(c, n, rows, cols, out);
+        else k_entries<T, K, RTE_SURFACE><<<grid, 256, 0, s>>>(c, n, rows, cols, out);
         HIP_LAUNCH_CHECK();
-        HIP_CHECK(hipStreamSynchronize(s));   // kt is released on return
+        HIP_CHECK(hipStreamSynchronize(s));
+    };
+    if (precision == RTE_FP64) {
+        const double q = kink_quantum(m.dev, kmax);
+        DevBuf kt = q > 0.0 ? kink_table(m, kappa, q, s) : march_table(m, kappa, s);
+        if (q > 0.0) launch(BandKappa<double, true>{kappa, kt.as<int64_t>(), q});
+        else launch(BandKappa<double, false>{kappa, kt.as<double>()});
     } else {
         DevBuf kf(sizeof(float) * (size_t)m.N);
         to_float(kappa, kf.as<float>(), m.N, s);
         DevBuf kt = march_table(m, kf.as<float>(), s);
-        auto c = make_ctx<float>(m, kind, BandKappa<float>{kf.as<float>(), kt.as<float>()}, s);
-        if (kind == RTE_VOLUME) k_entries<float, RTE_VOLUME><<<grid, 256, 0, s>>>(c, n, rows, cols, out);
-        else k_entries<float, RTE_SURFACE><<<grid, 256, 0, s>>>(c, n, rows, cols, out);
-        HIP_LAUNCH_CHECK();
-        HIP_CHECK(hipStreamSynchronize(s));   // kf and kt are released on return
+        launch(BandKappa<float, false>{kf.as<float>(), kt.as<float>()});
     }
 }
 
-template <typename T>
-void dense_fill_launch(const Mesh &m, int kind, BandKappa<T> kappa, const std::vector<FillTask> &tasks,
+template <typename T, bool K>
+void dense_fill_launch(const Mesh &m, int kind, BandKappa<T, K> kappa, const std::vector<FillTask> &tasks,
                        const int64_t *tgt_nat, const int64_t *src_nat, SliceMap sm, bool split, BandStore &B,
                        hipStream_t s) {
     if (tasks.empty()) return;
@@ -303,7 +368,7 @@ void dense_fill_launch(const Mesh &m, int kind, BandKappa<T> kappa, const std::v
     if (order.size() > ((size_t)1 << 31) / fill_split<T>())
         throw std::runtime_error("dense fill: too many tasks for one grid");
     DevBuf dt = upload_scratch(order, s);
-    auto c = make_ctx<T>(m, kind, kappa, s);
+    auto c = make_ctx(m, kind, kappa, s);
     const FillTask *d = dt.as<FillTask>();
     const unsigned gp = (unsigned)(npair * fill_split<T>()), gs = (unsigned)((order.size() - npair) * fill_split<T>());
     const FillTask *ds = d + npair;
@@ -312,13 +377,15 @@ void dense_fill_launch(const Mesh &m, int kind, BandKappa<T> kappa, const std::v
     auto launch = [&](auto nw) {
         constexpr int NW = decltype(nw)::value;
         if (split) {
-            if (gp) k_dense_fill<T, kPairedVolume, true, NW><<<gp, 256, 0, s>>>(c, d, tgt_nat, src_nat, sm);
-            if (gs && kind == RTE_VOLUME) k_dense_fill<T, RTE_VOLUME, true, NW><<<gs, 256, 0, s>>>(c, ds, tgt_nat, src_nat, sm);
-            else if (gs) k_dense_fill<T, RTE_SURFACE, true, NW><<<gs, 256, 0, s>>>(c, ds, tgt_nat, src_nat, sm);
+            if constexpr (sizeof(T) == 4) {   // BF16 parts of FP32 entries
+                if (gp) k_dense_fill<T, K, kPairedVolume, true, NW><<<gp, 256, 0, s>>>(c, d, tgt_nat, src_nat, sm);
+                if (gs && kind == RTE_VOLUME) k_dense_fill<T, K, RTE_VOLUME, true, NW><<<gs, 256, 0, s>>>(c, ds, tgt_nat, src_nat, sm);
+                else if (gs) k_dense_fill<T, K, RTE_SURFACE, true, NW><<<gs, 256, 0, s>>>(c, ds, tgt_nat, src_nat, sm);
+            }
         } else {
-            if (gp) k_dense_fill<T, kPairedVolume, false, NW><<<gp, 256, 0, s>>>(c, d, tgt_nat, src_nat, sm);
-            if (gs && kind == RTE_VOLUME) k_dense_fill<T, RTE_VOLUME, false, NW><<<gs, 256, 0, s>>>(c, ds, tgt_nat, src_nat, sm);
-            else if (gs) k_dense_fill<T, RTE_SURFACE, false, NW><<<gs, 256, 0, s>>>(c, ds, tgt_nat, src_nat, sm);
+            if (gp) k_dense_fill<T, K, kPairedVolume, false, NW><<<gp, 256, 0, s>>>(c, d, tgt_nat, src_nat, sm);
+            if (gs && kind == RTE_VOLUME) k_dense_fill<T, K, RTE_VOLUME, false, NW><<<gs, 256, 0, s>>>(c, ds, tgt_nat, src_nat, sm);
+            else if (gs) k_dense_fill<T, K, RTE_SURFACE, false, NW><<<gs, 256, 0, s>>>(c, ds, tgt_nat, src_nat, sm);
         }
     };
     switch (wall_mode(m.dev)) {
@@ -331,9 +398,11 @@ void dense_fill_launch(const Mesh &m, int kind, BandKappa<T> kappa, const std::v
     B.fill_events.push_back(std::move(ev));
     B.retire.push_back(std::move(dt));   // read by the queued launches
 }
-template void dense_fill_launch<double>(const Mesh &, int, BandKappa<double>, const std::vector<FillTask> &,
-                                        const int64_t *, const int64_t *, SliceMap, bool, BandStore &, hipStream_t);
-template void dense_fill_launch<float>(const Mesh &, int, BandKappa<float>, const std::vector<FillTask> &,
-                                       const int64_t *, const int64_t *, SliceMap, bool, BandStore &, hipStream_t);
+template void dense_fill_launch(const Mesh &, int, BandKappa<double, true>, const std::vector<FillTask> &, const int64_t *,
+                                const int64_t *, SliceMap, bool, BandStore &, hipStream_t);
+template void dense_fill_launch(const Mesh &, int, BandKappa<double, false>, const std::vector<FillTask> &, const int64_t *,
+                                const int64_t *, SliceMap, bool, BandStore &, hipStream_t);
+template void dense_fill_launch(const Mesh &, int, BandKappa<float, false>, const std::vector<FillTask> &, const int64_t *,
+                                const int64_t *, SliceMap, bool, BandStore &, hipStream_t);
 
 }  // namespace rte

@@ -11,14 +11,15 @@
 // at the wall.  One optical depth per vertex pair; near rule (degree 5)
 // when the grid Chebyshev distance is <= 2, degree 2 otherwise.
 //
-// FP64: tau from the kinks of kappa along the ray (march.h), g from a table by
-// offset; FP32: tau from a march in FP32 (march32.h), g point by point.
+// FP64: tau from the kinks of kappa along the ray (march.h), or from the march
+// through its tetrahedra (march_tets.h) when kink_quantum says so, g from a table by
+// offset; FP32: tau from that march in FP32, g point by point.
 #pragma once
 
 #include <type_traits>
 #include <utility>
 
-#include "rte_internal.h"
+#include "kernels.h"
 
 namespace rte {
 
@@ -37,21 +38,27 @@ __device__ __forceinline__ float recip(float x) { return __builtin_amdgcn_rcpf(x
 }  // namespace rte
 
 #include "march.h"
-#include "march32.h"
+#include "march_tets.h"
 
 namespace rte {
 
-template <typename T>
+// K: optical depths from the kinks of kappa (FP64), else by the march
+template <typename T, bool K>
 struct EntryCtx {
+    using Tab = DepthTab<T, K>;
     GridDev g;
     const T *__restrict__ kappa;   // [N] P1 vertex values of one band
-    const T *__restrict__ tab;     // the march's table: kinks of kappa (FP64), vertices of its tetrahedra (FP32)
+    const Tab *__restrict__ tab;   // kinks of kappa, or the vertices of its tetrahedra
+    double q;                      // the kinks' quantum
     StencilDev<T> st;
     const T *__restrict__ near;    // quadrature tables of the mesh: near [125][8][8], then far [24][4][8]
     StarTab star;                  // FP64: the same by offset (null: not built)
 };
-__device__ __forceinline__ KinkTab depth_src(const EntryCtx<double> &c) { return {c.tab, c.kappa}; }
-__device__ __forceinline__ KappaSrc depth_src(const EntryCtx<float> &c) { return {c.tab}; }
+template <typename T, bool K>
+__device__ __forceinline__ auto depth_src(const EntryCtx<T, K> &c) {
+    if constexpr (K) return KinkTab{c.tab, c.kappa, c.q};
+    else return KappaSrc<T>{c.tab};
+}
 
 // ---------------------------------------------------------------- compile-time Kuhn star
 struct TetInfo { int slot[4]; int bits; };
@@ -310,8 +317,8 @@ __device__ __forceinline__ int cells_in_grid(const GridDev &g, const int jj[3]) 
 }
 
 // kappa at the slot of the 3x3x3 block around vertex v (inside the grid)
-template <typename T>
-__device__ __forceinline__ T kappa_slot(const EntryCtx<T> &c, int64_t v, int slot) {
+template <typename T, bool K>
+__device__ __forceinline__ T kappa_slot(const EntryCtx<T, K> &c, int64_t v, int slot) {
     return c.kappa[v + (slot / 9 - 1) * c.g.stride[0] + (slot / 3 % 3 - 1) * c.g.stride[1] + (slot % 3 - 1)];
 }
 
@@ -319,8 +326,9 @@ __device__ __forceinline__ T kappa_slot(const EntryCtx<T> &c, int64_t v, int slo
 // flat index of j): near offsets from the near table, far ones by the degree-2
 // rule, |x - y|^2 = |h d|^2 + A.d + C per point and the 4 points of a
 // tetrahedron over one common denominator.
-__device__ __forceinline__ double vol_points(const EntryCtx<double> &c, int64_t v, int cellmask, const int d0, const int d1,
-                                     const int d2) {
+template <bool K>
+__device__ __forceinline__ double vol_points(const EntryCtx<double, K> &c, int64_t v, int cellmask, const int d0,
+                                             const int d1, const int d2) {
     const GridDev &g = c.g;
     double acc = 0.0;
     if (max(max(abs(d0), abs(d1)), abs(d2)) <= kNearCheb) {
@@ -355,14 +363,14 @@ __device__ __forceinline__ double vol_points(const EntryCtx<double> &c, int64_t 
     return acc * g.vol_scale;
 }
 
-template <int o, int... es>
-__device__ __forceinline__ void cell_corners(std::integer_sequence<int, es...>, const EntryCtx<double> &c, int64_t v,
+template <int o, bool K, int... es>
+__device__ __forceinline__ void cell_corners(std::integer_sequence<int, es...>, const EntryCtx<double, K> &c, int64_t v,
                                              const double *__restrict__ row, double &acc) {
     ((corner_used(es, o) ? (void)(acc = fma(row[o * 8 + es], kappa_slot(c, v, slot_of(es, o)), acc)) : (void)0), ...);
 }
-template <int... os>
-__device__ __forceinline__ double vol_cells(std::integer_sequence<int, os...>, const EntryCtx<double> &c, int64_t v, int cellmask,
-                                       const double *__restrict__ row) {
+template <bool K, int... os>
+__device__ __forceinline__ double vol_cells(std::integer_sequence<int, os...>, const EntryCtx<double, K> &c, int64_t v,
+                                            int cellmask, const double *__restrict__ row) {
     double acc = 0.0;
     ((((cellmask >> os) & 1) ? cell_corners<os>(std::make_integer_sequence<int, 8>{}, c, v, row, acc) : (void)0), ...);
     return acc;
@@ -381,8 +389,8 @@ struct Star {
 // instructions (24 tetrahedra); a source that misses cells (on
 // the boundary, at the hole) takes its cells' corner weights.  41^3: dense
 // fill 12.8 -> 7.7 ms, ACA entry launches 73.5 -> 70.4 (bound by the march).
-template <int>
-__device__ __forceinline__ double vol_quad(const EntryCtx<double> &c, const Star &s, const int d[3]) {
+template <int, bool K>
+__device__ __forceinline__ double vol_quad(const EntryCtx<double, K> &c, const Star &s, const int d[3]) {
     if (!c.star.w) return vol_points(c, s.v, s.cellmask, d[0], d[1], d[2]);
     const int64_t row = (int64_t)(d[0] - c.star.lo[0]) * c.star.st0 + (d[1] - c.star.lo[1]) * c.star.st1 +
                         (d[2] - c.star.lo[2]);
@@ -396,7 +404,8 @@ __device__ __forceinline__ double vol_quad(const EntryCtx<double> &c, const Star
     return acc;
 }
 
-__device__ __forceinline__ Star load_star(const EntryCtx<double> &c, const int jj[3], int cellmask) {
+template <bool K>
+__device__ __forceinline__ Star load_star(const EntryCtx<double, K> &c, const int jj[3], int cellmask) {
     Star s;
     s.v = (int64_t)jj[0] * c.g.stride[0] + (int64_t)jj[1] * c.g.stride[1] + jj[2];
     s.cellmask = cellmask;
@@ -407,7 +416,7 @@ __device__ __forceinline__ Star load_star(const EntryCtx<double> &c, const int j
     return s;
 }
 
-// FP32 entries, point by point (march32.h says why).
+// FP32 entries, point by point (march_tets.h says why).
 // Near field (grid offset d = x - x_j with |d_a| <= 2): the degree-5 rule's
 // sums, tabulated per mesh by cell and corner, so g is 64 products with the
 // star's kappa values (cells outside the grid skipped).
@@ -460,7 +469,7 @@ struct Star32 {
     int cellmask;
     float k[27];
 };
-__device__ __forceinline__ Star32 load_star(const EntryCtx<float> &c, const int jj[3], int cellmask) {
+__device__ __forceinline__ Star32 load_star(const EntryCtx<float, false> &c, const int jj[3], int cellmask) {
     const GridDev &g = c.g;
     Star32 r;
     r.cellmask = cellmask;
@@ -476,8 +485,8 @@ __device__ __forceinline__ Star32 load_star(const EntryCtx<float> &c, const int 
 }
 // g(x_j + d, j) without the 1/(4 pi)|e| factor.  FIRST: the axis whose square is
 // rounded by itself in |h d|^2.
-template <int FIRST>
-__device__ __forceinline__ float vol_quad(const EntryCtx<float> &c, const Star32 &s, const int d[3]) {
+template <int FIRST, bool K>
+__device__ __forceinline__ float vol_quad(const EntryCtx<float, K> &c, const Star32 &s, const int d[3]) {
     if (max(max(abs(d[0]), abs(d[1])), abs(d[2])) <= kNearCheb) return vol_near(c.near, s.k, s.cellmask, d);
     const GridDev &g = c.g;
     const float h2[3] = {(float)(g.h[0] * g.h[0]), (float)(g.h[1] * g.h[1]), (float)(g.h[2] * g.h[2])};
@@ -505,8 +514,8 @@ __device__ __forceinline__ float first_term(float att, float g) { return att * g
 // sum over the direct path and the walls of attenuation times the quadrature
 // of the source star of ss seen from target tt (or from its mirror image in
 // each wall); att_w[w] = R_w exp(-tau_w)
-template <typename T, int NW>
-__device__ __forceinline__ T vol_sum(const EntryCtx<T> &c, T att, const T att_w[6], const int tt[3],
+template <typename T, bool K, int NW>
+__device__ __forceinline__ T vol_sum(const EntryCtx<T, K> &c, T att, const T att_w[6], const int tt[3],
                                      const int ss[3]) {
     const GridDev &g = c.g;
     int cellmask = cells_in_grid(g, ss);
@@ -514,14 +523,14 @@ __device__ __forceinline__ T vol_sum(const EntryCtx<T> &c, T att, const T att_w[
         if (g.has_hole) cellmask &= ~hole_cells(g, ss);   // the hole's cells are in no star
     const auto star = load_star(c, ss, cellmask);
     const int dg[3] = {tt[0] - ss[0], tt[1] - ss[1], tt[2] - ss[2]};
-    T G = first_term(att, vol_quad<NW == kAnyWalls ? 0 : 1>(c, star, dg));
+    T G = first_term(att, vol_quad<NW == kAnyWalls ? 0 : 1, K>(c, star, dg));
     if constexpr (NW != kNoWall) {
         const int nw = NW == kOneWall ? 1 : g.n_walls;
         for (int w = 0; w < nw; ++w) {
             int mt[3];
             mirror_index(g, w, tt, mt);
             const int dgm[3] = {mt[0] - ss[0], mt[1] - ss[1], mt[2] - ss[2]};
-            G += att_w[w] * vol_quad<1>(c, star, dgm);
+            G += att_w[w] * vol_quad<1, K>(c, star, dgm);
         }
     }
     if constexpr (sizeof(T) == 4) return G * (T)g.vol_scale;
@@ -550,19 +559,23 @@ __device__ __forceinline__ T attenuations(const GridDev &g, const Src &kt, const
 }
 
 // The same for a group of P lanes of one wavefront (P a power of two, lane
-// number `sub`) that share the pair.  FP64: the families of every leg of every
-// path are dealt to the lanes and added in the order of kink_sum; FP32: the legs
+// number `sub`) that share the pair.  Kinks: the families of every leg of every
+// path are dealt to the lanes and added in the order of kink_sum; march: the legs
 // are.  The attenuations are those of a single lane bit for bit.  buf: LDS of the
-// group, kGroupTasks<T, NW> values.
-template <typename T, int NW>
-constexpr int kGroupTasks = (sizeof(T) == 8 ? 6 : 1) * (1 + 2 * NW);
+// group, group_tasks values.
+template <typename T, bool K>
+using GroupTask = std::conditional_t<K, Dd, T>;
+template <bool K>
+__host__ __device__ constexpr int group_tasks(int n_walls) {
+    return (K ? 6 : 1) * (1 + 2 * n_walls);
+}
 __device__ __forceinline__ void group_sync() {   // orders the LDS accesses of a wavefront
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     __builtin_amdgcn_wave_barrier();
 }
 template <int NW>
 __device__ __forceinline__ double group_attenuations(const GridDev &g, const KinkTab &kt, const int Pi[3],
-                                                     const int Qi[3], double att_w[6], int P, int sub, double *buf) {
+                                                     const int Qi[3], double att_w[6], int P, int sub, Dd *buf) {
     const int nw = NW == kAnyWalls ? g.n_walls : NW;
     for (int t = sub; t < 6 * (1 + 2 * nw); t += P) {
         const int leg = t / 6, f = t - 6 * leg;
@@ -591,50 +604,51 @@ __device__ __forceinline__ double group_attenuations(const GridDev &g, const Kin
             const WallInfo wi = wall_info(g, w);
             const int C = wall_plane(g, wi);
             const Legs l = reflect_legs(wi.axis, C, Pi, Qi);
-            const double *b = buf + 6 + 12 * w;
-            const double tau = l.p + l.q == 0 ? direct
-                                              : reflected_depth(g, kt, wi.axis, C, Pi, Qi, l, add_families(b) + add_families(b + 6));
+            const Dd *b = buf + 6 + 12 * w;
+            const double tau = l.p + l.q == 0
+                                   ? direct
+                                   : reflected_depth(g, kt, wi.axis, C, Pi, Qi, l, dd_add(add_families(b), add_families(b + 6)));
             att_w[w] = hole && hole_blocks_mirror(g, w, Pi, Qi) ? 0.0 : wi.R * exp(-tau);
         }
     }
     return att;
 }
-template <int NW>
-__device__ __forceinline__ float group_attenuations(const GridDev &g, const KappaSrc &kt, const int Pi[3],
-                                                    const int Qi[3], float att_w[6], int P, int sub, float *buf) {
+template <int NW, typename T>
+__device__ __forceinline__ T group_attenuations(const GridDev &g, const KappaSrc<T> &kt, const int Pi[3],
+                                                const int Qi[3], T att_w[6], int P, int sub, T *buf) {
     const int nw = NW == kAnyWalls ? g.n_walls : NW;
     for (int t = sub; t < 1 + 2 * nw; t += P) {
-        float A[3] = {(float)Pi[0], (float)Pi[1], (float)Pi[2]}, B[3] = {(float)Qi[0], (float)Qi[1], (float)Qi[2]};
+        T A[3] = {(T)Pi[0], (T)Pi[1], (T)Pi[2]}, B[3] = {(T)Qi[0], (T)Qi[1], (T)Qi[2]};
         if (NW != kNoWall && t > 0) {   // P to the wall, the wall to Q
             const WallInfo wi = wall_info(g, (t - 1) >> 1);
-            float X[3];
-            wall_point(wi.axis, (float)wall_plane(g, wi), A, B, X);
+            T X[3];
+            wall_point<T>(wi.axis, (T)wall_plane(g, wi), A, B, X);
 #pragma unroll
             for (int b = 0; b < 3; ++b) {
                 A[b] = t & 1 ? A[b] : X[b];
                 B[b] = t & 1 ? X[b] : B[b];
             }
         }
-        buf[t] = tau_segment(g, kt, A, B);
+        buf[t] = tau_segment<T>(g, kt, A, B);
     }
     group_sync();
     const bool hole = NW == kAnyWalls && g.has_hole;
-    const float att = hole && hole_blocks(g, Pi, Qi) ? 0.0f : exp(-buf[0]);
+    const T att = hole && hole_blocks(g, Pi, Qi) ? (T)0 : exp(-buf[0]);
     if constexpr (NW != kNoWall)
         for (int w = 0; w < nw; ++w)
             att_w[w] = hole && hole_blocks_mirror(g, w, Pi, Qi)
-                           ? 0.0f
-                           : (float)wall_info(g, w).R * exp(-(buf[1 + 2 * w] + buf[2 + 2 * w]));
+                           ? (T)0
+                           : (T)wall_info(g, w).R * exp(-(buf[1 + 2 * w] + buf[2 + 2 * w]));
     return att;
 }
 
 // G(i, j).  Every wall adds its own mirror-image term (one reflection per
 // ray).  The optical depths come first: the star of j is loaded after the
-// marches, so its values do not stay live through them.  FROM_J: FP64 rays are
-// walked from j (the depth is symmetric), for launches whose lanes share the
-// source: the lanes then meet the planes in step (KinkTab).
-template <typename T, int NW = kAnyWalls, bool FROM_J = false>
-__device__ T volume_entry(const EntryCtx<T> &c, int64_t i, int64_t j) {
+// marches, so its values do not stay live through them.  FROM_J: the kinks are
+// walked from j (the depth is the same to the bit), for launches whose lanes share
+// the source: the lanes then meet the planes in step (KinkTab).
+template <typename T, bool K, int NW = kAnyWalls, bool FROM_J = false>
+__device__ T volume_entry(const EntryCtx<T, K> &c, int64_t i, int64_t j) {
     const GridDev &g = c.g;
     int ii[3], jj[3];
     vtx_index(g, i, ii);
@@ -642,26 +656,26 @@ __device__ T volume_entry(const EntryCtx<T> &c, int64_t i, int64_t j) {
     if constexpr (NW == kAnyWalls)
         if (!vertex_active(g, ii)) return (T)0;   // a removed vertex (its column: an empty star)
     T att_w[6];
-    constexpr bool from_j = FROM_J && sizeof(T) == 8;
+    constexpr bool from_j = FROM_J && K;
     const T att = attenuations<T, NW>(g, depth_src(c), from_j ? jj : ii, from_j ? ii : jj, att_w);
-    return vol_sum<T, NW>(c, att, att_w, ii, jj);
+    return vol_sum<T, K, NW>(c, att, att_w, ii, jj);
 }
 
-// G(i, j) and G(j, i) together (lanes share j; FP32 rays are walked from i): the
+// G(i, j) and G(j, i) together (lanes share j; the march goes from i): the
 // optical depth along the segment (and along each reflected path, whose wall point
 // is the same seen from either end) is shared; each entry takes its own source
 // star and quadrature.
-template <typename T, int NW = kAnyWalls>
-__device__ __forceinline__ void volume_entry_pair(const EntryCtx<T> &c, int64_t i, int64_t j, T &gij, T &gji) {
+template <typename T, bool K, int NW = kAnyWalls>
+__device__ __forceinline__ void volume_entry_pair(const EntryCtx<T, K> &c, int64_t i, int64_t j, T &gij, T &gji) {
     const GridDev &g = c.g;
     int ii[3], jj[3];
     vtx_index(g, i, ii);
     vtx_index(g, j, jj);
     T att_w[6];
-    constexpr bool from_j = sizeof(T) == 8;
+    constexpr bool from_j = K;
     const T att = attenuations<T, NW>(g, depth_src(c), from_j ? jj : ii, from_j ? ii : jj, att_w);
-    gij = vol_sum<T, NW>(c, att, att_w, ii, jj);
-    gji = vol_sum<T, NW>(c, att, att_w, jj, ii);
+    gij = vol_sum<T, K, NW>(c, att, att_w, ii, jj);
+    gji = vol_sum<T, K, NW>(c, att, att_w, jj, ii);
     if constexpr (NW == kAnyWalls) {   // removed vertices have zero rows
         if (!vertex_active(g, ii)) gij = (T)0;
         if (!vertex_active(g, jj)) gji = (T)0;
@@ -706,8 +720,8 @@ __device__ __forceinline__ T tri_all(std::integer_sequence<int, ts...>, const T 
 
 // s(x, l) including 1/(4 pi) and the element areas; x given by its grid
 // coordinates (possibly outside the box for a mirror image) and index.
-template <typename T>
-__device__ T surf_quad(const EntryCtx<T> &c, const int xi[3], const int ll[3], bool near) {
+template <typename T, bool K>
+__device__ T surf_quad(const EntryCtx<T, K> &c, const int xi[3], const int ll[3], bool near) {
     const GridDev &g = c.g;
     T acc = (T)0;
 #pragma nounroll
@@ -786,8 +800,8 @@ __device__ __forceinline__ T tri_all_m(std::integer_sequence<int, ts...>, const 
     return acc;
 }
 
-template <typename T>
-__device__ T surf_quad_rects(const EntryCtx<T> &c, const int xi[3], const int ll[3], bool near) {
+template <typename T, bool K>
+__device__ T surf_quad_rects(const EntryCtx<T, K> &c, const int xi[3], const int ll[3], bool near) {
     const GridDev &g = c.g;
     T acc = (T)0;
     for (int f = 0; f < 12; ++f) {
@@ -860,8 +874,8 @@ __device__ T surf_quad_rects(const EntryCtx<T> &c, const int xi[3], const int ll
 }
 
 // S(i, l) from the attenuations of the pair
-template <typename T, int NW>
-__device__ __forceinline__ T surf_sum(const EntryCtx<T> &c, T att, const T att_w[6], const int ii[3], const int ll[3]) {
+template <typename T, bool K, int NW>
+__device__ __forceinline__ T surf_sum(const EntryCtx<T, K> &c, T att, const T att_w[6], const int ii[3], const int ll[3]) {
     const GridDev &g = c.g;
     if constexpr (NW == kAnyWalls) {
         T S = att == (T)0 ? (T)0 : first_term(att, surf_quad_rects(c, ii, ll, cheb3(ii, ll) <= kNearCheb));
@@ -883,8 +897,8 @@ __device__ __forceinline__ T surf_sum(const EntryCtx<T> &c, T att, const T att_w
     }
 }
 
-template <typename T, int NW = kAnyWalls, bool FROM_J = false>
-__device__ T surface_entry(const EntryCtx<T> &c, int64_t i, int64_t l) {
+template <typename T, bool K, int NW = kAnyWalls, bool FROM_J = false>
+__device__ T surface_entry(const EntryCtx<T, K> &c, int64_t i, int64_t l) {
     const GridDev &g = c.g;
     int ii[3], ll[3];
     vtx_index(g, i, ii);
@@ -892,21 +906,22 @@ __device__ T surface_entry(const EntryCtx<T> &c, int64_t i, int64_t l) {
     if constexpr (NW == kAnyWalls)
         if (!vertex_active(g, ii)) return (T)0;   // a removed vertex
     T att_w[6];
-    constexpr bool from_j = FROM_J && sizeof(T) == 8;
+    constexpr bool from_j = FROM_J && K;
     const T att = attenuations<T, NW>(g, depth_src(c), from_j ? ll : ii, from_j ? ii : ll, att_w);
-    return surf_sum<T, NW>(c, att, att_w, ii, ll);
+    return surf_sum<T, K, NW>(c, att, att_w, ii, ll);
 }
 
-template <typename T, int KIND, int NW = kAnyWalls, bool FROM_J = false>
-__device__ __forceinline__ T entry(const EntryCtx<T> &c, int64_t i, int64_t j) {
-    if constexpr (KIND == RTE_VOLUME) return volume_entry<T, NW, FROM_J>(c, i, j);
-    else return surface_entry<T, NW, FROM_J>(c, i, j);
+template <int KIND, int NW = kAnyWalls, bool FROM_J = false, typename T, bool K>
+__device__ __forceinline__ T entry(const EntryCtx<T, K> &c, int64_t i, int64_t j) {
+    if constexpr (KIND == RTE_VOLUME) return volume_entry<T, K, NW, FROM_J>(c, i, j);
+    else return surface_entry<T, K, NW, FROM_J>(c, i, j);
 }
 
 // The entry of a pair shared by a group of P lanes (group_attenuations); every
 // lane returns it.
-template <typename T, int KIND, int NW, bool FROM_J>
-__device__ __forceinline__ T group_entry(const EntryCtx<T> &c, int64_t i, int64_t j, int P, int sub, T *buf) {
+template <int KIND, int NW, bool FROM_J, typename T, bool K>
+__device__ __forceinline__ T group_entry(const EntryCtx<T, K> &c, int64_t i, int64_t j, int P, int sub,
+                                         GroupTask<T, K> *buf) {
     const GridDev &g = c.g;
     int ii[3], jj[3];
     vtx_index(g, i, ii);
@@ -914,10 +929,10 @@ __device__ __forceinline__ T group_entry(const EntryCtx<T> &c, int64_t i, int64_
     if constexpr (NW == kAnyWalls)
         if (!vertex_active(g, ii)) return (T)0;   // a removed vertex
     T att_w[6];
-    constexpr bool from_j = FROM_J && sizeof(T) == 8;
+    constexpr bool from_j = FROM_J && K;
     const T att = group_attenuations<NW>(g, depth_src(c), from_j ? jj : ii, from_j ? ii : jj, att_w, P, sub, buf);
-    if constexpr (KIND == RTE_VOLUME) return vol_sum<T, NW>(c, att, att_w, ii, jj);
-    else return surf_sum<T, NW>(c, att, att_w, ii, jj);
+    if constexpr (KIND == RTE_VOLUME) return vol_sum<T, K, NW>(c, att, att_w, ii, jj);
+    else return surf_sum<T, K, NW>(c, att, att_w, ii, jj);
 }
 
 }  // namespace rte

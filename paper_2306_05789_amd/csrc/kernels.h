@@ -1,6 +1,8 @@
 // Work descriptors shared by the host planners and the kernels.
 #pragma once
 
+#include <type_traits>
+
 #include "rte_internal.h"
 
 namespace rte {
@@ -112,25 +114,33 @@ struct EventTimer {
     }
 };
 
-template <typename T> struct EntryCtx;
 // One band's absorption as the entry kernels read it: the vertex values in the
-// entries' type, and the march's table of them.
-template <typename T>
+// entries' type, and the table of them that optical depths are taken from.  K:
+// kinks [6][n0 + 1][n1 + 1][n2 + 1] in units of q (march.h); else FP32 [N][6][4],
+// FP64 [N][8] (march_tets.h).
+template <typename T, bool K>
+using DepthTab = std::conditional_t<K, int64_t, T>;
+template <typename T, bool K>
 struct BandKappa {
     const T *v;     // [N]
-    const T *tab;   // FP64: kinks [6][n0 + 1][n1 + 1][n2 + 1] (march.h); FP32: [N][6][4] (march32.h)
+    const DepthTab<T, K> *tab;
+    double q = 0.0;
 };
+template <typename T, bool K> struct EntryCtx;
 // s: the stream on which the mesh's quadrature table is built if it is not yet there (FP64 volume entries)
-template <typename T> EntryCtx<T> make_ctx(const Mesh &m, int kind, BandKappa<T> kappa, hipStream_t s);
-// the march's table of `kappa` on the mesh, queued on s (scratch; the caller
+template <typename T, bool K> EntryCtx<T, K> make_ctx(const Mesh &m, int kind, BandKappa<T, K> kappa, hipStream_t s);
+// The quantum of a band's kinks on the grid, kmax its largest kappa; 0 when FP64
+// depths have to be marched instead (march.h).
+double kink_quantum(const GridDev &g, double kmax);
+// the table of `kappa` on the mesh, queued on s (scratch; the caller
 // keeps it until the launches that read it have run)
-DevBuf march_table(const Mesh &m, const double *kappa, hipStream_t s);
-DevBuf march_table(const Mesh &m, const float *kappa, hipStream_t s);
+DevBuf kink_table(const Mesh &m, const double *kappa, double q, hipStream_t s);
+template <typename T> DevBuf march_table(const Mesh &m, const T *kappa, hipStream_t s);
 void to_float(const double *in, float *out, int64_t n, hipStream_t s);
 // queues the fill on s without waiting: the task list and the launch's event
 // pair go to B.retire / B.fill_events (read by band_settle); split: write BF16 hi/lo
-template <typename T>
-void dense_fill_launch(const Mesh &m, int kind, BandKappa<T> kappa, const std::vector<FillTask> &tasks,
+template <typename T, bool K>
+void dense_fill_launch(const Mesh &m, int kind, BandKappa<T, K> kappa, const std::vector<FillTask> &tasks,
                        const int64_t *tgt_nat, const int64_t *src_nat, SliceMap sm, bool split, BandStore &B,
                        hipStream_t s);
 

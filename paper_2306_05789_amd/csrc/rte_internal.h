@@ -389,9 +389,9 @@ struct HMat {
 };
 
 // ---------------------------------------------------------------- entry points implemented in .hip files
-void entries_launch(const Mesh &m, int kind, const double *kappa, int64_t n, const int64_t *rows,
+void entries_launch(const Mesh &m, int kind, const double *kappa, double kmax, int64_t n, const int64_t *rows,
                     const int64_t *cols, double *out, int precision, hipStream_t s);
-void assemble_band(HMat &H, int band, const double *kappa_band, hipStream_t s);
+void assemble_band(HMat &H, int band, const double *kappa_band, double kmax, hipStream_t s);   // kmax: largest kappa of the band
 void band_settle(BandStore &B, hipStream_t s);   // after the band's last queued work
 void matvec_reserve(HMat &H, int n_bands);   // room for the per-band plans (before building them concurrently)
 void matvec_build(HMat &H, int band, hipStream_t s);
@@ -431,7 +431,7 @@ struct rte_hmat;
 namespace rte {
 std::unique_ptr<rte_hmat> assemble_hmat(const Mesh &m, std::shared_ptr<const Plan> plan,
                                         const rte_hmat_opts_t &opts, int n_bands, const double *kappa,
-                                        hipStream_t s);
+                                        const std::vector<double> &kmax, hipStream_t s);
 }
 struct rte_plan { std::unique_ptr<rte::Plan> p; };
 struct rte_hmat { rte::HMat h; };

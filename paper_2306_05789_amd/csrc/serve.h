@@ -9,7 +9,7 @@ struct Server;
 void mesh_init(Mesh &M, const rte_mesh_desc_t &d);
 Server *server_create(const rte_server_desc_t &d, hipStream_t s);
 void server_destroy(Server *S);
-int server_add_mesh(Server &S, const rte_mesh_desc_t &md, const double *kappa);
+int server_add_mesh(Server &S, const rte_mesh_desc_t &md, const double *kappa, double kmax);
 int64_t server_submit(Server &S, const rte_request_t &q);
 void server_step(Server &S, int32_t *n_active, int32_t *n_pending);
 void server_poll(Server &S, int64_t id, rte_request_info_t &info);

@@ -199,6 +199,7 @@ struct SrvOp {
 struct SrvMesh {
     Mesh mesh;
     DevBuf kappa;          // base field, natural order [N]
+    double kmax = 0.0;     // its largest value
     DevBuf kap_c;          // base field, cluster order [N] (after the first operator)
     DevBuf tgt_nat;        // volume cluster position -> vertex
     DevBuf src_pos;        // surface cluster position -> position in the caller's wall vector
@@ -325,6 +326,7 @@ struct Server {
         const auto t0 = std::chrono::steady_clock::now();
         DevBuf kap(sizeof(double) * (size_t)M.mesh.N);
         const double mult = std::pow(10.0, (double)level / desc.levels_per_decade);
+        const std::vector<double> kmax{mult * M.kmax};   // the product rounds as the field's does
         k_scale<<<(unsigned)((M.mesh.N + 255) / 256), 256, 0, as>>>(M.kappa.as<double>(), mult, M.mesh.N,
                                                                     kap.as<double>());
         HIP_LAUNCH_CHECK();
@@ -343,14 +345,14 @@ struct Server {
             try {
                 HIP_CHECK(hipSetDevice(device));
                 Sop = assemble_hmat(M.mesh, mesh_plan(M.mesh, opts(RTE_SURFACE)), opts(RTE_SURFACE), 1, kap.as<double>(),
-                                     as2);
+                                     kmax, as2);
             } catch (...) {
                 serr = std::current_exception();
             }
         });
         std::exception_ptr gerr;
         try {
-            op->G = assemble_hmat(M.mesh, mesh_plan(M.mesh, opts(RTE_VOLUME)), opts(RTE_VOLUME), 1, kap.as<double>(), as);
+            op->G = assemble_hmat(M.mesh, mesh_plan(M.mesh, opts(RTE_VOLUME)), opts(RTE_VOLUME), 1, kap.as<double>(), kmax, as);
         } catch (...) {
             gerr = std::current_exception();
         }
@@ -873,11 +875,12 @@ static void after_user(Server &S) {
     (void)hipEventDestroy(e);
 }
 
-int server_add_mesh(Server &S, const rte_mesh_desc_t &md, const double *kappa) {
+int server_add_mesh(Server &S, const rte_mesh_desc_t &md, const double *kappa, double kmax) {
     auto M = std::make_unique<SrvMesh>();
     mesh_init(M->mesh, md);
     RTE_REQUIRE(M->mesh.L > 0, "server: the mesh has no emitting face");
     M->kappa.alloc(sizeof(double) * (size_t)M->mesh.N);
+    M->kmax = kmax;
     after_user(S);
     HIP_CHECK(hipMemcpyAsync(M->kappa.p, kappa, M->kappa.bytes, hipMemcpyDeviceToDevice, S.s));
     HIP_CHECK(hipStreamSynchronize(S.s));
