@@ -460,6 +460,13 @@ void rte_server_destroy(rte_server_t s);
 const char *rte_status_string(rte_status_t s);
 const char *rte_last_error(void);
 const char *rte_version(void);
+/* Device memory of the library: *held the bytes of every operator, server and
+ * working buffer on all devices, idle scratch included; *idle the idle scratch
+ * of the current device.  Working buffers of assemblies, products, solves and
+ * requests are kept idle for the next call, at most an eighth of the device. */
+rte_status_t rte_memory_info(int64_t *held, int64_t *idle);
+/* Gives the idle scratch of the current device back to it (waits for the device). */
+rte_status_t rte_release_scratch(void);
 
 #ifdef __cplusplus
 }

@@ -460,6 +460,22 @@ const char *rte_status_string(rte_status_t s) {
 
 const char *rte_last_error(void) { return g_last_error.c_str(); }
 
+rte_status_t rte_memory_info(int64_t *held, int64_t *idle) {
+    return guard([&] {
+        RTE_REQUIRE(held && idle, "rte_memory_info: NULL argument");
+        *held = (int64_t)device_bytes_held();
+        *idle = (int64_t)pool_idle_bytes();
+        return RTE_OK;
+    });
+}
+
+rte_status_t rte_release_scratch(void) {
+    return guard([&] {
+        pool_trim();
+        return RTE_OK;
+    });
+}
+
 const char *rte_version(void) { return "rte-mi355x 0.1 (gfx950)"; }
 
 rte_status_t rte_mesh_create(const rte_mesh_desc_t *desc, rte_mesh_t *out) {

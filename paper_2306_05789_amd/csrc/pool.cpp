@@ -13,6 +13,7 @@
 // freed on each call they cost a 16-column product of the 29^3 operator 330 of
 // its 1050 us and the 13-column mixed one of 37x22x31 350 of 740.
 #include <algorithm>
+#include <atomic>
 #include <chrono>
 #include <map>
 
@@ -51,6 +52,26 @@ struct Clock {
     }
 };
 
+// Every device allocation of the library goes through these two.  Checking aid:
+// RTE_MEMORY_CAP in the environment is the number of bytes that they may hold together;
+// an allocation beyond it fails as on a full device.
+std::atomic<size_t> g_held{0};
+
+hipError_t device_malloc(void **p, size_t bytes) {
+    const size_t held = g_held.fetch_add(bytes) + bytes;
+    hipError_t e = hipSuccess;
+    if (const char *cap = std::getenv("RTE_MEMORY_CAP"))
+        if (held > std::strtoull(cap, nullptr, 10)) e = hipErrorOutOfMemory;
+    if (e == hipSuccess) e = hipMalloc(p, bytes);
+    if (e != hipSuccess) g_held.fetch_sub(bytes);
+    return e;
+}
+
+void device_free(void *p, size_t bytes) {
+    (void)hipFree(p);
+    g_held.fetch_sub(bytes);
+}
+
 constexpr size_t kGranule = (size_t)2 << 20;
 
 // keep at most an eighth of the device memory idle, dropping the least recently given back first
@@ -68,7 +89,7 @@ void cap_idle_locked(Pool &P, int dev) {
         auto it = std::min_element(P.idle.begin(), P.idle.end(), [&](const Idle &a, const Idle &b) {
             return (a.device == dev ? a.stamp : UINT64_MAX) < (b.device == dev ? b.stamp : UINT64_MAX);
         });
-        (void)hipFree(it->p);
+        device_free(it->p, it->cap);
         P.bytes[dev] -= it->cap;
         P.idle.erase(it);
     }
@@ -77,6 +98,8 @@ void cap_idle_locked(Pool &P, int dev) {
 }  // namespace
 
 double &alloc_ms_this_thread() { return t_alloc_ms; }
+
+size_t device_bytes_held() { return g_held.load(); }
 
 void *pool_take(size_t bytes, size_t *cap) {
     Clock c;
@@ -101,11 +124,11 @@ void *pool_take(size_t bytes, size_t *cap) {
         }
     }
     void *p = nullptr;
-    hipError_t e = hipMalloc(&p, want);
+    hipError_t e = device_malloc(&p, want);
     if (e == hipErrorOutOfMemory) {
         (void)hipGetLastError();
         pool_trim();
-        e = hipMalloc(&p, want);
+        e = device_malloc(&p, want);
     }
     if (e != hipSuccess)
         throw Error(e == hipErrorOutOfMemory ? RTE_E_OUT_OF_MEMORY : RTE_E_DEVICE,
@@ -119,7 +142,7 @@ void pool_give(void *p, size_t cap) {
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess) {
         (void)hipGetLastError();
-        (void)hipFree(p);
+        device_free(p, cap);
         return;
     }
     Pool &P = pool();
@@ -150,7 +173,7 @@ void pool_trim() {
     std::lock_guard<std::mutex> g(P.mu);
     for (auto it = P.idle.begin(); it != P.idle.end();) {
         if (it->device == dev) {
-            (void)hipFree(it->p);
+            device_free(it->p, it->cap);
             P.bytes[dev] -= it->cap;
             it = P.idle.erase(it);
         } else {
@@ -163,11 +186,11 @@ void DevBuf::alloc(size_t b) {
     release();
     if (b) {
         Clock c;
-        hipError_t e = hipMalloc(&p, b);
+        hipError_t e = device_malloc(&p, b);
         if (e == hipErrorOutOfMemory) {   // idle scratch may be what is missing
             (void)hipGetLastError();
             pool_trim();
-            e = hipMalloc(&p, b);
+            e = device_malloc(&p, b);
         }
         if (e != hipSuccess) {
             p = nullptr;
@@ -190,7 +213,7 @@ void DevBuf::release() noexcept {
         }
         if (!kept) {
             Clock c;
-            (void)hipFree(p);
+            device_free(p, pooled ? cap : bytes);
         }
     }
     p = nullptr;

@@ -261,6 +261,7 @@ void *pool_take(size_t bytes, size_t *cap);
 void pool_give(void *p, size_t cap);
 size_t pool_idle_bytes();   // idle pooled bytes on the current device
 void pool_trim();           // free the idle pooled buffers of the current device
+size_t device_bytes_held();   // bytes of every DevBuf and of the idle pools, all devices
 double &alloc_ms_this_thread();   // host ms this thread spent allocating and freeing device memory
 
 // Checking aid: with RTE_POISON_WORKSPACE set in the environment, scratch

@@ -165,6 +165,8 @@ SIGNATURES = {
     "rte_status_string": (C.c_char_p, [C.c_int]),
     "rte_last_error": (C.c_char_p, []),
     "rte_version": (C.c_char_p, []),
+    "rte_memory_info": (C.c_int, [C.POINTER(C.c_int64), C.POINTER(C.c_int64)]),
+    "rte_release_scratch": (C.c_int, []),
 }
 
 _lib = None
@@ -493,3 +495,15 @@ def rte_fixed_point_solve(mesh: Mesh, vol: HMat, surf: HMat, T_wall, T_out, J_ou
 
 def rte_version() -> str:
     return load().rte_version().decode()
+
+
+def rte_memory_info():
+    """(held, idle): device bytes of the library, and the idle scratch among them on the current device."""
+    held, idle = C.c_int64(), C.c_int64()
+    _check(load().rte_memory_info(C.byref(held), C.byref(idle)))
+    return held.value, idle.value
+
+
+def rte_release_scratch():
+    """Give the idle scratch of the current device back to it."""
+    _check(load().rte_release_scratch())
