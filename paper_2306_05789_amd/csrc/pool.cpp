@@ -72,9 +72,10 @@ void device_free(void *p, size_t bytes) {
     g_held.fetch_sub(bytes);
 }
 
-constexpr size_t kGranule = (size_t)2 << 20;
+constexpr size_t kGranule = (size_t)2 << 20, kPage = 4096;
+constexpr size_t kIdleMost = 4096;   // buffers (a search of the idle ones stays short)
 
-// keep at most an eighth of the device memory idle, dropping the least recently given back first
+// keep at most an eighth of the device memory and kIdleMost buffers idle, dropping the least recently given back first
 void cap_idle_locked(Pool &P, int dev) {
     size_t &total = P.total[dev];
     if (total == 0) {
@@ -85,7 +86,8 @@ void cap_idle_locked(Pool &P, int dev) {
             return;
         }
     }
-    while (P.bytes[dev] > total / 8) {
+    while (P.bytes[dev] > total / 8 || P.idle.size() > kIdleMost) {
+        if (P.bytes[dev] == 0) return;   // what is idle is another device's
         auto it = std::min_element(P.idle.begin(), P.idle.end(), [&](const Idle &a, const Idle &b) {
             return (a.device == dev ? a.stamp : UINT64_MAX) < (b.device == dev ? b.stamp : UINT64_MAX);
         });
@@ -101,18 +103,19 @@ double &alloc_ms_this_thread() { return t_alloc_ms; }
 
 size_t device_bytes_held() { return g_held.load(); }
 
-void *pool_take(size_t bytes, size_t *cap) {
+void *pool_take(size_t bytes, size_t *cap, bool exact) {
     Clock c;
     int dev = 0;
     HIP_CHECK(hipGetDevice(&dev));
-    const size_t want = (bytes + kGranule - 1) / kGranule * kGranule;
+    const size_t unit = exact ? kPage : kGranule;
+    const size_t want = (bytes + unit - 1) / unit * unit, most = exact ? want : 2 * want;
     Pool &P = pool();
     {
         std::lock_guard<std::mutex> g(P.mu);
-        // best fit among the idle buffers of this device that are at most twice as large
+        // best fit among the idle buffers of this device that are at most twice as large (exact: no larger)
         auto best = P.idle.end();
         for (auto it = P.idle.begin(); it != P.idle.end(); ++it)
-            if (it->device == dev && it->cap >= want && it->cap <= 2 * want &&
+            if (it->device == dev && it->cap >= want && it->cap <= most &&
                 (best == P.idle.end() || it->cap < best->cap))
                 best = it;
         if (best != P.idle.end()) {
@@ -221,10 +224,10 @@ void DevBuf::release() noexcept {
     pooled = settled = false;
 }
 
-DevBuf DevBuf::scratch(size_t b) {
+DevBuf DevBuf::scratch(size_t b, bool exact) {
     DevBuf d;
     if (b) {
-        d.p = pool_take(b, &d.cap);
+        d.p = pool_take(b, &d.cap, exact);
         d.pooled = true;
     }
     d.bytes = b;

@@ -210,7 +210,9 @@ std::shared_ptr<PlanCache> new_plan_cache();
 // ---------------------------------------------------------------- device memory helper
 // An owned device allocation.  DevBuf(b) / alloc(b) take it from hipMalloc
 // (on out-of-memory the idle scratch pool is released and the call retried);
-// DevBuf::scratch(b) takes it from the per-device scratch pool (pool.cpp).
+// DevBuf::scratch(b) takes it from the per-device scratch pool (pool.cpp), in steps of
+// 2 MiB and up to twice as large; exact: rounded to whole pages only, for buffers that
+// outlive the call (a request's state of some 10 KB must not hold 2 MiB).
 // A scratch buffer goes back to the pool on release only when `settled` was
 // set, which says that no queued work reads it any more (its stream has
 // drained); otherwise it is freed with hipFree, which waits for the device.
@@ -235,7 +237,7 @@ struct DevBuf {
     ~DevBuf() { release(); }
     void alloc(size_t b);
     void release() noexcept;
-    static DevBuf scratch(size_t b);
+    static DevBuf scratch(size_t b, bool exact = false);
     template <typename T> T *as() const { return static_cast<T *>(p); }
 
 private:
@@ -257,7 +259,7 @@ inline void settle(std::initializer_list<DevBuf *> bufs) {
 }
 
 // Scratch pool of the current device (pool.cpp).
-void *pool_take(size_t bytes, size_t *cap);
+void *pool_take(size_t bytes, size_t *cap, bool exact);
 void pool_give(void *p, size_t cap);
 size_t pool_idle_bytes();   // idle pooled bytes on the current device
 void pool_trim();           // free the idle pooled buffers of the current device

@@ -513,7 +513,7 @@ struct Server {
             r.ops.push_back(o);
         }
         r.state_bytes = state_bytes(r);
-        r.st = DevBuf::scratch((size_t)r.state_bytes);
+        r.st = DevBuf::scratch((size_t)r.state_bytes, true);
         HIP_CHECK(hipMemsetAsync(r.st.p, 0, r.st.bytes, s));   // T = 0, J = 0
         resident += r.state_bytes;
         // S^E_b = S_hat Q_b, Q_b = B_nu(T_wall), wall values in surface cluster order
@@ -606,7 +606,7 @@ struct Server {
 
     void retire(SrvReq &r) {
         const SrvMesh &M = *meshes[r.mesh];
-        r.out = DevBuf::scratch(sizeof(double) * (size_t)M.mesh.N);
+        r.out = DevBuf::scratch(sizeof(double) * (size_t)M.mesh.N, true);
         permute_scatter(M.tgt_nat.as<int64_t>(), M.mesh.N, 1, M.mesh.N, M.mesh.N, r.T(), r.out.as<double>(), s);
         HIP_CHECK(hipStreamSynchronize(s));
         for (int l : distinct_levels(r)) {
@@ -911,7 +911,7 @@ int64_t server_submit(Server &S, const rte_request_t &q) {
     }
     r->tol = q.tol;
     r->max_iter = q.max_iter;
-    r->Tw = DevBuf::scratch(sizeof(double) * (size_t)M.mesh.L);
+    r->Tw = DevBuf::scratch(sizeof(double) * (size_t)M.mesh.L, true);
     after_user(S);
     HIP_CHECK(hipMemcpyAsync(r->Tw.p, q.T_wall, r->Tw.bytes, hipMemcpyDeviceToDevice, S.s));
     HIP_CHECK(hipStreamSynchronize(S.s));

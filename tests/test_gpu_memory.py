@@ -53,3 +53,35 @@ def test_idle_scratch_is_given_back():
     assert torch.equal(y, y2)
     del G, S, mesh
     assert fresh() == base
+
+
+def test_a_request_holds_what_it_needs():
+    """Wall temperatures of queued requests, states of running ones and results that wait to be fetched take their own
+    bytes in whole pages: none of it may exceed the server's budget by a multiple of what it counts."""
+    from paper_2306_05789_amd.serve import Server
+    n, count = (6, 5, 7), 60
+    page = lambda b: -(-b // 4096) * 4096
+    srv = Server([0.5, 1.0, 2.0], leaf_size=16, precision=rte.RTE_MIXED_BF16, max_active=20)
+    mid = srv.add_mesh(n, field(n)[0].contiguous())
+    tw = torch.ones(inputs.n_emitting(n, inputs.ALL_FACES), device=DEV, dtype=torch.float64)
+    N, nb = 6 * 5 * 7, 2
+    warm = srv.submit(mid, [0, 1], [1.0, 1.0], tw, tol=1e-6)   # assembles the operator
+    while srv.poll(warm)["state"] != rte.RTE_REQ_DONE:
+        srv.step()
+    srv.fetch(warm, torch.empty(N, device=DEV, dtype=torch.float64))
+    base = fresh()
+    ids = [srv.submit(mid, [0, 1], [1.0, 1.0], tw, tol=1e-6) for _ in range(count)]
+    queued = rte.rte_memory_info()[0] - base
+    assert queued <= count * page(tw.numel() * 8)
+    srv.step()
+    running = rte.rte_memory_info()[0] - base
+    # 20 states, and the sweep's own small tables
+    assert running <= queued + 20 * page(8 * N * (2 + 4 * nb)) + 2 * MB
+    while any(srv.poll(i)["state"] != rte.RTE_REQ_DONE for i in ids):
+        srv.step()
+    held, idle = rte.rte_memory_info()
+    assert held - idle - base <= count * page(8 * N) + 2 * MB
+    for i in ids:
+        srv.fetch(i, torch.empty(N, device=DEV, dtype=torch.float64))
+    held, idle = rte.rte_memory_info()
+    assert held - idle - base <= 2 * MB
