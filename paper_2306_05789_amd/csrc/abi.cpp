@@ -181,9 +181,11 @@ namespace rte {
 
 // Assembly of one H-matrix per band on a validated plan and kappa (device,
 // [n_bands][N], natural order, kmax the bands' largest values); see rte_hmat_assemble.
-std::unique_ptr<rte_hmat> assemble_hmat(const Mesh &m, std::shared_ptr<const Plan> plan,
-                                        const rte_hmat_opts_t &o, int n_bands, const double *kappa,
-                                        const std::vector<double> &kmax, hipStream_t s) {
+// lean: without the memory that an assembly can do without; held says afterwards (also
+// when this throws) whether some was taken.
+static std::unique_ptr<rte_hmat> assemble_once(const Mesh &m, std::shared_ptr<const Plan> plan,
+                                               const rte_hmat_opts_t &o, int n_bands, const double *kappa,
+                                               const std::vector<double> &kmax, hipStream_t s, bool lean, bool &held) {
     const auto t0 = std::chrono::steady_clock::now();
     const double alloc0 = alloc_ms_this_thread();
     double alloc_other = 0.0;   // allocation time of the second band thread
@@ -251,6 +253,9 @@ std::unique_ptr<rte_hmat> assemble_hmat(const Mesh &m, std::shared_ptr<const Pla
     double wsum = 0, wr = 0;
     int maxr = 0;
     matvec_reserve(H, n_bands);   // the bands' plans are then built from two threads
+    StarBuf star;
+    if (H.kind == RTE_VOLUME && H.precision == RTE_FP64 && !lean) star = star_table(m, free_at_start / 16, s);
+    held = star.tab.w != nullptr;
     // Bands are independent: with more than one, a second host thread on its
     // own stream takes every other band as it comes free, so one band's ACA
     // tail and host work overlap the other's kernels.
@@ -258,7 +263,7 @@ std::unique_ptr<rte_hmat> assemble_hmat(const Mesh &m, std::shared_ptr<const Pla
         std::atomic<int> next{0};
         auto run = [&](hipStream_t st) {
             for (int b; (b = next.fetch_add(1)) < n_bands;) {
-                assemble_band(H, b, kappa + (int64_t)b * m.N, kmax[b], st);
+                assemble_band(H, b, kappa + (int64_t)b * m.N, kmax[b], star.tab, st);
                 matvec_build(H, b, st);   // host work while the band's last kernels run
                 band_settle(H.bands[b], st);
             }
@@ -327,6 +332,7 @@ std::unique_ptr<rte_hmat> assemble_hmat(const Mesh &m, std::shared_ptr<const Pla
     }
     matvec_build_all(H, s);
     HIP_CHECK(hipStreamSynchronize(s));
+    settle({&star.buf});
     rte_hmat_stats_t &st = H.stats;
     st.n_tgt = (int64_t)P.tgt_nat.size();
     st.n_src = (int64_t)P.src_nat.size();
@@ -357,6 +363,20 @@ std::unique_ptr<rte_hmat> assemble_hmat(const Mesh &m, std::shared_ptr<const Pla
     st.recompressed_blocks = rc_blocks;
     st.recompress_ms = rc_ms;
     return hm;
+}
+
+std::unique_ptr<rte_hmat> assemble_hmat(const Mesh &m, std::shared_ptr<const Plan> plan,
+                                        const rte_hmat_opts_t &o, int n_bands, const double *kappa,
+                                        const std::vector<double> &kmax, hipStream_t s) {
+    bool held = false;
+    try {
+        return assemble_once(m, plan, o, n_bands, kappa, kmax, s, false, held);
+    } catch (const Error &e) {
+        if (e.code != RTE_E_OUT_OF_MEMORY || !held) throw;
+    }
+    // what was held may be what is missing
+    (void)hipGetLastError();
+    return assemble_once(m, plan, o, n_bands, kappa, kmax, s, true, held);
 }
 
 }  // namespace rte

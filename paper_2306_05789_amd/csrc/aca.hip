@@ -904,7 +904,7 @@ void aca_batch(HMat &H, BandStore &B, BandKappa<T, K> kap, const std::vector<Aca
     st.cblock = cblock.as<int>();
     st.Us = Us.as<T>();
     st.Vs = Vs.as<T>();
-    auto c = make_ctx(*H.mesh, H.kind, kap, s);
+    auto c = make_ctx(*H.mesh, kap);
     const T eps = (T)H.opts.aca_eps;
     const int64_t *tn = H.tgt_nat.as<int64_t>(), *sn = H.src_nat.as<int64_t>();
     // every step raises a rank or consumes a zero row, so this bounds the steps
@@ -1230,7 +1230,7 @@ void assemble_typed(HMat &H, int band, BandKappa<T, K> kap, hipStream_t s) {
 
 }  // namespace
 
-void assemble_band(HMat &H, int band, const double *kappa_band, double kmax, hipStream_t s) {
+void assemble_band(HMat &H, int band, const double *kappa_band, double kmax, const StarTab &star, hipStream_t s) {
     // the band's kappa buffers go to B.retire only after every launch reading
     // them is queued (band_settle, which an ACA batch may call, releases what
     // B.retire holds)
@@ -1238,8 +1238,8 @@ void assemble_band(HMat &H, int band, const double *kappa_band, double kmax, hip
     if (H.precision == RTE_FP64) {
         const double q = kink_quantum(H.mesh->dev, kmax);
         DevBuf kt = q > 0.0 ? kink_table(*H.mesh, kappa_band, q, s) : march_table(*H.mesh, kappa_band, s);
-        if (q > 0.0) assemble_typed(H, band, BandKappa<double, true>{kappa_band, kt.as<int64_t>(), q}, s);
-        else assemble_typed(H, band, BandKappa<double, false>{kappa_band, kt.as<double>()}, s);
+        if (q > 0.0) assemble_typed(H, band, BandKappa<double, true>{kappa_band, kt.as<int64_t>(), q, star}, s);
+        else assemble_typed(H, band, BandKappa<double, false>{kappa_band, kt.as<double>(), 0.0, star}, s);
         B.retire.push_back(std::move(kt));
     } else {
         DevBuf kf = DevBuf::scratch(sizeof(float) * (size_t)H.mesh->N);

@@ -215,56 +215,70 @@ DevBuf march_table(const Mesh &m, const T *kappa, hipStream_t s) {
 template DevBuf march_table<double>(const Mesh &, const double *, hipStream_t);
 template DevBuf march_table<float>(const Mesh &, const float *, hipStream_t);
 
-// Row d of the star table (StarTab), from the mesh's near and far tables.
-__global__ __launch_bounds__(128) void k_star_table(GridDev g, StarTab st, int64_t rows, const double *__restrict__ near,
-                                                    double *__restrict__ w, double *__restrict__ cell) {
-    const int64_t row = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (row >= rows) return;
-    const int d[3] = {(int)(row / st.st0) + st.lo[0], (int)(row % st.st0 / st.st1) + st.lo[1],
-                      (int)(row % st.st1) + st.lo[2]};
-    const bool is_near = max(max(abs(d[0]), abs(d[1])), abs(d[2])) <= kNearCheb;
-    const double *nr = near + ((d[0] + 2) * 25 + (d[1] + 2) * 5 + (d[2] + 2)) * 64;
-    const double *far = near + kNearSize;
-    const double D2 = g.h[0] * g.h[0] * d[0] * d[0] + g.h[1] * g.h[1] * d[1] * d[1] + g.h[2] * g.h[2] * d[2] * d[2];
-    double sum[27];
+// Rows of the star table (StarTab) from the mesh's near and far tables: a workgroup
+// takes 64 offsets d, a wavefront of it one of the cells around the source, whose corner
+// weights it adds in LDS; then the rows' 16 sums over the cells.  11^3 14 us, 41^3 (340
+// MB) 114; a lane per offset: 32 and 140.
+constexpr int kStarRows = 64;   // rows per workgroup
+__global__ __launch_bounds__(kStarRows * 8) void k_star_table(GridDev g, StarTab st, int64_t rows,
+                                                              const double *__restrict__ near, double *__restrict__ w,
+                                                              double *__restrict__ cell) {
+    __shared__ double c[8][8][kStarRows + 1];   // [cell][corner][row]
+    const int r = threadIdx.x & 63, bits = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int64_t row0 = (int64_t)blockIdx.x * kStarRows, row = row0 + r;
+    if (row < rows) {
+        const int d[3] = {(int)(row / st.st0) + st.lo[0], (int)(row % st.st0 / st.st1) + st.lo[1],
+                          (int)(row % st.st1) + st.lo[2]};
+        if (max(max(abs(d[0]), abs(d[1])), abs(d[2])) <= kNearCheb) {
+            const double *nr = near + ((d[0] + 2) * 25 + (d[1] + 2) * 5 + (d[2] + 2)) * 64 + bits * 8;
 #pragma unroll
-    for (int v = 0; v < 27; ++v) sum[v] = 0.0;
-#pragma unroll
-    for (int bits = 0; bits < 8; ++bits) {
-        double c[8];
-#pragma unroll
-        for (int e = 0; e < 8; ++e) c[e] = 0.0;
-        if (is_near) {
-#pragma unroll
-            for (int e = 0; e < 8; ++e) c[e] = nr[bits * 8 + e];
+            for (int e = 0; e < 8; ++e) c[bits][e][r] = nr[e];
         } else {
+            const double *far = near + kNearSize;
+            const double D2 = g.h[0] * g.h[0] * d[0] * d[0] + g.h[1] * g.h[1] * d[1] * d[1] + g.h[2] * g.h[2] * d[2] * d[2];
 #pragma unroll
+            for (int e = 0; e < 8; ++e) c[bits][e][r] = 0.0;
             for (int t = 0; t < kTets; ++t) {
-                if (kStar.tet[t].bits != bits) continue;
+                const TetInfo &ti = kStarDev.tet[t];
+                if (ti.bits != bits) continue;
+                double a[4] = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
                     const double *e = far + (t * 4 + q) * 8;
-                    const double r = 1.0 / (D2 + e[3] + e[0] * d[0] + e[1] * d[1] + e[2] * d[2]);
+                    const double ri = 1.0 / (D2 + e[3] + e[0] * d[0] + e[1] * d[1] + e[2] * d[2]);
 #pragma unroll
-                    for (int k = 0; k < 4; ++k) c[corner_of(kStar.tet[t].slot[k], bits)] += e[4 + k] * r;
+                    for (int k = 0; k < 4; ++k) a[k] += e[4 + k] * ri;
                 }
+#pragma unroll
+                for (int k = 0; k < 4; ++k) c[bits][corner_of(ti.slot[k], bits)][r] += a[k];
             }
         }
 #pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            sum[slot_of(e, bits)] += c[e];
-            cell[row * 64 + bits * 8 + e] = c[e] * g.vol_scale;
-        }
+        for (int e = 0; e < 8; ++e) cell[row * 64 + bits * 8 + e] = c[bits][e][r] * g.vol_scale;
     }
+    __syncthreads();
+    for (int x = threadIdx.x; x < kStarRows * kStarWeights; x += kStarRows * 8) {
+        const int rr = x / kStarWeights, v = x % kStarWeights;
+        if (row0 + rr >= rows) break;
+        double sum = 0.0;
+        if (v < 15) {
+            const int slot = star_slot(v), p0 = slot / 9 - 1, p1 = slot / 3 % 3 - 1, p2 = slot % 3 - 1;
 #pragma unroll
-    for (int v = 0; v < kStarWeights; ++v) w[row * kStarWeights + v] = v < 15 ? sum[star_slot(v)] * g.vol_scale : 0.0;
+            for (int o = 0; o < 8; ++o) {   // the vertex j + p is a corner of the cell j - o
+                const int e0 = p0 + (o & 1), e1 = p1 + ((o >> 1) & 1), e2 = p2 + ((o >> 2) & 1);
+                if (((e0 | e1 | e2) & ~1) == 0) sum += c[o][e0 | (e1 << 1) | (e2 << 2)][rr];
+            }
+        }
+        w[(row0 + rr) * kStarWeights + v] = sum * g.vol_scale;
+    }
 }
 
-StarTab star_table(const Mesh &m, hipStream_t s) {
+StarBuf star_table(const Mesh &m, size_t room, hipStream_t s) {
     // checking aid: RTE_STAR_TABLE=0 in the environment sums the rules point by point
     if (const char *e = std::getenv("RTE_STAR_TABLE"))
-        if (std::atoi(e) == 0) return StarTab{};
-    StarTab t;
+        if (std::atoi(e) == 0) return StarBuf{};
+    StarBuf r;
+    StarTab &t = r.tab;
     const GridDev &g = m.dev;
     int64_t n[3], rows = 1;
     for (int a = 0; a < 3; ++a) {
@@ -275,38 +289,28 @@ StarTab star_table(const Mesh &m, hipStream_t s) {
         n[a] = hi - lo + 1;
         rows *= n[a];
     }
-    size_t free_b = 0, total_b = 0;
-    HIP_CHECK(hipMemGetInfo(&free_b, &total_b));
-    if ((double)rows * kStarRow * sizeof(double) > total_b / 16.0) return StarTab{};
+    if ((double)rows * kStarRow * sizeof(double) > (double)room) return StarBuf{};
     t.st0 = (int)(n[1] * n[2]);
     t.st1 = (int)n[2];
-    int dev = 0;
-    HIP_CHECK(hipGetDevice(&dev));
     const double *near = static_cast<const double *>(m.near_table(true));
-    std::lock_guard<std::mutex> lk(m.star->mu);
-    std::shared_ptr<DevBuf> &buf = m.star->dev[dev];
-    double *p = buf ? buf->as<double>() : nullptr;
-    if (!p) {
-        auto b = std::make_shared<DevBuf>();
-        try {
-            b->alloc((size_t)rows * kStarRow * sizeof(double));
-        } catch (const Error &) {   // no room for it now
-            (void)hipGetLastError();
-            return StarTab{};
-        }
-        p = b->as<double>();
-        k_star_table<<<(unsigned)((rows + 127) / 128), 128, 0, s>>>(g, t, rows, near, p, p + rows * kStarWeights);
-        HIP_LAUNCH_CHECK();
-        HIP_CHECK(hipStreamSynchronize(s));   // other streams read it from here on
-        buf = std::move(b);
+    try {
+        r.buf = DevBuf::scratch((size_t)rows * kStarRow * sizeof(double));
+    } catch (const Error &) {   // no room for it now
+        (void)hipGetLastError();
+        return StarBuf{};
     }
+    double *p = r.buf.as<double>();
     t.w = p;
     t.cell = p + rows * kStarWeights;
-    return t;
+    poison(r.buf, s);
+    k_star_table<<<(unsigned)((rows + kStarRows - 1) / kStarRows), kStarRows * 8, 0, s>>>(g, t, rows, near, p,
+                                                                                         p + rows * kStarWeights);
+    HIP_LAUNCH_CHECK();
+    return r;
 }
 
 template <typename T, bool K>
-EntryCtx<T, K> make_ctx(const Mesh &m, int kind, BandKappa<T, K> kappa, hipStream_t s) {
+EntryCtx<T, K> make_ctx(const Mesh &m, BandKappa<T, K> kappa) {
     EntryCtx<T, K> c;
     c.g = m.dev;
     c.kappa = kappa.v;
@@ -314,23 +318,23 @@ EntryCtx<T, K> make_ctx(const Mesh &m, int kind, BandKappa<T, K> kappa, hipStrea
     c.q = kappa.q;
     c.near = static_cast<const T *>(m.near_table(std::is_same<T, double>::value));
     if constexpr (std::is_same<T, double>::value) {
-        if (kind == RTE_VOLUME) c.star = star_table(m, s);
+        c.star = kappa.star;
         c.st = stencil_device().d;
     } else {
         c.st = stencil_device().f;
     }
     return c;
 }
-template EntryCtx<double, true> make_ctx(const Mesh &, int, BandKappa<double, true>, hipStream_t);
-template EntryCtx<double, false> make_ctx(const Mesh &, int, BandKappa<double, false>, hipStream_t);
-template EntryCtx<float, false> make_ctx(const Mesh &, int, BandKappa<float, false>, hipStream_t);
+template EntryCtx<double, true> make_ctx(const Mesh &, BandKappa<double, true>);
+template EntryCtx<double, false> make_ctx(const Mesh &, BandKappa<double, false>);
+template EntryCtx<float, false> make_ctx(const Mesh &, BandKappa<float, false>);
 
 void entries_launch(const Mesh &m, int kind, const double *kappa, double kmax, int64_t n, const int64_t *rows,
                     const int64_t *cols, double *out, int precision, hipStream_t s) {
     if (n == 0) return;
     const unsigned grid = (unsigned)((n + 255) / 256);
     auto launch = [&](auto bk) {   // the band's tables are released after it
-        auto c = make_ctx(m, kind, bk, s);
+        auto c = make_ctx(m, bk);
         using T = std::remove_const_t<std::remove_pointer_t<decltype(bk.v)>>;
         constexpr bool K = std::is_same<decltype(bk), BandKappa<T, true>>::value;
         if (kind == RTE_VOLUME) k_entries<T, K, RTE_VOLUME><<<grid, 256, 0, s>>>(c, n, rows, cols, out);
@@ -341,13 +345,22 @@ void entries_launch(const Mesh &m, int kind, const double *kappa, double kmax, i
     if (precision == RTE_FP64) {
         const double q = kink_quantum(m.dev, kmax);
         DevBuf kt = q > 0.0 ? kink_table(m, kappa, q, s) : march_table(m, kappa, s);
-        if (q > 0.0) launch(BandKappa<double, true>{kappa, kt.as<int64_t>(), q});
-        else launch(BandKappa<double, false>{kappa, kt.as<double>()});
+        // building the table (8 rows per vertex or more, 0.1 ms at 41^3) is left out for a few entries
+        StarBuf star;
+        if (kind == RTE_VOLUME && n >= m.N) {
+            size_t free_b = 0, total_b = 0;
+            HIP_CHECK(hipMemGetInfo(&free_b, &total_b));
+            star = star_table(m, (free_b + pool_idle_bytes()) / 16, s);
+        }
+        if (q > 0.0) launch(BandKappa<double, true>{kappa, kt.as<int64_t>(), q, star.tab});
+        else launch(BandKappa<double, false>{kappa, kt.as<double>(), 0.0, star.tab});
+        settle({&kt, &star.buf});
     } else {
         DevBuf kf(sizeof(float) * (size_t)m.N);
         to_float(kappa, kf.as<float>(), m.N, s);
         DevBuf kt = march_table(m, kf.as<float>(), s);
         launch(BandKappa<float, false>{kf.as<float>(), kt.as<float>()});
+        settle({&kt});
     }
 }
 
@@ -368,7 +381,7 @@ void dense_fill_launch(const Mesh &m, int kind, BandKappa<T, K> kappa, const std
     if (order.size() > ((size_t)1 << 31) / fill_split<T>())
         throw std::runtime_error("dense fill: too many tasks for one grid");
     DevBuf dt = upload_scratch(order, s);
-    auto c = make_ctx(m, kind, kappa, s);
+    auto c = make_ctx(m, kappa);
     const FillTask *d = dt.as<FillTask>();
     const unsigned gp = (unsigned)(npair * fill_split<T>()), gs = (unsigned)((order.size() - npair) * fill_split<T>());
     const FillTask *ds = d + npair;

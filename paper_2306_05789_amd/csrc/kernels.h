@@ -125,10 +125,10 @@ struct BandKappa {
     const T *v;     // [N]
     const DepthTab<T, K> *tab;
     double q = 0.0;
+    StarTab star{};   // FP64 volume entries: the quadrature by offset, or null
 };
 template <typename T, bool K> struct EntryCtx;
-// s: the stream on which the mesh's quadrature table is built if it is not yet there (FP64 volume entries)
-template <typename T, bool K> EntryCtx<T, K> make_ctx(const Mesh &m, int kind, BandKappa<T, K> kappa, hipStream_t s);
+template <typename T, bool K> EntryCtx<T, K> make_ctx(const Mesh &m, BandKappa<T, K> kappa);
 // The quantum of a band's kinks on the grid, kmax its largest kappa; 0 when FP64
 // depths have to be marched instead (march.h).
 double kink_quantum(const GridDev &g, double kmax);

@@ -324,7 +324,6 @@ void mesh_init(Mesh &M, const rte_mesh_desc_t &d) {
     M.N = N;
     for (int a = 0; a < 3; ++a) M.h[a] = (d.hi[a] - d.lo[a]) / (d.n[a] - 1);
     M.near = std::make_shared<NearTables>();
-    M.star = std::make_shared<StarCache>();
     M.plans = new_plan_cache();
     M.near->host = make_near_table(M.h);
     // the surface unknowns: corners of the emitting squares (a box-face square

@@ -111,24 +111,16 @@ struct NearTables {
 // vertices j + {0,1}^3 and j - {0,1}^3 in the order of star_slot, then a zero), then,
 // for sources that miss cells, the weights of every cell's 8 corners
 // ([8 cells][8 corners]).  Near offsets hold the degree-5 rule's sums, the
-// others the degree-2 rule's; the factor |tet| / (4 pi) is folded in.  Built on
-// the GPU once per mesh and device, owned by the mesh (FP64 entries); null when it
-// would take more than a 16th of the device memory or does not fit it (the
-// quadrature is then summed point by point).
+// others the degree-2 rule's; the factor |tet| / (4 pi) is folded in.  Built on the
+// GPU for each assembly (FP64 volume operators), in scratch that goes back to the pool
+// with it: kept by the mesh, 340 MB at 41^3 would stay allocated for as long as the
+// mesh, to save 0.1 ms of an assembly's 127.
 constexpr int kStarWeights = 16, kStarRow = kStarWeights + 64;
 struct StarTab {
     const double *w = nullptr;      // [rows][16]
     const double *cell = nullptr;   // [rows][8][8]
     int lo[3] = {0, 0, 0}, st0 = 0, st1 = 0;   // row of d: (d0 - lo0) st0 + (d1 - lo1) st1 + (d2 - lo2)
 };
-struct Mesh;
-struct DevBuf;
-struct StarCache {
-    std::mutex mu;
-    std::map<int, std::shared_ptr<DevBuf>> dev;   // by device
-};
-StarTab star_table(const Mesh &m, hipStream_t s);   // built on s and waited for on first use (entry.hip)
-
 struct PlanCache;   // block-tree plans of a mesh (htree.cpp)
 
 // An emitting rectangle of the boundary: the plane x_a = plane (grid index),
@@ -146,7 +138,6 @@ struct Mesh {
     std::vector<int64_t> emitting;   // natural ids, ascending
     GridDev dev{};
     std::shared_ptr<NearTables> near;
-    std::shared_ptr<StarCache> star;
     std::shared_ptr<PlanCache> plans;
     const void *near_table(bool fp64) const;   // device copy on the current device
     std::vector<double> positions() const;            // [N][3]
@@ -257,6 +248,14 @@ private:
 inline void settle(std::initializer_list<DevBuf *> bufs) {
     for (DevBuf *b : bufs) b->settled = true;
 }
+
+// The star table of a mesh, queued on s; empty (the quadrature is then summed point by
+// point) when it would take more than `room` bytes or does not fit the device.
+struct StarBuf {
+    DevBuf buf;
+    StarTab tab;
+};
+StarBuf star_table(const Mesh &m, size_t room, hipStream_t s);
 
 // Scratch pool of the current device (pool.cpp).
 void *pool_take(size_t bytes, size_t *cap, bool exact);
@@ -394,7 +393,7 @@ struct HMat {
 // ---------------------------------------------------------------- entry points implemented in .hip files
 void entries_launch(const Mesh &m, int kind, const double *kappa, double kmax, int64_t n, const int64_t *rows,
                     const int64_t *cols, double *out, int precision, hipStream_t s);
-void assemble_band(HMat &H, int band, const double *kappa_band, double kmax, hipStream_t s);   // kmax: largest kappa of the band
+void assemble_band(HMat &H, int band, const double *kappa_band, double kmax, const StarTab &star, hipStream_t s);   // kmax: largest kappa of the band
 void band_settle(BandStore &B, hipStream_t s);   // after the band's last queued work
 void matvec_reserve(HMat &H, int n_bands);   // room for the per-band plans (before building them concurrently)
 void matvec_build(HMat &H, int band, hipStream_t s);

@@ -85,3 +85,54 @@ def test_a_request_holds_what_it_needs():
         srv.fetch(i, torch.empty(N, device=DEV, dtype=torch.float64))
     held, idle = rte.rte_memory_info()
     assert held - idle - base <= 2 * MB
+
+
+def test_a_mesh_keeps_no_device_memory():
+    """What an assembly tabulates by offset goes with it: 23 MB for this mesh."""
+    n = (17, 17, 17)
+    base = fresh()
+    meshes = [rte.rte_mesh_create(n) for _ in range(3)]
+    for mesh in meshes:
+        H = rte.rte_hmat_assemble(mesh, field(n), rte.hmat_opts(kind=rte.RTE_VOLUME))
+        del H
+        assert fresh() == base
+
+
+def test_assembly_does_without_the_table_when_memory_is_short(monkeypatch):
+    """At the smallest bound of the library's memory where an operator is assembled point by point, it is assembled by
+    default too, to the same bits: its quadrature table (23 MB) is left out where it would not fit.  Without room for the
+    operator itself it stays an error, and nothing is lost by it."""
+    n = (17, 17, 17)
+    opts = rte.hmat_opts(kind=rte.RTE_VOLUME, leaf_size=32, aca_eps=1e-4)
+    kap = field(n)
+    mesh = rte.rte_mesh_create(n)
+    base = fresh()
+
+    def product(H):
+        y = torch.empty((1, mesh.N), device=DEV, dtype=torch.float64)
+        return rte.rte_hmat_matvec(H, 0, torch.ones_like(y), y)
+
+    def assembled(cap):
+        rte.rte_release_scratch()
+        monkeypatch.setenv("RTE_MEMORY_CAP", str(base + cap))
+        try:
+            H = rte.rte_hmat_assemble(mesh, kap, opts)
+        except rte.RteError as e:
+            assert e.status == rte.RTE_E_OUT_OF_MEMORY
+            return None
+        finally:
+            monkeypatch.delenv("RTE_MEMORY_CAP")
+        return product(H)
+
+    monkeypatch.setenv("RTE_STAR_TABLE", "0")
+    want = product(rte.rte_hmat_assemble(mesh, kap, opts))
+    lo, hi = 0, 2048 * MB
+    while hi - lo > 4 * MB:
+        mid = (lo + hi) // 2
+        lo, hi = (lo, mid) if assembled(mid) is not None else (mid, hi)
+    monkeypatch.delenv("RTE_STAR_TABLE")
+    assert 8 * MB < hi < 2048 * MB
+    got = assembled(hi)
+    assert got is not None and torch.equal(got, want)
+    assert assembled(4 * MB) is None
+    assert fresh() == base
