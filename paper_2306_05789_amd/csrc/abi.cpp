@@ -181,11 +181,11 @@ namespace rte {
 
 // Assembly of one H-matrix per band on a validated plan and kappa (device,
 // [n_bands][N], natural order, kmax the bands' largest values); see rte_hmat_assemble.
-// lean: without the memory that an assembly can do without; held says afterwards (also
-// when this throws) whether some was taken.
+// x says afterwards (also when this throws) whether memory that an assembly can do
+// without was taken.
 static std::unique_ptr<rte_hmat> assemble_once(const Mesh &m, std::shared_ptr<const Plan> plan,
                                                const rte_hmat_opts_t &o, int n_bands, const double *kappa,
-                                               const std::vector<double> &kmax, hipStream_t s, bool lean, bool &held) {
+                                               const std::vector<double> &kmax, hipStream_t s, AssemblyExtras &x) {
     const auto t0 = std::chrono::steady_clock::now();
     const double alloc0 = alloc_ms_this_thread();
     double alloc_other = 0.0;   // allocation time of the second band thread
@@ -253,9 +253,8 @@ static std::unique_ptr<rte_hmat> assemble_once(const Mesh &m, std::shared_ptr<co
     double wsum = 0, wr = 0;
     int maxr = 0;
     matvec_reserve(H, n_bands);   // the bands' plans are then built from two threads
-    StarBuf star;
-    if (H.kind == RTE_VOLUME && H.precision == RTE_FP64 && !lean) star = star_table(m, free_at_start / 16, s);
-    held = star.tab.w != nullptr;
+    if (H.kind == RTE_VOLUME && H.precision == RTE_FP64 && !x.lean) x.star = star_table(m, free_at_start / 16, s);
+    if (x.star.tab.w) x.held = true;
     // Bands are independent: with more than one, a second host thread on its
     // own stream takes every other band as it comes free, so one band's ACA
     // tail and host work overlap the other's kernels.
@@ -263,7 +262,7 @@ static std::unique_ptr<rte_hmat> assemble_once(const Mesh &m, std::shared_ptr<co
         std::atomic<int> next{0};
         auto run = [&](hipStream_t st) {
             for (int b; (b = next.fetch_add(1)) < n_bands;) {
-                assemble_band(H, b, kappa + (int64_t)b * m.N, kmax[b], star.tab, st);
+                assemble_band(H, b, kappa + (int64_t)b * m.N, kmax[b], x, st);
                 matvec_build(H, b, st);   // host work while the band's last kernels run
                 band_settle(H.bands[b], st);
             }
@@ -332,7 +331,7 @@ static std::unique_ptr<rte_hmat> assemble_once(const Mesh &m, std::shared_ptr<co
     }
     matvec_build_all(H, s);
     HIP_CHECK(hipStreamSynchronize(s));
-    settle({&star.buf});
+    settle({&x.star.buf});
     rte_hmat_stats_t &st = H.stats;
     st.n_tgt = (int64_t)P.tgt_nat.size();
     st.n_src = (int64_t)P.src_nat.size();
@@ -368,15 +367,19 @@ static std::unique_ptr<rte_hmat> assemble_once(const Mesh &m, std::shared_ptr<co
 std::unique_ptr<rte_hmat> assemble_hmat(const Mesh &m, std::shared_ptr<const Plan> plan,
                                         const rte_hmat_opts_t &o, int n_bands, const double *kappa,
                                         const std::vector<double> &kmax, hipStream_t s) {
-    bool held = false;
-    try {
-        return assemble_once(m, plan, o, n_bands, kappa, kmax, s, false, held);
-    } catch (const Error &e) {
-        if (e.code != RTE_E_OUT_OF_MEMORY || !held) throw;
+    {
+        AssemblyExtras x;
+        try {
+            return assemble_once(m, plan, o, n_bands, kappa, kmax, s, x);
+        } catch (const Error &e) {
+            if (e.code != RTE_E_OUT_OF_MEMORY || !x.held) throw;
+        }
     }
     // what was held may be what is missing
     (void)hipGetLastError();
-    return assemble_once(m, plan, o, n_bands, kappa, kmax, s, true, held);
+    AssemblyExtras x;
+    x.lean = true;
+    return assemble_once(m, plan, o, n_bands, kappa, kmax, s, x);
 }
 
 }  // namespace rte

@@ -821,11 +821,18 @@ void fill_dense_blocks(HMat &H, BandStore &B, BandKappa<T, K> kap, const std::ve
     if (split) B.bufs.push_back(std::move(lo));
 }
 
-// What the first pass leaves to the second, by block.
+// What the first pass leaves to the second, by block: at most `room` bytes in all; a
+// block beyond them starts again.  A batch's buffers are retired with their last block.
 template <typename T>
 struct AcaCarry {
-    std::vector<DevBuf> bufs;
-    std::map<size_t, AcaCarryRec<T>> at;
+    struct Group {
+        DevBuf reals, ints;
+        int left = 0;
+    };
+    std::vector<Group> groups;
+    std::map<size_t, std::pair<AcaCarryRec<T>, size_t>> at;   // record, group
+    size_t room = 0;
+    std::atomic<bool> *held = nullptr;
 };
 
 // One batch of blocks through the step-synchronous ACA.  A block that stops
@@ -938,10 +945,19 @@ void aca_batch(HMat &H, BandStore &B, BandKappa<T, K> kap, const std::vector<Aca
         for (int t = 0; t < nb; ++t) {
             auto it = carry.at.find(ids[t]);
             if (it == carry.at.end()) continue;
-            it->second.slot = t;
-            recs.push_back(it->second);
+            it->second.first.slot = t;
+            recs.push_back(it->second.first);
         }
         move_carry(recs, std::false_type());
+        for (int t = 0; t < nb; ++t) {
+            auto it = carry.at.find(ids[t]);
+            if (it == carry.at.end()) continue;
+            auto &g = carry.groups[it->second.second];
+            carry.at.erase(it);
+            if (--g.left > 0) continue;
+            B.retire.push_back(std::move(g.reals));
+            B.retire.push_back(std::move(g.ints));
+        }
     }
     // The active lists are rebuilt every kCompact steps (one host read of the
     // totals); in between, every step reuses them and the kernels skip the
@@ -1061,23 +1077,37 @@ void aca_batch(HMat &H, BandStore &B, BandKappa<T, K> kap, const std::vector<Aca
     {
         std::vector<AcaCarryRec<T>> recs;
         int64_t nreal = 0, nint = 0;
-        for (int t = 0; t < nb; ++t)
-            if (again(t)) {
-                nreal += 1 + (int64_t)tasks[t].kcap * (tasks[t].m + tasks[t].n);
-                nint += 3 + (tasks[t].m + 31) / 32;
+        for (int t = 0; t < nb; ++t) {
+            if (!again(t)) continue;
+            const int64_t re = 1 + (int64_t)tasks[t].kcap * (tasks[t].m + tasks[t].n), in = 3 + (tasks[t].m + 31) / 32;
+            if ((size_t)(nreal + re) * sizeof(T) + (size_t)(nint + in) * sizeof(int) > carry.room) continue;
+            recs.push_back({nullptr, nullptr, t, tasks[t].kcap});
+            nreal += re;
+            nint += in;
+        }
+        typename AcaCarry<T>::Group g;
+        try {
+            g.reals = DevBuf::scratch(sizeof(T) * (size_t)nreal);
+            g.ints = DevBuf::scratch(sizeof(int) * (size_t)nint);
+        } catch (const Error &) {   // no room for it now: these blocks start again
+            (void)hipGetLastError();
+            recs.clear();
+        }
+        if (!recs.empty()) {
+            *carry.held = true;
+            carry.room -= sizeof(T) * (size_t)nreal + sizeof(int) * (size_t)nint;
+            T *re = g.reals.template as<T>();
+            int *in = g.ints.template as<int>();
+            for (AcaCarryRec<T> &r : recs) {
+                const AcaTask &tk = tasks[r.slot];
+                r.reals = re;
+                r.ints = in;
+                re += 1 + (int64_t)tk.kcap * (tk.m + tk.n);
+                in += 3 + (tk.m + 31) / 32;
+                carry.at[ids[r.slot]] = {r, carry.groups.size()};
             }
-        if (nreal > 0) {
-            DevBuf reals_c = DevBuf::scratch(sizeof(T) * (size_t)nreal), ints_c = DevBuf::scratch(sizeof(int) * (size_t)nint);
-            nreal = nint = 0;
-            for (int t = 0; t < nb; ++t)
-                if (again(t)) {
-                    recs.push_back({reals_c.as<T>() + nreal, ints_c.as<int>() + nint, t, tasks[t].kcap});
-                    carry.at[ids[t]] = recs.back();
-                    nreal += 1 + (int64_t)tasks[t].kcap * (tasks[t].m + tasks[t].n);
-                    nint += 3 + (tasks[t].m + 31) / 32;
-                }
-            carry.bufs.push_back(std::move(reals_c));
-            carry.bufs.push_back(std::move(ints_c));
+            g.left = (int)recs.size();
+            carry.groups.push_back(std::move(g));
             move_carry(recs, std::true_type());
         }
     }
@@ -1154,7 +1184,7 @@ void aca_batch(HMat &H, BandStore &B, BandKappa<T, K> kap, const std::vector<Aca
 }
 
 template <typename T, bool K>
-void run_aca(HMat &H, BandStore &B, BandKappa<T, K> kap, hipStream_t s) {
+void run_aca(HMat &H, BandStore &B, BandKappa<T, K> kap, AssemblyExtras &x, hipStream_t s) {
     const Plan &P = *H.plan;
     const size_t nlr = P.lowrank.size();
     B.rank.assign(nlr, -1);
@@ -1184,7 +1214,12 @@ void run_aca(HMat &H, BandStore &B, BandKappa<T, K> kap, hipStream_t s) {
     if (const char *e = std::getenv("RTE_ACA_FIRST_CAP"))
         first_cap = std::min<int64_t>(kAcaMaxRank, std::max<int64_t>(1, std::atoll(e)));
     std::vector<size_t> todo(nlr), retry;
+    // Kept for the second pass: within a quarter of a batch's scratch.  Checking aid:
+    // RTE_ACA_CARRY in the environment is that bound in bytes.
     AcaCarry<T> carry;
+    carry.room = x.lean ? 0 : scratch_limit / 4;
+    if (const char *e = std::getenv("RTE_ACA_CARRY")) carry.room = std::min<size_t>(carry.room, std::strtoull(e, nullptr, 10));
+    carry.held = &x.held;
     for (size_t b = 0; b < nlr; ++b) todo[b] = b;
     for (int pass = 0; pass < 2 && !todo.empty(); ++pass) {
         const int64_t cap = pass == 0 ? first_cap : kAcaRetryRank;
@@ -1216,21 +1251,21 @@ void run_aca(HMat &H, BandStore &B, BandKappa<T, K> kap, hipStream_t s) {
         todo.swap(retry);
         retry.clear();
     }
-    for (DevBuf &d : carry.bufs) B.retire.push_back(std::move(d));   // the second pass has been queued
+    RTE_REQUIRE(carry.at.empty(), "ACA: blocks kept for a second pass were not taken up");
     for (size_t b : todo) fallback.push_back(P.lowrank[b]);
     fill_dense_blocks(H, B, kap, fallback, false, s);
 }
 
 template <typename T, bool K>
-void assemble_typed(HMat &H, int band, BandKappa<T, K> kap, hipStream_t s) {
+void assemble_typed(HMat &H, int band, BandKappa<T, K> kap, AssemblyExtras &x, hipStream_t s) {
     BandStore &B = H.bands[band];
     fill_dense_blocks(H, B, kap, H.plan->dense, H.kind == RTE_VOLUME, s);
-    run_aca(H, B, kap, s);
+    run_aca(H, B, kap, x, s);
 }
 
 }  // namespace
 
-void assemble_band(HMat &H, int band, const double *kappa_band, double kmax, const StarTab &star, hipStream_t s) {
+void assemble_band(HMat &H, int band, const double *kappa_band, double kmax, AssemblyExtras &x, hipStream_t s) {
     // the band's kappa buffers go to B.retire only after every launch reading
     // them is queued (band_settle, which an ACA batch may call, releases what
     // B.retire holds)
@@ -1238,14 +1273,14 @@ void assemble_band(HMat &H, int band, const double *kappa_band, double kmax, con
     if (H.precision == RTE_FP64) {
         const double q = kink_quantum(H.mesh->dev, kmax);
         DevBuf kt = q > 0.0 ? kink_table(*H.mesh, kappa_band, q, s) : march_table(*H.mesh, kappa_band, s);
-        if (q > 0.0) assemble_typed(H, band, BandKappa<double, true>{kappa_band, kt.as<int64_t>(), q, star}, s);
-        else assemble_typed(H, band, BandKappa<double, false>{kappa_band, kt.as<double>(), 0.0, star}, s);
+        if (q > 0.0) assemble_typed(H, band, BandKappa<double, true>{kappa_band, kt.as<int64_t>(), q, x.star.tab}, x, s);
+        else assemble_typed(H, band, BandKappa<double, false>{kappa_band, kt.as<double>(), 0.0, x.star.tab}, x, s);
         B.retire.push_back(std::move(kt));
     } else {
         DevBuf kf = DevBuf::scratch(sizeof(float) * (size_t)H.mesh->N);
         to_float(kappa_band, kf.as<float>(), H.mesh->N, s);
         DevBuf kt = march_table(*H.mesh, kf.as<float>(), s);
-        assemble_typed(H, band, BandKappa<float, false>{kf.as<float>(), kt.as<float>()}, s);
+        assemble_typed(H, band, BandKappa<float, false>{kf.as<float>(), kt.as<float>()}, x, s);
         B.retire.push_back(std::move(kf));
         B.retire.push_back(std::move(kt));
     }

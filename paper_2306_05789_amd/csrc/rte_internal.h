@@ -3,6 +3,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <atomic>
 #include <cstdint>
 #include <cstdlib>
 #include <initializer_list>
@@ -257,6 +258,15 @@ struct StarBuf {
 };
 StarBuf star_table(const Mesh &m, size_t room, hipStream_t s);
 
+// The memory that an assembly can do without: its star table, and what blocks that
+// reach the first rank cap keep for the second pass.  lean: an earlier attempt ran out
+// of memory while it held some of it (held), and this one does without.
+struct AssemblyExtras {
+    bool lean = false;
+    std::atomic<bool> held{false};   // the bands are assembled by two threads
+    StarBuf star;
+};
+
 // Scratch pool of the current device (pool.cpp).
 void *pool_take(size_t bytes, size_t *cap, bool exact);
 void pool_give(void *p, size_t cap);
@@ -393,7 +403,8 @@ struct HMat {
 // ---------------------------------------------------------------- entry points implemented in .hip files
 void entries_launch(const Mesh &m, int kind, const double *kappa, double kmax, int64_t n, const int64_t *rows,
                     const int64_t *cols, double *out, int precision, hipStream_t s);
-void assemble_band(HMat &H, int band, const double *kappa_band, double kmax, const StarTab &star, hipStream_t s);   // kmax: largest kappa of the band
+// kmax: largest kappa of the band
+void assemble_band(HMat &H, int band, const double *kappa_band, double kmax, AssemblyExtras &x, hipStream_t s);
 void band_settle(BandStore &B, hipStream_t s);   // after the band's last queued work
 void matvec_reserve(HMat &H, int n_bands);   // room for the per-band plans (before building them concurrently)
 void matvec_build(HMat &H, int band, hipStream_t s);

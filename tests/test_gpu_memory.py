@@ -136,3 +136,51 @@ def test_assembly_does_without_the_table_when_memory_is_short(monkeypatch):
     assert got is not None and torch.equal(got, want)
     assert assembled(4 * MB) is None
     assert fresh() == base
+
+
+@pytest.mark.parametrize("precision", [rte.RTE_FP64, rte.RTE_FP32], ids=["fp64", "fp32"])
+def test_second_pass_keeps_what_its_bound_allows(monkeypatch, precision):
+    """Blocks that reach the first rank cap go on from where they stopped, or start again where their factors would be
+    more than the bound: the same operator with all, some and none of them kept.  Where memory is just enough for an
+    assembly that keeps none, one that would keep all of them still succeeds."""
+    import numpy as np
+    n = (15, 14, 13)
+    opts = rte.hmat_opts(kind=rte.RTE_VOLUME, leaf_size=24, aca_eps=1e-7, precision=precision)
+    kap = field(n)
+    mesh = rte.rte_mesh_create(n, emit_faces=inputs.FACE_X_LO, walls=[(2, 0, 0.5)])
+    monkeypatch.setenv("RTE_ACA_FIRST_CAP", "16")
+    monkeypatch.setenv("RTE_STAR_TABLE", "0")
+    base = fresh()
+
+    def assembled(keep, cap=None):
+        rte.rte_release_scratch()
+        monkeypatch.setenv("RTE_ACA_CARRY", str(keep))
+        if cap is not None:
+            monkeypatch.setenv("RTE_MEMORY_CAP", str(base + cap))
+        try:
+            H = rte.rte_hmat_assemble(mesh, kap, opts)
+        except rte.RteError as e:
+            assert e.status == rte.RTE_E_OUT_OF_MEMORY
+            return None
+        finally:
+            monkeypatch.delenv("RTE_MEMORY_CAP", raising=False)
+        st = rte.rte_hmat_stats(H)
+        return st["aca_retried"], st["aca_entries"], [rte.rte_hmat_block_factors(H, 0, b) for b in range(st["n_lowrank"])]
+
+    everything = 1 << 40
+    retried, all_entries, kept = assembled(everything)
+    assert retried > 20
+    entries = [all_entries]
+    for keep in (32 << 10, 0):
+        r, e, got = assembled(keep)
+        assert r == retried
+        entries.append(e)
+        for (ka, ua, va), (kb, ub, vb) in zip(kept, got):
+            assert ka == kb and (ka <= 0 or (np.array_equal(ua, ub) and np.array_equal(va, vb)))
+    assert entries[0] < entries[1] < entries[2]   # a block that starts again evaluates its rows again
+    lo, hi = 0, 2048 * MB
+    while hi - lo > 2 * MB:
+        mid = (lo + hi) // 2
+        lo, hi = (lo, mid) if assembled(0, mid) is not None else (mid, hi)
+    assert assembled(everything, hi) is not None
+    assert fresh() == base
