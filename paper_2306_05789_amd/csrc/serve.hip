@@ -69,7 +69,10 @@ struct SrvCol {
 // forms all their operands before the groups' products and one takes all results
 // after them, instead of two per group, each 3 us long on a small mesh (4 bands of
 // 15^3: a request mix 2.50 -> 2.29 ms).  Above it a launch is long enough by itself.
+// At most kSrvPartCols columns (or one group): they are the launches' y dimension, whose
+// limit is 65535.
 constexpr int64_t kSrvPart = (int64_t)32 << 20;
+constexpr int64_t kSrvPartCols = 32768;
 
 // x[c] = S = (1 - a) B_nu(T) + a J (minus S_m on inner sweeps); a defect step
 // keeps S in S_m
@@ -664,17 +667,18 @@ struct Server {
                 }
             }
         }
-        // parts: groups [pgrp[p], pgrp[p + 1]) of at most kSrvPart of operands (or one
-        // group), their columns' x and y side by side
+        // parts: groups [pgrp[p], pgrp[p + 1]) of at most kSrvPart of operands and
+        // kSrvPartCols columns (or one group), their columns' x and y side by side
         std::vector<size_t> pgrp{0};
-        int64_t room = 0, used = 0;
+        int64_t room = 0, used = 0, pcols = 0;
         for (size_t gi = 0; gi < groups.size(); ++gi) {
-            const int64_t n = (int64_t)groups[gi].cols.size() * groups[gi].cols[0].N;
-            if (used > 0 && (used + n) * (int64_t)sizeof(double) > kSrvPart) {
+            const int64_t nc = (int64_t)groups[gi].cols.size(), n = nc * groups[gi].cols[0].N;
+            if (used > 0 && ((used + n) * (int64_t)sizeof(double) > kSrvPart || pcols + nc > kSrvPartCols)) {
                 pgrp.push_back(gi);
-                used = 0;
+                used = pcols = 0;
             }
             used += n;
+            pcols += nc;
             room = std::max(room, used);
         }
         pgrp.push_back(groups.size());
