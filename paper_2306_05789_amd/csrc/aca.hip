@@ -70,6 +70,7 @@ constexpr int kChunk = 1024;
 // than 8 lanes per entry while a quarter of that holds them.
 constexpr int kWideMin = 8, kWideMax = 32;
 constexpr int64_t kWideLanes = (int64_t)1 << 18;
+enum : int { kWideNever = 0, kWideMust = 2 };   // RTE_ACA_WIDE
 // Active blocks from which k_aca_pivot and k_aca_finish give a block one wavefront
 // instead of a workgroup: a batch starts with thousands of blocks of a hundred
 // columns, of which four wavefronts read one pass and then wait at two barriers
@@ -841,7 +842,7 @@ struct AcaCarry {
 template <typename T, bool K>
 void aca_batch(HMat &H, BandStore &B, BandKappa<T, K> kap, const std::vector<AcaTask> &tasks, const std::vector<size_t> &ids,
                int64_t uo, int64_t vo, std::vector<Block> &fallback, std::vector<size_t> &retry, AcaCarry<T> &carry,
-               hipStream_t s) {
+               int wide, bool &wide_seen, hipStream_t s) {
     {   // an earlier batch's scratch is freed first (a fill's task list may stay queued)
         size_t pending = 0;
         for (const DevBuf &d : B.retire) pending += d.bytes;
@@ -964,9 +965,6 @@ void aca_batch(HMat &H, BandStore &B, BandKappa<T, K> kap, const std::vector<Aca
     // blocks that have stopped, so a step costs five launches and no host
     // synchronisation.
     constexpr int kCompact = 8;
-    // checking aid: RTE_ACA_WIDE=0 in the environment keeps every launch at one lane per entry
-    const char *wide_env = std::getenv("RTE_ACA_WIDE");
-    const bool wide_on = !wide_env || std::atoi(wide_env) != 0;
     int64_t ht[5];
     for (int step = 0; step <= max_steps;) {
         k_aca_scan<T, false><<<1, 1024, 0, s>>>(st);
@@ -986,9 +984,10 @@ void aca_batch(HMat &H, BandStore &B, BandKappa<T, K> kap, const std::vector<Aca
             int P = kWideMin;
             while (P < kWideMax && P < parts) P <<= 1;
             while (P > kWideMin && n * P > kWideLanes / 4) P >>= 1;
-            return wide_on && n * P <= kWideLanes ? P : 1;
+            return wide != kWideNever && n * P <= kWideLanes ? P : 1;
         };
         const int Pr = lanes(nrow), Pc = lanes(ncol);
+        wide_seen = wide_seen || Pr > 1 || Pc > 1;
         auto lds = [parts](int P) { return (unsigned)(256 / P * parts * sizeof(GroupTask<T, K>)); };
         const int64_t wr = (nrow * Pr + 255) / 256, wc = (ncol * Pc + 255) / 256;
         const int split = (int)std::max<int64_t>(1, std::min<int64_t>(16, kDotsFill / std::max<int64_t>(nchunk, 1)));
@@ -1000,13 +999,22 @@ void aca_batch(HMat &H, BandStore &B, BandKappa<T, K> kap, const std::vector<Aca
         // the entry launches, compiled for the operator's kind and the mesh's wall mode (no wall, one, several)
         auto entries = [&](auto kind, auto nw) {
             constexpr int KIND = decltype(kind)::value, NW = decltype(nw)::value;
+            constexpr bool W = K || NW != kNoWall;   // else nothing to share (lanes)
             auto rows = [=]() {
-                if (Pr > 1) k_aca_wide<T, K, KIND, NW, false><<<(unsigned)wr, 256, lds(Pr), s>>>(c, st, nrow, Pr, tn, sn);
-                else k_aca_rows<T, K, KIND, NW><<<(unsigned)wr, 256, 0, s>>>(c, st, nrow, tn, sn);
+                if constexpr (W)
+                    if (Pr > 1) {
+                        k_aca_wide<T, K, KIND, NW, false><<<(unsigned)wr, 256, lds(Pr), s>>>(c, st, nrow, Pr, tn, sn);
+                        return;
+                    }
+                k_aca_rows<T, K, KIND, NW><<<(unsigned)wr, 256, 0, s>>>(c, st, nrow, tn, sn);
             };
             auto cols = [=]() {
-                if (Pc > 1) k_aca_wide<T, K, KIND, NW, true><<<(unsigned)wc, 256, lds(Pc), s>>>(c, st, ncol, Pc, tn, sn);
-                else k_aca_cols<T, K, KIND, NW><<<(unsigned)wc, 256, 0, s>>>(c, st, ncol, tn, sn);
+                if constexpr (W)
+                    if (Pc > 1) {
+                        k_aca_wide<T, K, KIND, NW, true><<<(unsigned)wc, 256, lds(Pc), s>>>(c, st, ncol, Pc, tn, sn);
+                        return;
+                    }
+                k_aca_cols<T, K, KIND, NW><<<(unsigned)wc, 256, 0, s>>>(c, st, ncol, tn, sn);
             };
             launch_rows = rows;
             launch_cols = cols;
@@ -1213,6 +1221,11 @@ void run_aca(HMat &H, BandStore &B, BandKappa<T, K> kap, AssemblyExtras &x, hipS
     int64_t first_cap = kAcaMaxRank;
     if (const char *e = std::getenv("RTE_ACA_FIRST_CAP"))
         first_cap = std::min<int64_t>(kAcaMaxRank, std::max<int64_t>(1, std::atoll(e)));
+    // Checking aid: RTE_ACA_WIDE in the environment, 0: every launch at one lane per entry;
+    // 2: an assembly without a launch of several lanes is an error.
+    const char *we = std::getenv("RTE_ACA_WIDE");
+    const int wide = we ? std::atoi(we) : 1;
+    bool wide_seen = false;
     std::vector<size_t> todo(nlr), retry;
     // Kept for the second pass: within a quarter of a batch's scratch.  Checking aid:
     // RTE_ACA_CARRY in the environment is that bound in bytes.
@@ -1237,7 +1250,7 @@ void run_aca(HMat &H, BandStore &B, BandKappa<T, K> kap, AssemblyExtras &x, hipS
             }
             const int64_t need = (int64_t)kcap * (m + n);
             if (!tasks.empty() && (size_t)(uo + vo + need) * sizeof(T) > scratch_limit) {
-                aca_batch(H, B, kap, tasks, ids, uo, vo, fallback, retry, carry, s);
+                aca_batch(H, B, kap, tasks, ids, uo, vo, fallback, retry, carry, wide, wide_seen, s);
                 tasks.clear();
                 ids.clear();
                 uo = vo = 0;
@@ -1247,10 +1260,11 @@ void run_aca(HMat &H, BandStore &B, BandKappa<T, K> kap, AssemblyExtras &x, hipS
             uo += (int64_t)kcap * m;
             vo += (int64_t)kcap * n;
         }
-        if (!tasks.empty()) aca_batch(H, B, kap, tasks, ids, uo, vo, fallback, retry, carry, s);
+        if (!tasks.empty()) aca_batch(H, B, kap, tasks, ids, uo, vo, fallback, retry, carry, wide, wide_seen, s);
         todo.swap(retry);
         retry.clear();
     }
+    RTE_REQUIRE(wide != kWideMust || wide_seen, "ACA: RTE_ACA_WIDE=2 and no launch with several lanes per entry");
     RTE_REQUIRE(carry.at.empty(), "ACA: blocks kept for a second pass were not taken up");
     for (size_t b : todo) fallback.push_back(P.lowrank[b]);
     fill_dense_blocks(H, B, kap, fallback, false, s);
