@@ -357,6 +357,8 @@ rte_status_t fixed_point_solve(const Mesh &m, const HMat &G, const HMat &S, cons
     std::vector<double> rv(2 * nb * nr);
     const bool mixed = d.precision == RTE_MIXED_BF16;
     DevBuf Jacc = words(mixed ? vecN * nb : 0), Sm = words(mixed ? vecN * nb : 0);
+    poison(Jacc, s);
+    poison(Sm, s);
 
     // the parts of a sweep: before the matvec, the matvec, after it
     auto enqueue_pre = [&](const double *sub) {
