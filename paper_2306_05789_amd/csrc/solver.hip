@@ -316,13 +316,14 @@ rte_status_t fixed_point_solve(const Mesh &m, const HMat &G, const HMat &S, cons
     BandParams bp{nb, d.grey, dconst.as<double>(), dconst.as<double>() + nb, dconst.as<double>() + 2 * nb};
 
     const int64_t vecN = N * nr;
-    // Buffers above 64 MiB are allocated for the solve: the pool settles on one
-    // placement of them, and on 49^3 with 32 bands and 16 right-hand sides (0.5 GB each)
-    // it is the slow one (low product 15.17 ms, 307 ms per solve; allocated 14.64 and
-    // 301); below, the allocation costs more than any placement.
+    // From the pool at every size: against allocating each for the solve, 27^3 in 2 FP64
+    // bands with 16 right-hand sides (5 MB a buffer) 5.5 -> 4.9 ms, mixed 33^3 in 4 bands
+    // (18 MB) 7.2 -> 5.4, in 16 (74 MB) 20.6 -> 17.4, in 64 (294 MB) 72.3 -> 68.2, 49^3 in 32
+    // (482 MB) 466 -> 464 and 478 -> 476 in two processes.  Those above 64 MiB take no idle
+    // buffer larger than themselves.
     auto words = [](int64_t n) {
         const size_t bytes = sizeof(double) * (size_t)n;
-        return bytes > ((size_t)64 << 20) ? DevBuf(bytes) : DevBuf::scratch(bytes);
+        return DevBuf::scratch(bytes, bytes > ((size_t)64 << 20));
     };
     DevBuf Tw = words(L * nr), Q = words(L * nr * nb), SE = words(vecN * nb), Sv = words(vecN * nb), J = words(vecN * nb),
            Jn = words(vecN * nb), T = words(vecN), part = words((int64_t)2 * kResidBlocks * nb * nr),
