@@ -236,3 +236,29 @@ def test_compressed_on_marched_entries(walls, kind):
         assert torch.linalg.norm(y - want) <= 30 * eps * torch.linalg.norm(want)
     for (ka, ua, va), (kb, ub, vb) in zip(*got):
         assert ka == kb and (ka <= 0 or (np.array_equal(ua, ub) and np.array_equal(va, vb)))
+
+
+@pytest.mark.parametrize("n0,wall", [(2940, False), (2960, False), (190, True), (204, True)],
+                         ids=["kinks", "march", "kinks-wall", "march-wall"])
+def test_long_boxes(n0, wall):
+    """The sums' 64 bits bound the box too: N^3 M / 6 < 2^32 (N cells of a ray's two largest extents, M = 1 or twice the
+    wall axis').  Rays over the whole length, on both sides of it."""
+    n, h = (n0, 2, 3), [1.0 / (n0 - 1), 1.0, 0.5]
+    kap = np.random.default_rng(n0).uniform(0.0, 1.0, n)
+    mesh = rte.rte_mesh_create(n, emit_faces=inputs.FACE_X_LO, walls=[(0, 1, 1.0)] if wall else None)
+    open_ = rte.rte_mesh_create(n, emit_faces=inputs.FACE_X_LO)
+    r = np.random.default_rng(1)
+    rows, cols = r.integers(n0 * 3, n0 * 6, 10), r.integers(0, 6, 10)
+    zero = np.zeros_like(kap)
+    sd = surface_entries(open_, zero, rows, cols)
+    sw = surface_entries(mesh, zero, rows, cols) - sd
+    for i, j, d, w, got in zip(rows, cols, sd, sw, surface_entries(mesh, kap, rows, cols)):
+        P, Q = [int(v) for v in np.unravel_index(i, n)], [int(v) for v in np.unravel_index(j, n)]
+        t = exact_depth(kap, h, P, Q)[0]
+        tw = exact_depth(kap, h, P, Q, 0, n0 - 1)[0] if wall else 0.0
+        a, b = math.exp(-t) * d, math.exp(-tw) * w if wall else 0.0
+        if n0 in (2940, 190):
+            tol = rounding(t) * a + rounding(tw) * b + 4 * U * (d + abs(w))
+        else:
+            tol = 32 * (n0 + 2) * U * ((1.0 + t) * a + (1.0 + tw) * b) + 4 * U * (d + abs(w))
+        assert abs(got - (a + b)) <= tol, (i, j, t, tw, got - (a + b), tol)
