@@ -965,7 +965,9 @@ void phase_b_valu(int W, unsigned gb, const LeafWork *lw, const Seg *sg, const d
 // wb: wavefronts per phase B workgroup.  FP64 with more than 4 right-hand
 // sides: the matrix-core kernels, 16 per pass.  Otherwise groups of at most 4
 // on the vector ALUs: with 16 per launch the accumulators (4 rows x 16
-// columns per lane) leave one wavefront per SIMD and the stream stalls.
+// columns per lane) leave one wavefront per SIMD and the stream stalls.  Two have
+// kernels of their own (29x31x33 in 2 FP64 bands 636 us, by those of four 744: the
+// columns that are not there are loaded all the same); three take those of four (761).
 template <int ST, int MODE, typename A>
 void launch_typed(const MatvecPlan &mp, int nrhs, const double *x, const double *y0, double *y, double *tb,
                   hipStream_t s, int wb) {
@@ -1011,6 +1013,8 @@ void launch_typed(const MatvecPlan &mp, int nrhs, const double *x, const double 
             const VtTask *vt = mp.vt.as<VtTask>();
             if (nr == 1)
                 k_phase_a<ST, MODE, A, 1><<<ga, 256, 0, s>>>(vt, mp.n_vt, x, mp.n_src, xbs, tb, mp.ktot, part, ldp, r0, nr);
+            else if (nr == 2)
+                k_phase_a<ST, MODE, A, 2><<<ga, 256, 0, s>>>(vt, mp.n_vt, x, mp.n_src, xbs, tb, mp.ktot, part, ldp, r0, nr);
             else
                 k_phase_a<ST, MODE, A, 4><<<ga, 256, 0, s>>>(vt, mp.n_vt, x, mp.n_src, xbs, tb, mp.ktot, part, ldp, r0, nr);
             HIP_LAUNCH_CHECK();
@@ -1025,6 +1029,8 @@ void launch_typed(const MatvecPlan &mp, int nrhs, const double *x, const double 
         const Seg *sg = mp.seg.as<Seg>();
         if (nr == 1)
             phase_b_valu<ST, MODE, A, 1>(wb, gb, lw, sg, x, mp.n_src, xbs, tb, mp.ktot, y0, y, mp.n_tgt, ybs, r0, nr, s);
+        else if (nr == 2)
+            phase_b_valu<ST, MODE, A, 2>(wb, gb, lw, sg, x, mp.n_src, xbs, tb, mp.ktot, y0, y, mp.n_tgt, ybs, r0, nr, s);
         else
             phase_b_valu<ST, MODE, A, 4>(wb, gb, lw, sg, x, mp.n_src, xbs, tb, mp.ktot, y0, y, mp.n_tgt, ybs, r0, nr, s);
         HIP_LAUNCH_CHECK();
