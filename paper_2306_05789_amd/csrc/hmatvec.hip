@@ -564,10 +564,13 @@ __device__ __forceinline__ void mf_products(const MfOps<MODE, NT> &o, int nt, f3
             } else {
                 // the leading products apart from the 2^-8 smaller ones: the latter then
                 // round at their own size, and a step leaves one rounding of the leading
-                // sum.  15x14x16, against the stored operator in FP64: rms error 3.2e-9, with
-                // all five in one sum 2.5e-8 (a mixed solve to 1e-10 takes 21 sweeps instead
-                // of 25), with the leading one added to it last 8.1e-9; 33^3 in 4 bands 1.009,
-                // 1.006 and 1.008 ms with one right-hand side, 1.070, 1.067 and 1.068 with 16
+                // sum.  Rms error against the stored operator in FP64: 15x14x16 3.2e-9,
+                // 37x29x31 4.4e-9; with all five in one sum 2.5e-8 and 1.6e-8 (a mixed solve of
+                // 17x9x9 to 1e-10 takes 21 sweeps instead of 25), with the leading one added to
+                // the others last 8.1e-9.  33^3 in 4 bands 1.009, 1.006 and 1.008 ms with one
+                // right-hand side, 1.070, 1.067 and 1.068 with 16; 11^3 17.1 us, all in one 16.3.
+                // The smaller ones summed in FP32 over a task or a leaf take 16.3 us to the same
+                // errors, but the product then depends on the launch shape by 1e-9 (1e-12 here).
                 f32x4 z = {0.0f, 0.0f, 0.0f, 0.0f}, y = {0.0f, 0.0f, 0.0f, 0.0f};
                 z = mfma(o.a[t], o.bx[0], z);
                 y = mfma(o.a[t], o.bx[2], y);
