@@ -6,6 +6,7 @@
 #include <atomic>
 #include <chrono>
 #include <algorithm>
+#include <cfloat>
 #include <cmath>
 #include <numeric>
 #include <cstring>
@@ -93,12 +94,25 @@ std::vector<double> check_kappa(const double *kappa, int64_t N, int n_bands, hip
     check_device_pointer(kappa, "kappa");
     auto h = to_host(kappa, N * n_bands, s);
     std::vector<double> kmax((size_t)n_bands, 0.0);
-    for (int b = 0; b < n_bands; ++b)
-        for (int64_t i = 0; i < N; ++i) {
-            const double v = h[(size_t)(b * N + i)];
-            RTE_REQUIRE(std::isfinite(v) && v >= 0.0, "kappa must be finite and >= 0");
-            kmax[b] = std::max(kmax[b], v);
+    for (int b = 0; b < n_bands; ++b) {
+        // four maxima and one flag, without a branch per value
+        const double *v = h.data() + (size_t)b * N;
+        double m[4] = {0.0, 0.0, 0.0, 0.0};
+        bool ok = true;
+        int64_t i = 0;
+        for (; i + 4 <= N; i += 4)
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                ok &= (v[i + u] >= 0.0) & (v[i + u] <= DBL_MAX);
+                m[u] = v[i + u] > m[u] ? v[i + u] : m[u];
+            }
+        for (; i < N; ++i) {
+            ok &= (v[i] >= 0.0) & (v[i] <= DBL_MAX);
+            m[0] = v[i] > m[0] ? v[i] : m[0];
         }
+        RTE_REQUIRE(ok, "kappa must be finite and >= 0");
+        kmax[b] = std::max(std::max(m[0], m[1]), std::max(m[2], m[3]));
+    }
     return kmax;
 }
 

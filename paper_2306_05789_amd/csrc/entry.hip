@@ -345,7 +345,7 @@ void entries_launch(const Mesh &m, int kind, const double *kappa, double kmax, i
     if (precision == RTE_FP64) {
         const double q = kink_quantum(m.dev, kmax);
         DevBuf kt = q > 0.0 ? kink_table(m, kappa, q, s) : march_table(m, kappa, s);
-        // building the table (8 rows per vertex or more, 0.1 ms at 41^3) is left out for a few entries
+        // a few entries are summed point by point: the table costs 30 us at 25^3 and 114 at 41^3
         StarBuf star;
         if (kind == RTE_VOLUME && n >= m.N) {
             size_t free_b = 0, total_b = 0;
@@ -356,11 +356,11 @@ void entries_launch(const Mesh &m, int kind, const double *kappa, double kmax, i
         else launch(BandKappa<double, false>{kappa, kt.as<double>(), 0.0, star.tab});
         settle({&kt, &star.buf});
     } else {
-        DevBuf kf(sizeof(float) * (size_t)m.N);
+        DevBuf kf = DevBuf::scratch(sizeof(float) * (size_t)m.N);
         to_float(kappa, kf.as<float>(), m.N, s);
         DevBuf kt = march_table(m, kf.as<float>(), s);
         launch(BandKappa<float, false>{kf.as<float>(), kt.as<float>()});
-        settle({&kt});
+        settle({&kf, &kt});
     }
 }
 
