@@ -140,11 +140,9 @@ __device__ __forceinline__ void load4(const void *p, uint32_t i, A v[4]) {
 // chunk or block (first < stride), two products at a time: v(k) the 4 elements at
 // p + at + k ld, c(k, r) at q + r ldq + k.  A wavefront is bound by the loads it has in
 // flight, so U elements are loaded together and without a branch on the lane (past
-// the end the last one, with c = 0); fewer when half of them reach the end.  FP64, one
-// right-hand side, against two at a time under a condition: 27x18x22 in 2 bands
-// phase A 93 -> 75 us, phase B 135 -> 123 (U = 4: 81 and 128; U = 8 held to 4
-// wavefronts per SIMD: 79 and 127); 41^3 388 -> 385 and 531 -> 507, near the rate of a
-// large read.
+// the end the last one, with c = 0, at most one per lane: valu_tail).  FP64, one
+// right-hand side, against two at a time under a condition, U = 8: 27x18x22 in 2 bands
+// 210 -> 188 us, 41^3 861 -> 831, near the rate of a large read.
 template <int U, bool TAIL, int ST, typename A, int NR>
 __device__ __forceinline__ void valu_batch(A (&acc)[NR][4], int k0, int stride, int n, const void *p, uint32_t at,
                                            int ld, const double *q, int64_t ldq, int nr) {
@@ -169,20 +167,30 @@ __device__ __forceinline__ void valu_batch(A (&acc)[NR][4], int k0, int stride, 
     }
 }
 
-template <int ST, typename A, int NR>
+// the last elements, at most U: the smallest even batch that holds them
+template <int U, int ST, typename A, int NR>
+__device__ __forceinline__ void valu_tail(A (&acc)[NR][4], int k0, int first, int stride, int n, const void *p, uint32_t at,
+                                          int ld, const double *q, int64_t ldq, int nr) {
+    if constexpr (U > 2)
+        if (n - k0 <= (U - 2) * stride) {
+            valu_tail<U - 2, ST>(acc, k0, first, stride, n, p, at, ld, q, ldq, nr);
+            return;
+        }
+    valu_batch<U, true, ST>(acc, k0 + first, stride, n, p, at, ld, q, ldq, nr);
+}
+
+template <int U, int ST, typename A, int NR>
 __device__ __forceinline__ void valu_sum(A (&acc)[NR][4], int first, int stride, int n, const void *p, uint32_t at,
                                          int ld, const double *q, int64_t ldq, int nr) {
-    constexpr int U = NR == 1 ? 8 : 4;
     n = __builtin_amdgcn_readfirstlane(n);
     ld = __builtin_amdgcn_readfirstlane(ld);
     int k0 = 0;
     for (; k0 + U * stride <= n; k0 += U * stride)
         valu_batch<U, false, ST>(acc, k0 + first, stride, n, p, at, ld, q, ldq, nr);
-    if (n - k0 > U / 2 * stride) valu_batch<U, true, ST>(acc, k0 + first, stride, n, p, at, ld, q, ldq, nr);
-    else if (n > k0) valu_batch<U / 2, true, ST>(acc, k0 + first, stride, n, p, at, ld, q, ldq, nr);
+    if (n > k0) valu_tail<U, ST>(acc, k0, first, stride, n, p, at, ld, q, ldq, nr);
 }
 
-template <int ST, int MODE, typename A, int NR>
+template <int ST, int MODE, typename A, int NR, int U>
 __global__ __launch_bounds__(256) void k_phase_a(const VtTask *__restrict__ tasks, int64_t ntask,
                                                  const double *__restrict__ x, int64_t ldx, int64_t xbs,
                                                  double *__restrict__ t, int64_t ldt, double *__restrict__ part,
@@ -208,7 +216,7 @@ __global__ __launch_bounds__(256) void k_phase_a(const VtTask *__restrict__ task
         for (int r = 0; r < NR; ++r)
 #pragma unroll
             for (int u = 0; u < 4; ++u) acc[r][u] = (A)0;
-        valu_sum<ST>(acc, g, G, tk.nj, tk.V, live ? l : l0, kp, x + (int64_t)r0 * ldx + tk.s0, ldx, nr);
+        if (live) valu_sum<U, ST>(acc, g, G, tk.nj, tk.V, l, kp, x + (int64_t)r0 * ldx + tk.s0, ldx, nr);
         // add the G row groups (lanes q, q + LQ, ...) in a fixed order
 #pragma unroll
         for (int r = 0; r < NR; ++r) {
@@ -241,7 +249,7 @@ __global__ __launch_bounds__(256) void k_phase_a_reduce(const VtReduce *__restri
 
 // a lane reads RPL = 4 consecutive rows of one column per load (16 or 32
 // bytes); 16 lanes cover a 64-row tile and 4 column groups run side by side
-template <int ST, int MODE, typename A, int NR, int W>
+template <int ST, int MODE, typename A, int NR, int U, int W>
 __global__ __launch_bounds__(64 * W) void k_phase_b(const LeafWork *__restrict__ leaves, const Seg *__restrict__ segs,
                                                     const double *__restrict__ x, int64_t ldx, int64_t xbs,
                                                     const double *__restrict__ t, int64_t ldt,
@@ -259,7 +267,7 @@ __global__ __launch_bounds__(64 * W) void k_phase_b(const LeafWork *__restrict__
     if (y0) y0 += (int64_t)lw.band * ybs;
     for (int rb = 0; rb < lw.rows; rb += 64) {
         const bool rlive = rb + RPL * rq < lw.rows;
-        const uint32_t cb = rlive ? rb + RPL * rq : rb;   // first row of this lane within a column
+        const uint32_t cb = rb + RPL * rq;   // first row of this lane within a column
         A acc[NR][RPL];
 #pragma unroll
         for (int r = 0; r < NR; ++r)
@@ -273,8 +281,9 @@ __global__ __launch_bounds__(64 * W) void k_phase_b(const LeafWork *__restrict__
             const Seg cur = sg;
             if (s + W < lw.seg1) sg = segs[s + W];
             const int64_t ldc = cur.is_lr ? ldt : ldx;
-            valu_sum<ST>(acc, cg, CG, cur.K, cur.data, cb, cur.ld, (cur.is_lr ? t : x) + (int64_t)r0 * ldc + cur.coef_off,
-                         ldc, nr);
+            if (rlive)   // one branch for all of the segment's loads
+                valu_sum<U, ST>(acc, cg, CG, cur.K, cur.data, cb, cur.ld, (cur.is_lr ? t : x) + (int64_t)r0 * ldc + cur.coef_off,
+                             ldc, nr);
         }
         // sum over the column groups (same order on every lane)
 #pragma unroll
@@ -953,16 +962,16 @@ __global__ void k_scatter(const int64_t *__restrict__ perm, int64_t n, int nrhs,
 }
 
 // phase B of the vector-ALU path with W wavefronts per workgroup
-template <int ST, int MODE, typename A, int NR>
+template <int ST, int MODE, typename A, int NR, int U>
 void phase_b_valu(int W, unsigned gb, const LeafWork *lw, const Seg *sg, const double *x, int64_t ldx, int64_t xbs,
                   const double *t, int64_t ldt, const double *y0, double *y, int64_t ldy, int64_t ybs, int r0, int nr,
                   hipStream_t s) {
     if (W == 2)
-        k_phase_b<ST, MODE, A, NR, 2><<<gb, 128, 0, s>>>(lw, sg, x, ldx, xbs, t, ldt, y0, y, ldy, ybs, r0, nr);
+        k_phase_b<ST, MODE, A, NR, U, 2><<<gb, 128, 0, s>>>(lw, sg, x, ldx, xbs, t, ldt, y0, y, ldy, ybs, r0, nr);
     else if (W == 4)
-        k_phase_b<ST, MODE, A, NR, 4><<<gb, 256, 0, s>>>(lw, sg, x, ldx, xbs, t, ldt, y0, y, ldy, ybs, r0, nr);
+        k_phase_b<ST, MODE, A, NR, U, 4><<<gb, 256, 0, s>>>(lw, sg, x, ldx, xbs, t, ldt, y0, y, ldy, ybs, r0, nr);
     else
-        k_phase_b<ST, MODE, A, NR, 8><<<gb, 512, 0, s>>>(lw, sg, x, ldx, xbs, t, ldt, y0, y, ldy, ybs, r0, nr);
+        k_phase_b<ST, MODE, A, NR, U, 8><<<gb, 512, 0, s>>>(lw, sg, x, ldx, xbs, t, ldt, y0, y, ldy, ybs, r0, nr);
 }
 
 // wb: wavefronts per phase B workgroup.  FP64 with more than 4 right-hand
@@ -1008,18 +1017,30 @@ void launch_typed(const MatvecPlan &mp, int nrhs, const double *x, const double 
             return;
         }
     }
+    // Columns and loads in flight per lane of the kernels of nr right-hand sides.  FP64
+    // with leaves of at most 32 rows takes 6 loads instead of 8: its segments are short, and
+    // four wavefronts per SIMD count more than a lane's loads (25x24x23, three walls, 3
+    // bands, leaves of 14 rows: 735 and 801 us, of 27: 419 and 443, of 54: 365 and 354; 41^3 of
+    // 17: 955 and 988, of 34: 838 and 831; FP32 is faster with 8 at every size).
+    const bool few = ST == ST_F64 && mp.max_rows <= 32;
+    auto by_count = [&](int nr, auto launch) {
+        constexpr std::integral_constant<int, 1> one{};
+        if (nr == 1 && few) launch(one, std::integral_constant<int, ST == ST_F64 ? 6 : 8>());
+        else if (nr == 1) launch(one, std::integral_constant<int, 8>());
+        else if (nr == 2) launch(std::integral_constant<int, 2>(), std::integral_constant<int, 4>());
+        else launch(std::integral_constant<int, 4>(), std::integral_constant<int, 4>());
+    };
     constexpr int kGroup = 4;
     for (int r0 = 0; r0 < nrhs; r0 += kGroup) {
         const int nr = std::min(kGroup, nrhs - r0);
         if (mp.n_vt) {
             const unsigned ga = (unsigned)((mp.n_vt + 3) / 4);
             const VtTask *vt = mp.vt.as<VtTask>();
-            if (nr == 1)
-                k_phase_a<ST, MODE, A, 1><<<ga, 256, 0, s>>>(vt, mp.n_vt, x, mp.n_src, xbs, tb, mp.ktot, part, ldp, r0, nr);
-            else if (nr == 2)
-                k_phase_a<ST, MODE, A, 2><<<ga, 256, 0, s>>>(vt, mp.n_vt, x, mp.n_src, xbs, tb, mp.ktot, part, ldp, r0, nr);
-            else
-                k_phase_a<ST, MODE, A, 4><<<ga, 256, 0, s>>>(vt, mp.n_vt, x, mp.n_src, xbs, tb, mp.ktot, part, ldp, r0, nr);
+            auto phase_a = [&](auto nrc, auto u) {
+                k_phase_a<ST, MODE, A, decltype(nrc)::value, decltype(u)::value>
+                    <<<ga, 256, 0, s>>>(vt, mp.n_vt, x, mp.n_src, xbs, tb, mp.ktot, part, ldp, r0, nr);
+            };
+            by_count(nr, phase_a);
             HIP_LAUNCH_CHECK();
             if (mp.n_red) {
                 k_phase_a_reduce<<<(unsigned)((mp.n_red + 3) / 4), 256, 0, s>>>(mp.red.as<VtReduce>(), mp.n_red, part,
@@ -1030,12 +1051,10 @@ void launch_typed(const MatvecPlan &mp, int nrhs, const double *x, const double 
         const unsigned gb = (unsigned)mp.n_leaf;
         const LeafWork *lw = mp.leaf.as<LeafWork>();
         const Seg *sg = mp.seg.as<Seg>();
-        if (nr == 1)
-            phase_b_valu<ST, MODE, A, 1>(wb, gb, lw, sg, x, mp.n_src, xbs, tb, mp.ktot, y0, y, mp.n_tgt, ybs, r0, nr, s);
-        else if (nr == 2)
-            phase_b_valu<ST, MODE, A, 2>(wb, gb, lw, sg, x, mp.n_src, xbs, tb, mp.ktot, y0, y, mp.n_tgt, ybs, r0, nr, s);
-        else
-            phase_b_valu<ST, MODE, A, 4>(wb, gb, lw, sg, x, mp.n_src, xbs, tb, mp.ktot, y0, y, mp.n_tgt, ybs, r0, nr, s);
+        by_count(nr, [&](auto nrc, auto u) {
+            phase_b_valu<ST, MODE, A, decltype(nrc)::value, decltype(u)::value>(
+                wb, gb, lw, sg, x, mp.n_src, xbs, tb, mp.ktot, y0, y, mp.n_tgt, ybs, r0, nr, s);
+        });
         HIP_LAUNCH_CHECK();
     }
 }
