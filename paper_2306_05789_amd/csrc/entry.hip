@@ -1,6 +1,7 @@
 // Kernels that evaluate kernel entries directly: arbitrary (row, col) pairs,
 // and the dense near-field leaves of the H-matrix (Section "Compression": a
 // block that reaches the leaves without being admissible is computed in full).
+#include <algorithm>
 #include <cmath>
 
 #include "entry_dev.h"
@@ -345,12 +346,17 @@ void entries_launch(const Mesh &m, int kind, const double *kappa, double kmax, i
     if (precision == RTE_FP64) {
         const double q = kink_quantum(m.dev, kmax);
         DevBuf kt = q > 0.0 ? kink_table(m, kappa, q, s) : march_table(m, kappa, s);
-        // a few entries are summed point by point: the table costs 30 us at 25^3 and 114 at 41^3
+        // The quadrature's table, for fewer entries than vertices only when it is small: 16 entries of 6x5x7
+        // with three walls take 182 us point by point and 136 with it; 25^3 (31 us for 66 MB) and larger
+        // are as fast without
         StarBuf star;
-        if (kind == RTE_VOLUME && n >= m.N) {
-            size_t free_b = 0, total_b = 0;
-            HIP_CHECK(hipMemGetInfo(&free_b, &total_b));
-            star = star_table(m, (free_b + pool_idle_bytes()) / 16, s);
+        if (kind == RTE_VOLUME) {
+            size_t room = (size_t)16 << 20, free_b = 0, total_b = 0;
+            if (n >= m.N) {
+                HIP_CHECK(hipMemGetInfo(&free_b, &total_b));
+                room = std::max(room, (free_b + pool_idle_bytes()) / 16);
+            }
+            star = star_table(m, room, s);
         }
         if (q > 0.0) launch(BandKappa<double, true>{kappa, kt.as<int64_t>(), q, star.tab});
         else launch(BandKappa<double, false>{kappa, kt.as<double>(), 0.0, star.tab});
