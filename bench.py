@@ -53,12 +53,12 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
 HBM_PEAK_GBS = 8000.0
-# HBM bytes per launch of the ACA entry launches (k_aca_rows / k_aca_cols, volume,
-# FP64), from rocprofv3 FETCH_SIZE and WRITE_SIZE passes over this benchmark's step,
+# HBM bytes per launch of the ACA entry launches (k_aca_rows / k_aca_cols / k_aca_wide,
+# volume, FP64), from rocprofv3 FETCH_SIZE and WRITE_SIZE passes over this benchmark's step,
 # calibrated on a plain 1 GiB copy (FETCH_SIZE reads half the bytes, WRITE_SIZE all):
 # the summary is profiles/cube41_grey_fp64_hmatrix_hbm_traffic.md.  Set to None
 # whenever those kernels change.
-ACA_ENTRY_TRAFFIC_BYTES = 434.5e6
+ACA_ENTRY_TRAFFIC_BYTES = 620.5e6
 FP64_PEAK_TFLOPS = 78.6
 # Algorithmic FP64 operations of one kernel entry, counted from the code of the
 # march and the quadrature with an FMA as 2 and a reciprocal, square root or

@@ -15,11 +15,13 @@
 //
 // GPU organisation: all admissible blocks of a band advance together, one
 // rank step at a time.  Steps 1 and 3 are flat launches with one lane per
-// matrix entry over every active block (a lane finds its block by binary
-// search in a prefix array), so the expensive entry evaluations keep every
-// lane busy whatever the block sizes; steps 2, 4 and 5 run one workgroup per
-// active block.  Reductions use wavefront shuffles and one LDS stage in a
-// fixed order, so results are bitwise reproducible.
+// matrix entry over every active block (a lane finds its block by a few steps from
+// its workgroup's hint), so the expensive entry evaluations keep every lane busy
+// whatever the block sizes; when few entries are left several lanes share one
+// (k_aca_wide).  Step 2 and the end of 4 and 5 run a wavefront or a workgroup per active
+// block, the dot products of 4 a workgroup or several per chunk of 1024 elements.
+// Reductions use wavefront shuffles and one LDS stage in a fixed order, so results are
+// bitwise reproducible.
 #include <algorithm>
 #include <map>
 #include <climits>

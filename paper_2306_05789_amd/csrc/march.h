@@ -1,5 +1,6 @@
-// Optical depth between grid vertices, exact for the P1 kappa (FP64 entries; those
-// in FP32 keep the march of march32.h).
+// Optical depth between grid vertices from the kinks of the P1 kappa along the ray, to
+// one rounding of the exact value (FP64 entries; those in FP32, and bands that the kinks
+// do not resolve, take the march of march_tets.h).
 //
 // Along a ray x(s) = V + s D, s in [0, 1], kappa is continuous and piecewise
 // linear, with a kink where the ray crosses a face of a Kuhn tetrahedron.  By

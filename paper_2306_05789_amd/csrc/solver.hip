@@ -319,8 +319,9 @@ rte_status_t fixed_point_solve(const Mesh &m, const HMat &G, const HMat &S, cons
     // From the pool at every size: against allocating each for the solve, 27^3 in 2 FP64
     // bands with 16 right-hand sides (5 MB a buffer) 5.5 -> 4.9 ms, mixed 33^3 in 4 bands
     // (18 MB) 7.2 -> 5.4, in 16 (74 MB) 20.6 -> 17.4, in 64 (294 MB) 72.3 -> 68.2, 49^3 in 32
-    // (482 MB) 466 -> 464 and 478 -> 476 in two processes.  Those above 64 MiB take no idle
-    // buffer larger than themselves.
+    // (482 MB) 301.5 -> 297.0 (means of five processes each, in turn: 297 to 305 and 293 to
+    // 300; a process keeps one placement of its buffers, a solve that allocates gets
+    // another).  Those above 64 MiB take no idle buffer larger than themselves.
     auto words = [](int64_t n) {
         const size_t bytes = sizeof(double) * (size_t)n;
         return DevBuf::scratch(bytes, bytes > ((size_t)64 << 20));
